@@ -64,8 +64,7 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
   auto koff_bytes = [&](int koff) -> size_t { return L.tiled ? (size_t)(koff / 16) * 1024 : (size_t)koff * esz; };
   // small batches are bound by streaming the weights: dedicated kernels
   const bool small_m = bf16 && M <= SKINNY_MAX_M;
-  auto run = [&](GemmArgs& g, int a, int shape, int n_split) -> int {
-    if (g.group_m <= 0) g.group_m = 8;
+  auto run = [&](GemmArgs& g, int a, int n_split = 1) -> int {
     g.m_pad = w.t_pad;
     if (!bf16) {
       // few tiles: split the reduction, bias / activation / routing with the sum (never beyond
@@ -81,31 +80,24 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
       }
       return launch_gemm_f32(g, a, false, st, n_split);
     }
-    if (small_m && !g.partial && (g.N & 31) == 0) return launch_skinny_bf16(g, a, (float*)(ws + w.off_kpart), st);
-    if (!small_m && M <= 1024 && !g.partial && !g.A1) {
-      // a few hundred rows and few tiles: split the reduction, epilogue in a second launch
-      const int sp = mid_split(M, g.N, g.K);
-      const int ldp = round_up(g.N, 32);
-      // (never beyond the scratch the workspace was sized with: the plain launch is always valid)
-      if (sp > 1 && (size_t)sp * M * ldp * 4 <= w.kpart_bytes) {
-        float* part = (float*)(ws + w.off_kpart);
-        GemmArgs gp = g;
-        gp.partial = 1; gp.C0 = part; gp.ldc0 = ldp; gp.split_col = ldp; gp.act_cols = 0;
-        gp.c0_tiled = 0; gp.c1_tiled = 0;
-        gp.bias = nullptr; gp.bias_cols = 0; gp.resid = nullptr; gp.out_f32 = 0;   // applied with the sum
-        if (launch_gemm_bf16(gp, ACT_NONE, false, GEMM_128x128, sp, st) != 0) return -1;
-        return launch_splitk_epilogue(part, sp, ldp, g, a, st);
-      }
+    if (small_m && (g.N & 31) == 0) return launch_skinny_bf16(g, a, (float*)(ws + w.off_kpart), st);
+    const bool dual = g.A1 != nullptr;
+    const bool paired = a == ACT_GLU;
+    GemmPlan plan = gemm_plan(M, g.N, g.K, paired, dual, !dual);
+    const int ldp = round_up(g.N, 32);
+    // (never beyond the scratch the workspace was sized with: the plain launch is always valid)
+    if (plan.split > 1 && (size_t)plan.split * M * ldp * 4 > w.kpart_bytes)
+      plan = gemm_plan(M, g.N, g.K, paired, dual, false);
+    if (plan.split > 1) {
+      float* part = (float*)(ws + w.off_kpart);
+      GemmArgs gp = g;
+      gp.partial = 1; gp.C0 = part; gp.ldc0 = ldp; gp.split_col = ldp; gp.act_cols = 0;
+      gp.c0_tiled = 0; gp.c1_tiled = 0;
+      gp.bias = nullptr; gp.bias_cols = 0; gp.resid = nullptr; gp.out_f32 = 0;   // applied with the sum
+      if (launch_gemm_bf16(gp, ACT_NONE, false, plan.shape, plan.split, st) != 0) return -1;
+      return launch_splitk_epilogue(part, plan.split, ldp, g, a, st);
     }
-    return launch_gemm_bf16(g, a, false, shape, n_split, st);
-  };
-  const int big_m = M > 1024;   // 256-row tiles only pay off with enough rows
-  // Share (percent) of the CU slots that 256x256 tiles keep busy: one workgroup per CU, whole
-  // rounds of 256.  Measured: where that share is high the large tile beats the smaller ones
-  // by 10-25 % (its main loop reads LDS half as often per MFMA), below about half it loses.
-  auto fill256 = [](int m, int n) -> int {
-    const int tiles = ((m + 255) / 256) * ((n + 255) / 256);
-    return tiles > 0 ? 100 * tiles / (256 * ((tiles + 255) / 256)) : 0;
+    return launch_gemm_bf16(g, a, false, plan.shape, 1, st);
   };
 
   // G1: X * [W1h | P1] (SwiGLU: [gate/up heavy pairs | Pg | P1]) -> h1 (activated) and t
@@ -118,18 +110,8 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
     g.split_col = acted;
     g.C0 = cat; g.ldc0 = L.k4; g.c0_tiled = L.tiled;
     g.C1 = tbuf; g.ldc1 = (int64_t)L.n_up * L.rp; g.c1_tiled = L.tiled;
-    g.group_m = 1;   // X is the large operand: its row tiles stay within one XCD
     g.bias = ep.b1; g.bias_cols = ep.b1 ? acted : 0;   // the activated neurons' biases (packed order)
-    // (few tiles: eight wavefronts on 64-deep slabs, whose row-major gather takes whole cache lines)
-    int wide = fill256(M, L.n1) >= 50 ? GEMM_256x256 : (L.n1 >= 4096 ? GEMM_256x128 : GEMM_128x128_KSPLIT);
-    // A product with fewer 256 x 256 tiles than CUs takes one tile's time whatever the count: where
-    // 128 x 320 tiles still fit one round, each CU's share is 0.63 of that (C5: 144 -> 224 tiles,
-    // 128 -> 116 us).  Not for gated layers (a wave tile of five column blocks cannot hold pairs).
-    if (!glu && wide == GEMM_256x256) {
-      const int t256 = ((M + 255) / 256) * ((L.n1 + 255) / 256), t320 = ((M + 127) / 128) * ((L.n1 + 319) / 320);
-      if (t256 <= 256 && t320 <= 256) wide = GEMM_128x320;
-    }
-    FFS_TRY(run(g, act, big_m ? wide : GEMM_128x128, 1));
+    FFS_TRY(run(g, act));
   }
   // G2 + G3 in one launch where the rank allows it (no neuron bias: that epilogue is G2's)
   bool fused_mid = false;
@@ -156,31 +138,21 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
     g.act_cols = g.N; g.split_col = L.mp;
     g.C0 = h2; g.ldc0 = L.mp; g.c0_tiled = L.tiled;
     g.bias = ep.b1 ? ep.b1 + L.kp : nullptr; g.bias_cols = ep.b1 ? L.mp : 0;   // the remainder neurons' biases
-    // (a short reduction leaves a 256x256 tile's epilogue uncovered: one workgroup per CU)
-    int g2s = (!glu && g.K >= 1024 && fill256(M, g.N) >= 90) ? GEMM_256x256 : GEMM_256x128;
-    // two left operands: 256 x 256 tiles with wave tiles of 64 x 128 read each token fragment for
-    // four weight blocks instead of two (the Llama shape: 231 -> 200 us)
-    if (glu && g.K >= 1024 && fill256(M, g.N) >= 80) g2s = GEMM_256x256_W64;
-    FFS_TRY(run(g, act, big_m ? g2s : GEMM_128x128, 1));
+    FFS_TRY(run(g, act));
     // G3: h2 * P2 -> t2 into cat[:, kp:]  (long reduction: split-K, fixed-order sum)
     g = {};
     g.A = h2; g.lda = L.mp; g.a_tiled = L.tiled;
     g.Bt = sp + L.off_p2; g.ldb = L.mp;
     g.M = M; g.N = L.rp; g.K = L.mp;
     g.split_col = L.rp;
-    g.group_m = 1;   // h2 is the large operand
-    if (w.g3_split > 1 && !small_m) {
+    if (!bf16 && w.g3_split > 1) {
       float* part = (float*)(ws + w.off_kpart);
       g.partial = 1; g.C0 = part; g.ldc0 = L.rp;
-      int g3s = big_m ? (w.g3_wide ? GEMM_256x128 : GEMM_128x128_KSPLIT) : GEMM_128x128;
-      if (w.g3_wide == 2) g3s = GEMM_256x320;
-      if (w.g3_wide == 3) g3s = GEMM_256x256;
-      FFS_TRY(run(g, ACT_NONE, g3s, w.g3_split));
-      FFS_TRY(launch_splitk_reduce(part, w.g3_split, M, L.rp, w.t_pad, cat + koff_bytes(L.kp), L.k4, L.tiled, st,
-                                   bf16 ? 0 : 1));
+      FFS_TRY(run(g, ACT_NONE, w.g3_split));
+      FFS_TRY(launch_splitk_reduce(part, w.g3_split, M, L.rp, w.t_pad, cat + koff_bytes(L.kp), L.k4, L.tiled, st, 1));
     } else {
       g.C0 = cat + koff_bytes(L.kp); g.ldc0 = L.k4; g.c0_tiled = L.tiled;
-      FFS_TRY(run(g, ACT_NONE, big_m ? GEMM_256x128 : GEMM_128x128, 1));
+      FFS_TRY(run(g, ACT_NONE));
     }
   }
   // G4: [h1 | t2] * [W2h ; Q2] -> Y   (one fp32 accumulation, one rounding: Eq. 2's sum)
@@ -194,14 +166,7 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
       g.bias = ep.b2; g.bias_cols = ep.b2 ? dm : 0;
       g.resid = ep.resid; g.ldr = dm; g.out_f32 = bf16 ? ep.out_f32 : 0;
     }
-    int shp = (big_m && fill256(M, dm) >= 90) ? GEMM_256x256 : GEMM_128x128;
-    // 256 x 320 tiles where they fill whole rounds of the 256 CUs and 256 x 256 tiles do not
-    // (C5: d_model 5120 = 16 x 320, 4096 rows: exactly 256 tiles; 107 -> 83 us)
-    if (big_m && shp == GEMM_128x128 && dm % 320 == 0) {
-      const int t320 = ((M + 255) / 256) * (dm / 320);
-      if (100 * t320 / (256 * ((t320 + 255) / 256)) >= 90) shp = GEMM_256x320;
-    }
-    return run(g, ACT_NONE, shp, 1);
+    return run(g, ACT_NONE);
   };
   if (L.k4 > 0) {
     FFS_TRY(down(Y, 0, L.k4, true));
@@ -322,10 +287,9 @@ int ffsplit_score_neurons(const ffsplit_desc_t* d, const void* X, int64_t T, con
     g.A = X; g.lda = d->d_model;
     g.Bt = Wt; g.ldb = w.dk;
     g.M = (int)T; g.N = w.n_gemm; g.K = d->d_model;
-    g.group_m = 8;
     g.act_cols = w.n_gemm;
     g.part_s2 = p2; g.part_s1 = p1; g.n_out = w.n_out;
-    if (bf16) FFS_TRY(launch_gemm_bf16(g, act_of(d), true, GEMM_256x128, 1, st));
+    if (bf16) FFS_TRY(launch_gemm_bf16(g, act_of(d), true, GEMM_256x256, 1, st));
     else FFS_TRY(launch_gemm_f32(g, act_of(d), true, st));
     FFS_TRY(launch_reduce_partials(p2, p1, w.tiles_m, w.n_out, d->d_ff, acc, st));
     *T_total += T;

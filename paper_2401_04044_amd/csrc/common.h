@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include "gemm_plan.h"
 
 namespace ffsplit {
 
@@ -81,7 +82,7 @@ struct GemmArgs {
   int64_t lda, ldb;   // row-major: elements per row; tiled: padded K of the buffer
   int M, N, K;
   int a_tiled;
-  int group_m;     // bf16 kernels: row tiles per rasterisation group (>= 1)
+  int group_m;     // bf16 kernels: row tiles per rasterisation group (0: chosen by the launcher)
   // epilogue
   // Columns [0, act_cols) get the activation; with ACT_GLU they are (gate, up)
   // pairs of 32-column blocks and produce act_cols/2 output columns.
@@ -126,16 +127,7 @@ struct Epilogue {
 int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int n_split = 1);
 // sum of fp32 partials [n_split][a.M][ldp] of a whole product + the fp32 store epilogue described by a
 int launch_splitk_epilogue_f32(const float* part, int n_split, int ldp, const GemmArgs& a, int act, hipStream_t st);
-// tile configurations of the bf16 kernel
-enum {
-  GEMM_256x128 = 0,        // 4 wavefronts, 3 stages: the default for large products
-  GEMM_128x128 = 1,        // 4 wavefronts, 3 stages: small or narrow products
-  GEMM_128x128_KSPLIT = 2, // 8 wavefronts, 64-deep slabs, reduction split inside the workgroup (few tiles)
-  GEMM_256x256 = 3,        // 8 wavefronts, 3 stages
-  GEMM_256x320 = 4,        // 4 wavefronts, wave tile 128 x 160 (one wavefront per SIMD): N a multiple of 320
-  GEMM_128x320 = 5,        // 4 wavefronts, wave tile 64 x 160
-  GEMM_256x256_W64 = 6     // 8 wavefronts as 4 x 2, wave tile 64 x 128: fewer reads of two left operands
-};
+// shape: one of gemm_plan.h.
 // n_split > 1 only with a.partial
 int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_split, hipStream_t st);
 // sum of the partials in a fixed order -> C (bf16, tiled or row-major; f32_out: fp32 row-major)

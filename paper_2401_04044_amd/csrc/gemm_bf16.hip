@@ -5,32 +5,44 @@
 // Data layouts
 //   "tiled": the matrix is cut into blocks of 32 rows x 16 k-elements (1 KiB).
 //     Inside a block the 16-byte chunk of lane l = 32 c + r holds row r,
-//     k-elements 8 c .. 8 c + 7, which is exactly the operand register image of
-//     v_mfma_f32_32x32x16_bf16.  Blocks are ordered [row block][k block], so a
-//     K slab of one row block is contiguous.  All packed weights and all
-//     intermediates between the chained products use this layout: global loads
-//     and LDS reads are then contiguous 1 KiB per wavefront instruction and free
-//     of bank conflicts by construction.
+//     k-elements 8 c .. 8 c + 7.  Blocks are ordered [row block][k block], so a K slab of one
+//     row block is contiguous.  All packed weights and all intermediates between the chained
+//     products use this layout: a load or LDS read of a wavefront is a contiguous 1 KiB, and the
+//     operand of v_mfma_f32_16x16x32_bf16 (row l & 15, k elements 8 (l >> 4) .. + 7 in lane l) is
+//     four contiguous 256-byte pieces of two neighbouring blocks: free of bank conflicts.
 //   "row-major": ordinary [rows, ld] (the caller's X and Y).
 //
-// Kernel: BM x BN workgroup tile; BK-deep slabs go from global memory straight into a ring of
-// LDS stages (global_load_lds_dwordx4, one 1 KiB operand block per wavefront instruction);
-// each wavefront owns a (BM/WGM) x (BN/WGN) sub-tile of 32x32 MFMA tiles.  The MFMA is issued
-// with the weights as the first operand so that a lane ends up with 4 consecutive output
-// columns of one row; one v_permlane32_swap turns that into 8 consecutive columns = one
-// 16-byte chunk of the tiled (or row-major) output.
+// Kernel: BM x BN workgroup tile; 32-deep slabs go from global memory straight into a ring of
+// LDS stages (buffer loads with LDS destination, one 1 KiB operand block per wavefront
+// instruction, addresses in scalar registers); each wavefront owns a (BM/WGM) x (BN/WGN) sub-tile
+// of 16x16 MFMA tiles.  The MFMA is issued with the weights as the first operand so that a lane
+// ends up with 4 consecutive output columns of one row; one v_permlane16_swap of two row tiles
+// turns that into 8 consecutive columns = one 16-byte chunk of the tiled (or row-major) output.
 //
+// What bounds it, and why it looks like this (measured on random normal operands):
+//   - Power.  A register-only loop of 32x32x16 MFMAs sustains 1.83 PFLOP/s (2.45 on zeros), of
+//     16x16x32 ones 2.09: hence the 16x16 shape.  4096 x 8192 x 8192 in this kernel: 1.52 PFLOP/s
+//     (1.96 on zeros); the 32x32 kernel it replaces ran the same chain of products at 1.2 at best.
+//   - The vector cache hands a CU 61 bytes per clock, the matrix cores eat a 128x128 tile's slab
+//     (16 KiB) in 256 clocks: small tiles are bound by loads, 256-wide ones are not.  LDS reads
+//     (250 bytes per clock) are not the limit with wave tiles of 64x64 or more.
+//   - Barriers.  Each step has one barrier, in its middle, where every read it must wait for was
+//     issued hundreds of clocks earlier; a wait for reads just issued stalled all eight wavefronts
+//     at the same point (the replaced kernel: 68 % MFMA busy at best).
+//   - Instruction order is written out and fenced; left to the scheduler the reads bunch up.
 // Epilogues: plain / GeLU / SwiGLU (on (gate, up) pairs of 32-column blocks)
 // with two output destinations, fp32 split-K partials, and the neuron-norm
 // column reduction of Sec. 4.1 (Eq. 3) for the calibration pass.
 #include "common.h"
 #include <atomic>
+#include <algorithm>
+#include <math.h>
 #include <type_traits>
 
 namespace ffsplit {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;  // native vector: stays in registers
 
 union Frag {
@@ -50,38 +62,41 @@ __device__ __forceinline__ float act_bf16(float z, float g) {
   return z;
 }
 
-// swap the upper 32 lanes of a with the lower 32 lanes of b
-__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
-  auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+// swap the odd 16-lane rows of a with the even ones of b
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
+  auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
   a = r[0];
   b = r[1];
 }
 
-// Epilogue shared by the GEMM kernels: activation, bf16 packing and the stores (or the
-// neuron-norm column sums).  acc[i][j] is the 32x32 tile (i, j) of the wavefront's sub-tile.
+// The wavefront's accumulators: acc[i][j] is the 16x16 MFMA tile of token rows 16 i and GEMM
+// columns 16 j of its sub-tile.  Forward (SCORE = false): weights are the first MFMA operand, so
+// lane l holds row l & 15, columns 4 (l >> 4) + 0..3.  SCORE: lane l holds column l & 15, rows
+// 4 (l >> 4) + 0..3.
+//
+// Epilogue: activation, bf16 packing and the stores (or the neuron-norm column sums).
 // EPI: the optional additions of GemmArgs (bias, residual stream, fp32 destination) are compiled
 // in; the plain instantiations carry none of their instructions.
 template <int BM, int BN, int WGM, int WGN, int ACT, bool SCORE, bool EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, f32x16_t (&acc)[BM / WGM / 32][BN / WGN / 32], int m0,
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, f32x4_t (&acc)[BM / WGM / 16][BN / WGN / 16], int m0,
                                               int n0, int tm, int wm, int wn, int lane, int tid, u32x4_t* smem) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WM = BM / WGM, WN = BN / WGN;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  // ---------------------------------------------------------------- epilogue
-  constexpr int JSTEP = (ACT == ACT_GLU) ? 2 : 1;
+  constexpr int TM = WM / 16, TN = WN / 16;
+  const int quad = lane >> 4;
   if (!SCORE) {
-    // lane: row = lane & 31; columns 8 g + 4 (lane >> 5) + 0..3 of each 32x32 tile
-    const int half = lane >> 5;
+    const int r0 = m0 + wm * WM;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int cb = n0 + wn * WN + j * 32;  // GEMM column of this 32-block
+      const int cb = n0 + wn * WN + j * 16;  // GEMM column of this tile
       if (cb >= p.N) continue;
       const bool act_here = cb < p.act_cols;
-      int oc;       // output column of the block
+      int oc;       // output column of the tile
       if (ACT == ACT_GLU) {
+        // (gate, up) pairs of 32-column blocks: the pair is written when its gate tile comes up
         if (act_here) {
-          if (j & 1) continue;  // the pair is written when its gate block comes up
-          oc = cb / 2;
+          if (j & 2) continue;
+          oc = (cb >> 6) * 32 + (cb & 31);
         } else {
           oc = cb - p.act_cols / 2;
         }
@@ -94,95 +109,87 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, f32x16_t (&acc)
       const bool to_c0 = oc < p.split_col;
       if (to_c0) { base = (char*)p.C0; ld = p.ldc0; occ = oc; tiled = p.c0_tiled; }
       else { base = (char*)p.C1; ld = p.ldc1; occ = oc - p.split_col; tiled = p.c1_tiled; }
-      // a neuron's bias (GEMM column cb + 8 g + 4 half + e), added before the activation
-      float bz[4][4];
+      if (p.partial) {
+        // fp32 split-K partial, row-major [split][M][ld]
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int c = cb + 8 * g + 4 * half;
-        float4 b4 = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (EPI && ACT != ACT_GLU && p.bias != nullptr && c + 3 < p.bias_cols) b4 = *(const float4*)(p.bias + c);
-        bz[g][0] = b4.x; bz[g][1] = b4.y; bz[g][2] = b4.z; bz[g][3] = b4.w;
-      }
-      const bool f32o = EPI && p.out_f32 && to_c0 && !tiled;
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int rblk = (m0 + wm * WM) / 32 + i;
-        const int row = rblk * 32 + (lane & 31);
-        if (p.partial) {
-          // fp32 split-K partial, row-major [split][M][ld]
-          if (row < p.M) {
-            float* dst = (float*)base + ((int64_t)blockIdx.y * p.M + row) * ld + occ + 4 * half;
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-              *(float4*)(dst + 8 * g) = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
-                                                    acc[i][j][4 * g + 3]);
-          }
-          continue;
+        for (int i = 0; i < TM; ++i) {
+          const int row = r0 + i * 16 + (lane & 15);
+          if (row < p.M)
+            *(f32x4_t*)((float*)base + ((int64_t)blockIdx.y * p.M + row) * ld + occ + 4 * quad) = acc[i][j];
         }
-        // the residual stream (fp32, row-major, same columns as the destination)
-        // (un-activated products start their accumulators from the residual instead: see the kernel)
-        const float* rrow = (EPI && ACT != ACT_NONE && p.resid != nullptr && to_c0 && !tiled && row < p.M)
-                                ? p.resid + (int64_t)row * p.ldr + occ + 4 * half : nullptr;
-        uint32_t pk[4][2];
+        continue;
+      }
+      // a neuron's bias (the lane's GEMM columns cb + 4 quad + e), added before the activation
+      float4 bz = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (EPI && ACT != ACT_GLU && p.bias != nullptr && cb + 4 * quad + 3 < p.bias_cols)
+        bz = *(const float4*)(p.bias + cb + 4 * quad);
+      const bool f32o = EPI && p.out_f32 && to_c0 && !tiled;
+      const bool col4_ok = occ + 4 * quad < p.n_store;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+      for (int ip = 0; ip < TM; ip += 2) {
+        uint32_t pk[2][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int i = ip + h, row = r0 + i * 16 + (lane & 15);
           float v[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            // (static tile indices: an activated pair is (gate j, value j + 1))
+            // (static tile indices: an activated pair is (gate j, value j + 2))
             constexpr int TNM1 = TN - 1;
-            const int j1 = j + 1 < TN ? j + 1 : TNM1;
-            const float gt = EPI ? acc[i][j][4 * g + e] + bz[g][e] : acc[i][j][4 * g + e];
-            const float z = (ACT == ACT_GLU && act_here) ? acc[i][j1][4 * g + e] : gt;
+            const int j1 = j + 2 < TN ? j + 2 : TNM1;
+            float gt = acc[i][j][e];
+            if (EPI) gt += e == 0 ? bz.x : e == 1 ? bz.y : e == 2 ? bz.z : bz.w;
+            const float z = (ACT == ACT_GLU && act_here) ? acc[i][j1][e] : gt;
             v[e] = act_here ? act_bf16<ACT>(z, gt) : z;
           }
-          const bool col_ok = occ + 8 * g + 4 * half < p.n_store;
-          if (EPI && rrow != nullptr && col_ok) {
-            const float4 r4 = *(const float4*)(rrow + 8 * g);
+          // the residual stream of an activated product (un-activated ones start from it: see the kernel)
+          if (EPI && ACT != ACT_NONE && p.resid != nullptr && to_c0 && !tiled && row < p.M && col4_ok) {
+            const float4 r4 = *(const float4*)(p.resid + (int64_t)row * p.ldr + occ + 4 * quad);
             v[0] += r4.x; v[1] += r4.y; v[2] += r4.z; v[3] += r4.w;
           }
           if (EPI && f32o) {
-            if (row < p.M && col_ok)
-              *(float4*)((float*)base + (int64_t)row * ld + occ + 8 * g + 4 * half) = make_float4(v[0], v[1], v[2], v[3]);
+            if (row < p.M && col4_ok)
+              *(float4*)((float*)base + (int64_t)row * ld + occ + 4 * quad) = make_float4(v[0], v[1], v[2], v[3]);
           } else {
-            pk[g][0] = pack_bf16x2(v[0], v[1]);
-            pk[g][1] = pack_bf16x2(v[2], v[3]);
+            pk[h][0] = pack_bf16x2(v[0], v[1]);
+            pk[h][1] = pack_bf16x2(v[2], v[3]);
           }
         }
         if (EPI && f32o) continue;
-        // groups (0,1) and (2,3) each cover 16 consecutive columns: after the swap the lower
-        // lanes hold columns 0..7 and the upper lanes columns 8..15 of those 16
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          swap32(pk[2 * t][0], pk[2 * t + 1][0]);
-          swap32(pk[2 * t][1], pk[2 * t + 1][1]);
-          const u32x4_t val = {pk[2 * t][0], pk[2 * t][1], pk[2 * t + 1][0], pk[2 * t + 1][1]};
-          const int col = occ + 16 * t;  // block of 16 output columns
-          if (tiled) {
-            if (rblk * 32 < p.m_pad)
-              *(u32x4_t*)(base + (((int64_t)rblk * (ld / 16) + col / 16) * 64 + lane) * 16) = val;
-          } else {
-            if (row < p.M && col + 8 * half < p.n_store)
-              *(u32x4_t*)(base + ((int64_t)row * ld + col + 8 * half) * 2) = val;
-          }
+        // Swapping the odd 16-lane rows of the first tile's registers with the even ones of the
+        // second's leaves lane l with row (l & 31) of the 32-row block and columns 8 (l >> 5) + 0..7:
+        // one 16-byte chunk of the tiled (or row-major) output.
+        swap16(pk[0][0], pk[1][0]);
+        swap16(pk[0][1], pk[1][1]);
+        const u32x4_t val = {pk[0][0], pk[0][1], pk[1][0], pk[1][1]};
+        const int rblk = r0 / 32 + ip / 2;
+        const int row = rblk * 32 + (lane & 31);
+        if (tiled) {
+          if (rblk * 32 < p.m_pad)
+            *(u32x4_t*)(base + (((int64_t)rblk * (ld / 16) + occ / 16) * 64 + lane) * 16) = val;
+        } else {
+          if (row < p.M && occ + 8 * (lane >> 5) < p.n_store)
+            *(u32x4_t*)(base + ((int64_t)row * ld + occ + 8 * (lane >> 5)) * 2) = val;
         }
       }
     }
   } else {
-    // lane: column = lane & 31; rows 8 g + 4 (lane >> 5) + 0..3 of each 32x32 tile
-    constexpr int BNO = BN / JSTEP;
+    constexpr int BNO = (ACT == ACT_GLU) ? BN / 2 : BN;
     float* red2 = (float*)smem;  // [WGM][BNO]
     float* red1 = red2 + WGM * BNO;
 #pragma unroll
-    for (int j = 0; j < TN; j += JSTEP) {
+    for (int j = 0; j < TN; ++j) {
+      if (ACT == ACT_GLU && (j & 2)) continue;
       float s2 = 0.f, s1 = 0.f;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = m0 + wm * WM + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-          const float z = acc[i][(ACT == ACT_GLU) ? j + 1 : j][v];
-          const float gt = acc[i][j][v];
+        for (int e = 0; e < 4; ++e) {
+          const int row = m0 + wm * WM + i * 16 + 4 * quad + e;
+          constexpr int TNM1 = TN - 1;
+          const int j1 = j + 2 < TN ? j + 2 : TNM1;
+          const float z = acc[i][(ACT == ACT_GLU) ? j1 : j][e];
+          const float gt = acc[i][j][e];
           // same activation forms as the forward epilogue: the scores rank what the forward computes
           // (the erf form costs about a fifth of the calibration pass, nothing hides it at one
           // workgroup per CU)
@@ -191,17 +198,18 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, f32x16_t (&acc)
           s2 += h * h;
           s1 += fabsf(h);
         }
-      s2 += __shfl_xor(s2, 32);
-      s1 += __shfl_xor(s1, 32);
-      if (lane < 32) {
-        const int cl = (wn * WN + j * 32) / JSTEP + lane;
+      s2 += __shfl_xor(s2, 16); s2 += __shfl_xor(s2, 32);
+      s1 += __shfl_xor(s1, 16); s1 += __shfl_xor(s1, 32);
+      if (lane < 16) {
+        const int c = wn * WN + j * 16;
+        const int cl = ((ACT == ACT_GLU) ? (c >> 6) * 32 + (c & 31) : c) + lane;
         red2[wm * BNO + cl] = s2;
         red1[wm * BNO + cl] = s1;
       }
     }
     __syncthreads();
     for (int t = tid; t < BNO; t += NT) {
-      const int col = n0 / JSTEP + t;
+      const int col = ((ACT == ACT_GLU) ? n0 / 2 : n0) + t;
       if (col < p.n_out) {
         float a2 = 0.f, a1 = 0.f;
 #pragma unroll
@@ -213,13 +221,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, f32x16_t (&acc)
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Direct-to-LDS variant: every wavefront instruction moves one 1 KiB operand block from global
-// memory straight into its LDS slot (global_load_lds_dwordx4), STAGES slabs deep, no staging
-// registers and no LDS store instructions.  One barrier per slab: it publishes the slab that is
-// about to be consumed and retires the one consumed last, whose slot the new loads overwrite.
-typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
+// 16 bytes per lane from base + lane offset + scalar offset straight into LDS (1 KiB per
+// wavefront instruction, lane l to dst + 16 l); the buffer resource spans the address space: the
+// callers' offsets never leave the operands
+__device__ __forceinline__ void buffer_to_lds(const void* base, lptr_t dst, uint32_t lane_off, uint32_t scalar_off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00027000), dst, 16,
+                                           lane_off, scalar_off, 0, 0);
+}
 
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt in
 // imm[3:0] and imm[15:14], expcnt imm[6:4], lgkmcnt imm[11:8])
@@ -227,51 +236,41 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
 }
+template <int N>
+__device__ __forceinline__ void wait_lgkmcnt() {
+  __builtin_amdgcn_s_waitcnt(0xc07f | ((N < 15 ? N : 15) << 8));
+}
 // workgroup barrier without a memory fence (the kernel orders its loads with explicit counters);
 // the memory clobber keeps the compiler from moving LDS accesses across it
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
+#define FFS_ORDER __builtin_amdgcn_sched_barrier(0)   // instructions keep the written order
 
-// KG > 1 splits the reduction inside the workgroup: KG groups of WGM x WGN wavefronts each take
-// every KG-th part of a slab for the same output tile; the groups' accumulators are summed through
-// LDS in a fixed order before the epilogue.  This gives small products (few tiles, long K)
-// more wavefronts per CU without partial sums in global memory.
-// wavefronts per SIMD the kernel is compiled for: a wave tile of 16 or more 32 x 32 accumulator
-// tiles (256+ registers) runs alone on its SIMD, with 512 registers per lane
-constexpr int gemm_waves_per_simd(int wm, int wn) { return (wm / 32) * (wn / 32) >= 16 ? 1 : 2; }
-
-template <int BM, int BN, int BK, int WGM, int WGN, int KG, int STAGES, int ACT, bool DUAL, bool SCORE, bool A_TILED,
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA, int ACT, bool DUAL, bool SCORE, bool A_TILED,
           bool EPI>
-__global__ void __launch_bounds__(WGM* WGN* KG * 64)
-    __attribute__((amdgpu_waves_per_eu(gemm_waves_per_simd(BM / WGM, BN / WGN), gemm_waves_per_simd(BM / WGM, BN / WGN))))
+__global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm_bf16_dl_kernel(const GemmArgs p) {
-  constexpr int NWT = WGM * WGN;               // wavefronts per k group
-  constexpr int NW = NWT * KG;
+  constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
-  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int TM = WM / 16, TN = WN / 16;    // 16x16 MFMA tiles of a wavefront
   constexpr int NA = DUAL ? 2 : 1;
-  constexpr int KB = BK / 16;                  // k blocks per slab
-  constexpr int KS = KB / KG;                  // k steps of a slab per wavefront
-  constexpr int A_BLK = NA * (BM / 32) * KB;   // 1 KiB blocks of one slab
-  constexpr int B_BLK = (BN / 32) * KB;
+  constexpr int A_BLK = NA * (BM / 16);        // 1 KiB operand blocks of one 32-deep slab
+  constexpr int B_BLK = BN / 16;
   // loads per wavefront and slab; where the weights' blocks do not divide over the wavefronts the
-  // last round is padded with repeats of the tile's last row block, which land in spare slots
-  // that nothing reads (every wavefront then issues the same number of loads, which the
-  // wait counts below rely on)
+  // last round is padded with repeats of the tile's last block, which land in spare slots that
+  // nothing reads (every wavefront then issues the same number of loads, which the wait counts
+  // below rely on)
   constexpr int LA = A_BLK / NW, LB = (B_BLK + NW - 1) / NW, LPW = LA + LB;
   constexpr int STAGE = (A_BLK + LB * NW) * 64;  // 16-byte chunks per stage
-  constexpr bool SWAP = !SCORE;
   static_assert(A_BLK % NW == 0, "the tokens' blocks must divide over the wavefronts");
-  static_assert(KB % KG == 0 && (KS == 1 || KS == 2), "one or two k steps per wavefront and slab");
-  static_assert(STAGES >= 2 && (STAGES - 1) * LPW + LPW <= 63, "loads in flight must fit the counter");
-  static_assert(ACT != ACT_GLU || (TN % 2 == 0), "GLU needs paired column blocks per wave");
-  static_assert(!(SCORE && KG > 1), "the score epilogue has no in-workgroup split");
+  static_assert(STAGES >= 3 && STAGES * LPW <= 63, "loads in flight must fit the counter");
+  static_assert(ACT != ACT_GLU || WN % 64 == 0, "(gate, up) pairs must lie inside one wavefront");
+  static_assert(TM % 2 == 0 && (!DUAL || A_TILED), "row tiles are stored in pairs; two left operands are tiled");
 
   extern __shared__ u32x4_t smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = wave / NWT, wloc = wave % NWT;
-  const int wm = wloc / WGN, wn = wloc % WGN;
+  const int wm = wave / WGN, wn = wave % WGN;
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tiles_m = (p.M + BM - 1) / BM;
   const int logical = xcd_remap(blockIdx.x, tiles_m * tiles_n);
@@ -282,306 +281,231 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
   const int m0 = tm * BM, n0 = tn * BN;
 
   // K range of this split (whole slabs)
-  const int kt_total = (p.K + BK - 1) / BK;
+  const int kt_total = (p.K + 31) / 32;
   const int kt_per = (kt_total + (int)gridDim.y - 1) / (int)gridDim.y;
   const int kt0 = blockIdx.y * kt_per;
   const int nk = min(kt_total, kt0 + kt_per) - kt0;
 
   // ---- the LPW blocks this wavefront moves per slab: block b = wave + i NW of the stage
-  // Row-major A: one load instruction covers 64 / CH rows x the slab's CH 16-byte chunks of each
-  // (32-deep slabs: 16 rows x 64 contiguous bytes = 16 cache lines; 64-deep: 8 rows x 128 bytes
-  // = 8 lines) instead of 32 rows x 32 bytes; the chunks are placed so that the fragment reads
-  // stay free of bank conflicts.
-  constexpr bool rowsN = !A_TILED && !DUAL && (KB == 2 || KB == 4);
-  constexpr int CH = 2 * KB, RPI = 64 / CH;   // chunks per row and slab, rows per instruction
-  // chunk swizzle of row rowl of block kb: 16 consecutive lanes of a fragment read (rows r..r+15,
-  // one chunk number) must fall into 16 different 16-byte bank groups
-  auto swz = [](int rowl, int kb) { return KB == 2 ? ((rowl >> 2) & 3) : ((rowl >> 1) | ((kb & 1) << 2)); };
-  const char* src[LPW];
-  const char* a_row[LA];   // row-major A: start of the lane's row (substitute for chunks past K)
-  int a_col[LA];           // row-major A: column of the lane's chunk inside the slab
+  // Tiled operands: the block's address is uniform, the lane adds 16 bytes times its number.
+  // Row-major A: one load instruction covers 16 rows x the slab's four 16-byte chunks; chunk c of
+  // row r goes to position 4 r + (c ^ (r >> 2)), so that the fragment reads (16 rows, one chunk
+  // number) of 16 consecutive lanes fall into 16 different 16-byte bank groups.
+  // All loads are buffer loads: the tile's base in scalar registers, a byte offset per lane that the
+  // loop never changes, and a scalar offset that walks along K.
+  uint32_t soff[LPW];       // uniform: the block's offset inside the tile
+  uint32_t a_row[LA];       // row-major A: offset of the lane's row from row m0
+  const uint32_t a_col = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;   // row-major A: the lane's chunk (column in the slab)
   const int mrb_last = (p.M + 31) / 32 - 1, nrb_last = (p.N + 31) / 32 - 1;
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
     const int b = wave + i * NW;
-    const int s = b / ((BM / 32) * KB), rb = (b / KB) % (BM / 32), kb = b % KB;
-    const char* base = (DUAL && s) ? (const char*)p.A1 : (const char*)p.A;
+    soff[i] = 0; a_row[i] = 0;
     if (A_TILED) {
-      int grb = m0 / 32 + rb;
-      grb = grb <= mrb_last ? grb : mrb_last;
-      src[i] = base + (((int64_t)grb * (p.lda / 16) + (int64_t)kt0 * KB + kb) * 64 + lane) * 16;
-      a_row[i] = nullptr; a_col[i] = 0;
+      const int rb = min(m0 / 32 + (b / 2) % (BM / 32), mrb_last) - m0 / 32;
+      soff[i] = ((uint32_t)rb * (uint32_t)(p.lda / 16) + (b & 1)) * 1024;
     } else {
-      int row = m0 + rb * 32 + (lane & 31);
-      a_col[i] = kb * 16 + (lane >> 5) * 8;
-      if (rowsN) {
-        // block (rb, kb) holds rows RPI kb .. RPI kb + RPI - 1 of the row block with all CH
-        // chunks of the slab: lane = CH rowl + position, chunk = position ^ swz
-        const int rowl = lane / CH;
-        row = m0 + rb * 32 + kb * RPI + rowl;
-        a_col[i] = ((lane % CH) ^ swz(rowl, kb)) * 8;
-      }
-      row = row < p.M ? row : p.M - 1;
-      a_row[i] = base + (int64_t)row * p.lda * 2;
-      src[i] = a_row[i] + ((int64_t)kt0 * BK + a_col[i]) * 2;
+      a_row[i] = (uint32_t)(min(m0 + b * 16 + (lane >> 2), p.M - 1) - m0) * (uint32_t)(p.lda * 2);
     }
-  }
-  // LDS offset (16-byte units) of the lane's A fragment inside a row block's KB blocks, per k block
-  int a_frag[2];   // per k step of the wavefront inside a slab
-  a_frag[0] = lane; a_frag[1] = 64 + lane;
-  if (rowsN) {
-    const int r = lane & 31, c = lane >> 5, kbr = r / RPI, rowl = r % RPI;
-#pragma unroll
-    for (int ls = 0; ls < KS; ++ls)
-      a_frag[ls] = kbr * 64 + rowl * CH + ((2 * (kg * KS + ls) + c) ^ swz(rowl, kbr));
   }
 #pragma unroll
   for (int i = 0; i < LB; ++i) {
-    const int b = wave + i * NW;
-    const int rb = min(b / KB, BN / 32 - 1), kb = b % KB;
-    int grb = n0 / 32 + rb;
-    grb = grb <= nrb_last ? grb : nrb_last;
-    src[LA + i] = (const char*)p.Bt + (((int64_t)grb * (p.ldb / 16) + (int64_t)kt0 * KB + kb) * 64 + lane) * 16;
+    const int b = min(wave + i * NW, B_BLK - 1);
+    const int rb = min(n0 / 32 + b / 2, nrb_last) - n0 / 32;
+    soff[LA + i] = ((uint32_t)rb * (uint32_t)(p.ldb / 16) + (b & 1)) * 1024;
   }
+  const uint32_t lane16 = lane * 16;
+  auto tile_base = [&](const void* a) {
+    return A_TILED ? (const char*)a + ((int64_t)(m0 / 32) * (p.lda / 16) + 2 * kt0) * 1024
+                   : (const char*)a + (int64_t)m0 * p.lda * 2;
+  };
+  const char* const base_a = tile_base(p.A);
+  const char* const base_a1 = tile_base(DUAL ? p.A1 : p.A);
+  const char* const base_b = (const char*)p.Bt + ((int64_t)(n0 / 32) * (p.ldb / 16) + 2 * kt0) * 1024;
 
-  // Part q of KS of the loads of slab rel (spread over the k steps, between the MFMAs)
-  auto issue_part = [&](int rel, int stage, int q) {
-    u32x4_t* st = smem + stage * STAGE;
-#pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-      if (i * KS / LPW != q) continue;
-      const char* g;
-      int slot;
-      if (i < LA) {
-        slot = wave + i * NW;
-        if (A_TILED) {
-          g = src[i] + (int64_t)rel * (KB * 1024);
-        } else {
-          // a chunk past K reads the start of the row instead: the weights are zero there
-          g = ((kt0 + rel) * BK + a_col[i] < p.K) ? src[i] + (int64_t)rel * (BK * 2) : a_row[i];
-        }
-      } else {
-        slot = A_BLK + wave + (i - LA) * NW;
-        g = src[i] + (int64_t)rel * (KB * 1024);
-      }
-      __builtin_amdgcn_global_load_lds((gptr_t)g, (lptr_t)(st + slot * 64), 16, 0, 0);
+  // load number i of slab rel into a stage; check: the slab may reach past K (row-major A)
+  auto issue = [&](int i, int rel, int stage, bool check) {
+    const int slot = i < LA ? wave + i * NW : A_BLK + wave + (i - LA) * NW;
+    const lptr_t dst = (lptr_t)(smem + stage * STAGE + slot * 64);
+    if (i >= LA) {
+      buffer_to_lds(base_b, dst, lane16, soff[i] + rel * 2048);
+    } else if (A_TILED) {
+      // (with two left operands the first BM / 16 blocks are A's, the others A1's: uniform per i)
+      static_assert(!DUAL || (BM / 16) % NW == 0, "a load belongs to one left operand");
+      buffer_to_lds((DUAL && i >= LA / 2) ? base_a1 : base_a, dst, lane16, soff[i] + rel * 2048);
+    } else if (!check) {
+      buffer_to_lds(base_a, dst, a_row[i] + a_col * 2, (kt0 + rel) * 64);
+    } else {
+      // a chunk past K reads the start of the row instead: the weights are zero there
+      const uint32_t col = (kt0 + rel) * 32 + a_col;
+      buffer_to_lds(base_a, dst, a_row[i] + (col < (uint32_t)p.K ? col * 2 : 0), 0);
     }
   };
 
-  f32x16_t acc[TM][TN];
+  f32x4_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   // Residual stream of an un-activated product: the accumulators start from it (same lane
-  // layout as the store epilogue: row lane & 31, columns 8 g + 4 (lane >> 5) + 0..3 of each
-  // tile), so its loads overlap the filling of the ring instead of forming one dependent
-  // round trip per tile between the last product and the stores.  This workgroup alone
-  // reads and later writes these elements, so the destination may be the residual buffer.
-  if (EPI && ACT == ACT_NONE && !SCORE && SWAP) {
-    if (p.resid != nullptr && !p.partial && !p.c0_tiled && kg == 0) {
+  // layout as the store epilogue), so its loads overlap the filling of the ring instead of forming
+  // one dependent round trip per tile between the last product and the stores.  This workgroup
+  // alone reads and later writes these elements, so the destination may be the residual buffer.
+  if (EPI && ACT == ACT_NONE && !SCORE) {
+    if (p.resid != nullptr && !p.partial && !p.c0_tiled) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        const int cb = n0 + wn * WN + j * 32;
+        const int cb = n0 + wn * WN + j * 16;
         if (cb >= p.N || cb >= p.split_col) continue;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-          const int row = m0 + wm * WM + i * 32 + (lane & 31);
-          if (row >= p.M) continue;
-          const float* rrow = p.resid + (int64_t)row * p.ldr + cb + 4 * (lane >> 5);
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            if (cb + 8 * g + 4 * (lane >> 5) < p.n_store) {
-              const float4 r4 = *(const float4*)(rrow + 8 * g);
-              acc[i][j][4 * g] = r4.x; acc[i][j][4 * g + 1] = r4.y; acc[i][j][4 * g + 2] = r4.z; acc[i][j][4 * g + 3] = r4.w;
-            }
+          const int row = m0 + wm * WM + i * 16 + (lane & 15);
+          if (row < p.M && cb + 4 * (lane >> 4) < p.n_store)
+            acc[i][j] = *(const f32x4_t*)(p.resid + (int64_t)row * p.ldr + cb + 4 * (lane >> 4));
         }
       }
     }
   }
 
-  // Fragment reads run one k step ahead of the MFMAs (two register sets), also across the
-  // slab boundary, so LDS traffic overlaps the matrix pipeline instead of following a barrier.
-  Frag fa[2][NA][TM], fb[2][TN];
-  auto read_frags = [&](int set, int stage, int ls) {
-    const int ks = kg * KS + ls;   // this wavefront's k block of the slab
-    const u32x4_t* sA = smem + stage * STAGE;
-    const u32x4_t* sB = sA + A_BLK * 64;
+  // Fragments: lane l of a 16-row tile holds row l & 15, k elements 8 (l >> 4) .. + 7 of the slab.
+  // Tiled operands: two 32x16 blocks per 32 rows, the tile's half of each.
+  Frag fa[DBLA ? 2 : 1][NA][TM], fb[2][TN];
+  const int tfrag = (lane >> 5) * 64 + ((lane >> 4) & 1) * 32 + (lane & 15);
+  const int rfrag = (lane & 15) * 4 + ((lane >> 4) ^ ((lane >> 2) & 3));
+  auto tile_off = [](int x) { return (x >> 1) * 128 + (x & 1) * 16; };   // tiled operand: 16-row tile x
+  const int a_off = A_TILED ? tfrag + wm * (TM / 2) * 128 : rfrag + wm * TM * 64;
+  const int b_off0 = A_BLK * 64 + tfrag + tile_off(wn * TN), b_off1 = A_BLK * 64 + tfrag + tile_off(wn * TN + 1);
+  auto read_a = [&](int set, int i, const u32x4_t* st) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int s = 0; s < NA; ++s) {
-        if (rowsN)
-          fa[set][s][i].u = sA[(wm * TM + i) * KB * 64 + a_frag[ls]];
-        else
-          fa[set][s][i].u = sA[((s * (BM / 32) + wm * TM + i) * KB + ks) * 64 + lane];
-      }
-#pragma unroll
-    for (int jj = 0; jj < TN; ++jj) fb[set][jj].u = sB[((wn * TN + jj) * KB + ks) * 64 + lane];
+    for (int s = 0; s < NA; ++s)
+      fa[DBLA ? set : 0][s][i].u = A_TILED ? st[a_off + s * (BM / 16) * 64 + tile_off(i)] : st[a_off + i * 64];
   };
-  auto mfma_step = [&](int set) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int jj = 0; jj < TN; ++jj) {
-        const Frag& af = fa[set][DUAL ? (jj & 1) : 0][i];
-        if (SWAP)
-          acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][jj].v, af.v, acc[i][jj], 0, 0, 0);
-        else
-          acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af.v, fb[set][jj].v, acc[i][jj], 0, 0, 0);
-      }
+  auto read_b = [&](int set, int j, const u32x4_t* st) {
+    fb[set][j].u = st[((j & 1) ? b_off1 : b_off0) + (j >> 1) * 128];
   };
-  // Instruction order of one k step: the memory instructions (first the LDS reads of the next
-  // step, then the direct loads) are dealt out evenly between the MFMAs; bursts of memory
-  // instructions stall the issuing wavefront and with it the matrix pipeline.
-  auto order_step = [&](auto nl) {
-    constexpr int nload = decltype(nl)::value;
-    constexpr int NR = NA * TM + TN, NM = TM * TN, TOT = NR + nload;
-    constexpr int PER = TOT / NM, REM = TOT % NM;
-    int done = 0;
-#pragma unroll
-    for (int m = 0; m < NM; ++m) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      const int cnt = PER + (m < REM ? 1 : 0);
-#pragma unroll
-      for (int q = 0; q < cnt; ++q) {
-        if (done < NR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        else __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-        ++done;
-      }
-    }
+  auto mma = [&](int set, int i, int j) {
+    const Frag& a = fa[DBLA ? set : 0][DUAL ? (j >> 1) & 1 : 0][i];
+    const Frag& b = fb[set][j];
+    if (SCORE) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, acc[i][j], 0, 0, 0);
+    else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.v, a.v, acc[i][j], 0, 0, 0);
   };
-  // slab s has landed once at most the loads of the slabs issued after it are outstanding;
-  // `last` is the last slab issued so far
-  auto wait_landed = [&](int s, int last, auto full) {
-    if (decltype(full)::value) {
-      wait_vmcnt<(STAGES - 2) * LPW>();
-    } else {
-      const int later = min(nk - 1, last) - s;
-      if (later <= 0) wait_vmcnt<0>();
-      else if (later == 1) wait_vmcnt<LPW>();
-      else if (later == 2) wait_vmcnt<2 * LPW>();
-      else if (later == 3) wait_vmcnt<3 * LPW>();
-      else if (later == 4) wait_vmcnt<4 * LPW>();
-      else if (later == 5) wait_vmcnt<5 * LPW>();
-      else wait_vmcnt<6 * LPW>();
-    }
+  // at most `later` slabs of loads may still be in flight
+  auto wait_slabs = [&](int later) {
+    if (later <= 0) wait_vmcnt<0>();
+    else if (later == 1) wait_vmcnt<LPW>();
+    else if (later == 2) wait_vmcnt<2 * LPW>();
+    else wait_vmcnt<3 * LPW>();
   };
-  static_assert(STAGES <= 8, "wait_landed covers up to six slabs in flight behind the awaited one");
+  static_assert(STAGES <= 5, "wait_slabs covers three slabs in flight");
 
-  // The wavefront's local k steps n = 0, 1, ... (slab n / KS, step n % KS).  During step n the
-  // fragments of step n + 1 are read.  Right after the reads of a slab's last step are issued
-  // comes that slab's barrier: it publishes the next slab (whose first read follows) and
-  // retires this one, whose stage the loads issued from then on refill STAGES slabs ahead.
-  const int nsteps = nk * KS;
-  // prologue: with one step per slab all STAGES stages are filled; with two, the last stage gets
-  // its first part only (its second part goes out with step 0, like every later slab's)
+  // Step s multiplies slab s from registers, reads the fragments of slab s + 1 and has one barrier,
+  // placed where the reads it depends on were issued long before (waiting for reads that were only
+  // just issued stalls every wavefront of the workgroup at the same point).
+  //   DBLA: all reads of slab s + 1 are dealt out over the first five eighths of the MFMAs; the
+  //     barrier after three quarters retires slab s + 1 (it is in registers now) and publishes
+  //     slab s + 2; slab s + 1 + STAGES goes out behind it.
+  //   otherwise: fragment row i of the left operand is overwritten as soon as its MFMAs are issued,
+  //     so the reads of slab s + 1 end with the step; the barrier in the middle retires slab s and
+  //     publishes slab s + 2; slab s + STAGES goes out behind it.
+  constexpr int AHEAD = DBLA ? 1 : 0;
 #pragma unroll
   for (int s = 0; s < STAGES; ++s)
     if (s < nk) {
 #pragma unroll
-      for (int q = 0; q < KS; ++q)
-        if (KS == 1 || s < STAGES - 1 || q == 0) issue_part(s, s, q);
+      for (int i = 0; i < LPW; ++i) issue(i, s, s, true);
     }
+  int stage = 0;   // stage of slab s
   if (nk > 0) {
-    wait_landed(0, KS == 1 ? STAGES - 1 : STAGES - 2, std::false_type{});
+    wait_slabs(min(nk, STAGES) - 2);   // slabs 0 and 1
     lds_barrier();
-    read_frags(0, 0, 0);
-    if (KS == 1) {
-      // slab 0 is already retired by that read: its barrier
-      wait_landed(1, STAGES - 1, std::false_type{});
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < TN; ++j) read_b(0, j, smem);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) read_a(0, i, smem);
+    if (DBLA) {
+      wait_lgkmcnt<0>();
+      lds_barrier();
+      if (STAGES < nk) {
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) issue(i, STAGES, 0, true);
+      }
     }
   }
-  // One unrolled group of U steps starting at step n0 (n0 % U == 0 keeps register sets and
-  // slab-local step numbers static).  FULL: every load referred to exists.
-  constexpr int U = 2;
-  int slab = 0, stage = 0;   // slab and stage of step n0
-  auto group = [&](int n0, auto full) {
-    constexpr bool FULL = decltype(full)::value;
+  auto step = [&](int s, auto setc, auto fullc) {
+    constexpr int set = decltype(setc)::value;
+    constexpr bool FULL = decltype(fullc)::value;   // every slab referred to exists, none reaches past K
+    const int ns = stage + 1 == STAGES ? 0 : stage + 1;
+    const u32x4_t* nx = smem + ns * STAGE;          // (past the end: stale data that is never used)
+    const int put = s + AHEAD + STAGES;             // the slab whose loads go out in this step
+    auto sync = [&](auto younger) {
+      if (FULL) wait_vmcnt<(STAGES - 3 + AHEAD) * LPW>();
+      else wait_slabs(min(nk - 1, put - 1) - (s + 2));
+      wait_lgkmcnt<decltype(younger)::value>();
+      lds_barrier();
+      FFS_ORDER;
+    };
+    FFS_ORDER;
+    if constexpr (DBLA) {
+      constexpr int NM = TM * TN, NR = TM + TN, RD = NM * 5 / 8, SB = NM * 3 / 4;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int ls = KS == 1 ? 0 : u;                 // step inside its slab
-      const bool last_of_slab = (ls == KS - 1);
-      const int nstage = stage + 1 == STAGES ? 0 : stage + 1;
-      // the step being prefetched: (slab, ls + 1) or (slab + 1, 0)
-      const int pslab = last_of_slab ? slab + 1 : slab;
-      const int pstage = last_of_slab ? nstage : stage;
-      const int pls = last_of_slab ? 0 : ls + 1;
-      if (FULL || n0 + u < nsteps) {
-        read_frags((u + 1) & 1, pstage, pls);   // (past the end: stale data that is never used)
-        // Loads: the latest barrier before this step retired slab r (with two steps per slab,
-        // r = slab - 1 at step 0, where stage "r = -1" is the last, still empty one); the parts
-        // of slab r + STAGES go out with the steps that follow that barrier.
-        {
-          const int r = KS == 1 ? slab : (ls == 0 ? slab - 1 : slab);
-          const int rstage = KS == 1 ? stage : (ls == 0 ? (stage == 0 ? STAGES - 1 : stage - 1) : stage);
-          const int q = KS == 1 ? 0 : (ls == 0 ? 1 : 0);
-          if (FULL || r + STAGES < nk) issue_part(r + STAGES, rstage, q);
+      for (int q = 0; q < NM; ++q) {
+        const int i = q / TN, j = (i & 1) ? TN - 1 - q % TN : q % TN;
+        mma(set, i, j);
+        FFS_ORDER;
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+          if (r * RD / NR == q) {
+            if (r < TN) read_b(set ^ 1, r, nx);
+            else read_a(set ^ 1, r - TN, nx);
+          }
+        FFS_ORDER;
+        if (q == SB - 1) sync(std::integral_constant<int, 0>{});
+#pragma unroll
+        for (int l = 0; l < LPW; ++l)
+          if (SB + l * (NM - SB) / LPW == q && (FULL || put < nk)) issue(l, put, ns, !FULL);
+        FFS_ORDER;
+      }
+    } else {
+      constexpr int RB = TM / 2 - 1;   // the barrier follows this row
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int jj = 0; jj < TN; ++jj) {
+          mma(set, i, (i & 1) ? TN - 1 - jj : jj);
+          FFS_ORDER;
+          // the row's share of the next slab's weight fragments, spread over its MFMAs
+#pragma unroll
+          for (int q = 0; q < TN; ++q)
+            if (q * TM == i * TN + jj) read_b(set ^ 1, q, nx);
+          FFS_ORDER;
         }
-        mfma_step(u & 1);
-        if (FULL) {
-          if (KS == 1) order_step(std::integral_constant<int, LPW>{});
-          else if (ls == 0) order_step(std::integral_constant<int, LPW - (LPW + 1) / 2>{});   // part 1
-          else order_step(std::integral_constant<int, (LPW + 1) / 2>{});                        // part 0
-        }
-        // barrier of slab pslab once the reads of its last step are issued
-        if (pls == KS - 1) {
-          wait_landed(pslab + 1, pslab + STAGES - 1, full);
-          asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        read_a(0, i, nx);
+        FFS_ORDER;
+        if (i == RB) sync(std::integral_constant<int, NA*(RB + 1) + ((RB + 1) * TN + TM - 1) / TM>{});
+        if (i > RB) {
+#pragma unroll
+          for (int l = 0; l < LPW; ++l)
+            if (l * (TM - RB - 1) / LPW == i - RB - 1 && (FULL || put < nk)) issue(l, put, stage, !FULL);
+          FFS_ORDER;
         }
       }
-      if (last_of_slab) { slab += 1; stage = nstage; }
     }
+    stage = ns;
   };
-  int n = 0;
-  // FULL while the group's last retired slab r satisfies r + STAGES < nk and the prefetched slab
-  // + STAGES - 1 <= nk - 1 (so the fixed wait count is right)
-  for (; (n + U - 1) / KS + 1 + STAGES < nk; n += U) group(n, std::true_type{});
-  for (; n < nsteps; n += U) group(n, std::false_type{});
-
-  if (KG > 1) {
-    // Sum the k groups' accumulators: groups 1 .. KG-1 park theirs in LDS (a lane's 16 bytes of
-    // one 32x32 tile quarter, contiguous per wavefront instruction), group 0 adds them in order.
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    constexpr int PER_WAVE = TM * TN * 4 * 64;   // 16-byte chunks parked per wavefront
-#pragma unroll 1
-    for (int g = 1; g < KG; ++g) {
-      if (kg == g) {
-        u32x4_t* dst = smem + wloc * PER_WAVE + lane;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const u32x4_t v = {__float_as_uint(acc[i][j][4 * q]), __float_as_uint(acc[i][j][4 * q + 1]),
-                                 __float_as_uint(acc[i][j][4 * q + 2]), __float_as_uint(acc[i][j][4 * q + 3])};
-              dst[((i * TN + j) * 4 + q) * 64] = v;
-            }
-      }
-      __syncthreads();
-      if (kg == 0) {
-        const u32x4_t* srcp = smem + wloc * PER_WAVE + lane;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const u32x4_t v = srcp[((i * TN + j) * 4 + q) * 64];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += __uint_as_float(v[e]);
-            }
-      }
-      if (g + 1 < KG) __syncthreads();
-    }
-    if (kg != 0) return;
+  int s = 0;
+  for (; s + 2 + AHEAD + STAGES < nk; s += 2) {
+    step(s, std::integral_constant<int, 0>{}, std::true_type{});
+    step(s + 1, std::integral_constant<int, 1>{}, std::true_type{});
   }
-  if (SCORE) lds_barrier();   // the epilogue reuses the stage memory
-  gemm_epilogue<BM, BN, WGM, WGN, ACT, SCORE, EPI>(p, acc, m0, n0, tm, wm, wn, lane, tid & (NWT * 64 - 1), smem);
+  for (; s < nk; s += 2) {
+    step(s, std::integral_constant<int, 0>{}, std::false_type{});
+    if (s + 1 < nk) step(s + 1, std::integral_constant<int, 1>{}, std::false_type{});
+  }
+  if (SCORE) {
+    wait_lgkmcnt<0>();
+    lds_barrier();   // the epilogue reuses the stage memory
+  }
+  gemm_epilogue<BM, BN, WGM, WGN, ACT, SCORE, EPI>(p, acc, m0, n0, tm, wm, wn, lane, tid, smem);
 }
 
 // Sum of fp32 split-K partials [n_split][M][N] (fixed order) -> bf16, tiled or row-major.
@@ -724,16 +648,13 @@ int launch_splitk_epilogue(const float* part, int n_split, int ldp, const GemmAr
 
 // ------------------------------------------------------------------ host launcher
 
-template <int BM, int BN, int BK, int WGM, int WGN, int KG, int STAGES, int ACT, bool DUAL, bool SCORE, bool A_TILED,
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA, int ACT, bool DUAL, bool SCORE, bool A_TILED,
           bool EPI>
 static int launch_dl_epi(const GemmArgs& a, int n_split, hipStream_t st) {
-  constexpr int NA = DUAL ? 2 : 1;
-  constexpr int NWH = WGM * WGN * KG, BBLK = (BN / 32) * (BK / 16);
-  constexpr size_t ring = (size_t)STAGES * ((size_t)NA * BM * BK * 2 + (size_t)((BBLK + NWH - 1) / NWH) * NWH * 1024);
-  constexpr size_t park = KG > 1 ? (size_t)BM * BN * 4 : 0;   // one k group's accumulators
-  constexpr size_t lds = ring > park ? ring : park;
+  constexpr int NWH = WGM * WGN;
+  constexpr size_t lds = (size_t)STAGES * 1024 * ((DUAL ? 2 : 1) * (BM / 16) + (BN / 16 + NWH - 1) / NWH * NWH);
   static_assert(lds <= 160 * 1024, "LDS budget of a CU");
-  auto kern = gemm_bf16_dl_kernel<BM, BN, BK, WGM, WGN, KG, STAGES, ACT, DUAL, SCORE, A_TILED, EPI>;
+  auto kern = gemm_bf16_dl_kernel<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, EPI>;
   // The kernel needs more dynamic LDS than the default limit: the attribute is set once per
   // device and instantiation.  The only state kept is this set-once bit mask (one bit per
   // device ordinal); setting the attribute twice from racing first calls is harmless.
@@ -746,50 +667,57 @@ static int launch_dl_epi(const GemmArgs& a, int n_split, hipStream_t st) {
       return -1;
     if (dev < 64) configured.fetch_or(bit, std::memory_order_release);
   }
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL(kern, dim3(tiles, n_split), dim3(WGM * WGN * KG * 64), lds, st, a);
+  const int tiles_m = (a.M + BM - 1) / BM, tiles = tiles_m * ((a.N + BN - 1) / BN);
+  // Tiles are numbered down groups of group_m row tiles, consecutive ones on one XCD.  The R tiles
+  // that an XCD runs at a time then read group_m BM + (R / group_m) BN rows per slab into its L2:
+  // least at group_m = sqrt(R BN / BM).  (With group_m = 1 a product of 1000 tokens with a 22144-wide
+  // weight pulled all weights into every XCD: 225 us instead of 164.)
+  GemmArgs g = a;
+  if (g.group_m <= 0) {
+    const int per_cu = lds <= 80 * 1024 ? 2 : 1;
+    const int r = std::max(1, std::min(32 * per_cu, tiles / 8));
+    g.group_m = std::max(1, std::min(tiles_m, (int)(sqrt((double)r * BN / BM) + 0.5)));
+  }
+  hipLaunchKernelGGL(kern, dim3(tiles, n_split), dim3(NWH * 64), lds, st, g);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int KG, int STAGES, int ACT, bool DUAL, bool SCORE, bool A_TILED>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA, int ACT, bool DUAL, bool SCORE, bool A_TILED>
 static int launch_dl_cfg(const GemmArgs& a, int n_split, hipStream_t st) {
   // (the calibration product, the gated products and the two-operand product take no additions)
   if constexpr (!SCORE && !DUAL && ACT != ACT_GLU) {
     if (a.bias != nullptr || a.resid != nullptr || a.out_f32)
-      return launch_dl_epi<BM, BN, BK, WGM, WGN, KG, STAGES, ACT, DUAL, SCORE, A_TILED, true>(a, n_split, st);
+      return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true>(a, n_split, st);
   } else {
     if (a.bias != nullptr || a.resid != nullptr || a.out_f32) return -1;
   }
-  return launch_dl_epi<BM, BN, BK, WGM, WGN, KG, STAGES, ACT, DUAL, SCORE, A_TILED, false>(a, n_split, st);
+  return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false>(a, n_split, st);
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int KG, int STAGES>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA>
 static int launch_dl_shape(const GemmArgs& a, int act, int n_split, hipStream_t st) {
   const bool dual = a.A1 != nullptr;
   const bool at = a.a_tiled != 0;
+  if (dual) return -1;
   if (act == ACT_NONE)
-    return at ? launch_dl_cfg<BM, BN, BK, WGM, WGN, KG, STAGES, ACT_NONE, false, false, true>(a, n_split, st)
-              : launch_dl_cfg<BM, BN, BK, WGM, WGN, KG, STAGES, ACT_NONE, false, false, false>(a, n_split, st);
+    return at ? launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_NONE, false, false, true>(a, n_split, st)
+              : launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_NONE, false, false, false>(a, n_split, st);
   if (act == ACT_GELU)
-    return at ? launch_dl_cfg<BM, BN, BK, WGM, WGN, KG, STAGES, ACT_GELU, false, false, true>(a, 1, st)
-              : launch_dl_cfg<BM, BN, BK, WGM, WGN, KG, STAGES, ACT_GELU, false, false, false>(a, 1, st);
-  if constexpr (BN / WGN >= 64 && (BN / WGN / 32) % 2 == 0) {
-    if (act == ACT_GLU && !dual)
-      return at ? launch_dl_cfg<BM, BN, BK, WGM, WGN, KG, STAGES, ACT_GLU, false, false, true>(a, 1, st)
-                : launch_dl_cfg<BM, BN, BK, WGM, WGN, KG, STAGES, ACT_GLU, false, false, false>(a, 1, st);
-    if constexpr ((2 * (BM / 32) * (BK / 16)) % (WGM * WGN * KG) == 0) {
-      // two left operands double the A part of a stage: fewer stages where that keeps two
-      // workgroups per CU (80 KiB each)
-      // (a 256 x 256 tile runs one workgroup per CU anyway: it keeps its three stages, 144 KiB)
-      constexpr int DST = (BM * BN >= 256 * 256) ? STAGES
-                          : (((size_t)STAGES * (2 * BM + BN) * BK * 2 > 80 * 1024 && STAGES > 2) ? 2 : STAGES);
-      if constexpr ((size_t)DST * (2 * BM + BN) * BK * 2 <= 160 * 1024) {
-        if (act == ACT_GLU && dual && at)
-          return launch_dl_cfg<BM, BN, BK, WGM, WGN, KG, DST, ACT_GLU, true, false, true>(a, 1, st);
-      }
-    }
+    return at ? launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GELU, false, false, true>(a, 1, st)
+              : launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GELU, false, false, false>(a, 1, st);
+  if constexpr ((BN / WGN) % 64 == 0) {
+    if (act == ACT_GLU)
+      return at ? launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GLU, false, false, true>(a, 1, st)
+                : launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GLU, false, false, false>(a, 1, st);
   }
   return -1;
+}
+
+// the gated product with two left operands (A1)
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA>
+static int launch_dl_dual(const GemmArgs& a, int act, hipStream_t st) {
+  if (act != ACT_GLU || !a.a_tiled) return -1;
+  return launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GLU, true, false, true>(a, 1, st);
 }
 
 int bf16_score_tile_m() { return 256; }
@@ -799,18 +727,23 @@ int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_sp
   if (score) {
     // calibration: row-major tokens, column sums of the activations in the epilogue
     if (a.a_tiled) return -1;
-    if (act == ACT_GELU) return launch_dl_cfg<256, 256, 32, 2, 4, 1, 3, ACT_GELU, false, true, false>(a, 1, st);
-    if (act == ACT_GLU) return launch_dl_cfg<256, 256, 32, 2, 4, 1, 3, ACT_GLU, false, true, false>(a, 1, st);
+    if (act == ACT_GELU) return launch_dl_cfg<256, 256, 2, 4, 4, false, ACT_GELU, false, true, false>(a, 1, st);
+    if (act == ACT_GLU) return launch_dl_cfg<256, 256, 2, 4, 4, false, ACT_GLU, false, true, false>(a, 1, st);
+    return -1;
+  }
+  if (a.A1 != nullptr) {
+    switch (shape) {
+      case GEMM_128x128: return launch_dl_dual<128, 128, 2, 2, 3, true>(a, act, st);
+      case GEMM_256x256: return launch_dl_dual<256, 256, 4, 2, 3, false>(a, act, st);
+    }
     return -1;
   }
   switch (shape) {
-    case GEMM_256x128: return launch_dl_shape<256, 128, 32, 2, 2, 1, 3>(a, act, n_split, st);
-    case GEMM_128x128: return launch_dl_shape<128, 128, 32, 2, 2, 1, 3>(a, act, n_split, st);
-    case GEMM_128x128_KSPLIT: return launch_dl_shape<128, 128, 64, 2, 2, 2, 4>(a, act, n_split, st);
-    case GEMM_256x256: return launch_dl_shape<256, 256, 32, 2, 4, 1, 3>(a, act, n_split, st);
-    case GEMM_256x320: return launch_dl_shape<256, 320, 32, 4, 2, 1, 3>(a, act, n_split, st);
-    case GEMM_128x320: return launch_dl_shape<128, 320, 32, 2, 2, 1, 3>(a, act, n_split, st);
-    case GEMM_256x256_W64: return launch_dl_shape<256, 256, 32, 4, 2, 1, 3>(a, act, n_split, st);
+    case GEMM_128x128: return launch_dl_shape<128, 128, 2, 2, 4, true>(a, act, n_split, st);
+    case GEMM_128x256: return launch_dl_shape<128, 256, 1, 4, 3, true>(a, act, n_split, st);
+    case GEMM_128x320: return launch_dl_shape<128, 320, 2, 4, 4, true>(a, act, n_split, st);
+    case GEMM_256x256: return launch_dl_shape<256, 256, 2, 4, 4, false>(a, act, n_split, st);
+    case GEMM_256x320: return launch_dl_shape<256, 320, 2, 4, 4, false>(a, act, n_split, st);
   }
   return -1;
 }

@@ -22,6 +22,7 @@
 // Heavy bf16 weights use the same block order with 4 KiB blocks (one 16-byte
 // MFMA operand per lane and 32-element step).
 #include "int4.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace ffsplit {
@@ -900,6 +901,20 @@ static int phase2_splits(int G) {
   return S;
 }
 
+// bytes of the fp32 partial sums of one bf16 product (0: its reduction is not split)
+static size_t gemm_scratch(int64_t T, int N, int K, bool glu, bool dual) {
+  if (N <= 0 || K <= 0) return 0;
+  int ranges = gemm_plan(T, N, K, glu, dual, !dual).split;
+  // At a few hundred rows the size keeps room for one range per idle CU (128 x 128 tiles, at least
+  // 256 reduction elements each), whatever the plan takes of it.
+  const int tiles = (int)((T + 127) / 128) * ((N + 127) / 128);
+  if (!dual && T <= 1024 && tiles < 128) {
+    const int room = std::min(std::min(256 / tiles, K / 256), 16);
+    ranges = std::max(ranges, room);
+  }
+  return ranges > 1 ? (size_t)ranges * T * round_up(N, 32) * 4 : 0;
+}
+
 FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
   FwdWs w = {};
   if (d.rem_kind == FFSPLIT_REM_W3H8 && T <= W3H8_DECODE_MAX_T) {
@@ -974,50 +989,7 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
     if (scratch > 0) off = align256(off + scratch);
   }
   if (L.tiled && L.rp > 0 && L.mp > 0 && T > 0) {
-    // Split the long reduction of h2 * P2 across workgroups (more splits cost more partial-sum
-    // traffic than they gain: measured).  Narrow products (rank <= 512 at 4096 rows) use 128x128
-    // tiles with the in-workgroup K split, one workgroup per CU; wider ones use 256x128 tiles,
-    // two workgroups per CU, with the number of splits that fills the 512 slots best.
-    const int tiles128 = (int)((T + 127) / 128) * ((L.rp + 127) / 128);
-    const int max_sp = L.mp / 512 > 0 ? L.mp / 512 : 1;   // keep >= 8 slabs of 64 per split
-    int sp;
-    if (tiles128 <= 128 || T <= 1024) {
-      w.g3_wide = 0;
-      sp = 256 / (tiles128 > 0 ? tiles128 : 1);
-    } else {
-      w.g3_wide = 1;
-      const int tiles256 = (int)((T + 255) / 256) * ((L.rp + 127) / 128);
-      sp = 1;
-      double best = 0.0;
-      for (int c = 1; c <= 8; ++c) {
-        const int wgs = tiles256 * c;
-        const double fill = (double)wgs / (512.0 * ((wgs + 511) / 512));
-        if (fill > best + 0.03) { best = fill; sp = c; }
-      }
-      // 256 x 320 tiles (eight wavefronts with wave tiles of 64 x 160: fewer fragment reads and
-      // barriers per product than 256 x 128 on four) where the rank is a multiple of 320 and some
-      // split count fills whole rounds of one workgroup per CU (C5: rank 1280, 16 x 4 tiles x 4
-      // splits = 256 workgroups; 201 -> 175 us); likewise 256 x 256 tiles on eight wavefronts where
-      // the rank is a multiple of 256 (the Llama shape: rank 1024, 16 x 4 x 4; 94 -> 83 us)
-      if (L.rp % 320 == 0) {
-        const int t320 = (int)((T + 255) / 256) * (L.rp / 320);
-        for (int c = 1; c <= 8 && c <= max_sp; ++c) {
-          const int wgs = t320 * c;
-          if (100 * wgs / (256 * ((wgs + 255) / 256)) >= 95) { w.g3_wide = 2; sp = c; break; }
-        }
-      } else if (L.rp % 256 == 0) {
-        const int t256 = (int)((T + 255) / 256) * (L.rp / 256);
-        for (int c = 1; c <= 8 && c <= max_sp; ++c) {
-          const int wgs = t256 * c;
-          if (100 * wgs / (256 * ((wgs + 255) / 256)) >= 95) { w.g3_wide = 3; sp = c; break; }
-        }
-      }
-    }
-    if (sp > max_sp) sp = max_sp;
-    if (sp > 16) sp = 16;
-    if (sp < 1) sp = 1;
-    w.g3_split = sp;
-    size_t scratch = sp > 1 ? (size_t)sp * T * L.rp * 4 : 0;
+    size_t scratch = 0;
     if (ffn2_fused_applies(L, T)) {
       const size_t fb = (size_t)ffn2_fused_splits((int)T, L.mp) * T * L.rp * 4;
       if (fb > scratch) scratch = fb;
@@ -1030,29 +1002,22 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
       const size_t sk = skinny_part_bytes(n_max, (int)T);
       if (sk > scratch) scratch = sk;
     }
-    if (T > SKINNY_MAX_M && T <= 1024) {
-      // a few hundred rows: products with few tiles keep split-K partials of their whole output
-      // (all four products: h2 * P2 too, when its own split above came out as 1)
-      const int ns[4] = {L.n1, L.n_up * L.mp, L.rp, L.dn};
-      const int ks[4] = {L.dk, L.rp, L.mp, L.k4};
-      for (int i = 0; i < 4; ++i) {
-        const size_t b = (size_t)mid_split(T, ns[i], ks[i]) * T * round_up(ns[i], 32) * 4;
-        if (mid_split(T, ns[i], ks[i]) > 1 && b > scratch) scratch = b;
-      }
+    if (T > SKINNY_MAX_M) {
+      // fp32 partial sums of the products whose reduction is split
+      const size_t b[4] = {gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false),
+                           gemm_scratch(T, L.n_up * L.mp, L.rp, L.n_up == 2, L.n_up == 2),
+                           gemm_scratch(T, L.rp, L.mp, false, false), gemm_scratch(T, d.d_model, L.k4, false, false)};
+      for (size_t v : b)
+        if (v > scratch) scratch = v;
     }
     w.kpart_bytes = scratch;
     if (scratch > 0) off = align256(off + scratch);
   } else if (L.tiled && T > 0 && T <= SKINNY_MAX_M) {
     int n_max = L.n1 > L.dn ? L.n1 : L.dn;
     off = align256(off + skinny_part_bytes(n_max, (int)T));
-  } else if (L.tiled && T > SKINNY_MAX_M && T <= 1024) {
-    const int ns[2] = {L.n1, L.dn};
-    const int ks[2] = {L.dk, L.k4};
-    size_t scratch = 0;
-    for (int i = 0; i < 2; ++i) {
-      const size_t b = (size_t)mid_split(T, ns[i], ks[i]) * T * round_up(ns[i], 32) * 4;
-      if (mid_split(T, ns[i], ks[i]) > 1 && b > scratch) scratch = b;
-    }
+  } else if (L.tiled && T > SKINNY_MAX_M) {
+    const size_t b1 = gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false), b4 = gemm_scratch(T, d.d_model, L.k4, false, false);
+    const size_t scratch = b1 > b4 ? b1 : b4;
     w.kpart_bytes = scratch;
     if (scratch > 0) off = align256(off + scratch);
   }

@@ -5,6 +5,7 @@
 #include "../../include/ffsplit.h"
 #include <stddef.h>
 #include <stdint.h>
+#include "gemm_plan.h"
 
 namespace ffsplit {
 
@@ -123,18 +124,6 @@ inline ScoreWs make_score_ws(const ffsplit_desc_t& d, int64_t T) {
   return w;
 }
 
-// A few hundred rows (above the weight-streaming kernels, up to 1024): a product with fewer than
-// 128 tiles of 128 x 128 is split along its reduction into about 256 workgroups (at least 256
-// reduction elements each); its fp32 partials then take the epilogue in a second launch.
-inline int mid_split(int64_t T, int N, int K) {
-  const int tiles = (int)((T + 127) / 128) * ((N + 127) / 128);
-  if (tiles <= 0 || tiles >= 128) return 1;
-  int sp = 256 / tiles;
-  if (sp > K / 256) sp = K / 256;
-  if (sp > 16) sp = 16;
-  return sp > 1 ? sp : 1;
-}
-
 // fp32 path: a product with few 64 x 64 tiles (its workgroups each walk the whole reduction in
 // 16-deep slabs, one after the other) is split along the reduction into up to about 192
 // workgroups of at least 64 reduction elements; fp32 partials, then one summing launch that
@@ -150,10 +139,9 @@ inline int f32_split(int64_t T, int N, int K) {
 
 struct FwdWs {
   size_t off_cat, off_t, off_h2, off_kpart;
-  size_t kpart_bytes;   // bytes of split-K scratch at off_kpart (65..1024 rows: checked before use)
+  size_t kpart_bytes;   // bytes of split-K scratch at off_kpart (checked before use)
   int t_pad;       // rows of the intermediates (T, padded to 32 when tiled)
-  int g3_split;    // split-K factor of the h2 * P2 product
-  int g3_wide;     // that product has enough tiles for 256x128 tiles (else: in-workgroup K split)
+  int g3_split;    // fp32 path: split-K factor of the h2 * P2 product
   // INT4 decode scratch
   size_t off_h, off_part, off_cnt;
   int n_split;

@@ -1,0 +1,65 @@
+"""GPU parity of the large-batch product kernel at sizes that reach each of its tile shapes and
+reduction splits with remainders on every side (rows, columns, reduction depth), against the CPU
+oracle.  Bars: the task's (1e-2 relative Frobenius, 2e-2 worst row)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ffsplit_oracle as orc
+from gpu_util import dev, host, assert_close, Guarded
+
+pytestmark = pytest.mark.gpu
+
+# T, d_model, d_ff, k, rank, act: what the choice of tiles gives for the four products
+CASES = [
+    (65, 72, 97, 39, 17, "gelu"),            # one ragged 128x128 tile each
+    (565, 256, 87, 0, 3, "swiglu"),          # no heavy neuron, gated, 128x128
+    (2911, 200, 6019, 2763, 3, "gelu"),      # 128x320 and 128x256; third product in 11 ranges
+    (1838, 80, 5539, 1, 3, "gelu"),          # 16 ranges; first slab shorter than 32
+    (4080, 136, 2085, 36, 129, "gelu"),      # 128x320 second product, d_model % 32 = 8
+    (1393, 64, 5212, 47, 2, "swiglu"),       # two left operands on 256x256
+    (4889, 440, 3391, 13, 2, "gelu"),        # 256x320 second product
+    (5036, 1592, 294, 1, 10, "gelu"),        # 128x256 last product, first product in ranges
+    (4370, 1968, 146, 3, 67, "gelu"),        # 128x320 last product
+    (4717, 1696, 294, 68, 11, "swiglu"),
+]
+
+
+@pytest.mark.parametrize("T,d,d_ff,k,r,act", CASES)
+def test_every_tile_shape_matches_oracle(T, d, d_ff, k, r, act):
+    import paper_2401_04044_amd as ff
+    rng = np.random.default_rng(T)
+
+    def bf(shape, std):   # values exactly representable in bf16
+        t = torch.from_numpy((rng.standard_normal(shape) * std).astype(np.float32))
+        return t.to(torch.bfloat16).to(torch.float32).numpy()
+
+    glu, m = act == "swiglu", d_ff - k
+    X, W1, W2 = bf((T, d), 1.0), bf((d, d_ff), d ** -0.5), bf((d_ff, d), 0.05)
+    Wg = bf((d, d_ff), d ** -0.5) if glu else None
+    fac = {"P1": bf((d, r), d ** -0.5), "Q1": bf((r, m), r ** -0.5), "P2": bf((m, r), 0.05), "Q2": bf((r, d), 0.5),
+           "Pg": bf((d, r), d ** -0.5) if glu else None, "Qg": bf((r, m), r ** -0.5) if glu else None}
+    idx = rng.permutation(d_ff)[:k].astype(np.int32)
+    desc = ff.make_desc(d, d_ff, act, "bf16", k, "lowrank", r)
+    idx_d = torch.from_numpy(idx).cuda()
+    split = ff.build_split(desc, dev(W1, "bf16"), dev(Wg, "bf16"), dev(W2, "bf16"), idx_d,
+                           {nm: dev(v, "bf16") for nm, v in fac.items()})
+    g = Guarded(ff.workspace_bytes(desc, ff.WS_FORWARD, T))
+    Y, Yh, Yr = ff.forward(desc, split, dev(X, "bf16"), None, True, g.view)
+    g.check("forward")
+    want, w1, w2 = orc.forward_split(X, W1, W2, Wg, idx, act, "lowrank", fac)
+    name = f"T{T} d{d} f{d_ff} k{k} r{r} {act}"
+    assert_close(host(Y), want, "bf16", name + " Y")
+    assert_close(host(Yr), w2, "bf16", name + " Y_rem")
+    if k:
+        assert_close(host(Yh), w1, "bf16", name + " Y_heavy")
+    if not glu:
+        # the store step with bias, residual and fp32 destination on the same tiles
+        b1 = bf((d_ff,), 0.3)
+        b2, res = rng.standard_normal(d).astype(np.float32), rng.standard_normal((T, d)).astype(np.float32)
+        Y = ff.forward_ex(desc, split, dev(X, "bf16"), b1_packed=ff.pack_neuron_bias(desc, dev(b1, "bf16"), idx_d),
+                          b2=torch.from_numpy(b2).cuda(), residual=torch.from_numpy(res).cuda(), y_f32=True,
+                          workspace=g.view)
+        g.check("forward_ex")
+        want = orc.forward_split_biased(X, W1, W2, idx, "lowrank", fac, b1, b2, res)[0]
+        assert_close(host(Y), want, "bf16", name + " biased")
