@@ -64,22 +64,9 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
   auto koff_bytes = [&](int koff) -> size_t { return L.tiled ? (size_t)(koff / 16) * 1024 : (size_t)koff * esz; };
   // small batches are bound by streaming the weights: dedicated kernels
   const bool small_m = bf16 && M <= SKINNY_MAX_M;
-  auto run = [&](GemmArgs& g, int a, int n_split = 1) -> int {
+  auto run = [&](GemmArgs& g, int a) -> int {
     g.m_pad = w.t_pad;
-    if (!bf16) {
-      // few tiles: split the reduction, bias / activation / routing with the sum (never beyond
-      // the scratch the workspace was sized with: the plain launch is always valid)
-      const int sp = (g.partial || g.A1) ? 1 : f32_split(M, g.N, g.K);
-      if (sp > 1 && (size_t)sp * M * g.N * 4 <= w.kpart_bytes) {
-        float* part = (float*)(ws + w.off_kpart);
-        GemmArgs gp = g;
-        gp.partial = 1; gp.C0 = part; gp.ldc0 = g.N; gp.split_col = g.N; gp.act_cols = 0;
-        gp.bias = nullptr; gp.bias_cols = 0; gp.resid = nullptr; gp.out_f32 = 0;
-        if (launch_gemm_f32(gp, ACT_NONE, false, st, sp) != 0) return -1;
-        return launch_splitk_epilogue_f32(part, sp, g.N, g, a, st);
-      }
-      return launch_gemm_f32(g, a, false, st, n_split);
-    }
+    if (!bf16) return launch_gemm_f32(g, a, false, st);
     if (small_m && (g.N & 31) == 0) return launch_skinny_bf16(g, a, (float*)(ws + w.off_kpart), st);
     const bool dual = g.A1 != nullptr;
     const bool paired = a == ACT_GLU;
@@ -123,7 +110,7 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
                                        L.rp, part, sp2, st);
       if (rc < 0) return FFSPLIT_E_HIP;
       if (rc == 0) {
-        FFS_TRY(launch_splitk_reduce(part, sp2, M, L.rp, w.t_pad, cat + koff_bytes(L.kp), L.k4, L.tiled, st, 0));
+        FFS_TRY(launch_splitk_reduce(part, sp2, M, L.rp, w.t_pad, cat + koff_bytes(L.kp), L.k4, L.tiled, st));
         fused_mid = true;
       }
     }
@@ -145,15 +132,8 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
     g.Bt = sp + L.off_p2; g.ldb = L.mp;
     g.M = M; g.N = L.rp; g.K = L.mp;
     g.split_col = L.rp;
-    if (!bf16 && w.g3_split > 1) {
-      float* part = (float*)(ws + w.off_kpart);
-      g.partial = 1; g.C0 = part; g.ldc0 = L.rp;
-      FFS_TRY(run(g, ACT_NONE, w.g3_split));
-      FFS_TRY(launch_splitk_reduce(part, w.g3_split, M, L.rp, w.t_pad, cat + koff_bytes(L.kp), L.k4, L.tiled, st, 1));
-    } else {
-      g.C0 = cat + koff_bytes(L.kp); g.ldc0 = L.k4; g.c0_tiled = L.tiled;
-      FFS_TRY(run(g, ACT_NONE));
-    }
+    g.C0 = cat + koff_bytes(L.kp); g.ldc0 = L.k4; g.c0_tiled = L.tiled;
+    FFS_TRY(run(g, ACT_NONE));
   }
   // G4: [h1 | t2] * [W2h ; Q2] -> Y   (one fp32 accumulation, one rounding: Eq. 2's sum)
   auto down = [&](void* out, int koff, int klen, bool with_ep) -> int {
@@ -264,14 +244,15 @@ int ffsplit_score_neurons(const ffsplit_desc_t* d, const void* X, int64_t T, con
     float* p2 = (float*)(ws + w.off_p2);
     float* p1 = (float*)(ws + w.off_p1);
     // transposed (neuron-major) copy of the up projection(s); rows beyond d_ff are zero
-    if (!reuse_tiled) FFS_TRY(launch_fill_zero(Wt, w.wt_bytes, st));
+    // (the tiled form writes its own padding)
+    if (!reuse_tiled && !bf16) FFS_TRY(launch_fill_zero(Wt, w.wt_bytes, st));
     PermArgs pa = {};
     pa.lds = d->d_ff;
     pa.dst = Wt;
     pa.ldd = w.dk;
     pa.dst_tiled = bf16;
-    pa.n_count = d->d_ff;
-    pa.c_count = d->d_model;
+    pa.n_count = d->d_ff; pa.n_pad = w.n_out;
+    pa.c_count = d->d_model; pa.c_pad = w.dk;
     if (reuse_tiled) {
       // nothing to do: the copy is in place
     } else if (glu) {
@@ -347,7 +328,9 @@ int ffsplit_build_split(const ffsplit_desc_t* d, const void* W1, const void* Wg,
   const int esz = d->dtype == FFSPLIT_BF16 ? 2 : 4;
   const Layout L = make_layout(*d);
   char* sp = (char*)split;
-  FFS_TRY(launch_fill_zero(split, L.total_bytes, st));
+  // the quantised kinds and fp32 rely on zeroed padding; the tiled bf16 blocks write their own
+  if (d->rem_kind == FFSPLIT_REM_INT4 || d->rem_kind == FFSPLIT_REM_W3H8 || !L.tiled)
+    FFS_TRY(launch_fill_zero(split, L.total_bytes, st));
 
   // remainder neurons in ascending order (needed when the library itself gathers them)
   int32_t* rest = nullptr;
@@ -370,7 +353,7 @@ int ffsplit_build_split(const ffsplit_desc_t* d, const void* W1, const void* Wg,
   if (k > 0) {
     pa = {};
     pa.lds = d->d_ff; pa.dst = sp + L.off_b1; pa.ldd = L.dk; pa.dst_tiled = L.tiled;
-    pa.n_count = k; pa.c_count = dm; pa.nmap = idx;
+    pa.n_count = k; pa.c_count = dm; pa.nmap = idx; pa.n_pad = L.kp; pa.c_pad = L.dk;
     if (glu) {
       pa.src = Wg; pa.glu_mode = 1; FFS_TRY(launch_permute_transpose(pa, esz, st));
       pa.src = W1; pa.glu_mode = 2; FFS_TRY(launch_permute_transpose(pa, esz, st));
@@ -379,7 +362,7 @@ int ffsplit_build_split(const ffsplit_desc_t* d, const void* W1, const void* Wg,
     }
     pa = {};
     pa.src = W2; pa.lds = dm; pa.dst = sp + L.off_b4; pa.ldd = L.k4; pa.dst_tiled = L.tiled;
-    pa.n_count = dm; pa.c_count = k; pa.cmap = idx;
+    pa.n_count = dm; pa.c_count = k; pa.cmap = idx; pa.n_pad = L.dn; pa.c_pad = L.kp;
     FFS_TRY(launch_permute_transpose(pa, esz, st));
   }
   if (m == 0 || d->rem_kind == FFSPLIT_REM_NONE) return FFSPLIT_OK;
@@ -388,7 +371,7 @@ int ffsplit_build_split(const ffsplit_desc_t* d, const void* W1, const void* Wg,
     // remainder neurons appended to the same blocks after the padded heavy part
     pa = {};
     pa.lds = d->d_ff; pa.dst = sp + L.off_b1; pa.ldd = L.dk; pa.dst_tiled = L.tiled;
-    pa.n_count = m; pa.c_count = dm; pa.nmap = rest;
+    pa.n_count = m; pa.c_count = dm; pa.nmap = rest; pa.n_pad = L.mp; pa.c_pad = L.dk;
     pa.row_off = (int64_t)L.n_up * L.kp;
     if (glu) {
       pa.src = Wg; pa.glu_mode = 1; FFS_TRY(launch_permute_transpose(pa, esz, st));
@@ -399,6 +382,7 @@ int ffsplit_build_split(const ffsplit_desc_t* d, const void* W1, const void* Wg,
     pa = {};
     pa.src = W2; pa.lds = dm; pa.dst = sp + L.off_b4; pa.ldd = L.k4; pa.dst_tiled = L.tiled;
     pa.n_count = dm; pa.c_count = m; pa.cmap = rest; pa.coff = L.kp;
+    pa.n_pad = L.dn; pa.c_pad = L.mp;
     FFS_TRY(launch_permute_transpose(pa, esz, st));
     return FFSPLIT_OK;
   }
@@ -411,6 +395,7 @@ int ffsplit_build_split(const ffsplit_desc_t* d, const void* W1, const void* Wg,
     // P^T rows of B1t after the heavy rows: [Pg^T ; P1^T] (SwiGLU) or [P1^T]
     pa = {};
     pa.lds = r; pa.dst = sp + L.off_b1; pa.ldd = L.dk; pa.dst_tiled = L.tiled; pa.n_count = r; pa.c_count = dm;
+    pa.n_pad = L.rp; pa.c_pad = L.dk;
     pa.row_off = (int64_t)L.n_up * L.kp;
     if (glu) {
       pa.src = Pg; FFS_TRY(launch_permute_transpose(pa, esz, st));
@@ -420,6 +405,7 @@ int ffsplit_build_split(const ffsplit_desc_t* d, const void* W1, const void* Wg,
     // Q1^T (and Qg^T, interleaved in 32-row blocks): [n_up*mp, rp]
     pa = {};
     pa.lds = m; pa.dst = sp + L.off_q1; pa.ldd = L.rp; pa.dst_tiled = L.tiled; pa.n_count = m; pa.c_count = r;
+    pa.n_pad = L.mp; pa.c_pad = L.rp;
     if (glu) {
       pa.src = Qg; pa.glu_mode = 1; FFS_TRY(launch_permute_transpose(pa, esz, st));
       pa.src = Q1; pa.glu_mode = 2; FFS_TRY(launch_permute_transpose(pa, esz, st));
@@ -429,11 +415,12 @@ int ffsplit_build_split(const ffsplit_desc_t* d, const void* W1, const void* Wg,
     // P2^T: [rp, mp]
     pa = {};
     pa.src = P2; pa.lds = r; pa.dst = sp + L.off_p2; pa.ldd = L.mp; pa.dst_tiled = L.tiled; pa.n_count = r; pa.c_count = m;
+    pa.n_pad = L.rp; pa.c_pad = L.mp;
     FFS_TRY(launch_permute_transpose(pa, esz, st));
     // Q2^T into the columns of B4t after the heavy ones
     pa = {};
     pa.src = Q2; pa.lds = dm; pa.dst = sp + L.off_b4; pa.ldd = L.k4; pa.dst_tiled = L.tiled; pa.n_count = dm; pa.c_count = r;
-    pa.coff = L.kp;
+    pa.coff = L.kp; pa.n_pad = L.dn; pa.c_pad = L.rp;
     FFS_TRY(launch_permute_transpose(pa, esz, st));
     return FFSPLIT_OK;
   }

@@ -49,7 +49,8 @@ __device__ __forceinline__ float silu_fast(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
-enum { ACT_NONE = 0, ACT_GELU = 1, ACT_GLU = 2 };
+enum { ACT_NONE = 0, ACT_GELU = 1, ACT_GLU = 2,
+       ACT_POLY = 3 };   // fp32 kernel only: see GemmArgs::poly
 
 // Exclusive prefix count of `flag` over the 1024 threads of a block, in thread
 // order, plus the block total.  wsum: 16 ints of LDS.  Every thread must call it.
@@ -107,6 +108,14 @@ struct GemmArgs {
   const float* resid;
   int64_t ldr;
   int out_f32;
+  // fp32 kernel: `batch` products at once, the operands and C0 (and resid) of product y start
+  // y times these strides further on (elements)
+  int64_t batch_a, batch_b, batch_c;
+  // ACT_POLY: C0 = poly[2] D + poly[1] resid + poly[0] I.  Ct (fp32 kernel, optional): a transposed copy
+  // [N, ldct] of C0, product y at Ct + y batch_ct
+  float poly[3];
+  float* Ct;
+  int64_t ldct, batch_ct;
   // score mode: per-row-tile partial column sums of h^2 and |h|
   float* part_s2;  // [tiles_m, n_out]
   float* part_s1;
@@ -123,16 +132,14 @@ struct Epilogue {
   int out_f32;
 };
 
-// n_split > 1: only with a.partial and no activation: fp32 partials [split][M][ldc0] into C0
-int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int n_split = 1);
-// sum of fp32 partials [n_split][a.M][ldp] of a whole product + the fp32 store epilogue described by a
-int launch_splitk_epilogue_f32(const float* part, int n_split, int ldp, const GemmArgs& a, int act, hipStream_t st);
+// batch > 1: that many products at the strides of GemmArgs (K, lda, ldb, split_col multiples of 4)
+int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int batch = 1);
 // shape: one of gemm_plan.h.
 // n_split > 1 only with a.partial
 int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_split, hipStream_t st);
-// sum of the partials in a fixed order -> C (bf16, tiled or row-major; f32_out: fp32 row-major)
+// sum of the partials in a fixed order -> C (bf16, tiled or row-major)
 int launch_splitk_reduce(const float* part, int n_split, int M, int N, int m_pad, void* C, int64_t ldc, int tiled,
-                         hipStream_t st, int f32_out = 0);
+                         hipStream_t st);
 // sum of the fp32 partials [n_split][a.M][ldp] of a whole product (written with a.partial, no
 // activation, GEMM column order) + the store epilogue described by a (activation act)
 int launch_splitk_epilogue(const float* part, int n_split, int ldp, const GemmArgs& a, int act, hipStream_t st);

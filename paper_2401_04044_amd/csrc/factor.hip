@@ -5,11 +5,19 @@
 //     Z [d, m] (W1[:, rest], Wg[:, rest] or W2[rest, :]^T),  Y^T = Omega Z^T  [r, d],
 //     B^T = orthonormal rows spanning the rows of Y^T,       C = B^T Z  [r, m],
 // so that Z ~= B C.  Omega [r, m] is a counter-based Rademacher matrix (the same signs on any
-// machine).  The rows of Y^T are orthonormalised with the Newton-Schulz iteration for the
-// polar factor, X <- (1.5 I - 0.5 X X^T) X from X = Y^T / ||Y||_F, because it consists of
-// products only: everything here runs on the fp32 GEMM of gemm.hip plus a few elementwise
-// kernels, in fp32, whatever the storage type of the weights.
+// machine).  The rows of Y^T are orthonormalised by an odd matrix iteration for the polar factor,
+// X <- (a I + b X X^T + c (X X^T)^2) X from X = Y^T / ||Y||_F, which consists of products only.
+//
+// Precision and where the work runs.  The sketch of bf16 weights has exact products (bf16 times +-1)
+// and fp32 sums, so it is a product for the bf16 matrix cores; the projection takes the fp32 basis
+// as three bf16 terms (8 + 8 + 8 bits, all of it) against the bf16 weights, again exact products
+// and fp32 sums.  The iteration is fp32 throughout (gemm.hip), the matrices of a layer side by side in
+// one launch.  fp32 weights are gathered and multiplied in fp32.
+// Measured (2048 x 7946, rank 512, two matrices): 8.2 ms before, with everything on fp32 vector
+// arithmetic and 36 steps of X <- (1.5 I - 0.5 X X^T) X, one matrix after the other.
 #include "factor.h"
+#include "prep.h"
+#include <algorithm>
 #include <math.h>
 
 namespace ffsplit {
@@ -21,31 +29,24 @@ __device__ __forceinline__ uint32_t fmix32(uint32_t h) {   // finaliser of the p
   return h;
 }
 
-template <typename T>
-__device__ __forceinline__ float ldf(const T* p, int64_t i);
-template <>
-__device__ __forceinline__ float ldf<float>(const float* p, int64_t i) { return p[i]; }
-template <>
-__device__ __forceinline__ float ldf<bf16_t>(const bf16_t* p, int64_t i) { return bf16_to_f32(p[i]); }
-
-// Z [d, m4] and Zt [m4, d] (fp32, zero in the padding columns) from the weights:
+// fp32 weights: Z [d, m4] and / or Zt [m4, d] (zero in the padding columns):
 // down = 0: Z[c][j] = W[c][rest[j]] (W [d, d_ff]);  down = 1: Z[c][j] = W[rest[j]][c] (W [d_ff, d])
-template <typename T>
-__global__ void gather_z_kernel(const T* W, int d, int d_ff, const int32_t* rest, int m, int m4, int down, float* Z,
+__global__ void gather_z_kernel(const float* W, int d, int d_ff, const int32_t* rest, int m, int m4, int down, float* Z,
                                 float* Zt) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= (int64_t)d * m4) return;
-  const int c = (int)(id / m4), j = (int)(id % m4);
+  // consecutive threads along the contiguous side of what is written
+  const int c = Z ? (int)(id / m4) : (int)(id % d), j = Z ? (int)(id % m4) : (int)(id / d);
   float v = 0.f;
   if (j < m) {
     const int n = rest[j];
-    v = down ? ldf<T>(W, (int64_t)n * d + c) : ldf<T>(W, (int64_t)c * d_ff + n);
+    v = down ? W[(int64_t)n * d + c] : W[(int64_t)c * d_ff + n];
   }
-  Z[id] = v;
-  Zt[(int64_t)j * d + c] = v;
+  if (Z) Z[id] = v;
+  else Zt[id] = v;
 }
 
-// Omega [r4, m4]: entry (i, j) = +-1 from the top bit of fmix32(index * 0x9E3779B1 + key),
+// fp32: Omega [r4, m4]: entry (i, j) = +-1 from the top bit of fmix32(index * 0x9E3779B1 + key),
 // index = i * m + j; zero in the padding
 __global__ void rademacher_kernel(float* Om, int r, int m, int r4, int m4, uint32_t key) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -59,9 +60,80 @@ __global__ void rademacher_kernel(float* Om, int r, int m, int r4, int m4, uint3
   Om[id] = v;
 }
 
-// sum of squares in two fixed-order stages: 256 block partials, then one block
+// the same test matrix in bf16 in the tiled layout [r32, Kp] (K = m), zero in the padding; one
+// wavefront per column block, walking down the row blocks
+__global__ void __launch_bounds__(256) rademacher_tiled_kernel(uint16_t* Om, int r, int m, int r32, int kp, uint32_t key) {
+  const int kb = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (kb * 16 >= kp) return;
+  const int k0 = kb * 16 + (lane >> 5) * 8;
+  for (int rb = blockIdx.y; rb < r32 / 32; rb += gridDim.y) {
+    const int i = rb * 32 + (lane & 31);
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      uint32_t v = 0;
+      if (i < r && k0 + e < m) v = (fmix32((uint32_t)(i * m + k0 + e) * 0x9E3779B1u + key) >> 31) ? 0xBF80u : 0x3F80u;
+      w[e >> 1] = (e & 1) ? (w[e >> 1] | (v << 16)) : v;
+    }
+    *(uint4*)(Om + (((int64_t)rb * (kp / 16) + kb) * 64 + lane) * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+}
+
+// dst (tiled [., ldd], 16-bit) row i, column j = src[row(i)][col(j)] with one of the two mapped by
+// `rest`: rows (by_rows) or columns.  rows x cols valid, zeros up to the padding.
+// 32 rows x 64 columns per workgroup through LDS.
+__global__ void __launch_bounds__(256) gather_tiled_kernel(const uint16_t* src, int64_t lds, const int32_t* rest, int by_rows,
+                                                           int rows, int cols, int cols_pad, uint16_t* dst) {
+  constexpr int LD = 72;
+  __shared__ __align__(16) uint16_t tile[32 * LD];
+  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 64, t = threadIdx.x, l = t & 63;
+  const int c = c0 + l;
+  const int64_t sc = c < cols ? (by_rows ? c : rest[c]) : -1;
+  uint16_t v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = r0 + i * 4 + (t >> 6);
+    v[i] = 0;
+    if (r < rows && sc >= 0) v[i] = src[(int64_t)(by_rows ? rest[r] : r) * lds + sc];
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) tile[(i * 4 + (t >> 6)) * LD + l] = v[i];
+  __syncthreads();
+  const int row = t & 31, c8 = (t >> 5) * 8;
+  if (c0 + c8 >= cols_pad) return;
+  const uint4 w = *(const uint4*)(tile + row * LD + c8);
+  *(uint4*)(dst + (((int64_t)blockIdx.y * (cols_pad / 16) + (c0 + c8) / 16) * 64 + ((c8 >> 3) & 1) * 32 + row) * 8) = w;
+}
+
+// X [r8, d] fp32 (row r and beyond zero) -> three bf16 terms whose sum is X to the last bit of
+// fp32 (each takes the leading 8 bits of what is left), tiled [r32, dk] each
+__global__ void __launch_bounds__(256) split_terms_kernel(const float* X, int r8, int d, int r32, int dk, uint16_t* hi,
+                                                          uint16_t* mid, uint16_t* lo) {
+  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;   // one 16-byte chunk of each term
+  const int kbs = dk / 16;
+  if (id >= (int64_t)(r32 / 32) * kbs * 64) return;
+  const int lane = (int)(id & 63), kb = (int)((id >> 6) % kbs), rb = (int)((id >> 6) / kbs);
+  const int row = rb * 32 + (lane & 31), k0 = kb * 16 + (lane >> 5) * 8;
+  uint32_t w[3][4];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float v = (row < r8 && k0 + e < d) ? X[(int64_t)row * d + k0 + e] : 0.f;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const uint32_t b = f32_to_bf16(v);
+      v -= bf16_to_f32((bf16_t)b);
+      w[t][e >> 1] = (e & 1) ? (w[t][e >> 1] | (b << 16)) : b;
+    }
+  }
+  *(uint4*)(hi + id * 8) = make_uint4(w[0][0], w[0][1], w[0][2], w[0][3]);
+  *(uint4*)(mid + id * 8) = make_uint4(w[1][0], w[1][1], w[1][2], w[1][3]);
+  *(uint4*)(lo + id * 8) = make_uint4(w[2][0], w[2][1], w[2][2], w[2][3]);
+}
+
+// sum of squares in two fixed-order stages: 256 block partials, then one block (blockIdx.y: matrix)
 __global__ void __launch_bounds__(256) sumsq_stage1_kernel(const float* x, int64_t n, float* part) {
   __shared__ float red[256];
+  x += n * blockIdx.y;
   float s = 0.f;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)256 * gridDim.x) s += x[i] * x[i];
   red[threadIdx.x] = s;
@@ -70,10 +142,11 @@ __global__ void __launch_bounds__(256) sumsq_stage1_kernel(const float* x, int64
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) part[blockIdx.y * 260 + blockIdx.x] = red[0];
 }
 __global__ void __launch_bounds__(256) sumsq_stage2_kernel(float* part, int n_part) {
   __shared__ float red[256];
+  part += blockIdx.x * 260;
   red[threadIdx.x] = (int)threadIdx.x < n_part ? part[threadIdx.x] : 0.f;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
@@ -82,26 +155,24 @@ __global__ void __launch_bounds__(256) sumsq_stage2_kernel(float* part, int n_pa
   }
   if (threadIdx.x == 0) part[256] = red[0] > 0.f ? 1.0f / sqrtf(red[0]) : 0.f;   // scale for the next kernel
 }
-__global__ void scale_kernel(float* x, int64_t n, const float* scale) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id < n) x[id] *= scale[0];
-}
 
-// S <- 1.5 I - 0.5 S  (n x n)
-__global__ void ns_update_kernel(float* S, int n) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)n * n) return;
-  const int i = (int)(id / n), j = (int)(id % n);
-  S[id] = (i == j ? 1.5f : 0.f) - 0.5f * S[id];
-}
-
-// dst[a][b] = src[b][a] (fp32), a < rows_dst, b < cols_dst
-__global__ void transpose_f32_kernel(const float* src, int64_t lds, float* dst, int64_t ldd, int rows_dst, int cols_dst) {
+// dst[a][b] = src[b][a] * scale (fp32; a < rows_dst, b < cols_dst), and src *= scale in place;
+// blockIdx.z: matrix (both contiguous)
+__global__ void scale_transpose_kernel(float* src, int64_t lds, float* dst, int64_t ldd, int rows_dst, int cols_dst,
+                                       const float* part) {
   __shared__ float tile[32][33];
+  const float scale = part[blockIdx.z * 260 + 256];
+  src += (int64_t)blockIdx.z * cols_dst * lds;
+  dst += (int64_t)blockIdx.z * rows_dst * ldd;
   const int a0 = blockIdx.y * 32, b0 = blockIdx.x * 32;
   for (int i = threadIdx.y; i < 32; i += 8) {
     const int b = b0 + i, a = a0 + threadIdx.x;
-    tile[i][threadIdx.x] = (b < cols_dst && a < rows_dst) ? src[(int64_t)b * lds + a] : 0.f;
+    float v = 0.f;
+    if (b < cols_dst && a < rows_dst) {
+      v = src[(int64_t)b * lds + a] * scale;
+      src[(int64_t)b * lds + a] = v;
+    }
+    tile[i][threadIdx.x] = v;
   }
   __syncthreads();
   for (int i = threadIdx.y; i < 32; i += 8) {
@@ -110,61 +181,112 @@ __global__ void transpose_f32_kernel(const float* src, int64_t lds, float* dst, 
   }
 }
 
-// dst [rows, cols] (bf16 or fp32, contiguous) = src[a][b] or src[b][a]
+// dst [rows, cols] (bf16 or fp32, contiguous) = src[a][b], or src[b][a] through LDS
 template <typename T>
 __global__ void emit_kernel(const float* src, int64_t lds, int transposed, T* dst, int rows, int cols) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)rows * cols) return;
-  const int a = (int)(id / cols), b = (int)(id % cols);
-  const float v = transposed ? src[(int64_t)b * lds + a] : src[(int64_t)a * lds + b];
-  if constexpr (sizeof(T) == 4) dst[id] = v;
-  else dst[id] = (T)(pack_bf16x2(v, 0.f) & 0xffffu);
+  __shared__ float tile[32][33];
+  const int a0 = blockIdx.y * 32, b0 = blockIdx.x * 32;
+  auto put = [&](int a, int b, float v) {
+    if constexpr (sizeof(T) == 4) dst[(int64_t)a * cols + b] = v;
+    else dst[(int64_t)a * cols + b] = (T)(pack_bf16x2(v, 0.f) & 0xffffu);
+  };
+  if (transposed) {
+    for (int i = threadIdx.y; i < 32; i += 8) {
+      const int b = b0 + i, a = a0 + threadIdx.x;
+      if (b < cols && a < rows) tile[i][threadIdx.x] = src[(int64_t)b * lds + a];
+    }
+    __syncthreads();
+  }
+  for (int i = threadIdx.y; i < 32; i += 8) {
+    const int a = a0 + i, b = b0 + threadIdx.x;
+    if (a < rows && b < cols) put(a, b, transposed ? tile[threadIdx.x][i] : src[(int64_t)a * lds + b]);
+  }
+}
+
+// Coefficients (a, b, c) of the steps.  Growth: the odd quintic published with the Muon optimiser (K.
+// Jordan et al., 2024), slope 3.4445 at zero and values in [0.68, 1.14] from about a quarter on, so
+// that it neither squashes singular values that are already large (which would cost digits: a
+// value mapped near zero keeps its absolute rounding error) nor overshoots.  Finish: (15 x - 10
+// x^3 + 3 x^5) / 8, cubic convergence to 1.  Budget as before: singular values down to 1 / (64 r)
+// of the Frobenius norm (a square Gaussian Y, r = d_model, has its smallest near r^-1.5 of it); a
+// basis direction below that comes out shorter than unit length.
+constexpr int MAX_STEPS = 48;
+int polar_steps(int r, float (*coef)[3]) {
+  auto range = [](const double* q, double& lo, double& hi) {
+    double a = 1e30, b = 0;
+    for (int i = 0; i <= 4000; ++i) {
+      const double x = lo + (hi - lo) * i / 4000.0, x2 = x * x, y = x * (q[0] + x2 * (q[1] + x2 * q[2]));
+      a = y < a ? y : a;
+      b = y > b ? y : b;
+    }
+    lo = a; hi = b;
+  };
+  const double grow[3] = {3.4445, -4.7750, 2.0315}, fin[3] = {1.875, -1.25, 0.375};
+  double lo = 1.0 / (64.0 * r), hi = 1.0;
+  int n = 0;
+  while ((lo < 0.6 || hi > 1.2) && n < MAX_STEPS - 8) {
+    for (int i = 0; i < 3; ++i) coef[n][i] = (float)grow[i];
+    range(grow, lo, hi);
+    ++n;
+  }
+  while ((lo < 1.0 - 3e-8 || hi > 1.0 + 3e-8) && n < MAX_STEPS) {
+    for (int i = 0; i < 3; ++i) coef[n][i] = (float)fin[i];
+    range(fin, lo, hi);
+    ++n;
+  }
+  return n;
 }
 
 struct FactorWs {
-  size_t off_z, off_zt, off_om, off_xa, off_xb, off_xt, off_s, off_sp, off_c, off_red, total;
-  int m4, r4;
-  int s_split;   // split of the reduction of the Gram product X X^T (r x r, few tiles, long K)
+  int mats, m4, r8, r32, mk, dk;
+  size_t off_z, off_zt, off_om, off_part, off_terms, off_x[2], off_xt[2], off_s, off_t, off_c, off_red, total;
+  size_t part_bytes, term_bytes;
 };
 
 FactorWs make_factor_ws(const ffsplit_desc_t& d) {
   FactorWs w = {};
-  const int m = d.d_ff - d.k;
-  w.m4 = round_up(m > 0 ? m : 4, 4);
-  w.r4 = round_up(d.rank > 0 ? d.rank : 4, 4);
+  const bool bf = d.dtype == FFSPLIT_BF16;
+  const int m = d.d_ff - d.k > 0 ? d.d_ff - d.k : 4, r = d.rank > 0 ? d.rank : 4, dm = d.d_model;
+  w.mats = d.act == FFSPLIT_ACT_SWIGLU ? 3 : 2;
+  w.m4 = round_up(m, 4);
+  w.r8 = round_up(r, 8);
+  w.r32 = round_up(r, 32);
+  w.mk = round_up(m, 64);
+  w.dk = round_up(dm, 64);
   size_t off = 0;
-  const size_t dm = (size_t)d.d_model;
-  w.off_z = off; off = align256(off + dm * w.m4 * 4);
-  w.off_zt = off; off = align256(off + dm * w.m4 * 4);
-  w.off_om = off; off = align256(off + (size_t)w.r4 * w.m4 * 4);
-  w.off_xa = off; off = align256(off + (size_t)w.r4 * dm * 4);
-  w.off_xb = off; off = align256(off + (size_t)w.r4 * dm * 4);
-  w.off_xt = off; off = align256(off + (size_t)w.r4 * dm * 4);
-  w.off_s = off; off = align256(off + (size_t)w.r4 * w.r4 * 4);
-  // The Gram product has (r / 64)^2 tiles of 64 x 64 and K = d_model: split it so that a few
-  // hundred workgroups exist, at least 16 slabs of 16 each (the partial sums need whole
-  // 8-column chunks).
-  {
-    const int tiles = ((w.r4 + 63) / 64) * ((w.r4 + 63) / 64);
-    int sp = 512 / (tiles > 0 ? tiles : 1);
-    if (sp > (int)dm / 256) sp = (int)dm / 256;
-    if (sp > 16) sp = 16;
-    if (sp < 1 || (w.r4 & 7)) sp = 1;
-    w.s_split = sp;
+  auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
+  if (bf) {
+    // one remainder matrix at a time: tiled [d_model, m] for the sketch, [m, d_model] for the projection
+    w.off_z = take(std::max((size_t)round_up(dm, 32) * w.mk, (size_t)round_up(m, 32) * w.dk) * 2);
+    w.off_om = take((size_t)w.r32 * w.mk * 2);
+    const GemmPlan p = gemm_plan(dm, w.r8, m, false, false, true);
+    w.part_bytes = p.split > 1 ? (size_t)p.split * dm * w.r32 * 4 : 0;
+    w.off_part = take(w.part_bytes);
+    w.term_bytes = align256((size_t)w.r32 * w.dk * 2);
+    w.off_terms = take(3 * w.term_bytes);
+    w.off_c = take((size_t)m * w.r8 * 4);   // (B^T Z)^T
+  } else {
+    w.off_z = take((size_t)dm * w.m4 * 4);
+    w.off_zt = take((size_t)dm * w.m4 * 4);
+    w.off_om = take((size_t)w.r8 * w.m4 * 4);
+    w.off_c = take((size_t)w.r8 * w.m4 * 4);   // B^T Z
   }
-  w.off_sp = off; if (w.s_split > 1) off = align256(off + (size_t)w.s_split * w.r4 * w.r4 * 4);
-  w.off_c = off; off = align256(off + (size_t)w.r4 * w.m4 * 4);
-  w.off_red = off; off = align256(off + 260 * 4);
+  for (int i = 0; i < 2; ++i) {
+    w.off_x[i] = take((size_t)w.mats * w.r8 * dm * 4);
+    w.off_xt[i] = take((size_t)w.mats * w.r8 * dm * 4);
+  }
+  w.off_s = take((size_t)w.mats * w.r8 * w.r8 * 4);
+  w.off_t = take((size_t)w.mats * w.r8 * w.r8 * 4);
+  w.off_red = take((size_t)w.mats * 260 * 4);
   w.total = off;
   return w;
 }
 
-int gemm_nt(const float* A, int64_t lda, const float* Bt, int64_t ldb, int M, int N, int K, float* C, int64_t ldc,
-            hipStream_t st) {
+GemmArgs gemm_nt(const void* A, int64_t lda, const void* Bt, int64_t ldb, int M, int N, int K, float* C, int64_t ldc) {
   GemmArgs g = {};
   g.A = A; g.lda = lda; g.Bt = Bt; g.ldb = ldb; g.M = M; g.N = N; g.K = K;
   g.split_col = N; g.C0 = C; g.ldc0 = ldc; g.n_store = N;
-  return launch_gemm_f32(g, ACT_NONE, false, st);
+  return g;
 }
 
 #define FK(expr)                 \
@@ -185,72 +307,134 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
   const int dm = d.d_model, m = d.d_ff - d.k, r = d.rank;
   if (m <= 0 || r <= 0) return 0;
   const FactorWs w = make_factor_ws(d);
-  const int m4 = w.m4, r4 = w.r4;
-  float* Z = (float*)(ws + w.off_z); float* Zt = (float*)(ws + w.off_zt); float* Om = (float*)(ws + w.off_om);
-  float* Xa = (float*)(ws + w.off_xa); float* Xb = (float*)(ws + w.off_xb); float* Xt = (float*)(ws + w.off_xt);
-  float* S = (float*)(ws + w.off_s); float* C = (float*)(ws + w.off_c); float* red = (float*)(ws + w.off_red);
-  float* Sp = (float*)(ws + w.off_sp);
+  const int m4 = w.m4, r8 = w.r8;
+  float* S = (float*)(ws + w.off_s); float* Tm = (float*)(ws + w.off_t); float* C = (float*)(ws + w.off_c);
+  float* red = (float*)(ws + w.off_red);
+  char* Z = ws + w.off_z;
   const bool bf = d.dtype == FFSPLIT_BF16;
-  // Steps of x <- 1.5 x - 0.5 x^3: a singular value far below 1 grows by 1.5 per step, then
-  // converges quadratically (about ten more steps to fp32 accuracy).  Budget: singular values
-  // down to 1 / (64 r) of the Frobenius norm (a square Gaussian Y, r = d_model, has its smallest
-  // near r^-1.5 of it); a basis direction below that comes out shorter than unit length.
-  const int n_iter = 10 + (int)ceil(log(64.0 * (double)r) / log(1.5));
-  const void* Ws[3] = {W1, Wg, W2};
-  for (int which = 0; which < 3; ++which) {
-    if (which == 1 && d.act != FFSPLIT_ACT_SWIGLU) continue;
-    const int down = which == 2;
-    const int64_t nz = (int64_t)dm * m4;
-    const unsigned gz = (unsigned)((nz + 255) / 256);
-    if (bf) hipLaunchKernelGGL(gather_z_kernel<bf16_t>, dim3(gz), dim3(256), 0, st, (const bf16_t*)Ws[which], dm, d.d_ff, rest, m, m4, down, Z, Zt);
-    else hipLaunchKernelGGL(gather_z_kernel<float>, dim3(gz), dim3(256), 0, st, (const float*)Ws[which], dm, d.d_ff, rest, m, m4, down, Z, Zt);
-    FKL();
-    uint32_t key = seed + 0x9E3779B9u * (uint32_t)which;
+  const int64_t nx = (int64_t)r8 * dm, ns = (int64_t)r8 * r8;
+  const void* Ws[3] = {W1, d.act == FFSPLIT_ACT_SWIGLU ? Wg : W2, W2};   // the last one is the down projection
+  const uint32_t stream_of[3] = {0, d.act == FFSPLIT_ACT_SWIGLU ? 1u : 2u, 2};
+
+  // ---- sketches: (Y^T)^T = Z Omega^T  [d, r8] per matrix
+  float* XT = (float*)(ws + w.off_xt[0]);
+  float* X = (float*)(ws + w.off_x[0]);
+  for (int i = 0; i < w.mats; ++i) {
+    const bool down = i == w.mats - 1;
+    const uint16_t* W = (const uint16_t*)Ws[i];
+    uint32_t key = seed + 0x9E3779B9u * stream_of[i];
     key ^= key >> 16; key *= 0x85EBCA6Bu; key ^= key >> 13; key *= 0xC2B2AE35u; key ^= key >> 16;
-    const int64_t no = (int64_t)r4 * m4;
-    hipLaunchKernelGGL(rademacher_kernel, dim3((unsigned)((no + 255) / 256)), dim3(256), 0, st, Om, r, m, r4, m4, key);
-    FKL();
-    // Y^T = Omega Z^T, scaled to unit Frobenius norm
-    FK(gemm_nt(Om, m4, Z, m4, r4, dm, m4, Xa, dm, st));
-    const int64_t nx = (int64_t)r4 * dm;
-    hipLaunchKernelGGL(sumsq_stage1_kernel, dim3(256), dim3(256), 0, st, Xa, nx, red);
-    hipLaunchKernelGGL(sumsq_stage2_kernel, dim3(1), dim3(256), 0, st, red, 256);
-    hipLaunchKernelGGL(scale_kernel, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st, Xa, nx, red + 256);
-    FKL();
-    float* X = Xa; float* Xn = Xb;
-    for (int it = 0; it < n_iter; ++it) {
-      if (w.s_split > 1) {
-        GemmArgs g = {};
-        g.A = X; g.lda = dm; g.Bt = X; g.ldb = dm; g.M = r4; g.N = r4; g.K = dm;
-        g.split_col = r4; g.C0 = Sp; g.ldc0 = r4; g.n_store = r4; g.partial = 1;
-        FK(launch_gemm_f32(g, ACT_NONE, false, st, w.s_split));
-        FK(launch_splitk_reduce(Sp, w.s_split, r4, r4, r4, S, r4, 0, st, 1));
-      } else {
-        FK(gemm_nt(X, dm, X, dm, r4, r4, dm, S, r4, st));
-      }
-      hipLaunchKernelGGL(ns_update_kernel, dim3((unsigned)(((int64_t)r4 * r4 + 255) / 256)), dim3(256), 0, st, S, r4);
-      hipLaunchKernelGGL(transpose_f32_kernel, dim3((r4 + 31) / 32, (dm + 31) / 32), dim3(32, 8), 0, st, X, (int64_t)dm, Xt,
-                         (int64_t)r4, dm, r4);
-      FKL();
-      FK(gemm_nt(S, r4, Xt, r4, r4, dm, r4, Xn, dm, st));
-      float* t = X; X = Xn; Xn = t;
-    }
-    // C = B^T Z
-    FK(gemm_nt(X, dm, Zt, dm, r4, m4, dm, C, m4, st));
-    // factors in the caller's convention and type
-    void* Pf = factors[which == 0 ? 0 : (which == 1 ? 2 : 4)];
-    void* Qf = factors[which == 0 ? 1 : (which == 1 ? 3 : 5)];
-    const float* psrc = down ? C : X;      // P = B [d, r] (up, gate) or C^T [m, r] (down)
-    const float* qsrc = down ? X : C;      // Q = C [r, m] (up, gate) or B^T [r, d] (down)
-    const int prow = down ? m : dm, qcol = down ? dm : m;
-    const int64_t pld = down ? m4 : dm, qld = down ? dm : m4;
-    const int64_t np_ = (int64_t)prow * r, nq = (int64_t)r * qcol;
     if (bf) {
-      hipLaunchKernelGGL(emit_kernel<bf16_t>, dim3((unsigned)((np_ + 255) / 256)), dim3(256), 0, st, psrc, pld, 1, (bf16_t*)Pf, prow, r);
-      hipLaunchKernelGGL(emit_kernel<bf16_t>, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, st, qsrc, qld, 0, (bf16_t*)Qf, r, qcol);
+      if (down) {
+        PermArgs pa = {};
+        pa.src = W; pa.lds = dm; pa.dst = Z; pa.ldd = w.mk; pa.dst_tiled = 1;
+        pa.n_count = dm; pa.c_count = m; pa.cmap = rest; pa.c_pad = w.mk;
+        FK(launch_permute_transpose(pa, 2, st));
+      } else {
+        hipLaunchKernelGGL(gather_tiled_kernel, dim3(w.mk / 64, (dm + 31) / 32), dim3(256), 0, st, W, (int64_t)d.d_ff, rest, 0,
+                           dm, m, w.mk, (uint16_t*)Z);
+        FKL();
+      }
+      const int kb = w.mk / 16;
+      hipLaunchKernelGGL(rademacher_tiled_kernel, dim3((kb + 3) / 4, 4), dim3(256), 0, st, (uint16_t*)(ws + w.off_om), r, m,
+                         w.r32, w.mk, key);
+      FKL();
+      GemmArgs g = gemm_nt(Z, w.mk, ws + w.off_om, w.mk, dm, r8, m, XT + i * nx, r8);
+      g.a_tiled = 1; g.out_f32 = 1;
+      const GemmPlan p = gemm_plan(dm, r8, m, false, false, true);
+      if (p.split > 1) {
+        GemmArgs gp = g;
+        gp.partial = 1; gp.C0 = ws + w.off_part; gp.ldc0 = w.r32; gp.split_col = w.r32; gp.out_f32 = 0;
+        FK(launch_gemm_bf16(gp, ACT_NONE, false, p.shape, p.split, st));
+        FK(launch_splitk_epilogue((const float*)(ws + w.off_part), p.split, w.r32, g, ACT_NONE, st));
+      } else {
+        FK(launch_gemm_bf16(g, ACT_NONE, false, p.shape, 1, st));
+      }
     } else {
-      hipLaunchKernelGGL(emit_kernel<float>, dim3((unsigned)((np_ + 255) / 256)), dim3(256), 0, st, psrc, pld, 1, (float*)Pf, prow, r);
-      hipLaunchKernelGGL(emit_kernel<float>, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, st, qsrc, qld, 0, (float*)Qf, r, qcol);
+      const unsigned gz = (unsigned)(((int64_t)dm * m4 + 255) / 256);
+      hipLaunchKernelGGL(gather_z_kernel, dim3(gz), dim3(256), 0, st, (const float*)Ws[i], dm, d.d_ff, rest, m, m4, (int)down,
+                         (float*)Z, (float*)nullptr);
+      const int64_t no = (int64_t)r8 * m4;
+      hipLaunchKernelGGL(rademacher_kernel, dim3((unsigned)((no + 255) / 256)), dim3(256), 0, st, (float*)(ws + w.off_om), r, m,
+                         r8, m4, key);
+      FKL();
+      FK(launch_gemm_f32(gemm_nt(Z, m4, ws + w.off_om, m4, dm, r8, m4, XT + i * nx, r8), ACT_NONE, false, st));
+    }
+  }
+  // ---- unit Frobenius norm, both orders
+  hipLaunchKernelGGL(sumsq_stage1_kernel, dim3(256, w.mats), dim3(256), 0, st, XT, nx, red);
+  hipLaunchKernelGGL(sumsq_stage2_kernel, dim3(w.mats), dim3(256), 0, st, red, 256);
+  hipLaunchKernelGGL(scale_transpose_kernel, dim3((dm + 31) / 32, (r8 + 31) / 32, w.mats), dim3(32, 8), 0, st, XT, (int64_t)r8, X,
+                     (int64_t)dm, r8, dm, red);
+  FKL();
+  // ---- polar factor
+  float coef[MAX_STEPS][3];
+  const int steps = polar_steps(r, coef);
+  for (int it = 0; it < steps; ++it) {
+    float* Xn = (float*)(ws + w.off_x[(it + 1) & 1]);
+    float* XTn = (float*)(ws + w.off_xt[(it + 1) & 1]);
+    GemmArgs g = gemm_nt(X, dm, X, dm, r8, r8, dm, S, r8);
+    g.batch_a = g.batch_b = nx; g.batch_c = ns;
+    FK(launch_gemm_f32(g, ACT_NONE, false, st, w.mats));
+    g = gemm_nt(S, r8, S, r8, r8, r8, r8, Tm, r8);   // (S is symmetric)
+    g.batch_a = g.batch_b = g.batch_c = ns; g.resid = S; g.ldr = r8;
+    for (int i = 0; i < 3; ++i) g.poly[i] = coef[it][i];
+    FK(launch_gemm_f32(g, ACT_POLY, false, st, w.mats));
+    g = gemm_nt(Tm, r8, XT, r8, r8, dm, r8, Xn, dm);
+    g.batch_a = ns; g.batch_b = g.batch_c = nx;
+    g.Ct = XTn; g.ldct = r8; g.batch_ct = nx;
+    FK(launch_gemm_f32(g, ACT_NONE, false, st, w.mats));
+    X = Xn; XT = XTn;
+  }
+  // ---- projections and factors in the caller's convention and type:
+  // P = B [d, r], Q = B^T Z [r, m] (up, gate);  P = Z^T B [m, r], Q = B^T [r, d] (down)
+  for (int i = 0; i < w.mats; ++i) {
+    const bool down = i == w.mats - 1;
+    void* Pf = factors[down ? 4 : (i == 0 ? 0 : 2)];
+    void* Qf = factors[down ? 5 : (i == 0 ? 1 : 3)];
+    const float* Xi = X + i * nx;
+    if (bf) {
+      if (down) {
+        hipLaunchKernelGGL(gather_tiled_kernel, dim3(w.dk / 64, (m + 31) / 32), dim3(256), 0, st, (const uint16_t*)Ws[i],
+                           (int64_t)dm, rest, 1, m, dm, w.dk, (uint16_t*)Z);
+        FKL();
+      } else {
+        PermArgs pa = {};
+        pa.src = Ws[i]; pa.lds = d.d_ff; pa.dst = Z; pa.ldd = w.dk; pa.dst_tiled = 1;
+        pa.n_count = m; pa.c_count = dm; pa.nmap = rest; pa.c_pad = w.dk;
+        FK(launch_permute_transpose(pa, 2, st));
+      }
+      char* term = ws + w.off_terms;
+      const int64_t chunks = (int64_t)(w.r32 / 32) * (w.dk / 16) * 64;
+      hipLaunchKernelGGL(split_terms_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st, Xi, r8, dm, w.r32, w.dk,
+                         (uint16_t*)term, (uint16_t*)(term + w.term_bytes), (uint16_t*)(term + 2 * w.term_bytes));
+      FKL();
+      for (int t = 2; t >= 0; --t) {   // smallest term first
+        GemmArgs g = gemm_nt(Z, w.dk, term + t * w.term_bytes, w.dk, m, r8, dm, C, r8);
+        g.a_tiled = 1; g.out_f32 = 1;
+        if (t < 2) { g.resid = C; g.ldr = r8; }
+        FK(launch_gemm_bf16(g, ACT_NONE, false, gemm_plan(m, r8, dm, false, false, false).shape, 1, st));
+      }
+    } else {
+      const unsigned gz = (unsigned)(((int64_t)dm * m4 + 255) / 256);
+      hipLaunchKernelGGL(gather_z_kernel, dim3(gz), dim3(256), 0, st, (const float*)Ws[i], dm, d.d_ff, rest, m, m4, (int)down,
+                         (float*)nullptr, (float*)(ws + w.off_zt));
+      FKL();
+      FK(launch_gemm_f32(gemm_nt(Xi, dm, ws + w.off_zt, dm, r8, m4, dm, C, m4), ACT_NONE, false, st));
+    }
+    // C is [m, r8] (bf16) or [r8, m4] (fp32)
+    const int64_t ldc = bf ? r8 : m4;
+    auto emit = [&](const float* src, int64_t lds, int transposed, void* dst, int rows, int cols) {
+      const dim3 grid((cols + 31) / 32, (rows + 31) / 32), block(32, 8);
+      if (bf) hipLaunchKernelGGL(emit_kernel<bf16_t>, grid, block, 0, st, src, lds, transposed, (bf16_t*)dst, rows, cols);
+      else hipLaunchKernelGGL(emit_kernel<float>, grid, block, 0, st, src, lds, transposed, (float*)dst, rows, cols);
+    };
+    if (down) {
+      emit(C, ldc, bf ? 0 : 1, Pf, m, r);
+      emit(Xi, dm, 0, Qf, r, dm);
+    } else {
+      emit(XT + i * nx, r8, 0, Pf, dm, r);
+      emit(C, ldc, bf ? 1 : 0, Qf, r, m);
     }
     FKL();
   }

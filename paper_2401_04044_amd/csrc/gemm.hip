@@ -7,139 +7,227 @@
 //     blocks), with the output columns routed to two destinations;
 //   - score: per-row-tile column sums of h^2 and |h| (the neuron-norm reduction
 //     of Sec. 4.1, Eq. 3), h never leaving registers.
-// Plain FMA tiles: the fp32 workload is tiny and latency-bound, and its 1e-5
-// error bar wants true fp32 products and the erf form of GeLU.
+// True fp32 products (v_mfma_f32_16x16x4_f32) and the erf form of GeLU: the error bar is 1e-5.
+//
+// Operands go straight from global memory into registers, no LDS and no barrier: the fp32 matrix
+// rate is a sixteenth of the bf16 one, so even a 32x32 wave tile asks for 32 bytes per clock and
+// CU where the vector cache delivers 61.  Lane l of a 16-row tile loads the 16 bytes of row l & 15,
+// k elements 4 (l >> 4) .. + 3 of a 16-deep slab; element t of both operands' registers feeds MFMA
+// t of the slab (any pairing of k works as long as both sides use the same).  PF slabs are in
+// flight per wavefront.
+// A workgroup is WGM x WGN wavefronts per k group and KW k groups, which take every KW-th slab and
+// add their accumulators through LDS in a fixed order: products of a hundred tokens are bound by
+// the latency of their chain of slabs, and this shortens it without partial sums in memory or a
+// second launch.  (BERT-base layer, 128 tokens: six launches with split reductions took 63 us.)
 #include "common.h"
+#include <algorithm>
 
 namespace ffsplit {
 
-// ------------------------------------------------------------------ fp32 FMA kernel
-// 64x64 tile, 16-deep K slabs, 256 threads; thread (ty, tx) owns rows ty + 16 i
-// and columns tx + 16 j (i, j = 0..3), so that column j and j + 2 are a
-// (gate, up) pair of 32-column blocks.
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
-template <int ACT, bool DUAL, bool SCORE>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs p) {
-  constexpr int BM = 64, BN = 64, BK = 16, LD = 65;
+template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE>
+__global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmArgs p) {
+  constexpr int BM = WGM * TM * 16, BN = WGN * TN * 16;
   constexpr int NA = DUAL ? 2 : 1;
-  __shared__ float sA[NA][BK][LD];
-  __shared__ float sB[BK][LD];
-  __shared__ float red[2][16][BN];
+  static_assert(ACT != ACT_GLU || TN == 4, "a (gate, up) pair of 32-column blocks per wavefront");
+  extern __shared__ float f32_smem[];
 
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kw = wave / (WGM * WGN), wt = wave % (WGM * WGN), wm = wt / WGN, wn = wt % WGN;
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * BM + wm * TM * 16, n0 = tn * BN + wn * TN * 16;   // the wavefront's corner
+  const int r16 = lane & 15, quad = lane >> 4;
 
-  const int lrow = tid >> 2, lk = (tid & 3) * 4;
-  int ga = m0 + lrow;
-  ga = ga < p.M ? ga : p.M - 1;
-  int gb = n0 + lrow;
-  gb = gb < p.N ? gb : p.N - 1;
-  const float* a_src[NA] = {(const float*)p.A + (int64_t)ga * p.lda + lk};
-  if (DUAL) a_src[NA - 1] = (const float*)p.A1 + (int64_t)ga * p.lda + lk;
-  const float* b_src = (const float*)p.Bt + (int64_t)gb * p.ldb + lk;
+  const float* a_src[NA][TM];
+  const float* b_src[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int64_t off = (int64_t)min(m0 + i * 16 + r16, p.M - 1) * p.lda + 4 * quad + p.batch_a * blockIdx.y;
+    a_src[0][i] = (const float*)p.A + off;
+    if (DUAL) a_src[NA - 1][i] = (const float*)p.A1 + off;
+  }
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+    b_src[j] = (const float*)p.Bt + (int64_t)min(n0 + j * 16 + r16, p.N - 1) * p.ldb + 4 * quad + p.batch_b * blockIdx.y;
 
-  float acc[4][4];
+  f32x4_t acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // gridDim.y > 1 (only with p.partial): this workgroup's range of the reduction, whole slabs
-  const int slabs = (p.K + BK - 1) / BK;
-  const int per = (slabs + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int k_begin = (int)blockIdx.y * per * BK;
-  const int k_end = min(p.K, k_begin + per * BK);
-  // the next slab's global loads are in flight while this one is multiplied
-  float4 va[NA], vb;
-  auto fetch = [&](int k0) {
-    const bool ok = k0 < k_end && (k0 + lk) < p.K;
+  const int slabs = (p.K + 15) / 16;
+  const int n = (slabs - kw + KW - 1) / KW;   // this k group's slabs: kw, kw + KW, ...
+  f32x4_t fa[PF][NA][TM], fb[PF][TN];
+  auto load = [&](int slot, int i) {
+    const int k0 = (kw + i * KW) * 16;
+    // whole chunks only (K is a multiple of 4): a chunk past K is zero on both sides
+    const bool ok = k0 + 4 * quad < p.K;
+    const int k = ok ? k0 : 0;
 #pragma unroll
-    for (int s = 0; s < NA; ++s) va[s] = ok ? *(const float4*)(a_src[s] + k0) : make_float4(0, 0, 0, 0);
-    vb = ok ? *(const float4*)(b_src + k0) : make_float4(0, 0, 0, 0);
-  };
-  fetch(k_begin);
-  for (int k0 = k_begin; k0 < k_end; k0 += BK) {
-    __syncthreads();
+    for (int t = 0; t < TM; ++t)
 #pragma unroll
-    for (int s = 0; s < NA; ++s) {
-      sA[s][lk + 0][lrow] = va[s].x; sA[s][lk + 1][lrow] = va[s].y;
-      sA[s][lk + 2][lrow] = va[s].z; sA[s][lk + 3][lrow] = va[s].w;
+      for (int s = 0; s < NA; ++s) {
+        fa[slot][s][t] = *(const f32x4_t*)(a_src[s][t] + k);
+        if (!ok) fa[slot][s][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+    for (int t = 0; t < TN; ++t) {
+      fb[slot][t] = *(const f32x4_t*)(b_src[t] + k);
+      if (!ok) fb[slot][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
-    sB[lk + 0][lrow] = vb.x; sB[lk + 1][lrow] = vb.y; sB[lk + 2][lrow] = vb.z; sB[lk + 3][lrow] = vb.w;
+  };
+  auto load_full = [&](int slot, int i) {
+    const int k = (kw + i * KW) * 16;
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int s = 0; s < NA; ++s) fa[slot][s][t] = *(const f32x4_t*)(a_src[s][t] + k);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) fb[slot][t] = *(const f32x4_t*)(b_src[t] + k);
+  };
+  auto mma = [&](int slot) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const float a = fa[slot][DUAL ? (j >> 1) & 1 : 0][i][t], b = fb[slot][j][t];
+          acc[i][j] = SCORE ? __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[i][j], 0, 0, 0)
+                            : __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, acc[i][j], 0, 0, 0);
+        }
+  };
+#pragma unroll
+  for (int u = 0; u < PF; ++u)
+    if (u < n) load(u, u);
+  int i = 0;
+  // the slabs loaded here are never the last one of the product, the only one that can be short
+  for (; i + 2 * PF < n; i += PF)
+#pragma unroll
+    for (int u = 0; u < PF; ++u) { mma(u); load_full(u, i + u + PF); }
+  for (; i < n; i += PF)
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+      if (i + u < n) {
+        mma(u);
+        if (i + u + PF < n) load(u, i + u + PF);
+      }
+
+  if constexpr (KW > 1) {
+    // Sum over the k groups: all but the first park their accumulators, then every wavefront adds
+    // up its share of the tiles and hands the sums to the first group.
+    constexpr int TILES = WGM * WGN * TM * TN;
+    f32x4_t* sm = (f32x4_t*)f32_smem;   // [KW][TILES][64]
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+      for (int b = 0; b < TN; ++b) sm[((kw * WGM * WGN + wt) * TM * TN + a * TN + b) * 64 + lane] = acc[a][b];
     __syncthreads();
-    fetch(k0 + BK);
+    for (int t = wave; t < TILES; t += WGM * WGN * KW) {
+      f32x4_t v = sm[t * 64 + lane];
 #pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      float a[NA][4], b[4];
+      for (int g = 1; g < KW; ++g) v += sm[(g * TILES + t) * 64 + lane];
+      sm[t * 64 + lane] = v;
+    }
+    __syncthreads();
+    if (kw != 0 && !SCORE) return;
+    if (kw == 0) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int s = 0; s < NA; ++s) a[s][i] = sA[s][k][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = sB[k][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[DUAL ? (j >> 1) : 0][i], b[j], acc[i][j]);
+        for (int b = 0; b < TN; ++b) acc[a][b] = sm[(wt * TM * TN + a * TN + b) * 64 + lane];
     }
   }
 
-  // output column (after GLU pairing) of local column block
-  const bool glu_here = (ACT == ACT_GLU) && (n0 < p.act_cols);
   if (!SCORE) {
+    // lane: row r16, columns 4 quad + 0..3 of each 16x16 tile
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (glu_here && j >= 2) continue;
-      const int cb = n0 + tx + 16 * j;
+    for (int j = 0; j < TN; ++j) {
+      const int cb = n0 + j * 16;
       if (cb >= p.N) continue;
-      int oc;
-      if (ACT == ACT_GLU) oc = glu_here ? (n0 / 2 + tx + 16 * j) : cb - p.act_cols / 2;
-      else oc = cb;
-      float* base;
-      int64_t ld;
-      if (oc < p.split_col) { base = (float*)p.C0 + oc; ld = p.ldc0; }
-      else { base = (float*)p.C1 + (oc - p.split_col); ld = p.ldc1; }
-      if (p.partial) base += (int64_t)blockIdx.y * p.M * p.ldc0;   // fp32 partials [split][M][ldc0]
+      const bool glu_here = ACT == ACT_GLU && cb < p.act_cols;
+      if (glu_here && j >= 2) continue;
+      const int oc = ACT == ACT_GLU ? (glu_here ? (cb >> 6) * 32 + (cb & 31) : cb - p.act_cols / 2) : cb;
+      const bool to_c0 = oc < p.split_col;
+      float* base = to_c0 ? (float*)p.C0 + oc : (float*)p.C1 + (oc - p.split_col);
+      const int64_t ld = to_c0 ? p.ldc0 : p.ldc1;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = m0 + ty + 16 * i;
+      for (int i2 = 0; i2 < TM; ++i2) {
+        const int row = m0 + i2 * 16 + r16;
         if (row >= p.M) continue;
-        float v;
-        // (a neuron's bias before the activation; the output bias of an un-activated product)
-        const float bz = (ACT != ACT_GLU && p.bias != nullptr && cb < p.bias_cols) ? p.bias[cb] : 0.f;
-        if (ACT == ACT_GLU) v = glu_here ? silu_f(acc[i][j]) * acc[i][(j + 2) & 3] : acc[i][j];
-        else if (ACT == ACT_GELU) v = cb < p.act_cols ? gelu_f(acc[i][j] + bz) : acc[i][j] + bz;
-        else v = acc[i][j] + bz;
-        if (p.resid != nullptr && !p.partial && oc < p.split_col) v += p.resid[(int64_t)row * p.ldr + oc];
-        base[(int64_t)row * ld] = v;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int c = cb + 4 * quad + e;
+          // (a neuron's bias before the activation; the output bias of an un-activated product)
+          const float bz = (ACT != ACT_GLU && p.bias != nullptr && c < p.bias_cols) ? p.bias[c] : 0.f;
+          const float z = acc[i2][j][e];
+          if (ACT == ACT_GLU) v[e] = glu_here ? silu_f(z) * acc[i2][(j + 2) % TN][e] : z;
+          else if (ACT == ACT_GELU) v[e] = c < p.act_cols ? gelu_f(z + bz) : z + bz;
+          else v[e] = z + bz;
+          if (ACT == ACT_POLY)
+            v[e] = c < p.N ? p.poly[2] * z + p.poly[1] * p.resid[p.batch_c * blockIdx.y + (int64_t)row * p.ldr + c] +
+                                 (row == c ? p.poly[0] : 0.f) : 0.f;
+          else if (p.resid != nullptr && to_c0 && c < p.N) v[e] += p.resid[(int64_t)row * p.ldr + oc + 4 * quad + e];
+        }
+        float* dst = base + p.batch_c * blockIdx.y + (int64_t)row * ld + 4 * quad;
+        // (the columns of one 16-byte piece share a destination: split_col is a multiple of 4)
+        if (cb + 4 * quad + 3 < p.N) {
+          *(f32x4_t*)dst = f32x4_t{v[0], v[1], v[2], v[3]};
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (cb + 4 * quad + e < p.N) dst[e] = v[e];
+        }
+        if (ACT == ACT_NONE && p.Ct != nullptr) {   // 16 lanes: 16 consecutive rows of one column
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (cb + 4 * quad + e < p.N) p.Ct[p.batch_ct * blockIdx.y + (int64_t)(cb + 4 * quad + e) * p.ldct + row] = v[e];
+        }
       }
     }
   } else {
-    constexpr int NJ = (ACT == ACT_GLU) ? 2 : 4;
-    constexpr int BNO = (ACT == ACT_GLU) ? 32 : 64;
+    // lane: column r16, rows 4 quad + 0..3 of each tile; one workgroup covers BM = 64 rows
+    constexpr int BNO = (ACT == ACT_GLU) ? BN / 2 : BN;
+    float* red2 = f32_smem;             // [WGM][BNO] (after the sum over the k groups has been read)
+    float* red1 = red2 + WGM * BNO;
+    if (KW > 1) __syncthreads();
+    if (kw == 0) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      float s2 = 0.f, s1 = 0.f;
+      for (int j = 0; j < TN; ++j) {
+        if (ACT == ACT_GLU && j >= 2) continue;
+        float s2 = 0.f, s1 = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = m0 + ty + 16 * i;
-        float h = (ACT == ACT_GLU) ? silu_f(acc[i][j]) * acc[i][j + 2] : gelu_f(acc[i][j]);
-        h = row < p.M ? h : 0.f;
-        s2 += h * h;
-        s1 += fabsf(h);
+        for (int i2 = 0; i2 < TM; ++i2)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float z = acc[i2][j][e];
+            float h = (ACT == ACT_GLU) ? silu_f(z) * acc[i2][(j + 2) % TN][e] : gelu_f(z);
+            h = m0 + i2 * 16 + 4 * quad + e < p.M ? h : 0.f;
+            s2 += h * h;
+            s1 += fabsf(h);
+          }
+        s2 += __shfl_xor(s2, 16); s2 += __shfl_xor(s2, 32);
+        s1 += __shfl_xor(s1, 16); s1 += __shfl_xor(s1, 32);
+        if (lane < 16) {
+          const int c = wn * TN * 16 + j * 16;
+          const int cl = ((ACT == ACT_GLU) ? (c >> 6) * 32 + (c & 31) : c) + lane;
+          red2[wm * BNO + cl] = s2;
+          red1[wm * BNO + cl] = s1;
+        }
       }
-      red[0][ty][tx + 16 * j] = s2;
-      red[1][ty][tx + 16 * j] = s1;
     }
     __syncthreads();
     if (tid < BNO) {
-      const int col = n0 / ((ACT == ACT_GLU) ? 2 : 1) + tid;
+      const int col = tn * BNO + tid;
       if (col < p.n_out) {
         float a2 = 0.f, a1 = 0.f;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) { a2 += red[0][w][tid]; a1 += red[1][w][tid]; }
+        for (int w = 0; w < WGM; ++w) { a2 += red2[w * BNO + tid]; a1 += red1[w * BNO + tid]; }
         p.part_s2[(int64_t)tm * p.n_out + col] = a2;
         p.part_s1[(int64_t)tm * p.n_out + col] = a1;
       }
@@ -147,84 +235,71 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs p) {
   }
 }
 
-// Sum of fp32 partials [n_split][M][ldp] of a whole product (GEMM column order, written with
-// a.partial and no activation) followed by the store epilogue of gemm_f32_kernel: bias,
-// activation (exact GeLU, or SwiGLU on (gate, up) pairs of 32-column blocks), routing to two
-// fp32 destinations, residual.  One thread per (row, output column), columns fastest.
-struct SplitEpiF32Args {
-  const float* part;
-  int n_split, M, ldp, n_out;
-  int act, act_cols, split_col;
-  float* C0;
-  float* C1;
-  int64_t ldc0, ldc1;
-  const float* bias;
-  int bias_cols;
-  const float* resid;
-  int64_t ldr;
-};
-
-__global__ void __launch_bounds__(256) splitk_epilogue_f32_kernel(const SplitEpiF32Args p) {
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= (int64_t)p.M * p.n_out) return;
-  const int row = (int)(id / p.n_out), oc = (int)(id % p.n_out);
-  const bool glu = p.act == ACT_GLU;
-  const bool pair = glu && oc < p.act_cols / 2;
-  int c = oc;   // GEMM column of the (gate) value
-  if (glu) c = pair ? (oc / 32) * 64 + (oc & 31) : oc + p.act_cols / 2;
-  float v = 0.f, u = 0.f;
-  for (int s = 0; s < p.n_split; ++s) {
-    const float* src = p.part + ((int64_t)s * p.M + row) * p.ldp + c;
-    v += src[0];
-    if (pair) u += src[32];
-  }
-  if (!glu && p.bias != nullptr && c < p.bias_cols) v += p.bias[c];
-  if (pair) v = silu_f(v) * u;
-  else if (p.act == ACT_GELU && c < p.act_cols) v = gelu_f(v);
-  if (oc < p.split_col) {
-    if (p.resid != nullptr) v += p.resid[(int64_t)row * p.ldr + oc];
-    p.C0[(int64_t)row * p.ldc0 + oc] = v;
-  } else {
-    p.C1[(int64_t)row * p.ldc1 + (oc - p.split_col)] = v;
-  }
-}
-
-int launch_splitk_epilogue_f32(const float* part, int n_split, int ldp, const GemmArgs& g, int act, hipStream_t st) {
-  SplitEpiF32Args a = {};
-  a.part = part; a.n_split = n_split; a.M = g.M; a.ldp = ldp;
-  a.n_out = act == ACT_GLU ? g.N - g.act_cols / 2 : g.N;
-  a.act = act; a.act_cols = g.act_cols; a.split_col = g.split_col;
-  a.C0 = (float*)g.C0; a.C1 = (float*)g.C1; a.ldc0 = g.ldc0; a.ldc1 = g.ldc1;
-  a.bias = g.bias; a.bias_cols = g.bias_cols; a.resid = g.resid; a.ldr = g.ldr;
-  if (act == ACT_GLU && (g.act_cols & 63)) return -1;
-  const int64_t n = (int64_t)a.M * a.n_out;
-  if (n <= 0) return 0;
-  hipLaunchKernelGGL(splitk_epilogue_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
 // ------------------------------------------------------------------ host launchers
 
-template <int ACT, bool DUAL, bool SCORE>
-static int launch_f32(const GemmArgs& a, int n_split, hipStream_t st) {
-  const int tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-  hipLaunchKernelGGL((gemm_f32_kernel<ACT, DUAL, SCORE>), dim3(tiles, n_split), dim3(256), 0, st, a);
+template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE>
+static int launch_f32(const GemmArgs& a, int batch, hipStream_t st) {
+  constexpr int BM = WGM * TM * 16, BN = WGN * TN * 16;
+  constexpr size_t lds = std::max((size_t)(KW > 1 ? KW * WGM * WGN * TM * TN * 1024 : 0), (size_t)(SCORE ? WGM * BN * 8 : 0));
+  static_assert(lds <= 64 * 1024, "within the default limit of dynamic LDS");
+  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, WGM, WGN, KW, PF, ACT, DUAL, SCORE>), dim3(tiles, batch),
+                     dim3(WGM * WGN * KW * 64), lds, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int n_split) {
+// Tile by estimated clocks: ceil(W / 256) workgroups one after the other on the fullest CU, each
+// bound by the matrix rate (256 flop per clock and CU) or by its loads (61 bytes per clock), plus
+// about 3000 clocks of launch, first loads, sum and store.
+struct F32Shape { int bm, bn, wgm, wgn; };
+template <int N>
+static int pick_f32(const F32Shape (&c)[N], int64_t M, int64_t Nn, int64_t K, int batch) {
+  int best = 0;
+  double best_t = 1e30;
+  for (int i = 0; i < N; ++i) {
+    const int64_t w = ((M + c[i].bm - 1) / c[i].bm) * ((Nn + c[i].bn - 1) / c[i].bn) * batch;
+    const double mfma = (double)c[i].bm * c[i].bn * K / 128, ld = 4.0 * K * (c[i].bm * c[i].wgn + c[i].bn * c[i].wgm) / 61;
+    const double t = (double)((w + 255) / 256) * (std::max(mfma, ld) + 3000.0);
+    if (t < best_t) { best_t = t; best = i; }
+  }
+  return best;
+}
+
+template <int ACT, bool DUAL>
+static int launch_f32_act(const GemmArgs& a, int batch, hipStream_t st) {
+  if constexpr (ACT == ACT_GLU) {
+    static const F32Shape c[] = {{128, 128, 2, 2}, {32, 64, 1, 1}, {16, 64, 1, 1}};
+    switch (pick_f32(c, a.M, a.N, a.K, batch)) {
+      case 0: return launch_f32<4, 4, 2, 2, 1, 2, ACT, DUAL, false>(a, batch, st);
+      case 1: return launch_f32<2, 4, 1, 1, 8, 3, ACT, DUAL, false>(a, batch, st);
+      default: return launch_f32<1, 4, 1, 1, 16, 3, ACT, DUAL, false>(a, batch, st);
+    }
+  } else {
+    static const F32Shape c[] = {{128, 128, 2, 2}, {64, 64, 2, 2}, {32, 32, 1, 1}, {16, 32, 1, 1}, {16, 16, 1, 1}};
+    switch (pick_f32(c, a.M, a.N, a.K, batch)) {
+      case 0: return launch_f32<4, 4, 2, 2, 1, 2, ACT, DUAL, false>(a, batch, st);
+      case 1: return launch_f32<2, 2, 2, 2, 4, 3, ACT, DUAL, false>(a, batch, st);
+      case 2: return launch_f32<2, 2, 1, 1, 16, 3, ACT, DUAL, false>(a, batch, st);
+      case 3: return launch_f32<1, 2, 1, 1, 16, 4, ACT, DUAL, false>(a, batch, st);
+      default: return launch_f32<1, 1, 1, 1, 16, 4, ACT, DUAL, false>(a, batch, st);
+    }
+  }
+}
+
+int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int batch) {
   if (a.M <= 0 || a.N <= 0) return 0;
+  if ((a.K & 3) || (a.lda & 3) || (a.ldb & 3) || (a.split_col & 3)) return -1;
   const bool dual = a.A1 != nullptr;
-  if (n_split > 1 && !(a.partial && act == ACT_NONE && !score)) return -1;
   if (score) {
-    if (act == ACT_GELU) return launch_f32<ACT_GELU, false, true>(a, 1, st);
-    if (act == ACT_GLU) return launch_f32<ACT_GLU, false, true>(a, 1, st);
+    if (act == ACT_GELU) return launch_f32<2, 4, 2, 2, 1, 2, ACT_GELU, false, true>(a, 1, st);
+    if (act == ACT_GLU) return launch_f32<2, 4, 2, 2, 1, 2, ACT_GLU, false, true>(a, 1, st);
     return -1;
   }
-  if (act == ACT_NONE) return launch_f32<ACT_NONE, false, false>(a, n_split, st);
-  if (act == ACT_GELU) return launch_f32<ACT_GELU, false, false>(a, 1, st);
-  if (act == ACT_GLU && !dual) return launch_f32<ACT_GLU, false, false>(a, 1, st);
-  if (act == ACT_GLU && dual) return launch_f32<ACT_GLU, true, false>(a, 1, st);
+  if (act == ACT_NONE) return launch_f32_act<ACT_NONE, false>(a, batch, st);
+  if (act == ACT_POLY) return launch_f32_act<ACT_POLY, false>(a, batch, st);
+  if (act == ACT_GELU) return launch_f32_act<ACT_GELU, false>(a, batch, st);
+  if (act == ACT_GLU && !dual) return launch_f32_act<ACT_GLU, false>(a, batch, st);
+  if (act == ACT_GLU && dual) return launch_f32_act<ACT_GLU, true>(a, batch, st);
   return -1;
 }
 

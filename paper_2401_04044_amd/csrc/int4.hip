@@ -954,40 +954,7 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
   w.off_cat = off; off = align256(off + (size_t)w.t_pad * L.k4 * L.esz);
   w.off_t = off; off = align256(off + (size_t)w.t_pad * L.n_up * L.rp * L.esz);
   w.off_h2 = off; off = align256(off + (size_t)w.t_pad * L.mp * L.esz);
-  w.g3_split = 1;
   w.off_kpart = off;
-  if (!L.tiled && L.rp > 0 && L.mp > 0 && T > 0) {
-    // fp32: the product h2 * P2 has few 64 x 64 tiles and a long reduction: split it so that
-    // about 256 workgroups exist, at least 8 slabs of 16 each
-    const int tiles64 = (int)((T + 63) / 64) * ((L.rp + 63) / 64);
-    int sp = 256 / (tiles64 > 0 ? tiles64 : 1);
-    if (sp > L.mp / 128) sp = L.mp / 128;
-    if (sp > 32) sp = 32;
-    if (sp < 1) sp = 1;
-    w.g3_split = sp;
-    size_t scratch = sp > 1 ? (size_t)sp * T * L.rp * 4 : 0;
-    // the other products' own splits (f32_split)
-    const int ns[3] = {L.n1, L.n_up * L.mp, L.dn};
-    const int ks[3] = {L.dk, L.rp, L.k4};
-    for (int i = 0; i < 3; ++i) {
-      const int s2 = f32_split(T, ns[i], ks[i]);
-      const size_t b = (size_t)s2 * T * ns[i] * 4;
-      if (s2 > 1 && b > scratch) scratch = b;
-    }
-    w.kpart_bytes = scratch;
-    if (scratch > 0) off = align256(off + scratch);
-  } else if (!L.tiled && T > 0) {
-    size_t scratch = 0;
-    const int ns[2] = {L.n1, L.dn};
-    const int ks[2] = {L.dk, L.k4};
-    for (int i = 0; i < 2; ++i) {
-      const int s2 = f32_split(T, ns[i], ks[i]);
-      const size_t b = (size_t)s2 * T * ns[i] * 4;
-      if (s2 > 1 && b > scratch) scratch = b;
-    }
-    w.kpart_bytes = scratch;
-    if (scratch > 0) off = align256(off + scratch);
-  }
   if (L.tiled && L.rp > 0 && L.mp > 0 && T > 0) {
     size_t scratch = 0;
     if (ffn2_fused_applies(L, T)) {

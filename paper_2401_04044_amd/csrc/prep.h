@@ -23,6 +23,7 @@ struct PermArgs {
   int64_t row_off;
   int glu_mode;
   int dst_tiled;   // dst in the 32x16-block tiled layout of gemm_bf16.hip, ldd = padded K
+  int n_pad, c_pad;   // tiled: zeros are written for n_count <= n < n_pad and c_count <= c < c_pad as well
 };
 
 int launch_fill_zero(void* p, size_t bytes, hipStream_t st);
