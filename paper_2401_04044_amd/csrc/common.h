@@ -113,7 +113,9 @@ struct GemmArgs {
   int64_t batch_a, batch_b, batch_c;
   // ACT_POLY: C0 = poly[2] D + poly[1] resid + poly[0] I.  Ct (fp32 kernel, optional): a transposed copy
   // [N, ldct] of C0, product y at Ct + y batch_ct
+  // sym (with Ct = the transposed destination, square tiles): C0 is symmetric, half of it is computed
   float poly[3];
+  int sym;
   float* Ct;
   int64_t ldct, batch_ct;
   // score mode: per-row-tile partial column sums of h^2 and |h|

@@ -19,6 +19,7 @@
 #include "prep.h"
 #include <algorithm>
 #include <math.h>
+#include <utility>
 
 namespace ffsplit {
 
@@ -203,35 +204,63 @@ __global__ void emit_kernel(const float* src, int64_t lds, int transposed, T* ds
   }
 }
 
-// Coefficients (a, b, c) of the steps.  Growth: the odd quintic published with the Muon optimiser (K.
-// Jordan et al., 2024), slope 3.4445 at zero and values in [0.68, 1.14] from about a quarter on, so
-// that it neither squashes singular values that are already large (which would cost digits: a
-// value mapped near zero keeps its absolute rounding error) nor overshoots.  Finish: (15 x - 10
-// x^3 + 3 x^5) / 8, cubic convergence to 1.  Budget as before: singular values down to 1 / (64 r)
-// of the Frobenius norm (a square Gaussian Y, r = d_model, has its smallest near r^-1.5 of it); a
-// basis direction below that comes out shorter than unit length.
+// Odd quintic with the least max |1 - p| on [lo, hi] (lo < hi not too close): the values 1 - e, 1 + e,
+// 1 - e, 1 + e at lo, the two interior extrema and hi (Remez exchange).
+void minimax_quintic(double lo, double hi, double* p) {
+  double q = (3 * lo + hi) / 4, r = (lo + 3 * hi) / 4;
+  for (int it = 0; it < 40; ++it) {
+    const double xs[4] = {lo, q, r, hi};
+    double A[4][5];
+    for (int i = 0; i < 4; ++i) {
+      const double x = xs[i], x2 = x * x;
+      A[i][0] = x; A[i][1] = x * x2; A[i][2] = x * x2 * x2; A[i][3] = (i & 1) ? -1 : 1; A[i][4] = 1;
+    }
+    for (int c = 0; c < 4; ++c) {   // elimination with row exchange
+      int best = c;
+      for (int i = c + 1; i < 4; ++i)
+        if (fabs(A[i][c]) > fabs(A[best][c])) best = i;
+      for (int j = 0; j < 5; ++j) std::swap(A[c][j], A[best][j]);
+      for (int i = 0; i < 4; ++i)
+        if (i != c) {
+          const double f = A[i][c] / A[c][c];
+          for (int j = c; j < 5; ++j) A[i][j] -= f * A[c][j];
+        }
+    }
+    for (int i = 0; i < 3; ++i) p[i] = A[i][4] / A[i][i];
+    const double disc = 9 * p[1] * p[1] - 20 * p[0] * p[2];
+    if (disc < 0) break;
+    const double r1 = (-3 * p[1] - sqrt(disc)) / (10 * p[2]), r2 = (-3 * p[1] + sqrt(disc)) / (10 * p[2]);
+    q = sqrt(std::max(std::min(r1, r2), lo * lo)); r = sqrt(std::max(std::max(r1, r2), lo * lo));
+  }
+}
+
+// Coefficients (a, b, c) of the steps.  While the singular values may reach below 0.15 of the largest:
+// the minimax quintic of [0.15, 1], which multiplies small ones by 3.66 and keeps the others between
+// 0.52 and 1 of the new largest (the fastest growth, slope 4.2, would map some large ones near zero,
+// where they keep their absolute rounding error).  Then the minimax quintic of the range itself, and
+// (15 x - 10 x^3 + 3 x^5) / 8 at the end, cubic convergence to 1.  Budget: singular values
+// down to 1 / (1024 r) of the Frobenius norm (a square Gaussian Y, r = d_model, has its smallest near
+// r^-1.5 of it); a basis direction below that comes out shorter than unit length.
 constexpr int MAX_STEPS = 48;
 int polar_steps(int r, float (*coef)[3]) {
-  auto range = [](const double* q, double& lo, double& hi) {
+  double lo = 1.0 / (1024.0 * r), hi = 1.0;
+  int n = 0;
+  while ((lo < 1.0 - 3e-8 || hi > 1.0 + 3e-8) && n < MAX_STEPS) {
+    double p[3] = {1.875, -1.25, 0.375};
+    if (lo < 0.15 * hi) {
+      minimax_quintic(0.15, 1.0, p);
+      p[0] /= hi; p[1] /= hi * hi * hi; p[2] /= hi * hi * hi * hi * hi;
+    } else if (hi - lo > 1e-3) {
+      minimax_quintic(lo, hi, p);
+    }
     double a = 1e30, b = 0;
     for (int i = 0; i <= 4000; ++i) {
-      const double x = lo + (hi - lo) * i / 4000.0, x2 = x * x, y = x * (q[0] + x2 * (q[1] + x2 * q[2]));
-      a = y < a ? y : a;
-      b = y > b ? y : b;
+      const double x = lo + (hi - lo) * i / 4000.0, x2 = x * x, y = x * (p[0] + x2 * (p[1] + x2 * p[2]));
+      a = std::min(a, y);
+      b = std::max(b, y);
     }
     lo = a; hi = b;
-  };
-  const double grow[3] = {3.4445, -4.7750, 2.0315}, fin[3] = {1.875, -1.25, 0.375};
-  double lo = 1.0 / (64.0 * r), hi = 1.0;
-  int n = 0;
-  while ((lo < 0.6 || hi > 1.2) && n < MAX_STEPS - 8) {
-    for (int i = 0; i < 3; ++i) coef[n][i] = (float)grow[i];
-    range(grow, lo, hi);
-    ++n;
-  }
-  while ((lo < 1.0 - 3e-8 || hi > 1.0 + 3e-8) && n < MAX_STEPS) {
-    for (int i = 0; i < 3; ++i) coef[n][i] = (float)fin[i];
-    range(fin, lo, hi);
+    for (int i = 0; i < 3; ++i) coef[n][i] = (float)p[i];
     ++n;
   }
   return n;
@@ -375,6 +404,7 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
     float* XTn = (float*)(ws + w.off_xt[(it + 1) & 1]);
     GemmArgs g = gemm_nt(X, dm, X, dm, r8, r8, dm, S, r8);
     g.batch_a = g.batch_b = nx; g.batch_c = ns;
+    g.sym = 1; g.Ct = S; g.ldct = r8; g.batch_ct = ns;
     FK(launch_gemm_f32(g, ACT_NONE, false, st, w.mats));
     g = gemm_nt(S, r8, S, r8, r8, r8, r8, Tm, r8);   // (S is symmetric)
     g.batch_a = g.batch_b = g.batch_c = ns; g.resid = S; g.ldr = r8;

@@ -9,12 +9,14 @@
 //     of Sec. 4.1, Eq. 3), h never leaving registers.
 // True fp32 products (v_mfma_f32_16x16x4_f32) and the erf form of GeLU: the error bar is 1e-5.
 //
-// Operands go straight from global memory into registers, no LDS and no barrier: the fp32 matrix
-// rate is a sixteenth of the bf16 one, so even a 32x32 wave tile asks for 32 bytes per clock and
-// CU where the vector cache delivers 61.  Lane l of a 16-row tile loads the 16 bytes of row l & 15,
-// k elements 4 (l >> 4) .. + 3 of a 16-deep slab; element t of both operands' registers feeds MFMA
-// t of the slab (any pairing of k works as long as both sides use the same).  PF slabs are in
-// flight per wavefront.
+// Every wavefront moves its own operands, no barrier in the loop: the fp32 matrix rate is a
+// sixteenth of the bf16 one, so even a 32x32 wave tile asks for 32 bytes per clock and CU where the
+// vector cache delivers 61.  It does so only if four neighbouring lanes read one 64-byte piece
+// (16 bytes per clock where every lane has its own row, the order the MFMA wants: 512 x 512 x 2048
+// twice took 34 us), so lane l loads chunk l & 3 of row l >> 2 of a 16 x 16 block and the wavefront
+// turns the block round in 1 KiB of LDS of its own: lane l then holds k elements 4 (l >> 4) .. + 3 of row
+// l & 15, and element t of both operands' registers feeds MFMA t of the slab (any pairing of k
+// works as long as both sides use the same).  PF slabs are in flight per wavefront.
 // A workgroup is WGM x WGN wavefronts per k group and KW k groups, which take every KW-th slab and
 // add their accumulators through LDS in a fixed order: products of a hundred tokens are bound by
 // the latency of their chain of slabs, and this shortens it without partial sums in memory or a
@@ -25,6 +27,16 @@
 namespace ffsplit {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+// 16 bytes at base + lane_off + scalar_off; a lane offset of ~0 is out of range and reads zero
+__device__ __forceinline__ f32x4_t buffer_f32x4(const float* base, uint32_t lane_off, uint32_t scalar_off) {
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+  const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(
+      __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xfffffff0u, 0x00027000), lane_off, scalar_off, 0);
+  f32x4_t f;
+  __builtin_memcpy(&f, &v, 16);
+  return f;
+}
 
 template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE>
 __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmArgs p) {
@@ -38,20 +50,25 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
   const int kw = wave / (WGM * WGN), wt = wave % (WGM * WGN), wm = wt / WGN, wn = wt % WGN;
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
+  // A symmetric result: one half of the tiles stores the other half's mirror images; alternate products
+  // of a batch take opposite halves (a CU tends to get the same tile of two of them).
+  if (ACT == ACT_NONE && p.sym && (blockIdx.y & 1 ? tn > tm : tn < tm)) return;
   const int m0 = tm * BM + wm * TM * 16, n0 = tn * BN + wn * TN * 16;   // the wavefront's corner
   const int r16 = lane & 15, quad = lane >> 4;
 
-  const float* a_src[NA][TM];
-  const float* b_src[TN];
+  // Buffer loads: the wavefront's corner in scalar registers, one byte offset per row tile, a scalar
+  // offset along K (rows past the end repeat the last one).  A chunk past K takes an offset beyond the range, which reads as zero: no branch
+  // stands between the loads, so the waits for them stay exact.
+  uint32_t a_off[TM], b_off[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int64_t off = (int64_t)min(m0 + i * 16 + r16, p.M - 1) * p.lda + 4 * quad + p.batch_a * blockIdx.y;
-    a_src[0][i] = (const float*)p.A + off;
-    if (DUAL) a_src[NA - 1][i] = (const float*)p.A1 + off;
-  }
+  for (int i = 0; i < TM; ++i)
+    a_off[i] = (uint32_t)(min(i * 16 + (lane >> 2), max(p.M - 1 - m0, 0)) * (int)p.lda + 4 * (lane & 3)) * 4;
 #pragma unroll
   for (int j = 0; j < TN; ++j)
-    b_src[j] = (const float*)p.Bt + (int64_t)min(n0 + j * 16 + r16, p.N - 1) * p.ldb + 4 * quad + p.batch_b * blockIdx.y;
+    b_off[j] = (uint32_t)(min(j * 16 + (lane >> 2), max(p.N - 1 - n0, 0)) * (int)p.ldb + 4 * (lane & 3)) * 4;
+  const float* const a_base = (const float*)p.A + (int64_t)min(m0, p.M - 1) * p.lda + p.batch_a * blockIdx.y;
+  const float* const a1_base = DUAL ? (const float*)p.A1 + (int64_t)min(m0, p.M - 1) * p.lda : a_base;
+  const float* const b_base = (const float*)p.Bt + (int64_t)min(n0, p.N - 1) * p.ldb + p.batch_b * blockIdx.y;
 
   f32x4_t acc[TM][TN];
 #pragma unroll
@@ -61,67 +78,79 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
 
   const int slabs = (p.K + 15) / 16;
   const int n = (slabs - kw + KW - 1) / KW;   // this k group's slabs: kw, kw + KW, ...
-  f32x4_t fa[PF][NA][TM], fb[PF][TN];
+  f32x4_t ga[PF][NA][TM], gb[PF][TN];   // in flight, as loaded
+  f32x4_t fa[2][NA][TM], fb[2][TN];     // the slab being multiplied and the next one
   auto load = [&](int slot, int i) {
     const int k0 = (kw + i * KW) * 16;
-    // whole chunks only (K is a multiple of 4): a chunk past K is zero on both sides
-    const bool ok = k0 + 4 * quad < p.K;
-    const int k = ok ? k0 : 0;
+    const bool ok = k0 + 4 * (lane & 3) < p.K;   // (K is a multiple of 4: whole chunks)
 #pragma unroll
-    for (int t = 0; t < TM; ++t)
-#pragma unroll
-      for (int s = 0; s < NA; ++s) {
-        fa[slot][s][t] = *(const f32x4_t*)(a_src[s][t] + k);
-        if (!ok) fa[slot][s][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      }
-#pragma unroll
-    for (int t = 0; t < TN; ++t) {
-      fb[slot][t] = *(const f32x4_t*)(b_src[t] + k);
-      if (!ok) fb[slot][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < TM; ++t) {
+      ga[slot][0][t] = buffer_f32x4(a_base, ok ? a_off[t] : ~0u, k0 * 4);
+      if (DUAL) ga[slot][NA - 1][t] = buffer_f32x4(a1_base, ok ? a_off[t] : ~0u, k0 * 4);
     }
+#pragma unroll
+    for (int t = 0; t < TN; ++t) gb[slot][t] = buffer_f32x4(b_base, ok ? b_off[t] : ~0u, k0 * 4);
   };
-  auto load_full = [&](int slot, int i) {
-    const int k = (kw + i * KW) * 16;
+  // Chunk c of row r of a block sits at 4 r + (c ^ (r >> 2)): 16 consecutive lanes write 256
+  // contiguous bytes and read 16 different 16-byte bank groups.  A wavefront's LDS accesses stay in order.
+  constexpr int BLKS = NA * TM + TN;
+  f32x4_t* const turn = (f32x4_t*)f32_smem + wave * BLKS * 64;
+  const int put_at = (lane & ~3) | ((lane & 3) ^ ((lane >> 4) & 3));
+  const int get_at = r16 * 4 + (quad ^ (r16 >> 2));
+  auto turn_round = [&](int slot, int set) {
 #pragma unroll
-    for (int t = 0; t < TM; ++t)
+    for (int s = 0; s < NA; ++s)
 #pragma unroll
-      for (int s = 0; s < NA; ++s) fa[slot][s][t] = *(const f32x4_t*)(a_src[s][t] + k);
+      for (int t = 0; t < TM; ++t) turn[(s * TM + t) * 64 + put_at] = ga[slot][s][t];
 #pragma unroll
-    for (int t = 0; t < TN; ++t) fb[slot][t] = *(const f32x4_t*)(b_src[t] + k);
+    for (int t = 0; t < TN; ++t) turn[(NA * TM + t) * 64 + put_at] = gb[slot][t];
+#pragma unroll
+    for (int s = 0; s < NA; ++s)
+#pragma unroll
+      for (int t = 0; t < TM; ++t) fa[set][s][t] = turn[(s * TM + t) * 64 + get_at];
+#pragma unroll
+    for (int t = 0; t < TN; ++t) fb[set][t] = turn[(NA * TM + t) * 64 + get_at];
   };
-  auto mma = [&](int slot) {
+  auto mma = [&](int set) {
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          const float a = fa[slot][DUAL ? (j >> 1) & 1 : 0][i][t], b = fb[slot][j][t];
+          const float a = fa[set][DUAL ? (j >> 1) & 1 : 0][i][t], b = fb[set][j][t];
           acc[i][j] = SCORE ? __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[i][j], 0, 0, 0)
                             : __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, acc[i][j], 0, 0, 0);
         }
   };
+  static_assert(PF % 2 == 0, "the register set of slab i is i & 1");
 #pragma unroll
-  for (int u = 0; u < PF; ++u)
-    if (u < n) load(u, u);
+  for (int u = 0; u < PF; ++u) load(u, u);
+  turn_round(0, 0);
+  load(0, PF);
   int i = 0;
-  // the slabs loaded here are never the last one of the product, the only one that can be short
-  for (; i + 2 * PF < n; i += PF)
+  for (; i + PF <= n; i += PF)
 #pragma unroll
-    for (int u = 0; u < PF; ++u) { mma(u); load_full(u, i + u + PF); }
-  for (; i < n; i += PF)
+    for (int u = 0; u < PF; ++u) {
+      __builtin_amdgcn_sched_barrier(0);   // keeps PF slabs in flight: the loads are not gathered
+      turn_round((u + 1) % PF, (u + 1) & 1);   // slab i + u + 1 (zeros past the end)
+      load((u + 1) % PF, i + u + 1 + PF);
+      mma(u & 1);
+    }
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < PF; ++u)
-      if (i + u < n) {
-        mma(u);
-        if (i + u + PF < n) load(u, i + u + PF);
-      }
+  for (int u = 0; u < PF - 1; ++u)
+    if (i + u < n) {
+      mma(u & 1);
+      if (u + 1 < PF - 1) turn_round((u + 1) % PF, (u + 1) & 1);
+    }
 
   if constexpr (KW > 1) {
     // Sum over the k groups: all but the first park their accumulators, then every wavefront adds
     // up its share of the tiles and hands the sums to the first group.
     constexpr int TILES = WGM * WGN * TM * TN;
-    f32x4_t* sm = (f32x4_t*)f32_smem;   // [KW][TILES][64]
+    f32x4_t* sm = (f32x4_t*)f32_smem;   // [KW][TILES][64], over the wavefronts' turning blocks
+    __syncthreads();
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -195,7 +224,7 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
     constexpr int BNO = (ACT == ACT_GLU) ? BN / 2 : BN;
     float* red2 = f32_smem;             // [WGM][BNO] (after the sum over the k groups has been read)
     float* red1 = red2 + WGM * BNO;
-    if (KW > 1) __syncthreads();
+    __syncthreads();
     if (kw == 0) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
@@ -240,7 +269,9 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
 template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE>
 static int launch_f32(const GemmArgs& a, int batch, hipStream_t st) {
   constexpr int BM = WGM * TM * 16, BN = WGN * TN * 16;
-  constexpr size_t lds = std::max((size_t)(KW > 1 ? KW * WGM * WGN * TM * TN * 1024 : 0), (size_t)(SCORE ? WGM * BN * 8 : 0));
+  constexpr size_t waves = WGM * WGN * KW;
+  constexpr size_t lds = std::max(waves * ((DUAL ? 2 : 1) * TM + TN) * 1024,
+                                  std::max(KW > 1 ? waves * TM * TN * 1024 : (size_t)0, (size_t)(SCORE ? WGM * BN * 8 : 0)));
   static_assert(lds <= 64 * 1024, "within the default limit of dynamic LDS");
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, WGM, WGN, KW, PF, ACT, DUAL, SCORE>), dim3(tiles, batch),
@@ -253,10 +284,11 @@ static int launch_f32(const GemmArgs& a, int batch, hipStream_t st) {
 // about 3000 clocks of launch, first loads, sum and store.
 struct F32Shape { int bm, bn, wgm, wgn; };
 template <int N>
-static int pick_f32(const F32Shape (&c)[N], int64_t M, int64_t Nn, int64_t K, int batch) {
+static int pick_f32(const F32Shape (&c)[N], int64_t M, int64_t Nn, int64_t K, int batch, bool square) {
   int best = 0;
   double best_t = 1e30;
   for (int i = 0; i < N; ++i) {
+    if (square && c[i].bm != c[i].bn) continue;
     const int64_t w = ((M + c[i].bm - 1) / c[i].bm) * ((Nn + c[i].bn - 1) / c[i].bn) * batch;
     const double mfma = (double)c[i].bm * c[i].bn * K / 128, ld = 4.0 * K * (c[i].bm * c[i].wgn + c[i].bn * c[i].wgm) / 61;
     const double t = (double)((w + 255) / 256) * (std::max(mfma, ld) + 3000.0);
@@ -268,19 +300,19 @@ static int pick_f32(const F32Shape (&c)[N], int64_t M, int64_t Nn, int64_t K, in
 template <int ACT, bool DUAL>
 static int launch_f32_act(const GemmArgs& a, int batch, hipStream_t st) {
   if constexpr (ACT == ACT_GLU) {
-    static const F32Shape c[] = {{128, 128, 2, 2}, {32, 64, 1, 1}, {16, 64, 1, 1}};
-    switch (pick_f32(c, a.M, a.N, a.K, batch)) {
-      case 0: return launch_f32<4, 4, 2, 2, 1, 2, ACT, DUAL, false>(a, batch, st);
-      case 1: return launch_f32<2, 4, 1, 1, 8, 3, ACT, DUAL, false>(a, batch, st);
-      default: return launch_f32<1, 4, 1, 1, 16, 3, ACT, DUAL, false>(a, batch, st);
+    static const F32Shape c[] = {{64, 128, 2, 2}, {32, 64, 1, 1}, {16, 64, 1, 1}};
+    switch (pick_f32(c, a.M, a.N, a.K, batch, false)) {
+      case 0: return launch_f32<2, 4, 2, 2, 1, 2, ACT, DUAL, false>(a, batch, st);
+      case 1: return launch_f32<2, 4, 1, 1, 8, 2, ACT, DUAL, false>(a, batch, st);
+      default: return launch_f32<1, 4, 1, 1, 8, 4, ACT, DUAL, false>(a, batch, st);
     }
   } else {
-    static const F32Shape c[] = {{128, 128, 2, 2}, {64, 64, 2, 2}, {32, 32, 1, 1}, {16, 32, 1, 1}, {16, 16, 1, 1}};
-    switch (pick_f32(c, a.M, a.N, a.K, batch)) {
-      case 0: return launch_f32<4, 4, 2, 2, 1, 2, ACT, DUAL, false>(a, batch, st);
-      case 1: return launch_f32<2, 2, 2, 2, 4, 3, ACT, DUAL, false>(a, batch, st);
-      case 2: return launch_f32<2, 2, 1, 1, 16, 3, ACT, DUAL, false>(a, batch, st);
-      case 3: return launch_f32<1, 2, 1, 1, 16, 4, ACT, DUAL, false>(a, batch, st);
+    // (128 x 128 on four wavefronts was slower everywhere: one wavefront per SIMD shows every wait)
+    static const F32Shape c[] = {{64, 64, 2, 2}, {32, 32, 1, 1}, {16, 32, 1, 1}, {16, 16, 1, 1}};
+    switch (pick_f32(c, a.M, a.N, a.K, batch, a.sym != 0)) {
+      case 0: return launch_f32<2, 2, 2, 2, 2, 4, ACT, DUAL, false>(a, batch, st);
+      case 1: return launch_f32<2, 2, 1, 1, 8, 4, ACT, DUAL, false>(a, batch, st);
+      case 2: return launch_f32<1, 2, 1, 1, 8, 4, ACT, DUAL, false>(a, batch, st);
       default: return launch_f32<1, 1, 1, 1, 16, 4, ACT, DUAL, false>(a, batch, st);
     }
   }
