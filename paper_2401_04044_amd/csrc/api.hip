@@ -64,10 +64,16 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
   auto koff_bytes = [&](int koff) -> size_t { return L.tiled ? (size_t)(koff / 16) * 1024 : (size_t)koff * esz; };
   // small batches are bound by streaming the weights: dedicated kernels
   const bool small_m = bf16 && M <= SKINNY_MAX_M;
+  bool first = true;   // the first product zeroes the arrival counters of those after it
   auto run = [&](GemmArgs& g, int a) -> int {
     g.m_pad = w.t_pad;
     if (!bf16) return launch_gemm_f32(g, a, false, st);
-    if (small_m && (g.N & 31) == 0) return launch_skinny_bf16(g, a, (float*)(ws + w.off_kpart), st);
+    if (small_m && (g.N & 31) == 0) {
+      unsigned* cnt = (unsigned*)(ws + w.off_cnt);
+      const bool clear = first;
+      first = false;
+      return launch_skinny_bf16(g, a, (float*)(ws + w.off_kpart), cnt, clear ? w.n_cnt : 0, st);
+    }
     const bool dual = g.A1 != nullptr;
     const bool paired = a == ACT_GLU;
     GemmPlan plan = gemm_plan(M, g.N, g.K, paired, dual, !dual);

@@ -155,12 +155,15 @@ constexpr int FFN2_FUSED_RANK = 512;
 int ffn2_fused_splits(int M, int mp);
 int launch_ffn2_fused(const void* T1, int64_t ldt, const void* Q1t, int64_t ldq, const void* P2t, int64_t ldp2, int M,
                       int mp, int rp, float* part, int n_split, hipStream_t st);
-// small-batch path (M <= SKINNY_MAX_M, N a multiple of 32): weight-streaming kernels, one or two
-// blocks of 32 tokens per pass over the weights (four blocks were measured no better than the
-// tiled GEMM at 128 rows); part: scratch of skinny_part_bytes(N, M) bytes
+// small-batch path (M <= SKINNY_MAX_M, N a multiple of 32): one weight-streaming launch per product;
+// part: scratch of skinny_part_bytes(M) bytes.  A product whose rows are too few for the machine cuts
+// its reduction across workgroups, which count their arrival in `counters` (skinny_counters(N) of
+// them, zero before the launch and left zero; null: no such cut); n_clear > 0 (with no cut): this
+// launch zeroes counters[0 .. n_clear).
 constexpr int SKINNY_MAX_M = 64;
-size_t skinny_part_bytes(int n_max, int M);
-int launch_skinny_bf16(const GemmArgs& a, int act, float* part, hipStream_t st);
+size_t skinny_part_bytes(int M);
+inline int skinny_counters(int n) { return n / 16; }
+int launch_skinny_bf16(const GemmArgs& a, int act, float* part, unsigned* counters, int n_clear, hipStream_t st);
 // the reduce half alone: sum of n_split ranges of partial tiles, activation, stores
 // (f16_out: the destinations hold fp16, saturating, instead of bf16)
 int launch_skinny_reduce(const GemmArgs& a, int act, const float* part, int n_split, int f16_out, hipStream_t st);

@@ -954,6 +954,10 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
   w.off_cat = off; off = align256(off + (size_t)w.t_pad * L.k4 * L.esz);
   w.off_t = off; off = align256(off + (size_t)w.t_pad * L.n_up * L.rp * L.esz);
   w.off_h2 = off; off = align256(off + (size_t)w.t_pad * L.mp * L.esz);
+  if (L.tiled && T <= SKINNY_MAX_M) {
+    w.n_cnt = skinny_counters(L.rp > L.dn ? L.rp : L.dn);
+    w.off_cnt = off; off = align256(off + (size_t)w.n_cnt * 4);
+  }
   w.off_kpart = off;
   if (L.tiled && L.rp > 0 && L.mp > 0 && T > 0) {
     size_t scratch = 0;
@@ -963,10 +967,7 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
     }
     if (T <= SKINNY_MAX_M) {
       // small batches take the weight-streaming kernels: room for their partial tiles
-      int n_max = L.n1 > L.n_up * L.mp ? L.n1 : L.n_up * L.mp;
-      if (L.dn > n_max) n_max = L.dn;
-      if (L.rp > n_max) n_max = L.rp;
-      const size_t sk = skinny_part_bytes(n_max, (int)T);
+      const size_t sk = skinny_part_bytes((int)T);
       if (sk > scratch) scratch = sk;
     }
     if (T > SKINNY_MAX_M) {
@@ -980,8 +981,7 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
     w.kpart_bytes = scratch;
     if (scratch > 0) off = align256(off + scratch);
   } else if (L.tiled && T > 0 && T <= SKINNY_MAX_M) {
-    int n_max = L.n1 > L.dn ? L.n1 : L.dn;
-    off = align256(off + skinny_part_bytes(n_max, (int)T));
+    off = align256(off + skinny_part_bytes((int)T));
   } else if (L.tiled && T > SKINNY_MAX_M) {
     const size_t b1 = gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false), b4 = gemm_scratch(T, d.d_model, L.k4, false, false);
     const size_t scratch = b1 > b4 ? b1 : b4;

@@ -1,17 +1,8 @@
-// Small-batch (at most 32 rows) bf16 products of the split feed-forward path, gfx950 only:
-// the decode regime, where every product is bound by streaming its weights from HBM once.
-//
-//   D[M, N] = A[M, K] * Bt[N, K]^T ,  M <= 32, weights in the 32 x 16-block tiled layout.
-//
-// One wavefront owns one 32-row block of the weights over a range of the reduction: it
-// streams that range's 1 KiB blocks (one 16-byte load per lane, contiguous across the
-// wavefront), pairs each with the matching 1 KiB block of the activations (tiled, or gathered
-// from a row-major matrix; they stay in cache) and feeds v_mfma_f32_32x32x16_bf16, two
-// groups of eight blocks deep in registers so that about 16 KiB per wavefront is in flight.
-// No LDS, no barrier.  The reduction is cut into S ranges so that a few thousand wavefronts
-// exist; their fp32 partial tiles are written in accumulator order and a second kernel adds
-// them in a fixed order, applies the activation and writes bf16 (tiled or row-major, one or
-// two destinations) with the same column rules as the large-batch kernels' epilogue.
+// Small-batch products of the split feed-forward path, gfx950 only: the decode regime, where every
+// product is bound by streaming its weights from HBM once.
+//   D[M, N] = A[M, K] * Bt[N, K]^T
+// rows16_kernel: bf16 weights in the 32 x 16-block tiled layout, M <= 64, one launch per product.
+// skinny_stream_q2_kernel + skinny_reduce_kernel: 8- and 3-bit weights (qformat.h), M <= 32.
 #include "common.h"
 #include "layout.h"
 #include "qformat.h"
@@ -28,111 +19,6 @@ union SFrag {
   u32x4_t u;
   bf16x8_t v;
 };
-
-constexpr int SK_U = 8;   // blocks per register group
-
-struct SkinnyArgs {
-  const void* A;
-  const void* A1;     // second left operand for odd 32-row blocks of the weights (or null)
-  const void* Bt;
-  int64_t lda, ldb;
-  int M, N, K;
-  int a_tiled;
-  int n_rb;           // 32-row blocks of the weights
-  int n_split;        // ranges of the reduction
-  int kb_per;         // 16-element k blocks per range
-  int n_tb;           // 32-token blocks of the activations (at most NT of the kernel)
-  float* part;        // [n_split][n_rb][NT][4][64] float4: accumulator order
-};
-
-template <bool A_TILED, int NT>
-__global__ void __launch_bounds__(256) skinny_stream_kernel(const SkinnyArgs p) {
-  constexpr int U = SK_U;   // blocks per register group
-  const int lane = threadIdx.x & 63;
-  const int task = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (task >= p.n_rb * p.n_split) return;
-  const int rb = task % p.n_rb, sp = task / p.n_rb;
-  const int kb_total = (p.K + 15) / 16;
-  const int kb0 = sp * p.kb_per;
-  const int kb1 = min(kb_total, kb0 + p.kb_per);
-  const int kb_last = kb1 - 1;
-
-  const char* wbase = (const char*)p.Bt + ((int64_t)rb * (p.ldb / 16) * 64 + lane) * 16;
-  // one activation base per block of 32 tokens (a block past the batch repeats the last one;
-  // its results are never read)
-  const char* abase[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int tb = min(t, p.n_tb - 1);
-    abase[t] = (const char*)((p.A1 != nullptr && (rb & 1)) ? p.A1 : p.A);
-    if (A_TILED) {
-      abase[t] += ((int64_t)tb * (p.lda / 16) * 64 + lane) * 16;
-    } else {
-      const int row = min(tb * 32 + (lane & 31), p.M - 1);
-      abase[t] += ((int64_t)row * p.lda + (lane >> 5) * 8) * 2;
-    }
-  }
-  // block kb of the weights / of the activations; past the range: the last block again (its
-  // product is masked out below), so that the loads stay unconditional
-  auto wload = [&](int kb) { return *(const u32x4_t*)(wbase + (int64_t)min(kb, kb_last) * 1024); };
-  auto aload = [&](int t, int kb) {
-    const int k = min(kb, kb_last);
-    if (A_TILED) return *(const u32x4_t*)(abase[t] + (int64_t)k * 1024);
-    // row-major: a chunk past K (K is a multiple of 8) reads the row's first chunk instead;
-    // the weights are zero there
-    const int col = k * 16 + (lane >> 5) * 8;
-    return *(const u32x4_t*)(abase[t] + (col < p.K ? (int64_t)k * 32 : -(int64_t)((lane >> 5) * 16)));
-  };
-
-  f32x16_t acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-  u32x4_t w0[U], a0[NT][U], w1[U], a1[NT][U];
-  auto load = [&](u32x4_t* w, u32x4_t (*a)[U], int kb) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      w[u] = wload(kb + u);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) a[t][u] = aload(t, kb + u);
-    }
-  };
-  auto compute = [&](const u32x4_t* w, u32x4_t (*a)[U], int kb) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      SFrag wf;
-      wf.u = w[u];
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        SFrag af;
-        af.u = (kb + u < kb1) ? a[t][u] : u32x4_t{0, 0, 0, 0};
-        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf.v, af.v, acc[t], 0, 0, 0);
-      }
-    }
-  };
-  if (kb0 < kb1) {
-    load(w0, a0, kb0);
-    for (int kb = kb0; kb < kb1; kb += 2 * U) {
-      load(w1, a1, kb + U);
-      if (NT > 1) __builtin_amdgcn_sched_barrier(0);   // keep the batch of loads ahead of the arithmetic
-      compute(w0, a0, kb);
-      if (NT > 1) __builtin_amdgcn_sched_barrier(0);
-      load(w0, a0, kb + 2 * U);
-      if (NT > 1) __builtin_amdgcn_sched_barrier(0);
-      compute(w1, a1, kb + U);
-      if (NT > 1) __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  // lane: row (token) = lane & 31; columns 8 g + 4 (lane >> 5) + 0..3 of the block in acc[4 g ..]
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    float4* dst = (float4*)p.part + ((int64_t)((sp * p.n_rb + rb) * NT + t) * 4) * 64 + lane;
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      dst[g * 64] = make_float4(acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]);
-  }
-}
 
 // The same product with the weights in the quantised tiled format (32 x 64 blocks of 8- or
 // 3-bit codes plus fp16 group scales; qformat.h).  The packed blocks are the only traffic that
@@ -415,7 +301,6 @@ struct SkinnyReduceArgs {
   int c0_tiled, c1_tiled, n_store;
   int f16_out;   // destinations hold fp16 (saturating) instead of bf16
   int rb_split, n_split_b;   // row blocks from rb_split on have n_split_b ranges
-  int n_tb, nt;              // 32-token blocks to write / token blocks per row block in part
   const float* bias;         // as in GemmArgs
   int bias_cols;
   const float* resid;
@@ -429,9 +314,9 @@ __device__ __forceinline__ uint32_t pack_f16x2_sat(float lo, float hi) {
   return v.u;
 }
 
-// Activation and store of four consecutive output columns (registers 4 g .. 4 g + 3 of row
-// block rb, token row lane & 31): v the block's sums, u the up block's sums for a (gate, up) pair.
-__device__ __forceinline__ void sk_emit(const SkinnyReduceArgs& p, int rb, int tb, int g, int lane, float v[4],
+// Activation and store of four consecutive output columns (columns c .. c + 3 of row block rb, of
+// token `row`): v the block's sums, u the up block's sums for a (gate, up) pair.
+__device__ __forceinline__ void sk_emit(const SkinnyReduceArgs& p, int rb, int c4, int row, float v[4],
                                         const float u[4]) {
   const int cb = rb * 32;
   const bool act_here = cb < p.act_cols;
@@ -439,8 +324,8 @@ __device__ __forceinline__ void sk_emit(const SkinnyReduceArgs& p, int rb, int t
   int oc = cb;
   if (glu) oc = act_here ? cb / 2 : cb - p.act_cols / 2;
   {
-    // a neuron's bias (GEMM column cb + 8 g + 4 (lane >> 5) + e), before the activation
-    const int c = cb + 8 * g + 4 * (lane >> 5);
+    // a neuron's bias (GEMM column cb + c4 + e), before the activation
+    const int c = cb + c4;
     if (!glu && p.bias != nullptr && c + 3 < p.bias_cols) {
       const float4 b4 = *(const float4*)(p.bias + c);
       v[0] += b4.x; v[1] += b4.y; v[2] += b4.z; v[3] += b4.w;
@@ -457,8 +342,7 @@ __device__ __forceinline__ void sk_emit(const SkinnyReduceArgs& p, int rb, int t
       for (int e = 0; e < 4; ++e) v[e] = gelu_fast(v[e]);
     }
   }
-  const int row = tb * 32 + (lane & 31);
-  const int col0 = oc + 8 * g + 4 * (lane >> 5);   // first of this thread's four output columns
+  const int col0 = oc + c4;   // first of this thread's four output columns
   char* base;
   int64_t ld;
   int col, tiled;
@@ -478,8 +362,8 @@ __device__ __forceinline__ void sk_emit(const SkinnyReduceArgs& p, int rb, int t
   const uint2 val = p.f16_out ? make_uint2(pack_f16x2_sat(v[0], v[1]), pack_f16x2_sat(v[2], v[3]))
                               : make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
   if (tiled) {
-    // (rows past M in the last 32-row block hold repeats of row M - 1, finite)
-    const int64_t chunk = ((int64_t)tb * (ld / 16) + col / 16) * 64 + ((col >> 3) & 1) * 32 + (lane & 31);
+    // (rows past M hold repeats of row M - 1; past the last block of 16 rows nothing is written or read)
+    const int64_t chunk = ((int64_t)(row >> 5) * (ld / 16) + col / 16) * 64 + ((col >> 3) & 1) * 32 + (row & 31);
     *(uint2*)(base + chunk * 16 + (col & 7) * 2) = val;
   } else if (row < p.M && col < p.n_store) {
     *(uint2*)(base + ((int64_t)row * ld + col) * 2) = val;
@@ -488,17 +372,17 @@ __device__ __forceinline__ void sk_emit(const SkinnyReduceArgs& p, int rb, int t
 
 __global__ void __launch_bounds__(256) skinny_reduce_kernel(const SkinnyReduceArgs p) {
   const int id = blockIdx.x * 256 + threadIdx.x;
-  if (id >= p.n_rb * p.n_tb * 256) return;
-  const int rb = (id >> 8) / p.n_tb, tb = (id >> 8) % p.n_tb, g = (id >> 6) & 3, lane = id & 63;
+  if (id >= p.n_rb * 256) return;
+  const int rb = id >> 8, g = (id >> 6) & 3, lane = id & 63;
   const bool pair = p.act == ACT_GLU && rb * 32 < p.act_cols;
   if (pair && (rb & 1)) return;   // the pair is written from its gate block
   auto sum_block = [&](int b) {
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4* src = (const float4*)p.part + (((int64_t)b * p.nt + tb) * 4 + g) * 64 + lane;
+    const float4* src = (const float4*)p.part + ((int64_t)b * 4 + g) * 64 + lane;
     // eight independent loads at a time, added in range order (24 at a time, all ranges of the
     // usual products in one round trip, measured slower: 5.9 vs 4.3 us, and 8.4 vs 5.0 us where
     // there are few ranges and most of the 24 were repeats)
-    const int64_t step = (int64_t)p.n_rb * p.nt * 256;
+    const int64_t step = (int64_t)p.n_rb * 256;
     const int ns = b < p.rb_split ? p.n_split : p.n_split_b;
     constexpr int NB = 8;
     for (int sp = 0; sp < ns; sp += NB) {
@@ -518,131 +402,247 @@ __global__ void __launch_bounds__(256) skinny_reduce_kernel(const SkinnyReduceAr
     const float4 u = sum_block(rb + 1);
     uu[0] = u.x; uu[1] = u.y; uu[2] = u.z; uu[3] = u.w;
   }
-  sk_emit(p, rb, tb, g, lane, v, uu);
+  sk_emit(p, rb, 8 * g + 4 * (lane >> 5), lane & 31, v, uu);
 }
 
-// The whole product in one launch, where it has enough 32-row blocks to fill the machine
-// without cutting the reduction across workgroups: a workgroup of NW wavefronts owns RB
-// adjacent row blocks (RB = 2: a (gate, up) pair, or two blocks that share the activation
-// blocks) over the whole reduction, the wavefronts take an NW-th each with the same two-deep
-// register prefetch as skinny_stream_kernel, add their accumulators through LDS in a fixed
-// order, and wavefront g < 4 applies the activation to accumulator registers 4 g .. and stores.
-// DUAL: the odd block of the pair reads the second left operand.
-struct SkinnyFusedArgs {
-  SkinnyArgs s;
+// A product of at most 64 tokens in one launch, bound by streaming its weights once.
+// A workgroup of four wavefronts owns 16 weight rows (RB = 1) or two such pieces (RB = 2: a 32-row
+// block, or 16 gate rows and their 16 up rows) over one range of the reduction.  The wavefronts share
+// the range evenly and keep a ring of U steps of 32 reduction elements in registers, each refilled as
+// it is used; a step past the range is an out-of-range buffer load (zero), so nothing in the loop is
+// masked, and the last round of the ring loads nothing.  The accumulators meet in LDS and are added
+// in a fixed order.  Pieces of 16 rows and 16 tokens (v_mfma_f32_16x16x32_bf16) make twice as many
+// workgroups of the same rows as 32 x 32 ones, and with up to 16 tokens half the activation loads.
+// With n_split > 1 the ranges of one unit are added by the last of its workgroups to arrive, in range
+// order: the second launch that this replaces cost 4-5 us, more than the sums are worth, and the
+// result does not depend on the order of arrival.
+// Measured (us; 32 x 32 blocks with a reduce launch or 4-8 wavefronts before -> now): Llama-2-7B-sized
+// low-rank layer, 8 tokens 47.6 -> 34.1, 32 tokens 49.9 -> 45.4, 64 tokens 71.7 -> 60.9; four
+// OPT-13B-sized layers, 16 tokens 248 -> 185 (3.1 TB/s of weights); OPT-1.3B-sized layer, 1 token
+// 36 -> 21, 48 tokens 46.5 -> 28.6.  Sixteen wavefronts per workgroup instead of four: 41.8 and 244
+// at the first and the fourth; eight: 39.7 and 219 (with a ring of eight); a ring of 12 costs 2 % more
+// than one of 4-6, because what it holds past the range is loaded for nothing.
+constexpr int ROWS16_MAX_SPLIT = 8;
+constexpr int ROWS16_NW = 4;      // wavefronts of a workgroup
+constexpr int ROWS16_WGS = 256;   // workgroups of a full machine
+
+struct Rows16Args {
+  const void* A;
+  const void* A1;      // DUAL: the up rows' left operand
+  const void* Bt;
+  int64_t lda, ldb;
+  int M, K, steps;     // steps of 32 reduction elements
+  int pair_units;      // GLU: units below this are (gate, up) pairs
+  int n_units, n_split;
+  float* part;         // [unit][n_split][pieces][64] float4
+  unsigned* counters;  // one per unit
+  unsigned* clear;     // counters of later launches to zero
+  int n_clear;
   SkinnyReduceArgs e;
 };
 
-template <bool A_TILED, int RB, int NW, bool DUAL>
-__global__ void __launch_bounds__(NW * 64) skinny_fused_kernel(const SkinnyFusedArgs q) {
-  // blocks per register group: four keep the kernel at three workgroups per CU (at most 168
-  // registers per lane); eight, two per CU, measured 4 us slower per step at the OPT-13B shape
-  constexpr int U = 4;
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t sk_rsrc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ u32x4_t sk_load(rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+// partial sums cross workgroups of one launch: device-scope accesses go to the point where the
+// per-XCD L2 caches are coherent
+__device__ __forceinline__ void sk_st_dev(float4* p, float4 v) {
+  unsigned long long* q = (unsigned long long*)p;
+  __hip_atomic_store(q, (unsigned long long)__float_as_uint(v.x) | ((unsigned long long)__float_as_uint(v.y) << 32),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(q + 1, (unsigned long long)__float_as_uint(v.z) | ((unsigned long long)__float_as_uint(v.w) << 32),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float4 sk_ld_dev(const float4* p) {
+  const unsigned long long* q = (const unsigned long long*)p;
+  const unsigned long long a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float4(__uint_as_float((unsigned)a), __uint_as_float((unsigned)(a >> 32)), __uint_as_float((unsigned)b),
+                     __uint_as_float((unsigned)(b >> 32)));
+}
+
+// One unit: pieces at rows 16 sub[i] of the 32-row blocks rb[i].
+template <bool A_TILED, int TB, int RB, int NW, int U, bool DUAL, bool SPLIT>
+__device__ __forceinline__ void rows16_unit(const Rows16Args& p, int unit, int sp, const int (&rb)[RB],
+                                            const int (&sub)[RB], bool pair, float4* red, int* flag) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   constexpr int NA = DUAL ? 2 : 1;
-  extern __shared__ float red_mem[];
-  float (*red)[RB][16][64] = (float (*)[RB][16][64])red_mem;   // [NW][RB][16][64]
-  const SkinnyArgs& p = q.s;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int rb0 = blockIdx.x * RB;
-  const int kb_total = (p.K + 15) / 16;
-  const int per = (kb_total + NW - 1) / NW;
-  const int kb0 = wave * per;
-  const int kb1 = min(kb_total, kb0 + per);      // may be empty: the wavefront then adds zeros
-  const int kb_last = kb_total - 1;
+  // this workgroup's range, then this wavefront's share of it (may be empty: it then adds zeros)
+  const int w0 = (int)((int64_t)p.steps * sp / p.n_split), wn = (int)((int64_t)p.steps * (sp + 1) / p.n_split) - w0;
+  const int s0 = w0 + wn * wave / NW, s1 = w0 + wn * (wave + 1) / NW;
+  const int r = lane & 15, q8 = (lane >> 4) * 8;
 
-  const char* wbase[RB];
+  // tiled: a step is two 1 KiB blocks of 32 rows x 16 reduction elements; the lane's 16 bytes are
+  // row r of a 16-row half, elements q8 ..
+  const uint32_t lofs = (uint32_t)((lane >> 5) * 1024 + ((lane >> 4) & 1) * 512 + r * 16);
+  rsrc_t wr[RB];
+  uint32_t wofs[RB];
 #pragma unroll
-  for (int i = 0; i < RB; ++i) wbase[i] = (const char*)p.Bt + ((int64_t)(rb0 + i) * (p.ldb / 16) * 64 + lane) * 16;
-  const char* abase[NA];
-#pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    abase[i] = (const char*)(i ? p.A1 : p.A);
-    if (A_TILED) abase[i] += (int64_t)lane * 16;
-    else abase[i] += ((int64_t)min(lane & 31, p.M - 1) * p.lda + (lane >> 5) * 8) * 2;
+  for (int i = 0; i < RB; ++i) {
+    wr[i] = sk_rsrc((const char*)p.Bt + (int64_t)rb[i] * (p.ldb / 16) * 1024, (uint32_t)s1 * 2048u);
+    wofs[i] = lofs + (uint32_t)sub[i] * 256u;
   }
-  auto wload = [&](int i, int kb) { return *(const u32x4_t*)(wbase[i] + (int64_t)min(kb, kb_last) * 1024); };
-  auto aload = [&](int i, int kb) {
-    const int k = min(kb, kb_last);
-    if (A_TILED) return *(const u32x4_t*)(abase[i] + (int64_t)k * 1024);
-    const int col = k * 16 + (lane >> 5) * 8;     // a chunk past K reads the row's first chunk (weights are zero there)
-    return *(const u32x4_t*)(abase[i] + (col < p.K ? (int64_t)k * 32 : -(int64_t)((lane >> 5) * 16)));
-  };
-  f32x16_t acc[RB];
+  const int k_end = min(p.K, s1 * 32);
+  rsrc_t ar[NA][(TB + 1) / 2];   // tiled: one per block of 32 tokens
+  uint32_t aofs[TB];
 #pragma unroll
-  for (int i = 0; i < RB; ++i)
+  for (int i = 0; i < NA; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
-  u32x4_t w0[RB][U], a0[NA][U], w1[RB][U], a1[NA][U];
-  auto load = [&](u32x4_t (*w)[U], u32x4_t (*a)[U], int kb) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-      for (int i = 0; i < RB; ++i) w[i][u] = wload(i, kb + u);
-#pragma unroll
-      for (int i = 0; i < NA; ++i) a[i][u] = aload(i, kb + u);
+    for (int t = 0; t < TB; t += 2) {
+      const char* base = (const char*)(i ? p.A1 : p.A);
+      ar[i][t / 2] = A_TILED ? sk_rsrc(base + (int64_t)(t / 2) * (p.lda / 16) * 1024, (uint32_t)s1 * 2048u)
+                             : sk_rsrc(base, (uint32_t)(p.M * (int)p.lda * 2));
     }
-  };
-  auto compute = [&](u32x4_t (*w)[U], u32x4_t (*a)[U], int kb) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+  for (int t = 0; t < TB; ++t) {
+    if (A_TILED) aofs[t] = lofs + (uint32_t)(t & 1) * 256u;
+    else aofs[t] = (uint32_t)(min(t * 16 + r, p.M - 1) * (int)p.lda + q8) * 2u;
+  }
+  u32x4_t w[U][RB], a[U][NA][TB];
+  auto load = [&](int u, int s) {
 #pragma unroll
-      for (int i = 0; i < RB; ++i) {
-        SFrag wf, af;
-        wf.u = w[i][u];
-        af.u = (kb + u < kb1) ? a[DUAL ? i : 0][u] : u32x4_t{0, 0, 0, 0};
-        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf.v, af.v, acc[i], 0, 0, 0);
+    for (int i = 0; i < RB; ++i) w[u][i] = sk_load(wr[i], wofs[i] + (uint32_t)s * 2048u);
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        if (A_TILED) a[u][i][t] = sk_load(ar[i][t / 2], aofs[t] + (uint32_t)s * 2048u);
+        else a[u][i][t] = sk_load(ar[i][t / 2], s * 32 + q8 < k_end ? aofs[t] + (uint32_t)s * 64u : 0xfffffff0u);
       }
   };
-  load(w0, a0, kb0);
-  for (int kb = kb0; kb < kb1; kb += 2 * U) {
-    // (the scheduling barriers keep each batch of loads ahead of the arithmetic of the batch before)
-    load(w1, a1, kb + U);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(w0, a0, kb);
-    __builtin_amdgcn_sched_barrier(0);
-    load(w0, a0, kb + 2 * U);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(w1, a1, kb + U);
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  f32x4_t acc[RB][TB];
 #pragma unroll
   for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) red[wave][i][v][lane] = acc[i][v];
-  __syncthreads();
-  if (wave >= 4) return;
-  const int g = wave;
-  float sum[RB][4];
+    for (int t = 0; t < TB; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](int u) {
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < RB; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float t = red[0][i][4 * g + e][lane];
-      for (int w = 1; w < NW; ++w) t += red[w][i][4 * g + e][lane];
-      sum[i][e] = t;
+      for (int t = 0; t < TB; ++t) {
+        SFrag wf, af;
+        wf.u = w[u][i];
+        af.u = a[u][DUAL ? i : 0][t];
+        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.v, af.v, acc[i][t], 0, 0, 0);
+      }
+  };
+  if (s0 < s1) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(u, s0 + u);
+    for (int s = s0 + U; s < s1; s += U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        step(u);
+        load(u, s + u);
+      }
     }
-  const bool pair = q.e.act == ACT_GLU && rb0 * 32 < q.e.act_cols;
-  if (RB == 2 && pair) {
-    sk_emit(q.e, rb0, 0, g, lane, sum[0], sum[RB - 1]);
-  } else {
-    const float none[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < RB; ++i) sk_emit(q.e, rb0 + i, 0, g, lane, sum[i], none);
+    for (int u = 0; u < U; ++u) step(u);
+  }
+  // lane: token t * 16 + r, rows 4 (lane >> 4) + 0..3 of the piece
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+      red[((wave * RB + i) * TB + t) * 64 + lane] = make_float4(acc[i][t][0], acc[i][t][1], acc[i][t][2], acc[i][t][3]);
+  __syncthreads();
+  auto lds_sum = [&](int piece) {
+    float4 v = red[piece * 64 + lane];
+#pragma unroll
+    for (int w2 = 1; w2 < NW; ++w2) {
+      const float4 x = red[(w2 * RB * TB + piece) * 64 + lane];
+      v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+    }
+    return v;
+  };
+  const int c4 = 4 * (lane >> 4);
+  const float none[4] = {0.f, 0.f, 0.f, 0.f};
+  if (SPLIT && p.n_split > 1) {
+    float4* mine = (float4*)p.part + ((int64_t)unit * p.n_split + sp) * RB * TB * 64 + lane;
+    for (int pc = wave; pc < RB * TB; pc += NW) sk_st_dev(mine + pc * 64, lds_sum(pc));
+    // Every thread waits for its own device-scope stores before the barrier, and only after it does
+    // thread 0 count this workgroup in: whoever reads n_split - 1 finds all partial sums in place.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const bool last = __hip_atomic_fetch_add(&p.counters[unit], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                        (unsigned)(p.n_split - 1);
+      if (last) __hip_atomic_store(&p.counters[unit], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *flag = last;
+    }
+    __syncthreads();
+    if (!*flag) return;
+    for (int pc = wave; pc < RB * TB; pc += NW) {
+      const float4* src = (const float4*)p.part + (int64_t)unit * p.n_split * RB * TB * 64 + pc * 64 + lane;
+      float4 x[ROWS16_MAX_SPLIT];
+#pragma unroll
+      for (int s = 0; s < ROWS16_MAX_SPLIT; ++s)
+        x[s] = sk_ld_dev(src + (int64_t)min(s, p.n_split - 1) * RB * TB * 64);
+      float v[4] = {x[0].x, x[0].y, x[0].z, x[0].w};
+#pragma unroll
+      for (int s = 1; s < ROWS16_MAX_SPLIT; ++s)
+        if (s < p.n_split) { v[0] += x[s].x; v[1] += x[s].y; v[2] += x[s].z; v[3] += x[s].w; }
+      const int i = RB > 1 ? pc / TB : 0, t = pc % TB;
+      sk_emit(p.e, i ? rb[RB - 1] : rb[0], 16 * (i ? sub[RB - 1] : sub[0]) + c4, t * 16 + r, v, none);
+    }
+    return;
+  }
+  if (RB == 2 && pair) {
+    for (int t = wave; t < TB; t += NW) {
+      const float4 g = lds_sum(t), up = lds_sum(TB + t);
+      float v[4] = {g.x, g.y, g.z, g.w};
+      const float uu[4] = {up.x, up.y, up.z, up.w};
+      sk_emit(p.e, rb[0], 16 * sub[0] + c4, t * 16 + r, v, uu);
+    }
+    return;
+  }
+  for (int pc = wave; pc < RB * TB; pc += NW) {
+    const float4 sum = lds_sum(pc);
+    float v[4] = {sum.x, sum.y, sum.z, sum.w};
+    const int i = RB > 1 ? pc / TB : 0, t = pc % TB;
+    sk_emit(p.e, i ? rb[RB - 1] : rb[0], 16 * (i ? sub[RB - 1] : sub[0]) + c4, t * 16 + r, v, none);
+  }
+}
+
+// GLU: units below pair_units are (gate, up) pairs, the others hold RB pieces
+template <bool A_TILED, int TB, int RB, int NW, int U, bool GLU, bool DUAL>
+__global__ void __launch_bounds__(NW * 64) rows16_kernel(const Rows16Args p) {
+  extern __shared__ float4 red4[];
+  __shared__ int flag;
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < p.n_clear; i += NW * 64) p.clear[i] = 0u;
+  const int unit = (int)blockIdx.x % p.n_units, sp = (int)blockIdx.x / p.n_units;
+  if (GLU && unit < p.pair_units) {
+    const int rb[2] = {unit & ~1, unit | 1}, sub[2] = {unit & 1, unit & 1};
+    rows16_unit<A_TILED, TB, 2, NW, U, DUAL, false>(p, unit, 0, rb, sub, true, red4, &flag);
+    return;
+  }
+  if constexpr (!DUAL) {
+    const int v = unit - p.pair_units;
+    if constexpr (RB == 2) {
+      const int rb[2] = {p.pair_units + v, p.pair_units + v}, sub[2] = {0, 1};
+      rows16_unit<A_TILED, TB, 2, NW, U, false, false>(p, unit, 0, rb, sub, false, red4, &flag);
+    } else {
+      const int rb[1] = {p.pair_units + (v >> 1)}, sub[1] = {v & 1};
+      rows16_unit<A_TILED, TB, 1, NW, U, false, !GLU>(p, unit, sp, rb, sub, false, red4, &flag);
+    }
   }
 }
 
 }  // namespace
 
-int skinny_token_blocks(int M) { return M <= 32 ? 1 : 2; }
-
-size_t skinny_part_bytes(int n_max, int M) {
-  // at most ~2048 wavefront tasks: n_rb * n_split <= 2048 + n_rb, one 4 KiB tile each per block of 32 tokens
-  return (size_t)(2048 + (n_max + 31) / 32) * 4096 * skinny_token_blocks(M);
+size_t skinny_part_bytes(int M) {
+  // where a reduction is cut, at most ROWS16_WGS workgroups, one KiB each per block of 16 tokens
+  return (size_t)ROWS16_WGS * 1024 * (M <= 16 ? 1 : M <= 32 ? 2 : 4);
 }
 
-// g as for the large-batch launcher (M <= 32; destinations tiled with one row block, or
-// row-major); part: scratch of skinny_part_bytes(N) bytes.
 static void fill_reduce_args(SkinnyReduceArgs& r, const GemmArgs& g, int act) {
   r.n_rb = g.N / 32; r.M = g.M; r.N = g.N;
   r.act = act; r.act_cols = g.act_cols; r.split_col = g.split_col;
@@ -651,80 +651,51 @@ static void fill_reduce_args(SkinnyReduceArgs& r, const GemmArgs& g, int act) {
   r.bias = g.bias; r.bias_cols = g.bias_cols; r.resid = g.resid; r.ldr = g.ldr; r.out_f32 = g.out_f32;
 }
 
-template <bool AT, int RB, int NW, bool DUAL>
-static int launch_fused_cfg(const SkinnyFusedArgs& q, hipStream_t st) {
-  hipLaunchKernelGGL((skinny_fused_kernel<AT, RB, NW, DUAL>), dim3(q.s.n_rb / RB), dim3(NW * 64), (size_t)NW * RB * 4096,
-                     st, q);
+template <bool AT, int RB, int U, bool GLU, bool DUAL>
+static int launch_rows16(const Rows16Args& a, hipStream_t st) {
+  const dim3 grid(a.n_units * a.n_split), blk(ROWS16_NW * 64);
+  const size_t lds = (size_t)ROWS16_NW * (GLU ? 2 : RB) * 1024;   // times the blocks of 16 tokens
+  if (a.M <= 16) hipLaunchKernelGGL((rows16_kernel<AT, 1, RB, ROWS16_NW, U, GLU, DUAL>), grid, blk, lds, st, a);
+  else if (a.M <= 32) hipLaunchKernelGGL((rows16_kernel<AT, 2, RB, ROWS16_NW, U, GLU, DUAL>), grid, blk, 2 * lds, st, a);
+  else hipLaunchKernelGGL((rows16_kernel<AT, 4, RB, ROWS16_NW, 4, GLU, DUAL>), grid, blk, 4 * lds, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// 0 launched, -1 failed, 1 not applicable (too few row blocks for one workgroup per RB of them,
-// or a reduction too short to share among the wavefronts)
-static int launch_skinny_fused(const SkinnyArgs& a, const GemmArgs& g, int act, int kb_total, hipStream_t st) {
-  SkinnyFusedArgs q = {};
-  q.s = a;
-  fill_reduce_args(q.e, g, act);
-  q.e.n_tb = 1; q.e.nt = 1;
-  const bool at = g.a_tiled != 0, dual = g.A1 != nullptr, glu = act == ACT_GLU;
-  const int n_rb = a.n_rb;
-  if (dual) {
-    if (!at || !glu || (n_rb & 1) || n_rb / 2 < 256 || kb_total < 4 * 4) return 1;
-    return launch_fused_cfg<true, 2, 4, true>(q, st);
-  }
-  if (!(n_rb & 1) && n_rb / 2 >= 256 && kb_total >= 4 * 8)
-    return at ? launch_fused_cfg<true, 2, 4, false>(q, st) : launch_fused_cfg<false, 2, 4, false>(q, st);
-  // Fewer than about a hundred workgroups cannot pull the weights fast enough (measured: 40-66
-  // workgroups of 8-16 wavefronts took 1.4-2x the time of the split version with its reduce).
-  if (glu) {   // (gate, up) pairs stay in one workgroup
-    if (!(n_rb & 1) && n_rb / 2 >= 96 && kb_total >= 8 * 8)
-      return at ? launch_fused_cfg<true, 2, 8, false>(q, st) : launch_fused_cfg<false, 2, 8, false>(q, st);
-    return 1;
-  }
-  if (n_rb >= 96 && kb_total >= 8 * 8)
-    return at ? launch_fused_cfg<true, 1, 8, false>(q, st) : launch_fused_cfg<false, 1, 8, false>(q, st);
-  return 1;
-}
-
-int launch_skinny_bf16(const GemmArgs& g, int act, float* part, hipStream_t st) {
+// g as for the large-batch launcher (destinations tiled or row-major).
+int launch_skinny_bf16(const GemmArgs& g, int act, float* part, unsigned* counters, int n_clear, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0) return 0;
   if (g.M > SKINNY_MAX_M || (g.N & 31) || g.partial) return -1;
-  const int nt = skinny_token_blocks(g.M);
-  SkinnyArgs a = {};
-  a.n_tb = (g.M + 31) / 32;
+  const bool glu = act == ACT_GLU && g.act_cols > 0, dual = g.A1 != nullptr, at = g.a_tiled != 0;
+  if ((dual && (!at || !glu || g.act_cols != g.N)) || (glu && (g.act_cols & 63))) return -1;
+  Rows16Args a = {};
   a.A = g.A; a.A1 = g.A1; a.Bt = g.Bt; a.lda = g.lda; a.ldb = g.ldb;
-  a.M = g.M; a.N = g.N; a.K = g.K; a.a_tiled = g.a_tiled;
-  a.n_rb = g.N / 32;
-  const int kb_total = (g.K + 15) / 16;
-  if (nt == 1) {
-    const int fused = launch_skinny_fused(a, g, act, kb_total, st);
-    if (fused <= 0) return fused;   // launched (0) or failed (-1); 1 = not applicable
+  a.M = g.M; a.K = g.K; a.steps = (g.K + 31) / 32;
+  fill_reduce_args(a.e, g, act);
+  a.part = part; a.counters = counters;
+  a.clear = counters; a.n_clear = n_clear;
+  a.pair_units = glu ? g.act_cols / 32 : 0;
+  const int blocks = (g.N - (glu ? g.act_cols : 0)) / 32;
+  // Units of 16 rows while all their workgroups find a CU of their own, else of 32 (which share the
+  // activation loads): with 16 rows throughout the OPT-13B-sized layers take 2 % more, with 32 from
+  // half as many units on the Llama-sized one 4 % more.  What is left of the machine is filled by
+  // cutting the reduction, at least 32 steps a range; one and a quarter rounds of workgroups instead
+  // of one take 2 % (Llama-sized) to 12 % (OPT-13B-sized) more.
+  const bool one = a.pair_units + 2 * blocks <= ROWS16_WGS;
+  a.n_units = a.pair_units + blocks * (one ? 2 : 1);
+  a.n_split = 1;
+  if (one && !glu && n_clear == 0 && counters != nullptr) {
+    int S = ROWS16_WGS / a.n_units;
+    if (S > a.steps / 32) S = a.steps / 32;
+    if (S > ROWS16_MAX_SPLIT) S = ROWS16_MAX_SPLIT;
+    a.n_split = S < 1 ? 1 : S;
   }
-  // enough ranges for about 1024 wavefronts (one per SIMD), at least 32 blocks (32 KiB of weights)
-  // each.  Measured per decode step (Llama shape / OPT-13B shape): 2048 wavefronts 48.5 / 60.8 us,
-  // 1024: 48.4 / 56.6, 768: 49.5 / 56.9, 512: 50.8 / 60.4; 16 blocks each: 53.1 / 62.0, 64: 52.7 / 59.7.
-  const int max_s = kb_total / 32 > 0 ? kb_total / 32 : 1;
-  int S = 1024 / a.n_rb;
-  if (S > max_s) S = max_s;
-  if (S < 1) S = 1;
-  a.kb_per = (kb_total + S - 1) / S;
-  a.n_split = (kb_total + a.kb_per - 1) / a.kb_per;
-  a.part = part;
-  const int tasks = a.n_rb * a.n_split;
-  const dim3 grid((tasks + 3) / 4), blk(256);
-  if (g.a_tiled) {
-    if (nt == 1) hipLaunchKernelGGL((skinny_stream_kernel<true, 1>), grid, blk, 0, st, a);
-    else hipLaunchKernelGGL((skinny_stream_kernel<true, 2>), grid, blk, 0, st, a);
-  } else {
-    if (nt == 1) hipLaunchKernelGGL((skinny_stream_kernel<false, 1>), grid, blk, 0, st, a);
-    else hipLaunchKernelGGL((skinny_stream_kernel<false, 2>), grid, blk, 0, st, a);
+  if (dual) return launch_rows16<true, 2, 4, true, true>(a, st);
+  if (at) {
+    if (glu) return one ? launch_rows16<true, 1, 4, true, false>(a, st) : launch_rows16<true, 2, 6, true, false>(a, st);
+    return one ? launch_rows16<true, 1, 4, false, false>(a, st) : launch_rows16<true, 2, 6, false, false>(a, st);
   }
-  if (hipGetLastError() != hipSuccess) return -1;
-  SkinnyReduceArgs r = {};
-  fill_reduce_args(r, g, act);
-  r.part = part; r.n_split = a.n_split; r.rb_split = r.n_rb; r.n_split_b = a.n_split;
-  r.n_tb = a.n_tb; r.nt = nt;
-  hipLaunchKernelGGL(skinny_reduce_kernel, dim3(r.n_rb * r.n_tb), dim3(256), 0, st, r);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  if (glu) return one ? launch_rows16<false, 1, 4, true, false>(a, st) : launch_rows16<false, 2, 6, true, false>(a, st);
+  return one ? launch_rows16<false, 1, 4, false, false>(a, st) : launch_rows16<false, 2, 6, false, false>(a, st);
 }
 
 int launch_skinny_reduce(const GemmArgs& g, int act, const float* part, int n_split, int f16_out, hipStream_t st) {
@@ -734,7 +705,7 @@ int launch_skinny_reduce(const GemmArgs& g, int act, const float* part, int n_sp
 int launch_skinny_reduce2(const GemmArgs& g, int act, const float* part, int n_split, int rb_split, int n_split_b,
                           int f16_out, hipStream_t st) {
   SkinnyReduceArgs r = {};
-  r.f16_out = f16_out; r.rb_split = rb_split; r.n_split_b = n_split_b; r.n_tb = 1; r.nt = 1;
+  r.f16_out = f16_out; r.rb_split = rb_split; r.n_split_b = n_split_b;
   r.part = part; r.n_rb = g.N / 32; r.n_split = n_split; r.M = g.M; r.N = g.N;
   r.act = act; r.act_cols = g.act_cols; r.split_col = g.split_col;
   r.C0 = g.C0; r.C1 = g.C1; r.ldc0 = g.ldc0; r.ldc1 = g.ldc1;

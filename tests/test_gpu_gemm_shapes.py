@@ -1,5 +1,5 @@
-"""GPU parity of the large-batch product kernel at sizes that reach each of its tile shapes and
-reduction splits with remainders on every side (rows, columns, reduction depth), against the CPU
+"""GPU parity of the bf16 product kernels at sizes that reach each tile shape, unit and
+reduction split with remainders on every side (rows, columns, reduction depth), against the CPU
 oracle.  Bars: the task's (1e-2 relative Frobenius, 2e-2 worst row)."""
 import numpy as np
 import pytest
@@ -25,7 +25,21 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("T,d,d_ff,k,r,act", CASES)
+# At most 64 tokens (one launch per product): blocks of 16 tokens, 16- and 32-row units, reductions
+# cut across workgroups, depths that end inside a step of 32.
+SMALL = [
+    (1, 72, 97, 39, 17, "gelu"),             # reduction shorter than the wavefronts' shares
+    (16, 264, 2600, 3, 40, "swiglu"),        # pairs and single pieces in one launch
+    (17, 1056, 9000, 100, 64, "gelu"),       # third product: 4 units in 8 ranges
+    (32, 4128, 300, 20, 9, "gelu"),          # last product on 32-row units
+    (5, 1000, 6000, 2300, 900, "swiglu"),    # first product on 32-row units beside pairs
+    (33, 544, 4300, 700, 65, "swiglu"),      # third product in 3 ranges
+    (49, 776, 4300, 1, 130, "gelu"),         # d_model % 32 = 8; second product on 32-row units
+    (64, 2048, 1030, 1028, 1, "gelu"),       # two remainder neurons
+]
+
+
+@pytest.mark.parametrize("T,d,d_ff,k,r,act", CASES + SMALL)
 def test_every_tile_shape_matches_oracle(T, d, d_ff, k, r, act):
     import paper_2401_04044_amd as ff
     rng = np.random.default_rng(T)
