@@ -736,6 +736,8 @@ int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_sp
     case GEMM_128x320: return launch_dl_shape<128, 320, 2, 4, 4, true>(a, act, n_split, st);
     case GEMM_256x256: return launch_dl_shape<256, 256, 2, 4, 4, false>(a, act, n_split, st);
     case GEMM_256x320: return launch_dl_shape<256, 320, 2, 4, 4, false>(a, act, n_split, st);
+    case GEMM_64x64: return launch_dl_shape<64, 64, 2, 2, 5, true>(a, act, n_split, st);
+    case GEMM_64x128: return launch_dl_shape<64, 128, 2, 2, 5, true>(a, act, n_split, st);
   }
   return -1;
 }

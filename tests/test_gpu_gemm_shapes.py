@@ -12,16 +12,19 @@ pytestmark = pytest.mark.gpu
 
 # T, d_model, d_ff, k, rank, act: what the choice of tiles gives for the four products
 CASES = [
-    (65, 72, 97, 39, 17, "gelu"),            # one ragged 128x128 tile each
-    (565, 256, 87, 0, 3, "swiglu"),          # no heavy neuron, gated, 128x128
-    (2911, 200, 6019, 2763, 3, "gelu"),      # 128x320 and 128x256; third product in 11 ranges
-    (1838, 80, 5539, 1, 3, "gelu"),          # 16 ranges; first slab shorter than 32
+    (65, 72, 97, 39, 17, "gelu"),            # one row past a 64x64 tile
+    (565, 256, 87, 0, 3, "swiglu"),          # no heavy neuron, gated: 64x128 and 128x128
+    (2911, 200, 6019, 2763, 3, "gelu"),      # 128x320 and 128x256; third product 64x64 and last 128x128 in 5 ranges
+    (1838, 80, 5539, 1, 3, "gelu"),          # 64x64 in 16 ranges; first slab shorter than 32
     (4080, 136, 2085, 36, 129, "gelu"),      # 128x320 second product, d_model % 32 = 8
-    (1393, 64, 5212, 47, 2, "swiglu"),       # two left operands on 256x256
+    (1393, 64, 5212, 47, 2, "swiglu"),       # two left operands on 256x256; 64x64 in 11 ranges
     (4889, 440, 3391, 13, 2, "gelu"),        # 256x320 second product
-    (5036, 1592, 294, 1, 10, "gelu"),        # 128x256 last product, first product in ranges
+    (5036, 1592, 294, 1, 10, "gelu"),        # 64x128 second and 128x256 last product
     (4370, 1968, 146, 3, 67, "gelu"),        # 128x320 last product
     (4717, 1696, 294, 68, 11, "swiglu"),
+    (321, 1048, 1500, 70, 130, "gelu"),      # 64x64 throughout, one row past a tile
+    (700, 1544, 2300, 300, 67, "swiglu"),    # gated 64x128 in 3 ranges, un-gated 64x128
+    (150, 2056, 1200, 33, 300, "gelu"),      # first product 64x64 in 8 ranges
 ]
 
 
