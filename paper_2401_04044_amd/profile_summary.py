@@ -29,48 +29,43 @@ G = r"gemm_bf16_dl_kernel<"
 SIGNATURES = {
     "C5_stack_layer": [
         ("pre-norm  token_rmsnorm_kernel", r"token_rmsnorm_kernel<true>", 4096, 1),
-        ("G1 X [W1h | P1]  128x320 tiles", G + r"128, 320, 32, 2, 2, 1, 3, 1, false, false, false, false>", 224, 1),
-        ("G2 gelu(t Q1)  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 1, false, false, true, false>", 1232, 1),
-        ("G3 h2 P2  256x320 tiles x 4 splits", G + r"256, 320, 32, 4, 2, 1, 3, 0, false, false, true, false>", 64, 4, G),
-        ("G3 sum of the splits", r"splitk_reduce_kernel", 2560, 1),
-        ("G4 [h1 | t2] [W2h ; Q2] + residual, fp32 out  256x320 tiles", G + r"256, 320, 32, 4, 2, 1, 3, 0, false, false, true, true>", 256, 1),
+        ("G1 X [W1h | P1]  128x320 tiles", G + r"128, 320, 2, 4, 4, true, 1, false, false, false, false>", 224, 1),
+        ("G2 gelu(t Q1)  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false>", 2464, 1),
+        ("G3 h2 P2  256x256 tiles x 3 ranges", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 80, 3),
+        ("G3 sum of the ranges", r"splitk_epilogue_kernel", 2560, 1),
+        ("G4 [h1 | t2] [W2h ; Q2] + residual, fp32 out  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 0, false, false, true, true>", 256, 1),
     ],
     "C5_prefill": [
-        ("G1  128x320 tiles", G + r"128, 320, 32, 2, 2, 1, 3, 1, false, false, false, false>", 224, 1),
-        ("G2  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 1, false, false, true, false>", 1232, 1),
-        ("G3  256x320 tiles x 4 splits", G + r"256, 320, 32, 4, 2, 1, 3, 0, false, false, true, false>", 64, 4, G),
-        ("G3 sum of the splits", r"splitk_reduce_kernel", 2560, 1),
-        ("G4  256x320 tiles", G + r"256, 320, 32, 4, 2, 1, 3, 0, false, false, true, false>", 256, 1, r"splitk_reduce_kernel"),
+        ("G1  128x320 tiles", G + r"128, 320, 2, 4, 4, true, 1, false, false, false, false>", 224, 1),
+        ("G2  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false>", 2464, 1),
+        ("G3  256x256 tiles x 3 ranges", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 80, 3),
+        ("G3 sum of the ranges", r"splitk_epilogue_kernel", 2560, 1),
+        ("G4  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 0, false, false, true, false>", 256, 1, r"splitk_epilogue_kernel"),
     ],
     "C3_prefill": [
-        ("G1 X [gate/up heavy | Pg | P1]  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 2, false, false, false, false>", 208, 1),
-        ("G2 silu(tg Qg) * (tu Q1), two left operands  256x256 tiles", G + r"256, 256, 32, 4, 2, 1, 3, 2, true, false, true, false>", 1312, 1),
-        ("G3 h2 P2  256x256 tiles x 4 splits", G + r"256, 256, 32, 2, 4, 1, 3, 0, false, false, true, false>", 64, 4, G),
-        ("G3 sum of the splits", r"splitk_reduce_kernel", 2048, 1),
-        ("G4  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 0, false, false, true, false>", 256, 1, r"splitk_reduce_kernel"),
+        ("G1 X [gate/up heavy | Pg | P1]  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 2, false, false, false, false>", 208, 1),
+        ("G2 silu(tg Qg) * (tu Q1), two left operands  256x256 tiles", G + r"256, 256, 4, 2, 3, false, 2, true, false, true, false>", 1312, 1),
+        ("G3 h2 P2  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 256, 1, G),
+        ("G4  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 0, false, false, true, false>", 512, 1, G),
     ],
     "C2_prefill": [
-        ("G1  128x128 tiles, in-workgroup K split", G + r"128, 128, 64, 2, 2, 2, 4, 1, false, false, false, false>", 192, 1),
-        ("G2  256x128 tiles", G + r"256, 128, 32, 2, 2, 1, 3, 1, false, false, true, false>", 1008, 1),
-        ("G3  128x128 tiles, K split 2 x 2", G + r"128, 128, 64, 2, 2, 2, 4, 0, false, false, true, false>", 128, 2),
-        ("G3 sum of the splits", r"splitk_reduce_kernel", 1024, 1),
-        ("G4  128x128 tiles", G + r"128, 128, 32, 2, 2, 1, 3, 0, false, false, true, false>", 512, 1),
+        ("G1  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 1, false, false, false, false>", 192, 1),
+        ("G2  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false>", 1024, 1),
+        ("G3  128x128 tiles x 2 ranges", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 128, 2),
+        ("G3 sum of the ranges", r"splitk_epilogue_kernel", 1024, 1),
+        ("G4  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 512, 1),
     ],
     "C2_prefill_T16384": [
-        ("G1  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 1, false, false, false, false>", 192, 1),
         ("G2 + G3 in one launch, h2 never stored: 128 rows x 2 neuron ranges", r"ffn2_fused_kernel", 256, 1),
         ("sum of the ranges", r"splitk_reduce_kernel", 4096, 1),
-        ("G4  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 0, false, false, true, false>", 512, 1),
     ],
     "C4_int4_decode": [
         ("phase 1: gate/up, activation", r"int4_phase1_kernel<4, 8, 2>", 253, 1),
         ("phase 2: down, sum", r"int4_phase2_kernel", 32, 8),
     ],
     "C4_int4_prefill": [
-        ("expand up/gate to bf16", r"expand_up_kernel", 44288, 1),
-        ("expand down to bf16", r"expand_down_kernel", 22144, 1),
-        ("G1 X [W1 ; Wg]  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 2, false, false, false, false>", 1392, 1),
-        ("G4 h W2  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 0, false, false, true, false>", 256, 1, G + r"256, 256, 32, 2, 4, 1, 3, 2,"),
+        ("expand up/gate to bf16", r"expand_up_kernel", 11072, 1),
+        ("expand down to bf16", r"expand_down_kernel", 5568, 1),
     ],
     "C4_w3h8_decode": [
         ("up/gate stream (int8 heavy + int3 rest)", r"skinny_stream_q2_kernel<false>", 764, 1),
@@ -79,24 +74,20 @@ SIGNATURES = {
         ("sum", r"skinny_reduce_kernel", 128, 1),
     ],
     "C3_lowrank_decode": [
-        ("G1 stream", r"skinny_stream_kernel<false, 1>", 200, 1),
-        ("G1 sum, activation", r"skinny_reduce_kernel", 100, 1),
-        ("G2 (two left operands, SwiGLU)", r"skinny_fused_kernel<true, 2, 4, true>", 328, 1),
-        ("G3 stream", r"skinny_stream_kernel<true, 1>", 160, 1),
-        ("G3 sum", r"skinny_reduce_kernel", 32, 1),
-        ("G4", r"skinny_fused_kernel<true, 1, 8, false>", 128, 1),
+        ("G1", r"rows16_kernel<false, 1, 1, 4, 4, true, false>", 164, 1),
+        ("G2 (two left operands, SwiGLU)", r"rows16_kernel<true, 1, 2, 4, 4, true, true>", 656, 1),
+        ("G3, 4 ranges", r"rows16_kernel<true, 1, 1, 4, 4, false, false>", 256, 1, r"rows16_kernel<true, 1, 2, 4, 4, true, true>"),
+        ("G4", r"rows16_kernel<true, 1, 1, 4, 4, false, false>", 256, 1, r"rows16_kernel<true, 1, 1,"),
     ],
     "C5_lowrank_decode": [
-        ("G1 stream", r"skinny_stream_kernel<false, 1>", 165, 1),
-        ("G1 sum, activation", r"skinny_reduce_kernel", 66, 1),
-        ("G2", r"skinny_fused_kernel<true, 2, 4, false>", 308, 1),
-        ("G3 stream", r"skinny_stream_kernel<true, 1>", 250, 1),
-        ("G3 sum", r"skinny_reduce_kernel", 40, 1),
-        ("G4", r"skinny_fused_kernel<true, 1, 8, false>", 160, 1),
+        ("G1", r"rows16_kernel<false, 1, 1, 4, 4, false, false>", 132, 1),
+        ("G2", r"rows16_kernel<true, 1, 2, 4, 6, false, false>", 616, 1),
+        ("G3, 3 ranges", r"rows16_kernel<true, 1, 1, 4, 4, false, false>", 240, 1),
+        ("G4", r"rows16_kernel<true, 1, 2, 4, 6, false, false>", 160, 1),
     ],
     "C2_calibration": [
-        ("re-tile W1 (neuron-major)", r"permute_transpose_kernel<unsigned short>", 256, 64),
-        ("score product X W1, gelu, column sums  256x256 tiles", G + r"256, 256, 32, 2, 4, 1, 3, 1, false, true, false, false>", 512, 1),
+        ("re-tile W1 (neuron-major)", r"permute_transpose_tiled_kernel<true>", 128, 32),
+        ("score product X W1, gelu, column sums  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 1, false, true, false, false>", 512, 1),
         ("sum of the row tiles' partials", r"reduce_partials_kernel", 32, 1),
         ("row norms of W2, score", r"finalize_scores_kernel<true>", 2048, 1),
         ("selection: bit search + compaction", r"select_compact_kernel<8>", 1, 1),
