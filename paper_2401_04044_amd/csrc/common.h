@@ -157,12 +157,12 @@ int launch_ffn2_fused(const void* T1, int64_t ldt, const void* Q1t, int64_t ldq,
                       int mp, int rp, float* part, int n_split, hipStream_t st);
 // small-batch path (M <= SKINNY_MAX_M, N a multiple of 32): one weight-streaming launch per product;
 // part: scratch of skinny_part_bytes(M) bytes.  A product whose rows are too few for the machine cuts
-// its reduction across workgroups, which count their arrival in `counters` (skinny_counters(N) of
-// them, zero before the launch and left zero; null: no such cut); n_clear > 0 (with no cut): this
-// launch zeroes counters[0 .. n_clear).
+// its reduction across workgroups, which count their arrival in `counters` (SKINNY_COUNTERS of them: a
+// cut product has at most that many pieces of 16 rows; zero before the launch and left zero; null: no
+// such cut); n_clear > 0 (with no cut): this launch zeroes counters[0 .. n_clear).
 constexpr int SKINNY_MAX_M = 64;
 size_t skinny_part_bytes(int M);
-inline int skinny_counters(int n) { return n / 16; }
+constexpr int SKINNY_COUNTERS = 128;
 int launch_skinny_bf16(const GemmArgs& a, int act, float* part, unsigned* counters, int n_clear, hipStream_t st);
 // the reduce half alone: sum of n_split ranges of partial tiles, activation, stores
 // (f16_out: the destinations hold fp16, saturating, instead of bf16)

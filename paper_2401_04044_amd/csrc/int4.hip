@@ -973,7 +973,7 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
   w.off_t = off; off = align256(off + (size_t)w.t_pad * L.n_up * L.rp * L.esz);
   w.off_h2 = off; off = align256(off + (size_t)w.t_pad * L.mp * L.esz);
   if (L.tiled && T <= SKINNY_MAX_M) {
-    w.n_cnt = skinny_counters(L.rp > L.dn ? L.rp : L.dn);
+    w.n_cnt = SKINNY_COUNTERS;
     w.off_cnt = off; off = align256(off + (size_t)w.n_cnt * 4);
   }
   w.off_kpart = off;

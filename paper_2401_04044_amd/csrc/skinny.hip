@@ -425,6 +425,7 @@ __global__ void __launch_bounds__(256) skinny_reduce_kernel(const SkinnyReduceAr
 constexpr int ROWS16_MAX_SPLIT = 8;
 constexpr int ROWS16_NW = 4;      // wavefronts of a workgroup
 constexpr int ROWS16_WGS = 256;   // workgroups of a full machine
+static_assert(ROWS16_WGS / 2 <= SKINNY_COUNTERS, "a product is cut only if two ranges of it fit one round");
 
 struct Rows16Args {
   const void* A;
