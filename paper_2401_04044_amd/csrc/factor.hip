@@ -16,10 +16,9 @@
 // Measured (2048 x 7946, rank 512, two matrices): 8.2 ms before, with everything on fp32 vector
 // arithmetic and 36 steps of X <- (1.5 I - 0.5 X X^T) X, one matrix after the other.
 #include "factor.h"
+#include "polar_steps.h"
 #include "prep.h"
 #include <algorithm>
-#include <math.h>
-#include <utility>
 
 namespace ffsplit {
 
@@ -204,68 +203,6 @@ __global__ void emit_kernel(const float* src, int64_t lds, int transposed, T* ds
   }
 }
 
-// Odd quintic with the least max |1 - p| on [lo, hi] (lo < hi not too close): the values 1 - e, 1 + e,
-// 1 - e, 1 + e at lo, the two interior extrema and hi (Remez exchange).
-void minimax_quintic(double lo, double hi, double* p) {
-  double q = (3 * lo + hi) / 4, r = (lo + 3 * hi) / 4;
-  for (int it = 0; it < 40; ++it) {
-    const double xs[4] = {lo, q, r, hi};
-    double A[4][5];
-    for (int i = 0; i < 4; ++i) {
-      const double x = xs[i], x2 = x * x;
-      A[i][0] = x; A[i][1] = x * x2; A[i][2] = x * x2 * x2; A[i][3] = (i & 1) ? -1 : 1; A[i][4] = 1;
-    }
-    for (int c = 0; c < 4; ++c) {   // elimination with row exchange
-      int best = c;
-      for (int i = c + 1; i < 4; ++i)
-        if (fabs(A[i][c]) > fabs(A[best][c])) best = i;
-      for (int j = 0; j < 5; ++j) std::swap(A[c][j], A[best][j]);
-      for (int i = 0; i < 4; ++i)
-        if (i != c) {
-          const double f = A[i][c] / A[c][c];
-          for (int j = c; j < 5; ++j) A[i][j] -= f * A[c][j];
-        }
-    }
-    for (int i = 0; i < 3; ++i) p[i] = A[i][4] / A[i][i];
-    const double disc = 9 * p[1] * p[1] - 20 * p[0] * p[2];
-    if (disc < 0) break;
-    const double r1 = (-3 * p[1] - sqrt(disc)) / (10 * p[2]), r2 = (-3 * p[1] + sqrt(disc)) / (10 * p[2]);
-    q = sqrt(std::max(std::min(r1, r2), lo * lo)); r = sqrt(std::max(std::max(r1, r2), lo * lo));
-  }
-}
-
-// Coefficients (a, b, c) of the steps.  While the singular values may reach below 0.15 of the largest:
-// the minimax quintic of [0.15, 1], which multiplies small ones by 3.66 and keeps the others between
-// 0.52 and 1 of the new largest (the fastest growth, slope 4.2, would map some large ones near zero,
-// where they keep their absolute rounding error).  Then the minimax quintic of the range itself, and
-// (15 x - 10 x^3 + 3 x^5) / 8 at the end, cubic convergence to 1.  Budget: singular values
-// down to 1 / (1024 r) of the Frobenius norm (a square Gaussian Y, r = d_model, has its smallest near
-// r^-1.5 of it); a basis direction below that comes out shorter than unit length.
-constexpr int MAX_STEPS = 48;
-int polar_steps(int r, float (*coef)[3]) {
-  double lo = 1.0 / (1024.0 * r), hi = 1.0;
-  int n = 0;
-  while ((lo < 1.0 - 3e-8 || hi > 1.0 + 3e-8) && n < MAX_STEPS) {
-    double p[3] = {1.875, -1.25, 0.375};
-    if (lo < 0.15 * hi) {
-      minimax_quintic(0.15, 1.0, p);
-      p[0] /= hi; p[1] /= hi * hi * hi; p[2] /= hi * hi * hi * hi * hi;
-    } else if (hi - lo > 1e-3) {
-      minimax_quintic(lo, hi, p);
-    }
-    double a = 1e30, b = 0;
-    for (int i = 0; i <= 4000; ++i) {
-      const double x = lo + (hi - lo) * i / 4000.0, x2 = x * x, y = x * (p[0] + x2 * (p[1] + x2 * p[2]));
-      a = std::min(a, y);
-      b = std::max(b, y);
-    }
-    lo = a; hi = b;
-    for (int i = 0; i < 3; ++i) coef[n][i] = (float)p[i];
-    ++n;
-  }
-  return n;
-}
-
 struct FactorWs {
   int mats, m4, r8, r32, mk, dk;
   size_t off_z, off_zt, off_om, off_part, off_terms, off_x[2], off_xt[2], off_s, off_t, off_c, off_red, total;
@@ -397,7 +334,7 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
                      (int64_t)dm, r8, dm, red);
   FKL();
   // ---- polar factor
-  float coef[MAX_STEPS][3];
+  float coef[POLAR_MAX_STEPS][3];
   const int steps = polar_steps(r, coef);
   for (int it = 0; it < steps; ++it) {
     float* Xn = (float*)(ws + w.off_x[(it + 1) & 1]);

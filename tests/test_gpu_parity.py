@@ -423,10 +423,15 @@ FACT_CASES = [
     ("gelu_f32", f32_variant(reduced(C2, 96, 160, rank=16)), 1e-4),
     ("swiglu_f32_ragged", f32_variant(reduced(C3, 64, 203, rank=18)), 1e-4),
     ("gelu_f32_full_side", f32_variant(reduced(C2, 64, 200, rank=64)), 1e-4),
-    # d_model >= 512 and a rank that is a multiple of 8: the Gram product of the orthonormalisation
-    # is split along its reduction
-    ("gelu_f32_split_gram", f32_variant(reduced(C2, 512, 300, rank=24)), 1e-4),
-    ("swiglu_f32_split_gram", f32_variant(reduced(C3, 768, 260, rank=40)), 1e-4),
+    # a Gram product of few entries and a long reduction
+    ("gelu_f32_long_gram", f32_variant(reduced(C2, 512, 300, rank=24)), 1e-4),
+    ("swiglu_f32_long_gram", f32_variant(reduced(C3, 768, 260, rank=40)), 1e-4),
+    # ranks that need all the growth steps; remainders on every side of the 32x32 and 64x64 tiles
+    # (rank 300: the last product of a step on 64x64, rank 690: the Gram product too)
+    ("gelu_f32_rank300", f32_variant(reduced(C2, 1000, 1400, rank=300)), 1e-4),
+    ("gelu_f32_rank690", f32_variant(reduced(C2, 1000, 1100, rank=690)), 1e-4),
+    ("gelu_bf16_rank300", reduced(C2, 1000, 1400, rank=300), 6e-3),
+    ("swiglu_bf16_rank256", reduced(C3, 512, 900, rank=256), 6e-3),
     ("swiglu_bf16", reduced(C3, 192, 700, rank=64), 6e-3),
     ("gelu_bf16", reduced(C2, 256, 1000, rank=100), 6e-3),
 ]
@@ -469,6 +474,53 @@ def test_factorize_remainder_matches_oracle(ff, name, cfg, tol):
     torch.cuda.synchronize()
     ref = orc.forward_split(X, L["W1"], L["W2"], L["Wg"], idx, cfg.act, "lowrank", got)
     assert_close(host(Y), ref[0], cfg.dtype, f"factorize {name}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["rank1", "zero", "dominated"])
+@pytest.mark.parametrize("d,d_ff,r", [(512, 900, 256), (1000, 1100, 300)])
+def test_factorize_degenerate_remainder(ff, dtype, kind, d, d_ff, r):
+    """Remainders whose sketch has rank one (its only singular value is the whole Frobenius norm), is
+    zero, or is dominated by one direction: finite factors whose product is the remainder (rank one,
+    zero) or the oracle's product, the basis orthonormal where the sketch has full rank, and a
+    finite forward pass on them that the oracle agrees with."""
+    base = reduced(C2, d, d_ff, rank=r)
+    cfg = f32_variant(base) if dtype == "f32" else base
+    L = {k: v.copy() if isinstance(v, np.ndarray) else v for k, v in wl.make_layer(cfg).items()}
+    idx = L["planted"]
+    rest = wl.remainder_order(idx, cfg.d_ff)
+    rng = np.random.default_rng(r)
+
+    def outer(n_rows, n_cols, scale):   # exact in bf16: a power of two times a bf16 number
+        u = 2.0 ** rng.integers(-2, 3, n_rows) * rng.choice([-1.0, 1.0], n_rows)
+        return np.outer(u, wl.bf16_round((scale * rng.standard_normal(n_cols)).astype(np.float32)))
+
+    if kind == "dominated":
+        L["W1"][:, rest] = wl.bf16_round((L["W1"][:, rest] + outer(d, len(rest), 1.0)).astype(np.float32))
+        L["W2"][rest] = wl.bf16_round((L["W2"][rest] + outer(len(rest), d, 1.0)).astype(np.float32))
+    else:
+        L["W1"][:, rest] = outer(d, len(rest), 0.02) if kind == "rank1" else 0.0
+        L["W2"][rest] = outer(len(rest), d, 0.02) if kind == "rank1" else 0.0
+    Ld = layer_to_dev(L, dtype)
+    desc = desc_for(ff, cfg, "lowrank")
+    idx_d = torch.from_numpy(idx).cuda()
+    fd = ff.factorize_remainder(desc, Ld["W1"], None, Ld["W2"], idx_d, seed=5)
+    torch.cuda.synchronize()
+    got = {k: host(v) for k, v in fd.items() if v is not None}
+    assert all(np.isfinite(v).all() for v in got.values())
+    want = orc.factorize_remainder(L["W1"], L["W2"], None, idx, r, seed=5) if kind == "dominated" else None
+    tol = 1e-4 if dtype == "f32" else 6e-3
+    for p, q, Z in (("P1", "Q1", L["W1"][:, rest]), ("P2", "Q2", L["W2"][rest])):
+        assert relf(got[p] @ got[q], Z if want is None else want[p] @ want[q]) < tol, p
+    if kind == "dominated":
+        B = got["P1"]
+        assert np.linalg.norm(B.T @ B - np.eye(r)) / np.sqrt(r) < tol
+    T = 50
+    X = wl.make_tokens(cfg, T)
+    split = ff.build_split(desc, Ld["W1"], None, Ld["W2"], idx_d, fd)
+    Y = guarded_forward(ff, desc, split, dev(X, dtype))
+    ref = orc.forward_split(X, L["W1"], L["W2"], None, idx, cfg.act, "lowrank", got)
+    assert_close(host(Y), ref[0], dtype, f"factorize {kind} {dtype}")
 
 
 # ---------------------------------------------------------------- seeded sweep over odd shapes
