@@ -139,6 +139,8 @@ int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int 
 // shape: one of gemm_plan.h.
 // n_split > 1 only with a.partial
 int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_split, hipStream_t st);
+// gated product with two left operands on 256 x 256 tiles (gemm_dual.hip); everything tiled
+int launch_gemm_dual(const GemmArgs& a, hipStream_t st);
 // sum of the partials in a fixed order -> C (bf16, tiled or row-major)
 int launch_splitk_reduce(const float* part, int n_split, int M, int N, int m_pad, void* C, int64_t ldc, int tiled,
                          hipStream_t st);

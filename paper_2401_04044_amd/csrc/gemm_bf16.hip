@@ -726,7 +726,7 @@ int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_sp
   if (a.A1 != nullptr) {
     switch (shape) {
       case GEMM_128x128: return launch_dl_dual<128, 128, 2, 2, 3, true>(a, act, st);
-      case GEMM_256x256: return launch_dl_dual<256, 256, 4, 2, 3, false>(a, act, st);
+      case GEMM_256x256: return act == ACT_GLU ? launch_gemm_dual(a, st) : -1;
     }
     return -1;
   }

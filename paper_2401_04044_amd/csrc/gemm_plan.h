@@ -9,7 +9,7 @@ enum {
   GEMM_128x128 = 0,   // 4 wavefronts, wave tile 64x64, two workgroups per CU
   GEMM_128x256 = 1,   // 4 wavefronts, wave tile 128x64, two workgroups per CU
   GEMM_128x320 = 2,   // 8 wavefronts, wave tile 64x80
-  GEMM_256x256 = 3,   // 8 wavefronts, wave tile 128x64 (64x128 with two left operands)
+  GEMM_256x256 = 3,   // 8 wavefronts, wave tile 128x64 (two left operands: gemm_dual.hip)
   GEMM_256x320 = 4,   // 8 wavefronts, wave tile 128x80
   GEMM_64x64 = 5,     // 4 wavefronts, wave tile 32x32
   GEMM_64x128 = 6,    // 4 wavefronts, wave tile 32x64
