@@ -371,9 +371,10 @@ __device__ __forceinline__ void sk_emit(const SkinnyReduceArgs& p, int rb, int c
 }
 
 __global__ void __launch_bounds__(256) skinny_reduce_kernel(const SkinnyReduceArgs p) {
-  const int id = blockIdx.x * 256 + threadIdx.x;
-  if (id >= p.n_rb * 256) return;
-  const int rb = id >> 8, g = (id >> 6) & 3, lane = id & 63;
+  // one workgroup per row block, one wavefront per g: both uniform, so that the partial sums' addresses
+  // are scalar but for the lane
+  const int rb = blockIdx.x, lane = threadIdx.x & 63;
+  const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool pair = p.act == ACT_GLU && rb * 32 < p.act_cols;
   if (pair && (rb & 1)) return;   // the pair is written from its gate block
   auto sum_block = [&](int b) {
