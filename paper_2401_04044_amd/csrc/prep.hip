@@ -57,13 +57,16 @@ __global__ void permute_transpose_kernel(const PermArgs a) {
 // The same for 16-bit elements into the tiled layout: 64 columns n x 64 rows c per workgroup through
 // LDS, 16-byte stores (a wavefront writes two runs of 512 bytes).  The element-wise form above moved
 // 67 MB (2048 x 8192 in and out) in 28 us.  Where a row is 16-byte aligned and the columns
-// are not permuted (VEC) the loads are 16 bytes too.
+// are not permuted (VEC) the loads are 16 bytes too; elsewhere they are single elements, 32 rows per
+// workgroup: small matrices are bound by their latency, and with 64 rows, sixteen loads a thread, a
+// 512 x 1327 one took 7.8 us, longer than element-wise (4.6 us and its share of a fill).
 // Zeros are written up to n_pad and c_pad (at least to the end of a chunk).
 template <bool VEC>
 __global__ void __launch_bounds__(256) permute_transpose_tiled_kernel(const PermArgs a) {
+  constexpr int CT = VEC ? 64 : 32;   // rows c per workgroup
   constexpr int LD = 72;   // elements per LDS row: 16-byte aligned, rows shifted by four banks
-  __shared__ __align__(16) uint16_t tile[64 * LD];
-  const int n0 = blockIdx.x * 64, c0 = blockIdx.y * 64, t = threadIdx.x;
+  __shared__ __align__(16) uint16_t tile[CT * LD];
+  const int n0 = blockIdx.x * 64, c0 = blockIdx.y * CT, t = threadIdx.x;
   const uint16_t* src = (const uint16_t*)a.src;
   if (VEC) {
 #pragma unroll
@@ -78,20 +81,24 @@ __global__ void __launch_bounds__(256) permute_transpose_tiled_kernel(const Perm
     }
   } else {
     const int n = n0 + (t & 63);
-    const int64_t scol = n < a.n_count ? (a.nmap ? a.nmap[a.nmap_off + n] : n) : -1;
-    uint16_t v[16];
+    // (unconditional loads of clamped indices: none waits for another)
+    const int nc = min(n, a.n_count - 1);
+    const int64_t scol = a.nmap ? a.nmap[a.nmap_off + nc] : nc;
+    uint16_t v[CT / 4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int c = c0 + i * 4 + (t >> 6);
-      v[i] = 0;
-      if (c < a.c_count && scol >= 0) v[i] = src[(int64_t)(a.cmap ? a.cmap[a.cmap_off + c] : c) * a.lds + scol];
+    for (int i = 0; i < CT / 4; ++i) {
+      const int cc = min(c0 + i * 4 + (t >> 6), a.c_count - 1);
+      v[i] = src[(int64_t)(a.cmap ? a.cmap[a.cmap_off + cc] : cc) * a.lds + scol];
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) tile[(i * 4 + (t >> 6)) * LD + (t & 63)] = v[i];
+    for (int i = 0; i < CT / 4; ++i) {
+      const int c = i * 4 + (t >> 6);
+      tile[c * LD + (t & 63)] = (c0 + c < a.c_count && n < a.n_count) ? v[i] : (uint16_t)0;
+    }
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < CT / 32; ++i) {
     const int nn = t & 63, c8 = (i * 4 + (t >> 6)) * 8, nq = n0 + nn;
     if (nq >= max(a.n_count, a.n_pad) || c0 + c8 >= max(a.c_count, a.c_pad)) continue;
     uint32_t w[4];
@@ -111,8 +118,8 @@ int launch_permute_transpose(const PermArgs& a, int esize, hipStream_t st) {
   if (a.n_count <= 0 || a.c_count <= 0) return 0;
   if (esize == 2 && a.dst_tiled && (a.coff & 7) == 0) {
     const int nn = a.n_pad > a.n_count ? a.n_pad : a.n_count, cn = a.c_pad > a.c_count ? a.c_pad : a.c_count;
-    const dim3 grid((nn + 63) / 64, (cn + 63) / 64);
     const bool vec = a.nmap == nullptr && (a.lds & 7) == 0 && (a.n_count & 7) == 0 && ((uintptr_t)a.src & 15) == 0;
+    const dim3 grid((nn + 63) / 64, vec ? (cn + 63) / 64 : (cn + 31) / 32);
     if (vec) hipLaunchKernelGGL(permute_transpose_tiled_kernel<true>, grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(permute_transpose_tiled_kernel<false>, grid, dim3(256), 0, st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
