@@ -76,11 +76,11 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
     }
     const bool dual = g.A1 != nullptr;
     const bool paired = a == ACT_GLU;
-    GemmPlan plan = gemm_plan(M, g.N, g.K, paired, dual, !dual);
+    GemmPlan plan = gemm_plan(M, g.N, g.K, paired, dual, g.a_tiled != 0, !dual);
     const int ldp = round_up(g.N, 32);
     // (never beyond the scratch the workspace was sized with: the plain launch is always valid)
     if (plan.split > 1 && (size_t)plan.split * M * ldp * 4 > w.kpart_bytes)
-      plan = gemm_plan(M, g.N, g.K, paired, dual, false);
+      plan = gemm_plan(M, g.N, g.K, paired, dual, g.a_tiled != 0, false);
     if (plan.split > 1) {
       float* part = (float*)(ws + w.off_kpart);
       GemmArgs gp = g;

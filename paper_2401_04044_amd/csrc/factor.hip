@@ -225,7 +225,7 @@ FactorWs make_factor_ws(const ffsplit_desc_t& d) {
     // one remainder matrix at a time: tiled [d_model, m] for the sketch, [m, d_model] for the projection
     w.off_z = take(std::max((size_t)round_up(dm, 32) * w.mk, (size_t)round_up(m, 32) * w.dk) * 2);
     w.off_om = take((size_t)w.r32 * w.mk * 2);
-    const GemmPlan p = gemm_plan(dm, w.r8, m, false, false, true);
+    const GemmPlan p = gemm_plan(dm, w.r8, m, false, false, true, true);
     w.part_bytes = p.split > 1 ? (size_t)p.split * dm * w.r32 * 4 : 0;
     w.off_part = take(w.part_bytes);
     w.term_bytes = align256((size_t)w.r32 * w.dk * 2);
@@ -307,7 +307,7 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
       FKL();
       GemmArgs g = gemm_nt(Z, w.mk, ws + w.off_om, w.mk, dm, r8, m, XT + i * nx, r8);
       g.a_tiled = 1; g.out_f32 = 1;
-      const GemmPlan p = gemm_plan(dm, r8, m, false, false, true);
+      const GemmPlan p = gemm_plan(dm, r8, m, false, false, true, true);
       if (p.split > 1) {
         GemmArgs gp = g;
         gp.partial = 1; gp.C0 = ws + w.off_part; gp.ldc0 = w.r32; gp.split_col = w.r32; gp.out_f32 = 0;
@@ -380,7 +380,7 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
         GemmArgs g = gemm_nt(Z, w.dk, term + t * w.term_bytes, w.dk, m, r8, dm, C, r8);
         g.a_tiled = 1; g.out_f32 = 1;
         if (t < 2) { g.resid = C; g.ldr = r8; }
-        FK(launch_gemm_bf16(g, ACT_NONE, false, gemm_plan(m, r8, dm, false, false, false).shape, 1, st));
+        FK(launch_gemm_bf16(g, ACT_NONE, false, gemm_plan(m, r8, dm, false, false, true, false).shape, 1, st));
       }
     } else {
       const unsigned gz = (unsigned)(((int64_t)dm * m4 + 255) / 256);

@@ -1,6 +1,7 @@
 // Internal: tile shapes of the bf16 GEMM (gemm_bf16.hip) and the choice among them for one
 // product.  Pure host arithmetic, also used to size workspaces.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 namespace ffsplit {
@@ -22,38 +23,51 @@ struct GemmPlan {
 };
 
 // Choice by estimated time.  A launch of W workgroups puts ceil(W / 256) of them on the fullest
-// CU; each walks its share of the 32-deep slabs at the shape's measured time per slab (t1: alone
-// on its CU, t2: both of two residents) and pays a fixed part (ring filling, store).  Partial sums
-// cost their traffic at 4.2 TB/s and a launch.  Measured on random operands (us per slab): 128x128
-// 0.21 alone, 0.40 as a pair (bound by the 61 bytes per clock a CU's vector cache delivers);
-// 128x256 0.38 / 0.70; 128x320 0.50; 256x256 0.66; 256x320 1.0 (the last two are at the power
-// limit: 1.5 PFLOP/s); 64x64 0.15 / 0.21 and 64x128 0.19 / 0.34 (four resp. eight MFMAs a wavefront
-// between barriers: bound by the latency of a slab, so they pay where larger tiles leave CUs idle or
-// need a split and its summing launch.  With them (us, before -> now): OPT-1.3B-sized layer, 65
-// tokens 45 -> 37, 300 with biases 56.4 -> 49.2, 1000 61 -> 55, 2000 81.5 -> 76.8; a 768-wide one,
-// 400 tokens 37 -> 27.6; Llama-2-7B-sized, 200 tokens 89.4 -> 82.5; the OPT-13B-sized one is unchanged).
-// 128x320, 256x320 and 64x64 have no gated form (a wavefront's columns do not hold
-// whole (gate, up) pairs); two left operands: 128x128 and 256x256 only, never split.
-inline GemmPlan gemm_plan(int64_t M, int N, int K, bool glu, bool dual, bool can_split) {
-  struct Shape { int bm, bn, per_cu; double t1, t2, fixed; };
-  static const Shape single[GEMM_SHAPES] = {{128, 128, 2, 0.215, 0.40, 2.5}, {128, 256, 2, 0.38, 0.70, 3.0},
-                                            {128, 320, 1, 0.50, 0, 4.0},     {256, 256, 1, 0.66, 0, 6.0},
-                                            {256, 320, 1, 1.0, 0, 6.0},     {64, 64, 2, 0.15, 0.21, 2.5},
-                                            {64, 128, 2, 0.19, 0.34, 2.5}};
-  static const Shape two[GEMM_SHAPES] = {{128, 128, 2, 0.30, 0.55, 3.0}, {}, {}, {256, 256, 1, 0.85, 0, 6.0}, {}, {}, {}};
+// CU; each walks its share of the 32-deep slabs at the shape's time per slab (t1: alone on its CU,
+// t2: both of two residents) and pays a fixed part (ring filling, store).  `row`: factor of t1 and
+// t2 for a row-major left operand, whose loads fetch 64 bytes of a row at a time.  Partial sums
+// cost a launch, their traffic and a dependent load per range.
+// The figures (us) are a least-squares fit to the DIFFERENCES between whole forward passes that run
+// one product on another tile or number of ranges: 4000 such runs over 489 products of 65 to 8192
+// tokens, model widths 512 to 5120.  What every choice pays alike is not in them (the power limit
+// above all: 256x256 tiles of a large product take 0.66 us a slab by themselves), so they rank the
+// choices and do not predict a launch's length: the traced length is up to 1.5 times the estimate.
+// The chosen tile's pass is 0.24 % longer than the best one's on average, 1.6 % in the 95th
+// percentile; with figures from products timed alone, one after another, it was 1.25 % and 7 %
+// (too many ranges, and ranges where none was best).
+// 128x320, 256x320 and 64x64 have no gated form (a wavefront's columns do not hold whole (gate, up)
+// pairs); two left operands: 128x128 and 256x256 only, never split.
+struct GemmShape { int bm, bn, per_cu; double t1, t2, fixed, row; };
+inline const GemmShape& gemm_shape(int shape, bool dual) {
+  static const GemmShape single[GEMM_SHAPES] = {{128, 128, 2, 0.177, 0.332, 2.6, 1.21}, {128, 256, 2, 0.287, 0.526, 4.4, 1.12},
+                                                {128, 320, 1, 0.359, 0, 4.3, 1.11},     {256, 256, 1, 0.453, 0, 6.8, 1.08},
+                                                {256, 320, 1, 0.565, 0, 8.1, 1.09},     {64, 64, 2, 0.105, 0.154, 1.5, 1.155},
+                                                {64, 128, 2, 0.135, 0.239, 1.9, 1.14}};
+  static const GemmShape two[GEMM_SHAPES] = {{128, 128, 2, 0.150, 0.332, 2.5, 1.0}, {}, {}, {256, 256, 1, 0.428, 0, 5.9, 1.0}, {}, {}, {}};
+  return dual ? two[shape] : single[shape];
+}
+inline bool gemm_shape_usable(const GemmShape& c, bool glu) { return c.bm > 0 && !(glu && (c.bn == 320 || c.bn == 64)); }
+constexpr int GEMM_MAX_SPLIT = 16, GEMM_MIN_SLABS = 8;   // ranges of a reduction; slabs of 32 per range
+constexpr double GEMM_SUM_US = 3.4, GEMM_SUM_RANGE_US = 0.29, GEMM_SUM_BYTES_PER_US = 3.4e6;
+inline size_t gemm_part_bytes(int64_t M, int N, int split) { return (size_t)split * M * ((N + 31) / 32 * 32) * 4; }
+
+// A reduction is split only to fill one round of the machine (256 CUs times the residents of a CU).
+inline GemmPlan gemm_plan(int64_t M, int N, int K, bool glu, bool dual, bool a_tiled, bool can_split) {
   GemmPlan best = {GEMM_128x128, 1};
   double best_t = 1e30;
   const int slabs = (K + 31) / 32;
   for (int s = 0; s < GEMM_SHAPES; ++s) {
-    const Shape& c = dual ? two[s] : single[s];
-    if (c.bm == 0 || (glu && (c.bn == 320 || c.bn == 64))) continue;
+    const GemmShape& c = gemm_shape(s, dual);
+    if (!gemm_shape_usable(c, glu)) continue;
+    const double row = a_tiled ? 1.0 : c.row;
     const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    for (int sp = 1; sp <= (can_split ? 16 : 1) && (sp == 1 || slabs / sp >= 8); ++sp) {
+    for (int sp = 1; sp == 1 || (can_split && sp <= GEMM_MAX_SPLIT && slabs / sp >= GEMM_MIN_SLABS &&
+                                 tiles * sp <= 256 * c.per_cu); ++sp) {
       const int64_t load = (tiles * sp + 255) / 256;
       const int n = (slabs + sp - 1) / sp;
-      double t = c.per_cu == 1 ? load * (n * c.t1 + c.fixed)
-                               : (load / 2) * (n * c.t2 + c.fixed) + (load & 1) * (n * c.t1 + c.fixed);
-      if (sp > 1) t += 4.0 + (double)sp * M * N * 4 / 4.2e6;
+      double t = c.per_cu == 1 ? load * (n * c.t1 * row + c.fixed)
+                               : (load / 2) * (n * c.t2 * row + c.fixed) + (load & 1) * (n * c.t1 * row + c.fixed);
+      if (sp > 1) t += GEMM_SUM_US + GEMM_SUM_RANGE_US * (sp - 1) + (double)gemm_part_bytes(M, N, sp) / GEMM_SUM_BYTES_PER_US;
       if (t < best_t) { best_t = t; best.shape = s; best.split = sp; }
     }
   }

@@ -920,9 +920,9 @@ static int phase2_splits(int G) {
 }
 
 // bytes of the fp32 partial sums of one bf16 product (0: its reduction is not split)
-static size_t gemm_scratch(int64_t T, int N, int K, bool glu, bool dual) {
+static size_t gemm_scratch(int64_t T, int N, int K, bool glu, bool dual, bool a_tiled) {
   if (N <= 0 || K <= 0) return 0;
-  int ranges = gemm_plan(T, N, K, glu, dual, !dual).split;
+  int ranges = gemm_plan(T, N, K, glu, dual, a_tiled, !dual).split;
   // At a few hundred rows the size keeps room for one range per idle CU (128 x 128 tiles, at least
   // 256 reduction elements each), whatever the plan takes of it.
   const int tiles = (int)((T + 127) / 128) * ((N + 127) / 128);
@@ -990,9 +990,9 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
     }
     if (T > SKINNY_MAX_M) {
       // fp32 partial sums of the products whose reduction is split
-      const size_t b[4] = {gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false),
-                           gemm_scratch(T, L.n_up * L.mp, L.rp, L.n_up == 2, L.n_up == 2),
-                           gemm_scratch(T, L.rp, L.mp, false, false), gemm_scratch(T, d.d_model, L.k4, false, false)};
+      const size_t b[4] = {gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false, false),
+                           gemm_scratch(T, L.n_up * L.mp, L.rp, L.n_up == 2, L.n_up == 2, true),
+                           gemm_scratch(T, L.rp, L.mp, false, false, true), gemm_scratch(T, d.d_model, L.k4, false, false, true)};
       for (size_t v : b)
         if (v > scratch) scratch = v;
     }
@@ -1001,7 +1001,7 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
   } else if (L.tiled && T > 0 && T <= SKINNY_MAX_M) {
     off = align256(off + skinny_part_bytes((int)T));
   } else if (L.tiled && T > SKINNY_MAX_M) {
-    const size_t b1 = gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false), b4 = gemm_scratch(T, d.d_model, L.k4, false, false);
+    const size_t b1 = gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false, false), b4 = gemm_scratch(T, d.d_model, L.k4, false, false, true);
     const size_t scratch = b1 > b4 ? b1 : b4;
     w.kpart_bytes = scratch;
     if (scratch > 0) off = align256(off + scratch);

@@ -10,21 +10,37 @@ from gpu_util import dev, host, assert_close, Guarded
 
 pytestmark = pytest.mark.gpu
 
-# T, d_model, d_ff, k, rank, act: what the choice of tiles gives for the four products
+# T, d_model, d_ff, k, rank, act: tiles (x ranges of the reduction) of the four products; test_gemm_plan.py
+# checks that every form is among them
 CASES = [
-    (65, 72, 97, 39, 17, "gelu"),            # one row past a 64x64 tile
-    (565, 256, 87, 0, 3, "swiglu"),          # no heavy neuron, gated: 64x128 and 128x128
-    (2911, 200, 6019, 2763, 3, "gelu"),      # 128x320 and 128x256; third product 64x64 and last 128x128 in 5 ranges
-    (1838, 80, 5539, 1, 3, "gelu"),          # 64x64 in 16 ranges; first slab shorter than 32
-    (4080, 136, 2085, 36, 129, "gelu"),      # 128x320 second product, d_model % 32 = 8
-    (1393, 64, 5212, 47, 2, "swiglu"),       # two left operands on 256x256; 64x64 in 11 ranges
-    (4889, 440, 3391, 13, 2, "gelu"),        # 256x320 second product
-    (5036, 1592, 294, 1, 10, "gelu"),        # 64x128 second and 128x256 last product
-    (4370, 1968, 146, 3, 67, "gelu"),        # 128x320 last product
-    (4717, 1696, 294, 68, 11, "swiglu"),
-    (321, 1048, 1500, 70, 130, "gelu"),      # 64x64 throughout, one row past a tile
-    (700, 1544, 2300, 300, 67, "swiglu"),    # gated 64x128 in 3 ranges, un-gated 64x128
-    (150, 2056, 1200, 33, 300, "gelu"),      # first product 64x64 in 8 ranges
+    (65, 72, 97, 39, 17, "gelu"),              # 64x64, 64x64, 64x64, 64x64
+    (565, 256, 87, 0, 3, "swiglu"),            # 64x128, 128x128, 64x64, 64x64
+    (2911, 200, 6019, 2763, 3, "gelu"),        # 128x320, 128x320, 64x64 x5, 64x64
+    (1838, 80, 5539, 1, 3, "gelu"),            # 64x64, 128x256, 64x64 x6, 64x64
+    (4080, 136, 2085, 36, 129, "gelu"),        # 64x64, 128x320, 64x64, 64x64
+    (1393, 64, 5212, 47, 2, "swiglu"),         # 64x128, 128x128, 64x64 x6, 64x64
+    (4889, 440, 3391, 13, 2, "gelu"),          # 64x64, 256x320, 64x64 x3, 64x128
+    (5036, 1592, 294, 1, 10, "gelu"),          # 64x64, 64x64, 64x64, 128x320
+    (4370, 1968, 146, 3, 67, "gelu"),          # 64x64, 64x64, 64x64, 128x320
+    (4717, 1696, 294, 68, 11, "swiglu"),       # 64x128, 128x128, 64x64, 128x320
+    (321, 1048, 1500, 70, 130, "gelu"),        # 64x64, 64x64, 64x64, 64x64
+    (700, 1544, 2300, 300, 67, "swiglu"),      # 64x128, 128x128, 64x64 x4, 64x64
+    (150, 2056, 1200, 33, 300, "gelu"),        # 64x64 x5, 64x64, 64x64, 64x64
+    (100, 88, 2282, 114, 40, "swiglu"),        # 64x128, 128x128, 64x64 x5, 64x64
+    (5070, 592, 4005, 40, 80, "gelu"),         # 64x64, 128x128, 64x128 x3, 64x128
+    (5978, 176, 6112, 305, 78, "gelu"),        # 64x128, 128x256, 128x128 x5, 64x64
+    (2641, 3160, 261, 2, 40, "swiglu"),        # 64x128 x3, 128x128, 64x64, 128x320
+    (4365, 3816, 105, 1, 40, "gelu"),          # 64x128 x3, 64x64, 64x64, 256x320
+    (1887, 144, 4921, 984, 78, "swiglu"),      # 128x128, 256x256, 64x64 x4, 64x64
+    (108, 1592, 84, 0, 40, "gelu"),            # 64x64 x5, 64x64, 64x64, 64x64
+    (3729, 72, 1210, 968, 40, "gelu"),         # 128x128, 64x64, 64x64, 64x64
+    (4039, 72, 1995, 997, 40, "swiglu"),       # 128x256, 128x128, 64x64, 64x64
+    (1831, 72, 6306, 5044, 40, "gelu"),        # 128x320, 64x128, 64x64, 64x64 x4
+    (5013, 72, 2740, 2192, 40, "gelu"),        # 128x256, 64x128, 64x64, 64x64
+    (82, 3784, 3089, 2471, 311, "swiglu"),     # 128x128 x5, 128x128, 64x64, 64x64 x2
+    (4562, 80, 7616, 3808, 40, "gelu"),        # 256x320, 256x320, 64x64 x3, 64x128 x3
+    (87, 4008, 8069, 6455, 84, "gelu"),        # 128x128 x4, 64x64, 64x64, 64x128 x4
+    (5002, 840, 919, 735, 59, "swiglu"),       # 256x256, 128x128, 64x64, 128x128
 ]
 
 
