@@ -95,7 +95,8 @@ typedef struct {
 /* Static description of a status code. */
 const char* ffsplit_status_string(int status);
 
-/* Bytes of scratch the given call needs for T tokens (pure host arithmetic). */
+/* Bytes of scratch the given call needs for T tokens (pure host arithmetic).  Never less for
+ * more tokens: a workspace sized for the largest batch serves every smaller one.          */
 size_t ffsplit_workspace_bytes(const ffsplit_desc_t* desc, int32_t call_id, int64_t T);
 
 /* Bytes of the packed split produced by ffsplit_build_split (pure host arithmetic). */

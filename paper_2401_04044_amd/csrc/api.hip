@@ -78,8 +78,9 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
     const bool paired = a == ACT_GLU;
     GemmPlan plan = gemm_plan(M, g.N, g.K, paired, dual, g.a_tiled != 0, !dual);
     const int ldp = round_up(g.N, 32);
-    // (never beyond the scratch the workspace was sized with: the plain launch is always valid)
-    if (plan.split > 1 && (size_t)plan.split * M * ldp * 4 > w.kpart_bytes)
+    // (never beyond the scratch the workspace was sized with: the plain launch is always valid; the
+    // separate halves Y_heavy and Y_rem have reductions of their own)
+    if (plan.split > 1 && gemm_part_bytes(M, g.N, plan.split) > w.kpart_bytes)
       plan = gemm_plan(M, g.N, g.K, paired, dual, g.a_tiled != 0, false);
     if (plan.split > 1) {
       float* part = (float*)(ws + w.off_kpart);

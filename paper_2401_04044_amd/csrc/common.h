@@ -155,6 +155,7 @@ int bf16_score_tile_m();
 // not grant the LDS the kernel needs (nothing launched).
 constexpr int FFN2_FUSED_RANK = 512;
 int ffn2_fused_splits(int M, int mp);
+size_t ffn2_fused_part_room(int M, int mp);   // bytes of part for any batch of at most M rows
 int launch_ffn2_fused(const void* T1, int64_t ldt, const void* Q1t, int64_t ldq, const void* P2t, int64_t ldp2, int M,
                       int mp, int rp, float* part, int n_split, hipStream_t st);
 // small-batch path (M <= SKINNY_MAX_M, N a multiple of 32): one weight-streaming launch per product;

@@ -15,6 +15,7 @@
 // rank elements of (t tile, Q1 chunk) in phase 1 and 16 neurons of the P2 chunk in phase 2, so
 // the ring keeps running across the phases and across chunks.
 #include "common.h"
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 #include <utility>
@@ -350,6 +351,12 @@ int ffn2_fused_splits(int M, int mp) {
   if (S > chunks) S = chunks;
   const int cps = (chunks + S - 1) / S;
   return (chunks + cps - 1) / cps;
+}
+
+size_t ffn2_fused_part_room(int M, int mp) {
+  // up to 256 row tiles the ranges and tiles make at most 256 workgroups, beyond them there is one range
+  const int64_t chunks = (mp + FC - 1) / FC, rows = std::max<int64_t>(M, std::min<int64_t>(chunks * M, 256 * FBM));
+  return (size_t)rows * FFN2_FUSED_RANK * 4;
 }
 
 int launch_ffn2_fused(const void* T1, int64_t ldt, const void* Q1t, int64_t ldq, const void* P2t, int64_t ldp2, int M,

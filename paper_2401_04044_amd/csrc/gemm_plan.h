@@ -74,4 +74,26 @@ inline GemmPlan gemm_plan(int64_t M, int N, int K, bool glu, bool dual, bool a_t
   return best;
 }
 
+// Bytes that hold the partial sums of any plan of at most M rows, so that a workspace sized for a batch
+// serves every smaller one (the plans' own need rises and falls with M).  A plan of `sp` ranges has at
+// most one round of tiles, and its summing costs less than the shape would lose without it.
+inline size_t gemm_part_room(int64_t M, int N, int K, bool glu, bool a_tiled) {
+  size_t room = 0;
+  const int slabs = (K + 31) / 32;
+  for (int s = 0; s < GEMM_SHAPES; ++s) {
+    const GemmShape& c = gemm_shape(s, false);
+    if (!gemm_shape_usable(c, glu)) continue;
+    const int64_t tiles_n = (N + c.bn - 1) / c.bn;
+    for (int sp = 2; sp <= GEMM_MAX_SPLIT && slabs / sp >= GEMM_MIN_SLABS; ++sp) {
+      const int64_t rows = 256 * c.per_cu / (sp * tiles_n) * c.bm;
+      const double gain = (slabs - (slabs + sp - 1) / sp) * c.t1 * (a_tiled ? 1.0 : c.row) - GEMM_SUM_US - GEMM_SUM_RANGE_US * (sp - 1);
+      if (rows <= 0 || gain <= 0) continue;
+      const size_t fits = gemm_part_bytes(rows < M ? rows : M, N, sp), pays = (size_t)(gain * GEMM_SUM_BYTES_PER_US) + 256;
+      const size_t b = fits < pays ? fits : pays;
+      if (b > room) room = b;
+    }
+  }
+  return room;
+}
+
 }  // namespace ffsplit

@@ -919,20 +919,6 @@ static int phase2_splits(int G) {
   return S;
 }
 
-// bytes of the fp32 partial sums of one bf16 product (0: its reduction is not split)
-static size_t gemm_scratch(int64_t T, int N, int K, bool glu, bool dual, bool a_tiled) {
-  if (N <= 0 || K <= 0) return 0;
-  int ranges = gemm_plan(T, N, K, glu, dual, a_tiled, !dual).split;
-  // At a few hundred rows the size keeps room for one range per idle CU (128 x 128 tiles, at least
-  // 256 reduction elements each), whatever the plan takes of it.
-  const int tiles = (int)((T + 127) / 128) * ((N + 127) / 128);
-  if (!dual && T <= 1024 && tiles < 128) {
-    const int room = std::min(std::min(256 / tiles, K / 256), 16);
-    ranges = std::max(ranges, room);
-  }
-  return ranges > 1 ? (size_t)ranges * T * round_up(N, 32) * 4 : 0;
-}
-
 FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
   FwdWs w = {};
   if (d.rem_kind == FFSPLIT_REM_W3H8 && T <= W3H8_DECODE_MAX_T) {
@@ -953,6 +939,9 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
     w.off_img = 0;
     w.off_dense = align256(LD.total_bytes);
     w.total_bytes = w.off_dense + make_fwd_ws(dd, LD, T).total_bytes;
+    // (never less than the smaller batches' own scratch)
+    const int64_t t_small = d.rem_kind == FFSPLIT_REM_INT4 ? INT4_DECODE_MAX_T : W3H8_DECODE_MAX_T;
+    w.total_bytes = std::max(w.total_bytes, make_fwd_ws(d, L, t_small).total_bytes);
     return w;
   }
   if (d.rem_kind == FFSPLIT_REM_INT4) {
@@ -972,39 +961,24 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
   w.off_cat = off; off = align256(off + (size_t)w.t_pad * L.k4 * L.esz);
   w.off_t = off; off = align256(off + (size_t)w.t_pad * L.n_up * L.rp * L.esz);
   w.off_h2 = off; off = align256(off + (size_t)w.t_pad * L.mp * L.esz);
-  if (L.tiled && T <= SKINNY_MAX_M) {
+  w.off_cnt = w.off_kpart = off;
+  if (L.tiled && T > 0) {
+    // What follows does not shrink as T grows, so that a buffer sized for a batch serves every smaller one.
     w.n_cnt = SKINNY_COUNTERS;
-    w.off_cnt = off; off = align256(off + (size_t)w.n_cnt * 4);
-  }
-  w.off_kpart = off;
-  if (L.tiled && L.rp > 0 && L.mp > 0 && T > 0) {
-    size_t scratch = 0;
-    if (ffn2_fused_applies(L, T)) {
-      const size_t fb = (size_t)ffn2_fused_splits((int)T, L.mp) * T * L.rp * 4;
-      if (fb > scratch) scratch = fb;
-    }
-    if (T <= SKINNY_MAX_M) {
-      // small batches take the weight-streaming kernels: room for their partial tiles
-      const size_t sk = skinny_part_bytes((int)T);
-      if (sk > scratch) scratch = sk;
-    }
+    w.off_kpart = align256(off + (size_t)w.n_cnt * 4);
+    // partial sums: at most SKINNY_MAX_M tokens take the weight-streaming kernels ...
+    w.kpart_bytes = skinny_part_bytes((int)std::min<int64_t>(T, SKINNY_MAX_M));
     if (T > SKINNY_MAX_M) {
-      // fp32 partial sums of the products whose reduction is split
-      const size_t b[4] = {gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false, false),
-                           gemm_scratch(T, L.n_up * L.mp, L.rp, L.n_up == 2, L.n_up == 2, true),
-                           gemm_scratch(T, L.rp, L.mp, false, false, true), gemm_scratch(T, d.d_model, L.k4, false, false, true)};
-      for (size_t v : b)
-        if (v > scratch) scratch = v;
+      // ... more of them the tiled ones, whose reductions may be split
+      const bool glu = L.n_up == 2, lr = L.rp > 0 && L.mp > 0;
+      const size_t b[4] = {gemm_part_room(T, L.n1, d.d_model, glu, false),
+                           lr && !glu ? gemm_part_room(T, L.mp, L.rp, false, true) : 0,   // (two left operands: never)
+                           lr ? gemm_part_room(T, L.rp, L.mp, false, true) : 0,
+                           gemm_part_room(T, d.d_model, L.k4, false, true)};
+      for (size_t v : b) w.kpart_bytes = std::max(w.kpart_bytes, v);
+      if (ffn2_fused_applies(L, T)) w.kpart_bytes = std::max(w.kpart_bytes, ffn2_fused_part_room((int)T, L.mp));
     }
-    w.kpart_bytes = scratch;
-    if (scratch > 0) off = align256(off + scratch);
-  } else if (L.tiled && T > 0 && T <= SKINNY_MAX_M) {
-    off = align256(off + skinny_part_bytes((int)T));
-  } else if (L.tiled && T > SKINNY_MAX_M) {
-    const size_t b1 = gemm_scratch(T, L.n1, d.d_model, L.n_up == 2, false, false), b4 = gemm_scratch(T, d.d_model, L.k4, false, false, true);
-    const size_t scratch = b1 > b4 ? b1 : b4;
-    w.kpart_bytes = scratch;
-    if (scratch > 0) off = align256(off + scratch);
+    off = align256(w.off_kpart + w.kpart_bytes);
   }
   w.total_bytes = off > 0 ? off : 256;
   return w;

@@ -164,45 +164,84 @@ def test_argument_errors_of_the_epilogue_norm_stack_and_probe_calls():
     assert L.ffsplit_probe_stream_read(odd, 32, 8, fake, None) == -4
 
 
-def test_forward_workspace_has_room_for_every_split_product():
-    """65..1024 rows of the low-rank chain (bf16): a product with few tiles is split along its
-    reduction and keeps fp32 partials [split][T][N] in the call's workspace.  The size the library
-    reports must cover the intermediates plus the largest of those scratch buffers, for each of
-    the four products (a scratch sized for three of them once let the fourth write past the
-    workspace).  The policy is restated here from its description: fewer than 128 tiles of
-    128 x 128 -> min(256 / tiles, K / 256, 16) splits."""
+def test_forward_workspace_serves_every_smaller_batch():
+    """ffsplit_workspace_bytes does not shrink as T grows, forward and stack, every remainder kind: a
+    buffer sized for the largest batch is accepted for all smaller ones (the calls refuse one that is
+    smaller than the figure for their own T)."""
     import numpy as np
     import paper_2401_04044_amd as ff
+
+    def check(desc, ts):
+        for call in (ff.WS_FORWARD, ff.WS_STACK):
+            got = [ff.workspace_bytes(desc, call, int(t)) for t in ts]
+            bad = [(t0, t1, b0, b1) for t0, t1, b0, b1 in zip(ts, ts[1:], got, got[1:]) if b1 < b0]
+            assert not bad, (desc.d_model, desc.d_ff, desc.rem_kind, bad[:3])
+
+    every = list(range(1, 4200)) + list(range(4200, 70000, 611))
+    for args in ((2048, 8192, "gelu", "bf16", 246, "lowrank", 512), (4096, 11008, "swiglu", "bf16", 550, "lowrank", 1024),
+                 (5120, 20480, "gelu", "bf16", 819, "lowrank", 1280), (4096, 11008, "swiglu", "bf16", 550, "dense"),
+                 (4096, 11008, "swiglu", "bf16", 550, "int4", 0, 128), (4096, 11008, "swiglu", "bf16", 550, "w3h8", 0, 128),
+                 (512, 560, "gelu", "bf16", 40, "lowrank", 500), (768, 3072, "gelu", "f32", 154, "lowrank", 64)):
+        check(ff.make_desc(*args), every)
+    rng = np.random.default_rng(9)
+    for _ in range(150):
+        kind = ("lowrank", "dense", "none", "int4", "w3h8")[int(rng.integers(0, 5))]
+        d = 128 * int(rng.integers(1, 17)) if kind in ("int4", "w3h8") else 8 * int(rng.integers(1, 300))
+        d_ff = int(rng.integers(8, 6000))
+        k = int(rng.integers(0, d_ff))
+        r = int(rng.integers(1, min(d, d_ff - k) + 1)) if kind == "lowrank" else 0
+        desc = ff.make_desc(d, d_ff, "swiglu" if rng.integers(0, 2) else "gelu", "bf16", k, kind, r, 128 if kind in ("int4", "w3h8") else 0)
+        check(desc, sorted(set(rng.integers(1, 400, 100)) | set((2.0 ** rng.uniform(6, 17, 200)).astype(int))))
+
+
+def test_forward_workspace_has_room_for_every_split_product(tmp_path):
+    """More than 64 rows of the low-rank chain (bf16): a product whose reduction is split keeps fp32
+    partials [split][T][N] in the call's workspace.  The size the library reports must cover the
+    intermediates plus the largest of those scratch buffers, for each of the four products (a scratch
+    sized for three of them once let the fourth write past the workspace).  The number of ranges is
+    taken from the planner itself."""
+    import subprocess
+    import numpy as np
+    import paper_2401_04044_amd as ff
+
+    src, so = tmp_path / "plan.cpp", tmp_path / "plan.so"
+    src.write_text('#include "gemm_plan.h"\n'
+                   'extern "C" int split_of(long M, int N, int K, int glu, int a_tiled) {\n'
+                   '  return ffsplit::gemm_plan(M, N, K, glu, false, a_tiled, true).split; }\n')
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-shared", "-fPIC",
+                           "-I" + os.path.join(ROOT, "paper_2401_04044_amd", "csrc"), str(src), "-o", str(so)])
+    lib = ctypes.CDLL(str(so))
+    lib.split_of.argtypes = [ctypes.c_long] + [ctypes.c_int] * 4
 
     def up(v, q):
         return (v + q - 1) // q * q
 
-    def split_of(T, N, K):
-        tiles = ((T + 127) // 128) * ((N + 127) // 128)
-        if tiles >= 128:
-            return 1
-        return max(1, min(256 // tiles, K // 256, 16))
-
     rng = np.random.default_rng(5)
-    for _ in range(300):
+    seen = 0
+    for _ in range(600):
         glu = bool(rng.integers(0, 2))
         d = int(rng.integers(8, 400)) * 8
         d_ff = int(rng.integers(64, 6000))
         k = int(rng.integers(0, d_ff // 2))
         m = d_ff - k
         r = int(rng.integers(1, min(d, m) + 1))
-        T = int(rng.integers(65, 1025))
+        T = int(rng.integers(65, 1025)) if rng.integers(0, 2) else int(2 ** rng.uniform(10, 14))
         desc = ff.make_desc(d, d_ff, "swiglu" if glu else "gelu", "bf16", k, "lowrank", r)
         n_up = 2 if glu else 1
         kp, rp, mp = up(k, 64), up(r, 64), up(m, 64)
         k4, tp = kp + rp, up(T, 32)
         inter = sum(up(tp * c * 2, 256) for c in (k4, n_up * rp, mp))
-        products = [(n_up * k4, d), (rp, mp), (d, k4)]          # G1, G3, G4
+        products = [(n_up * k4, d, glu, 0), (rp, mp, 0, 1), (d, k4, 0, 1)]   # G1, G3, G4
         if not glu:
-            products.append((mp, rp))                           # G2 (two left operands: never split)
-        need = max(split_of(T, N, K) * T * up(N, 32) * 4 if split_of(T, N, K) > 1 else 0 for N, K in products)
+            products.append((mp, rp, 0, 1))                     # G2 (two left operands: never split)
+        need = 0
+        for N, K, g, tiled in products:
+            sp = lib.split_of(T, N, K, g, tiled)
+            seen += sp > 1
+            need = max(need, sp * T * up(N, 32) * 4 if sp > 1 else 0)
         got = ff.workspace_bytes(desc, ff.WS_FORWARD, T)
         assert got >= inter + need, (d, d_ff, k, r, T, glu, got, inter, need)
+    assert seen > 100   # split products among the 2100 drawn
 
 
 def test_forward_workspace_has_room_for_the_fused_middle_products():
