@@ -1,6 +1,6 @@
-"""GPU parity of the bf16 product kernels at sizes that reach each tile shape, unit and
+"""GPU parity of the bf16 and fp32 product kernels at sizes that reach each tile shape, unit and
 reduction split with remainders on every side (rows, columns, reduction depth), against the CPU
-oracle.  Bars: the task's (1e-2 relative Frobenius, 2e-2 worst row)."""
+oracle.  Bars: the task's (bf16 1e-2 relative Frobenius, 2e-2 worst row; fp32 a thousandth of that)."""
 import numpy as np
 import pytest
 import torch
@@ -96,3 +96,42 @@ def test_every_tile_shape_matches_oracle(T, d, d_ff, k, r, act):
         g.check("forward_ex")
         want = orc.forward_split_biased(X, W1, W2, idx, "lowrank", fac, b1, b2, res)[0]
         assert_close(host(Y), want, "bf16", name + " biased")
+
+
+# fp32: every tile of gated (one and two left operands) and plain products; depths of half a slab of 16, and
+# of fewer slabs than there are k groups (d_model 8 and 72)
+F32 = [
+    (1, 8, 70, 3, 5, "gelu"),                # 16x16 throughout
+    (7, 72, 300, 20, 30, "swiglu"),          # 16x64, two left operands 16x64
+    (300, 520, 1300, 100, 130, "swiglu"),    # two left operands 32x64; 16x16, 32x32
+    (517, 1032, 1500, 150, 70, "swiglu"),    # 32x64, two left operands 64x128; 16x32, 64x64
+    (1000, 264, 2000, 500, 100, "swiglu"),   # 64x128, two left operands 64x128
+    (517, 1032, 2500, 400, 300, "gelu"),     # 32x32, 64x64
+    (900, 1000, 3000, 600, 200, "gelu"),     # 64x64 first and last product
+    (300, 776, 3000, 150, 64, "gelu"),       # 16x32 first product
+]
+
+
+@pytest.mark.parametrize("T,d,d_ff,k,r,act", F32)
+def test_every_fp32_tile_matches_oracle(T, d, d_ff, k, r, act):
+    import paper_2401_04044_amd as ff
+    rng = np.random.default_rng(T + d)
+    glu, m = act == "swiglu", d_ff - k
+
+    def f32(shape, std):
+        return (rng.standard_normal(shape) * std).astype(np.float32)
+
+    X, W1, W2 = f32((T, d), 1.0), f32((d, d_ff), d ** -0.5), f32((d_ff, d), 0.05)
+    Wg = f32((d, d_ff), d ** -0.5) if glu else None
+    fac = {"P1": f32((d, r), d ** -0.5), "Q1": f32((r, m), r ** -0.5), "P2": f32((m, r), 0.05), "Q2": f32((r, d), 0.5),
+           "Pg": f32((d, r), d ** -0.5) if glu else None, "Qg": f32((r, m), r ** -0.5) if glu else None}
+    idx = rng.permutation(d_ff)[:k].astype(np.int32)
+    desc = ff.make_desc(d, d_ff, act, "f32", k, "lowrank", r)
+    split = ff.build_split(desc, dev(W1, "f32"), dev(Wg, "f32"), dev(W2, "f32"), torch.from_numpy(idx).cuda(),
+                           {nm: dev(v, "f32") for nm, v in fac.items()})
+    g = Guarded(ff.workspace_bytes(desc, ff.WS_FORWARD, T))
+    got = ff.forward(desc, split, dev(X, "f32"), None, True, g.view)
+    g.check("forward")
+    want = orc.forward_split(X, W1, W2, Wg, idx, act, "lowrank", fac)
+    for y, w, nm in zip(got, want, ("Y", "Y_heavy", "Y_rem")):
+        assert_close(host(y), w, "f32", f"f32 T{T} d{d} f{d_ff} k{k} r{r} {act} {nm}")
