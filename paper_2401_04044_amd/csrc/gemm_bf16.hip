@@ -697,10 +697,9 @@ static int launch_dl_shape(const GemmArgs& a, int act, int n_split, hipStream_t 
   if (act == ACT_GELU)
     return at ? launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GELU, false, false, true>(a, 1, st)
               : launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GELU, false, false, false>(a, 1, st);
+  // (a gated product reads the caller's row-major tokens; the tiled one has two left operands)
   if constexpr ((BN / WGN) % 64 == 0) {
-    if (act == ACT_GLU)
-      return at ? launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GLU, false, false, true>(a, 1, st)
-                : launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GLU, false, false, false>(a, 1, st);
+    if (act == ACT_GLU && !at) return launch_dl_cfg<BM, BN, WGM, WGN, STAGES, DBLA, ACT_GLU, false, false, false>(a, 1, st);
   }
   return -1;
 }

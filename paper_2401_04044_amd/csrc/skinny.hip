@@ -668,7 +668,8 @@ int launch_skinny_bf16(const GemmArgs& g, int act, float* part, unsigned* counte
   if (g.M <= 0 || g.N <= 0) return 0;
   if (g.M > SKINNY_MAX_M || (g.N & 31) || g.partial) return -1;
   const bool glu = act == ACT_GLU && g.act_cols > 0, dual = g.A1 != nullptr, at = g.a_tiled != 0;
-  if ((dual && (!at || !glu || g.act_cols != g.N)) || (glu && (g.act_cols & 63))) return -1;
+  // (a gated product reads the caller's row-major tokens, or two tiled left operands)
+  if ((dual && (!at || !glu || g.act_cols != g.N)) || (glu && ((g.act_cols & 63) || at != dual))) return -1;
   Rows16Args a = {};
   a.A = g.A; a.A1 = g.A1; a.Bt = g.Bt; a.lda = g.lda; a.ldb = g.ldb;
   a.M = g.M; a.K = g.K; a.steps = (g.K + 31) / 32;
@@ -693,7 +694,6 @@ int launch_skinny_bf16(const GemmArgs& g, int act, float* part, unsigned* counte
   }
   if (dual) return launch_rows16<true, 2, 4, true, true>(a, st);
   if (at) {
-    if (glu) return one ? launch_rows16<true, 1, 4, true, false>(a, st) : launch_rows16<true, 2, 6, true, false>(a, st);
     return one ? launch_rows16<true, 1, 4, false, false>(a, st) : launch_rows16<true, 2, 6, false, false>(a, st);
   }
   if (glu) return one ? launch_rows16<false, 1, 4, true, false>(a, st) : launch_rows16<false, 2, 6, true, false>(a, st);
