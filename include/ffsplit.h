@@ -18,7 +18,7 @@
  *   - Element type of X, Y and all dense weights/factors is desc->dtype.
  *   - The library allocates nothing, keeps no state between calls (apart from
  *     a set-once, thread-safe note per device that a kernel's shared-memory limit
- *     has been raised, or that the device refused it and the kernel is not used there)
+ *     has been raised)
  *     and never synchronises: a call validates its arguments on the host, enqueues
  *     kernels on `stream` (a hipStream_t passed as void*, NULL = default stream)
  *     and returns.  Outputs are valid once the caller has synchronised the stream.
@@ -215,10 +215,7 @@ int ffsplit_factorize_remainder(const ffsplit_desc_t* desc, const void* W1, cons
  * buffers that receive FFN_1(X) and FFN_2~(X) separately (diagnostic; costs
  * extra launches).  Accumulation is fp32; intermediates between the chained
  * products are stored in desc->dtype.
- * LOWRANK: the activated remainder act((X P1) Q1) [T, m] is such an intermediate,
- * except for un-gated BF16 layers of rank 449..512 from 8192 tokens on, where it
- * is multiplied by P2 chunk by chunk without being stored (rounded to bf16 all
- * the same; only the order of the fp32 partial sums differs).
+ * LOWRANK: the activated remainder act((X P1) Q1) [T, m] is such an intermediate.
  * INT4: up to 192 tokens run in passes of 16 through weight-streaming kernels
  * that apply the group scales in fp32; above that the dequantised weights
  * float(s) * q are first written once, rounded to bf16, into the workspace

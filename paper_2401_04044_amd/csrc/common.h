@@ -141,23 +141,10 @@ int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int 
 int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_split, hipStream_t st);
 // gated product with two left operands on 256 x 256 tiles (gemm_dual.hip); everything tiled
 int launch_gemm_dual(const GemmArgs& a, hipStream_t st);
-// sum of the partials in a fixed order -> C (bf16, tiled or row-major)
-int launch_splitk_reduce(const float* part, int n_split, int M, int N, int m_pad, void* C, int64_t ldc, int tiled,
-                         hipStream_t st);
 // sum of the fp32 partials [n_split][a.M][ldp] of a whole product (written with a.partial, no
 // activation, GEMM column order) + the store epilogue described by a (activation act)
 int launch_splitk_epilogue(const float* part, int n_split, int ldp, const GemmArgs& a, int act, hipStream_t st);
 int bf16_score_tile_m();
-// The two middle products of the low-rank remainder in one launch (ffn2_fused.hip):
-// part[n_split][M][512] = per neuron range, gelu(T1 * Q1t^T) * P2t^T, all operands tiled bf16 with
-// the padded reduction lengths given (ldt, ldq = 512 = rp; ldp2 = mp, a multiple of 64).
-// n_split must be ffn2_fused_splits(M, mp).  Returns 0, -1 on an error, 1 where the device does
-// not grant the LDS the kernel needs (nothing launched).
-constexpr int FFN2_FUSED_RANK = 512;
-int ffn2_fused_splits(int M, int mp);
-size_t ffn2_fused_part_room(int M, int mp);   // bytes of part for any batch of at most M rows
-int launch_ffn2_fused(const void* T1, int64_t ldt, const void* Q1t, int64_t ldq, const void* P2t, int64_t ldp2, int M,
-                      int mp, int rp, float* part, int n_split, hipStream_t st);
 // small-batch path (M <= SKINNY_MAX_M, N a multiple of 32): one weight-streaming launch per product;
 // part: scratch of skinny_part_bytes(M) bytes.  A product whose rows are too few for the machine cuts
 // its reduction across workgroups, which count their arrival in `counters` (SKINNY_COUNTERS of them: a

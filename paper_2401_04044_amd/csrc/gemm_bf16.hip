@@ -508,39 +508,6 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
   gemm_epilogue<BM, BN, WGM, WGN, ACT, SCORE, EPI>(p, acc, m0, n0, tm, wm, wn, lane, tid, smem);
 }
 
-// Sum of fp32 split-K partials [n_split][M][N] (fixed order) -> bf16, tiled or row-major.
-__global__ void splitk_reduce_kernel(const float* part, int n_split, int M, int N, int m_pad, void* C, int64_t ldc,
-                                     int tiled) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // one 8-column chunk each
-  const int cpr = N / 8;
-  if (id >= (int64_t)m_pad * cpr) return;
-  const int row = (int)(id / cpr), c8 = (int)(id % cpr) * 8;
-  float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (row < M)
-    for (int s = 0; s < n_split; ++s) {
-      const float4 a = *(const float4*)(part + ((int64_t)s * M + row) * N + c8);
-      const float4 b = *(const float4*)(part + ((int64_t)s * M + row) * N + c8 + 4);
-      v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w; v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
-    }
-  const uint4 val = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]),
-                               pack_bf16x2(v[6], v[7]));
-  if (tiled) {
-    const int64_t blk = (int64_t)(row / 32) * (ldc / 16) + c8 / 16;
-    *(uint4*)((char*)C + ((blk * 64) + ((c8 >> 3) & 1) * 32 + (row & 31)) * 16) = val;
-  } else if (row < M) {
-    *(uint4*)((char*)C + ((int64_t)row * ldc + c8) * 2) = val;
-  }
-}
-
-int launch_splitk_reduce(const float* part, int n_split, int M, int N, int m_pad, void* C, int64_t ldc, int tiled,
-                         hipStream_t st) {
-  const int64_t n = (int64_t)m_pad * (N / 8);
-  if (n <= 0) return 0;
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, n_split, M, N,
-                     m_pad, C, ldc, tiled);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
 // Sum of fp32 split-K partials [n_split][M][ldp] of a whole product (GEMM column order) followed
 // by the store epilogue of the large-batch kernel: activation (GeLU, or SwiGLU on (gate, up)
 // pairs of 32-column blocks), routing to two destinations, bf16, tiled or row-major.  Used for

@@ -976,7 +976,6 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
                            lr ? gemm_part_room(T, L.rp, L.mp, false, true) : 0,
                            gemm_part_room(T, d.d_model, L.k4, false, true)};
       for (size_t v : b) w.kpart_bytes = std::max(w.kpart_bytes, v);
-      if (ffn2_fused_applies(L, T)) w.kpart_bytes = std::max(w.kpart_bytes, ffn2_fused_part_room((int)T, L.mp));
     }
     off = align256(w.off_kpart + w.kpart_bytes);
   }

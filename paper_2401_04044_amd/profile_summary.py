@@ -30,14 +30,14 @@ SIGNATURES = {
     "C5_stack_layer": [
         ("pre-norm  token_rmsnorm_kernel", r"token_rmsnorm_kernel<true>", 4096, 1),
         ("G1 X [W1h | P1]  128x320 tiles", G + r"128, 320, 2, 4, 4, true, 1, false, false, false, false>", 224, 1),
-        ("G2 gelu(t Q1)  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false>", 2464, 1),
+        ("G2 gelu(t Q1)  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 1, false, false, true, false>", 992, 1),
         ("G3 h2 P2  256x256 tiles x 3 ranges", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 80, 3),
         ("G3 sum of the ranges", r"splitk_epilogue_kernel", 2560, 1),
         ("G4 [h1 | t2] [W2h ; Q2] + residual, fp32 out  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 0, false, false, true, true>", 256, 1),
     ],
     "C5_prefill": [
         ("G1  128x320 tiles", G + r"128, 320, 2, 4, 4, true, 1, false, false, false, false>", 224, 1),
-        ("G2  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false>", 2464, 1),
+        ("G2  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 1, false, false, true, false>", 992, 1),
         ("G3  256x256 tiles x 3 ranges", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 80, 3),
         ("G3 sum of the ranges", r"splitk_epilogue_kernel", 2560, 1),
         ("G4  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 0, false, false, true, false>", 256, 1, r"splitk_epilogue_kernel"),
@@ -46,7 +46,7 @@ SIGNATURES = {
         ("G1 X [gate/up heavy | Pg | P1]  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 2, false, false, false, false>", 208, 1),
         ("G2 silu(tg Qg) * (tu Q1), two left operands  256x256 tiles", r"gemm_dual_kernel", 1312, 1),
         ("G3 h2 P2  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 256, 1, G),
-        ("G4  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 0, false, false, true, false>", 512, 1, G),
+        ("G4  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 256, 1),
     ],
     "C2_prefill": [
         ("G1  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 1, false, false, false, false>", 192, 1),
@@ -56,8 +56,10 @@ SIGNATURES = {
         ("G4  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 512, 1),
     ],
     "C2_prefill_T16384": [
-        ("G2 + G3 in one launch, h2 never stored: 128 rows x 2 neuron ranges", r"ffn2_fused_kernel", 256, 1),
-        ("sum of the ranges", r"splitk_reduce_kernel", 4096, 1),
+        ("G1  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 1, false, false, false, false>", 192, 1),
+        ("G2  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false>", 4096, 1),
+        ("G3  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 0, false, false, true, false>", 256, 1),
+        ("G4  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 0, false, false, true, false>", 1024, 1),
     ],
     "C4_int4_decode": [
         ("phase 1: gate/up, activation", r"int4_phase1_kernel<4, 8, 2>", 253, 1),
