@@ -139,11 +139,15 @@ struct FwdWs {
 };
 
 // INT4 remainder: up to this many tokens take the weight-streaming decode kernels, 16 tokens
-// per pass; beyond it the weights are expanded to bf16 once and the dense chain runs
-// (expanding plus the chain at that size costs about as much as 12 passes).
+// per pass; beyond it the weights are expanded to bf16 once and the dense chain runs.  Both sides (us,
+// passes / expanded): Llama-2-7B-sized layer, 64 tokens 106 / 182, 96 159 / 152, 128 212 / 167, 192
+// 316 / 189; OPT-1.3B-sized, 32 tokens 39 / 42, 64 78 / 50, 192 236 / 51.  The line lies above the
+// crossing (about 95 and 35 tokens): it was drawn for a slower chain.  Moving it moves the batches in
+// between from weights scaled in fp32 to weights rounded to bf16.
 constexpr int INT4_DECODE_MAX_T = 192;
 // W3H8: up to this many tokens stream the packed codes, 32 tokens per pass; beyond it they are
-// expanded (four passes cost less than expanding plus the chain at that size)
+// expanded.  Both sides: Llama-2-7B-sized layer, 128 tokens 167 / 232, 192 251 / 252, 256 334 / 267;
+// OPT-1.3B-sized, 96 tokens 69 / 79, 128 92 / 79.
 constexpr int W3H8_DECODE_MAX_T = 128;
 
 inline size_t build_ws_bytes(const ffsplit_desc_t& d) { return align256((size_t)8 * d.d_ff) + 256; }
