@@ -45,8 +45,8 @@ SIGNATURES = {
     "C3_prefill": [
         ("G1 X [gate/up heavy | Pg | P1]  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 2, false, false, false, false>", 208, 1),
         ("G2 silu(tg Qg) * (tu Q1), two left operands  256x256 tiles", r"gemm_dual_kernel", 1312, 1),
-        ("G3 h2 P2  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 256, 1, G),
-        ("G4  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 256, 1),
+        ("G3 h2 P2  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 256, 1, r"gemm_dual_kernel"),
+        ("G4  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 256, 1, G + r"128, 128, 2, 2, 4, true, 0"),
     ],
     "C2_prefill": [
         ("G1  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 1, false, false, false, false>", 192, 1),
