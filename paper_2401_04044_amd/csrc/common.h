@@ -49,8 +49,7 @@ __device__ __forceinline__ float silu_fast(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
-enum { ACT_NONE = 0, ACT_GELU = 1, ACT_GLU = 2,
-       ACT_POLY = 3 };   // fp32 kernel only: see GemmArgs::poly
+enum { ACT_NONE = 0, ACT_GELU = 1, ACT_GLU = 2 };
 
 // Exclusive prefix count of `flag` over the 1024 threads of a block, in thread
 // order, plus the block total.  wsum: 16 ints of LDS.  Every thread must call it.
@@ -108,16 +107,6 @@ struct GemmArgs {
   const float* resid;
   int64_t ldr;
   int out_f32;
-  // fp32 kernel: `batch` products at once, the operands and C0 (and resid) of product y start
-  // y times these strides further on (elements)
-  int64_t batch_a, batch_b, batch_c;
-  // ACT_POLY: C0 = poly[2] D + poly[1] resid + poly[0] I.  Ct (fp32 kernel, optional): a transposed copy
-  // [N, ldct] of C0, product y at Ct + y batch_ct
-  // sym (with Ct = the transposed destination, square tiles): C0 is symmetric, half of it is computed
-  float poly[3];
-  int sym;
-  float* Ct;
-  int64_t ldct, batch_ct;
   // score mode: per-row-tile partial column sums of h^2 and |h|
   float* part_s2;  // [tiles_m, n_out]
   float* part_s1;
@@ -134,8 +123,8 @@ struct Epilogue {
   int out_f32;
 };
 
-// batch > 1: that many products at the strides of GemmArgs (K, lda, ldb, split_col multiples of 4)
-int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int batch = 1);
+// K, lda, ldb, split_col multiples of 4
+int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st);
 // shape: one of gemm_plan.h.
 // n_split > 1 only with a.partial
 int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_split, hipStream_t st);

@@ -6,17 +6,15 @@
 //     B^T = orthonormal rows spanning the rows of Y^T,       C = B^T Z  [r, m],
 // so that Z ~= B C.  Omega [r, m] is a counter-based Rademacher matrix (the same signs on any
 // machine).  The rows of Y^T are orthonormalised by an odd matrix iteration for the polar factor,
-// X <- (a I + b X X^T + c (X X^T)^2) X from X = Y^T / ||Y||_F, which consists of products only.
+// X <- (a I + b X X^T + c (X X^T)^2) X from X = Y^T / ||Y||_F (polar.hip), which consists of products only.
 //
 // Precision and where the work runs.  The sketch of bf16 weights has exact products (bf16 times +-1)
 // and fp32 sums, so it is a product for the bf16 matrix cores; the projection takes the fp32 basis
 // as three bf16 terms (8 + 8 + 8 bits, all of it) against the bf16 weights, again exact products
-// and fp32 sums.  The iteration is fp32 throughout (gemm.hip), the matrices of a layer side by side in
+// and fp32 sums.  The iteration is fp32 throughout, the matrices of a layer side by side in
 // one launch.  fp32 weights are gathered and multiplied in fp32.
-// Measured (2048 x 7946, rank 512, two matrices): 8.2 ms before, with everything on fp32 vector
-// arithmetic and 36 steps of X <- (1.5 I - 0.5 X X^T) X, one matrix after the other.
 #include "factor.h"
-#include "polar_steps.h"
+#include "polar.h"
 #include "prep.h"
 #include <algorithm>
 
@@ -105,10 +103,12 @@ __global__ void __launch_bounds__(256) gather_tiled_kernel(const uint16_t* src, 
   *(uint4*)(dst + (((int64_t)blockIdx.y * (cols_pad / 16) + (c0 + c8) / 16) * 64 + ((c8 >> 3) & 1) * 32 + row) * 8) = w;
 }
 
-// X [r8, d] fp32 (row r and beyond zero) -> three bf16 terms whose sum is X to the last bit of
-// fp32 (each takes the leading 8 bits of what is left), tiled [r32, dk] each
-__global__ void __launch_bounds__(256) split_terms_kernel(const float* X, int r8, int d, int r32, int dk, uint16_t* hi,
-                                                          uint16_t* mid, uint16_t* lo) {
+// X [r8, ldx] fp32 (row r and beyond zero; in the copy that the state names) -> three bf16 terms whose sum is X to
+// the last bit of fp32 (each takes the leading 8 bits of what is left), tiled [r32, dk] each
+__global__ void __launch_bounds__(256) split_terms_kernel(const float* X, const PolarState* state, int64_t flip, int64_t ldx,
+                                                          int r8, int d, int r32, int dk, uint16_t* hi, uint16_t* mid,
+                                                          uint16_t* lo) {
+  X += state->parity * flip;
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;   // one 16-byte chunk of each term
   const int kbs = dk / 16;
   if (id >= (int64_t)(r32 / 32) * kbs * 64) return;
@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(256) split_terms_kernel(const float* X, int r8
   uint32_t w[3][4];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    float v = (row < r8 && k0 + e < d) ? X[(int64_t)row * d + k0 + e] : 0.f;
+    float v = (row < r8 && k0 + e < d) ? X[(int64_t)row * ldx + k0 + e] : 0.f;
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
       const uint32_t b = f32_to_bf16(v);
@@ -144,8 +144,10 @@ __global__ void __launch_bounds__(256) sumsq_stage1_kernel(const float* x, int64
   }
   if (threadIdx.x == 0) part[blockIdx.y * 260 + blockIdx.x] = red[0];
 }
-__global__ void __launch_bounds__(256) sumsq_stage2_kernel(float* part, int n_part) {
+// (it also zeroes the polar iteration's queue)
+__global__ void __launch_bounds__(256) sumsq_stage2_kernel(float* part, int n_part, unsigned* queue, int queue_words) {
   __shared__ float red[256];
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < queue_words; i += 256 * gridDim.x) queue[i] = 0u;
   part += blockIdx.x * 260;
   red[threadIdx.x] = (int)threadIdx.x < n_part ? part[threadIdx.x] : 0.f;
   __syncthreads();
@@ -156,9 +158,9 @@ __global__ void __launch_bounds__(256) sumsq_stage2_kernel(float* part, int n_pa
   if (threadIdx.x == 0) part[256] = red[0] > 0.f ? 1.0f / sqrtf(red[0]) : 0.f;   // scale for the next kernel
 }
 
-// dst[a][b] = src[b][a] * scale (fp32; a < rows_dst, b < cols_dst), and src *= scale in place;
+// dst[a][b] = src[b][a] * scale (fp32; a < rows_dst, b < cols_dst), zero for cols_dst <= b < ldd;
 // blockIdx.z: matrix (both contiguous)
-__global__ void scale_transpose_kernel(float* src, int64_t lds, float* dst, int64_t ldd, int rows_dst, int cols_dst,
+__global__ void scale_transpose_kernel(const float* src, int64_t lds, float* dst, int64_t ldd, int rows_dst, int cols_dst,
                                        const float* part) {
   __shared__ float tile[32][33];
   const float scale = part[blockIdx.z * 260 + 256];
@@ -167,24 +169,22 @@ __global__ void scale_transpose_kernel(float* src, int64_t lds, float* dst, int6
   const int a0 = blockIdx.y * 32, b0 = blockIdx.x * 32;
   for (int i = threadIdx.y; i < 32; i += 8) {
     const int b = b0 + i, a = a0 + threadIdx.x;
-    float v = 0.f;
-    if (b < cols_dst && a < rows_dst) {
-      v = src[(int64_t)b * lds + a] * scale;
-      src[(int64_t)b * lds + a] = v;
-    }
-    tile[i][threadIdx.x] = v;
+    tile[i][threadIdx.x] = b < cols_dst && a < rows_dst ? src[(int64_t)b * lds + a] * scale : 0.f;
   }
   __syncthreads();
   for (int i = threadIdx.y; i < 32; i += 8) {
     const int a = a0 + i, b = b0 + threadIdx.x;
-    if (a < rows_dst && b < cols_dst) dst[(int64_t)a * ldd + b] = tile[threadIdx.x][i];
+    if (a < rows_dst && b < ldd) dst[(int64_t)a * ldd + b] = tile[threadIdx.x][i];
   }
 }
 
-// dst [rows, cols] (bf16 or fp32, contiguous) = src[a][b], or src[b][a] through LDS
+// dst [rows, cols] (bf16 or fp32, contiguous) = src[a][b], or src[b][a] through LDS; with a state, src is the
+// copy that it names
 template <typename T>
-__global__ void emit_kernel(const float* src, int64_t lds, int transposed, T* dst, int rows, int cols) {
+__global__ void emit_kernel(const float* src, const PolarState* state, int64_t flip, int64_t lds, int transposed, T* dst,
+                            int rows, int cols) {
   __shared__ float tile[32][33];
+  if (state) src += state->parity * flip;
   const int a0 = blockIdx.y * 32, b0 = blockIdx.x * 32;
   auto put = [&](int a, int b, float v) {
     if constexpr (sizeof(T) == 4) dst[(int64_t)a * cols + b] = v;
@@ -205,7 +205,8 @@ __global__ void emit_kernel(const float* src, int64_t lds, int transposed, T* ds
 
 struct FactorWs {
   int mats, m4, r8, r32, mk, dk;
-  size_t off_z, off_zt, off_om, off_part, off_terms, off_x[2], off_xt[2], off_s, off_t, off_c, off_red, total;
+  size_t off_z, off_zt, off_om, off_part, off_terms, off_xt, off_c, off_red, off_polar, total;
+  PolarWs polar;
   size_t part_bytes, term_bytes;
 };
 
@@ -237,12 +238,9 @@ FactorWs make_factor_ws(const ffsplit_desc_t& d) {
     w.off_om = take((size_t)w.r8 * w.m4 * 4);
     w.off_c = take((size_t)w.r8 * w.m4 * 4);   // B^T Z
   }
-  for (int i = 0; i < 2; ++i) {
-    w.off_x[i] = take((size_t)w.mats * w.r8 * dm * 4);
-    w.off_xt[i] = take((size_t)w.mats * w.r8 * dm * 4);
-  }
-  w.off_s = take((size_t)w.mats * w.r8 * w.r8 * 4);
-  w.off_t = take((size_t)w.mats * w.r8 * w.r8 * 4);
+  w.off_xt = take((size_t)w.mats * w.r8 * dm * 4);
+  w.polar = make_polar_ws(w.mats, r, dm);
+  w.off_polar = take(w.polar.bytes);
   w.off_red = take((size_t)w.mats * 260 * 4);
   w.total = off;
   return w;
@@ -274,17 +272,18 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
   if (m <= 0 || r <= 0) return 0;
   const FactorWs w = make_factor_ws(d);
   const int m4 = w.m4, r8 = w.r8;
-  float* S = (float*)(ws + w.off_s); float* Tm = (float*)(ws + w.off_t); float* C = (float*)(ws + w.off_c);
+  float* C = (float*)(ws + w.off_c);
   float* red = (float*)(ws + w.off_red);
   char* Z = ws + w.off_z;
   const bool bf = d.dtype == FFSPLIT_BF16;
-  const int64_t nx = (int64_t)r8 * dm, ns = (int64_t)r8 * r8;
+  const PolarWs& pw = w.polar;
+  const int64_t nx = (int64_t)r8 * dm;
   const void* Ws[3] = {W1, d.act == FFSPLIT_ACT_SWIGLU ? Wg : W2, W2};   // the last one is the down projection
   const uint32_t stream_of[3] = {0, d.act == FFSPLIT_ACT_SWIGLU ? 1u : 2u, 2};
 
   // ---- sketches: (Y^T)^T = Z Omega^T  [d, r8] per matrix
-  float* XT = (float*)(ws + w.off_xt[0]);
-  float* X = (float*)(ws + w.off_x[0]);
+  float* XT = (float*)(ws + w.off_xt);
+  float* X = (float*)(ws + w.off_polar + pw.off_x);
   for (int i = 0; i < w.mats; ++i) {
     const bool down = i == w.mats - 1;
     const uint16_t* W = (const uint16_t*)Ws[i];
@@ -327,39 +326,25 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
       FK(launch_gemm_f32(gemm_nt(Z, m4, ws + w.off_om, m4, dm, r8, m4, XT + i * nx, r8), ACT_NONE, false, st));
     }
   }
-  // ---- unit Frobenius norm, both orders
+  // ---- unit Frobenius norm, rows of d, polar factor
   hipLaunchKernelGGL(sumsq_stage1_kernel, dim3(256, w.mats), dim3(256), 0, st, XT, nx, red);
-  hipLaunchKernelGGL(sumsq_stage2_kernel, dim3(w.mats), dim3(256), 0, st, red, 256);
-  hipLaunchKernelGGL(scale_transpose_kernel, dim3((dm + 31) / 32, (r8 + 31) / 32, w.mats), dim3(32, 8), 0, st, XT, (int64_t)r8, X,
-                     (int64_t)dm, r8, dm, red);
+  hipLaunchKernelGGL(sumsq_stage2_kernel, dim3(w.mats), dim3(256), 0, st, red, 256,
+                     (unsigned*)(ws + w.off_polar + pw.off_queue), pw.queue_words);
+  hipLaunchKernelGGL(scale_transpose_kernel, dim3(pw.dk / 32, (r8 + 31) / 32, w.mats), dim3(32, 8), 0, st, XT, (int64_t)r8, X,
+                     (int64_t)pw.dk, r8, dm, red);
   FKL();
-  // ---- polar factor
-  float coef[POLAR_MAX_STEPS][3];
-  const int steps = polar_steps(r, coef);
-  for (int it = 0; it < steps; ++it) {
-    float* Xn = (float*)(ws + w.off_x[(it + 1) & 1]);
-    float* XTn = (float*)(ws + w.off_xt[(it + 1) & 1]);
-    GemmArgs g = gemm_nt(X, dm, X, dm, r8, r8, dm, S, r8);
-    g.batch_a = g.batch_b = nx; g.batch_c = ns;
-    g.sym = 1; g.Ct = S; g.ldct = r8; g.batch_ct = ns;
-    FK(launch_gemm_f32(g, ACT_NONE, false, st, w.mats));
-    g = gemm_nt(S, r8, S, r8, r8, r8, r8, Tm, r8);   // (S is symmetric)
-    g.batch_a = g.batch_b = g.batch_c = ns; g.resid = S; g.ldr = r8;
-    for (int i = 0; i < 3; ++i) g.poly[i] = coef[it][i];
-    FK(launch_gemm_f32(g, ACT_POLY, false, st, w.mats));
-    g = gemm_nt(Tm, r8, XT, r8, r8, dm, r8, Xn, dm);
-    g.batch_a = ns; g.batch_b = g.batch_c = nx;
-    g.Ct = XTn; g.ldct = r8; g.batch_ct = nx;
-    FK(launch_gemm_f32(g, ACT_NONE, false, st, w.mats));
-    X = Xn; XT = XTn;
-  }
+  const PolarState* state = nullptr;
+  FK(launch_polar(pw, ws + w.off_polar, &state, st));
+  if (!bf) FK(launch_polar_settle(pw, ws + w.off_polar, state, st));
+  const int64_t flip = w.mats * pw.nx;
   // ---- projections and factors in the caller's convention and type:
   // P = B [d, r], Q = B^T Z [r, m] (up, gate);  P = Z^T B [m, r], Q = B^T [r, d] (down)
   for (int i = 0; i < w.mats; ++i) {
     const bool down = i == w.mats - 1;
     void* Pf = factors[down ? 4 : (i == 0 ? 0 : 2)];
     void* Qf = factors[down ? 5 : (i == 0 ? 1 : 3)];
-    const float* Xi = X + i * nx;
+    const float* Xi = X + i * pw.nx;
+    const PolarState* si = bf ? state + i : nullptr;
     if (bf) {
       if (down) {
         hipLaunchKernelGGL(gather_tiled_kernel, dim3(w.dk / 64, (m + 31) / 32), dim3(256), 0, st, (const uint16_t*)Ws[i],
@@ -373,8 +358,8 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
       }
       char* term = ws + w.off_terms;
       const int64_t chunks = (int64_t)(w.r32 / 32) * (w.dk / 16) * 64;
-      hipLaunchKernelGGL(split_terms_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st, Xi, r8, dm, w.r32, w.dk,
-                         (uint16_t*)term, (uint16_t*)(term + w.term_bytes), (uint16_t*)(term + 2 * w.term_bytes));
+      hipLaunchKernelGGL(split_terms_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st, Xi, si, flip,
+                         (int64_t)pw.dk, r8, dm, w.r32, w.dk, (uint16_t*)term, (uint16_t*)(term + w.term_bytes), (uint16_t*)(term + 2 * w.term_bytes));
       FKL();
       for (int t = 2; t >= 0; --t) {   // smallest term first
         GemmArgs g = gemm_nt(Z, w.dk, term + t * w.term_bytes, w.dk, m, r8, dm, C, r8);
@@ -387,21 +372,21 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
       hipLaunchKernelGGL(gather_z_kernel, dim3(gz), dim3(256), 0, st, (const float*)Ws[i], dm, d.d_ff, rest, m, m4, (int)down,
                          (float*)nullptr, (float*)(ws + w.off_zt));
       FKL();
-      FK(launch_gemm_f32(gemm_nt(Xi, dm, ws + w.off_zt, dm, r8, m4, dm, C, m4), ACT_NONE, false, st));
+      FK(launch_gemm_f32(gemm_nt(Xi, pw.dk, ws + w.off_zt, dm, r8, m4, dm, C, m4), ACT_NONE, false, st));
     }
     // C is [m, r8] (bf16) or [r8, m4] (fp32)
     const int64_t ldc = bf ? r8 : m4;
-    auto emit = [&](const float* src, int64_t lds, int transposed, void* dst, int rows, int cols) {
+    auto emit = [&](const float* src, const PolarState* s, int64_t lds, int transposed, void* dst, int rows, int cols) {
       const dim3 grid((cols + 31) / 32, (rows + 31) / 32), block(32, 8);
-      if (bf) hipLaunchKernelGGL(emit_kernel<bf16_t>, grid, block, 0, st, src, lds, transposed, (bf16_t*)dst, rows, cols);
-      else hipLaunchKernelGGL(emit_kernel<float>, grid, block, 0, st, src, lds, transposed, (float*)dst, rows, cols);
+      if (bf) hipLaunchKernelGGL(emit_kernel<bf16_t>, grid, block, 0, st, src, s, flip, lds, transposed, (bf16_t*)dst, rows, cols);
+      else hipLaunchKernelGGL(emit_kernel<float>, grid, block, 0, st, src, s, flip, lds, transposed, (float*)dst, rows, cols);
     };
     if (down) {
-      emit(C, ldc, bf ? 0 : 1, Pf, m, r);
-      emit(Xi, dm, 0, Qf, r, dm);
+      emit(C, nullptr, ldc, bf ? 0 : 1, Pf, m, r);
+      emit(Xi, si, pw.dk, 0, Qf, r, dm);
     } else {
-      emit(XT + i * nx, r8, 0, Pf, dm, r);
-      emit(C, ldc, bf ? 1 : 0, Qf, r, m);
+      emit(Xi, si, pw.dk, 1, Pf, dm, r);
+      emit(C, nullptr, ldc, bf ? 1 : 0, Qf, r, m);
     }
     FKL();
   }

@@ -12,8 +12,7 @@
 // Every wavefront moves its own operands, no barrier in the loop: the fp32 matrix rate is a
 // sixteenth of the bf16 one, so even a 32x32 wave tile asks for 32 bytes per clock and CU where the
 // vector cache delivers 61.  It does so only if four neighbouring lanes read one 64-byte piece
-// (16 bytes per clock where every lane has its own row, the order the MFMA wants: 512 x 512 x 2048
-// twice took 34 us), so lane l loads chunk l & 3 of row l >> 2 of a 16 x 16 block and the wavefront
+// (16 bytes per clock where every lane has its own row, the order the MFMA wants), so lane l loads chunk l & 3 of row l >> 2 of a 16 x 16 block and the wavefront
 // turns the block round in 1 KiB of LDS of its own: lane l then holds k elements 4 (l >> 4) .. + 3 of row
 // l & 15, and element t of both operands' registers feeds MFMA t of the slab (any pairing of k
 // works as long as both sides use the same).  PF slabs are in flight per wavefront.
@@ -50,9 +49,6 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
   const int kw = wave / (WGM * WGN), wt = wave % (WGM * WGN), wm = wt / WGN, wn = wt % WGN;
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
-  // A symmetric result: one half of the tiles stores the other half's mirror images; alternate products
-  // of a batch take opposite halves (a CU tends to get the same tile of two of them).
-  if (ACT == ACT_NONE && p.sym && (blockIdx.y & 1 ? tn > tm : tn < tm)) return;
   const int m0 = tm * BM + wm * TM * 16, n0 = tn * BN + wn * TN * 16;   // the wavefront's corner
   const int r16 = lane & 15, quad = lane >> 4;
 
@@ -66,9 +62,9 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
 #pragma unroll
   for (int j = 0; j < TN; ++j)
     b_off[j] = (uint32_t)(min(j * 16 + (lane >> 2), max(p.N - 1 - n0, 0)) * (int)p.ldb + 4 * (lane & 3)) * 4;
-  const float* const a_base = (const float*)p.A + (int64_t)min(m0, p.M - 1) * p.lda + p.batch_a * blockIdx.y;
+  const float* const a_base = (const float*)p.A + (int64_t)min(m0, p.M - 1) * p.lda;
   const float* const a1_base = DUAL ? (const float*)p.A1 + (int64_t)min(m0, p.M - 1) * p.lda : a_base;
-  const float* const b_base = (const float*)p.Bt + (int64_t)min(n0, p.N - 1) * p.ldb + p.batch_b * blockIdx.y;
+  const float* const b_base = (const float*)p.Bt + (int64_t)min(n0, p.N - 1) * p.ldb;
 
   f32x4_t acc[TM][TN];
 #pragma unroll
@@ -198,12 +194,9 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
           if (ACT == ACT_GLU) v[e] = glu_here ? silu_f(z) * acc[i2][(j + 2) % TN][e] : z;
           else if (ACT == ACT_GELU) v[e] = c < p.act_cols ? gelu_f(z + bz) : z + bz;
           else v[e] = z + bz;
-          if (ACT == ACT_POLY)
-            v[e] = c < p.N ? p.poly[2] * z + p.poly[1] * p.resid[p.batch_c * blockIdx.y + (int64_t)row * p.ldr + c] +
-                                 (row == c ? p.poly[0] : 0.f) : 0.f;
-          else if (p.resid != nullptr && to_c0 && c < p.N) v[e] += p.resid[(int64_t)row * p.ldr + oc + 4 * quad + e];
+          if (p.resid != nullptr && to_c0 && c < p.N) v[e] += p.resid[(int64_t)row * p.ldr + oc + 4 * quad + e];
         }
-        float* dst = base + p.batch_c * blockIdx.y + (int64_t)row * ld + 4 * quad;
+        float* dst = base + (int64_t)row * ld + 4 * quad;
         // (the columns of one 16-byte piece share a destination: split_col is a multiple of 4)
         if (cb + 4 * quad + 3 < p.N) {
           *(f32x4_t*)dst = f32x4_t{v[0], v[1], v[2], v[3]};
@@ -211,11 +204,6 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             if (cb + 4 * quad + e < p.N) dst[e] = v[e];
-        }
-        if (ACT == ACT_NONE && p.Ct != nullptr) {   // 16 lanes: 16 consecutive rows of one column
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (cb + 4 * quad + e < p.N) p.Ct[p.batch_ct * blockIdx.y + (int64_t)(cb + 4 * quad + e) * p.ldct + row] = v[e];
         }
       }
     }
@@ -267,14 +255,14 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
 // ------------------------------------------------------------------ host launchers
 
 template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE>
-static int launch_f32(const GemmArgs& a, int batch, hipStream_t st) {
+static int launch_f32(const GemmArgs& a, hipStream_t st) {
   constexpr int BM = WGM * TM * 16, BN = WGN * TN * 16;
   constexpr size_t waves = WGM * WGN * KW;
   constexpr size_t lds = std::max(waves * ((DUAL ? 2 : 1) * TM + TN) * 1024,
                                   std::max(KW > 1 ? waves * TM * TN * 1024 : (size_t)0, (size_t)(SCORE ? WGM * BN * 8 : 0)));
   static_assert(lds <= 64 * 1024, "within the default limit of dynamic LDS");
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, WGM, WGN, KW, PF, ACT, DUAL, SCORE>), dim3(tiles, batch),
+  hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, WGM, WGN, KW, PF, ACT, DUAL, SCORE>), dim3(tiles),
                      dim3(WGM * WGN * KW * 64), lds, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -284,12 +272,11 @@ static int launch_f32(const GemmArgs& a, int batch, hipStream_t st) {
 // about 3000 clocks of launch, first loads, sum and store.
 struct F32Shape { int bm, bn, wgm, wgn; };
 template <int N>
-static int pick_f32(const F32Shape (&c)[N], int64_t M, int64_t Nn, int64_t K, int batch, bool square) {
+static int pick_f32(const F32Shape (&c)[N], int64_t M, int64_t Nn, int64_t K) {
   int best = 0;
   double best_t = 1e30;
   for (int i = 0; i < N; ++i) {
-    if (square && c[i].bm != c[i].bn) continue;
-    const int64_t w = ((M + c[i].bm - 1) / c[i].bm) * ((Nn + c[i].bn - 1) / c[i].bn) * batch;
+    const int64_t w = ((M + c[i].bm - 1) / c[i].bm) * ((Nn + c[i].bn - 1) / c[i].bn);
     const double mfma = (double)c[i].bm * c[i].bn * K / 128, ld = 4.0 * K * (c[i].bm * c[i].wgn + c[i].bn * c[i].wgm) / 61;
     const double t = (double)((w + 255) / 256) * (std::max(mfma, ld) + 3000.0);
     if (t < best_t) { best_t = t; best = i; }
@@ -298,40 +285,39 @@ static int pick_f32(const F32Shape (&c)[N], int64_t M, int64_t Nn, int64_t K, in
 }
 
 template <int ACT, bool DUAL>
-static int launch_f32_act(const GemmArgs& a, int batch, hipStream_t st) {
+static int launch_f32_act(const GemmArgs& a, hipStream_t st) {
   if constexpr (ACT == ACT_GLU) {
     static const F32Shape c[] = {{64, 128, 2, 2}, {32, 64, 1, 1}, {16, 64, 1, 1}};
-    switch (pick_f32(c, a.M, a.N, a.K, batch, false)) {
-      case 0: return launch_f32<2, 4, 2, 2, 1, 2, ACT, DUAL, false>(a, batch, st);
-      case 1: return launch_f32<2, 4, 1, 1, 8, 2, ACT, DUAL, false>(a, batch, st);
-      default: return launch_f32<1, 4, 1, 1, 8, 4, ACT, DUAL, false>(a, batch, st);
+    switch (pick_f32(c, a.M, a.N, a.K)) {
+      case 0: return launch_f32<2, 4, 2, 2, 1, 2, ACT, DUAL, false>(a, st);
+      case 1: return launch_f32<2, 4, 1, 1, 8, 2, ACT, DUAL, false>(a, st);
+      default: return launch_f32<1, 4, 1, 1, 8, 4, ACT, DUAL, false>(a, st);
     }
   } else {
     // (128 x 128 on four wavefronts was slower everywhere: one wavefront per SIMD shows every wait)
     static const F32Shape c[] = {{64, 64, 2, 2}, {32, 32, 1, 1}, {16, 32, 1, 1}, {16, 16, 1, 1}};
-    switch (pick_f32(c, a.M, a.N, a.K, batch, a.sym != 0)) {
-      case 0: return launch_f32<2, 2, 2, 2, 2, 4, ACT, DUAL, false>(a, batch, st);
-      case 1: return launch_f32<2, 2, 1, 1, 8, 4, ACT, DUAL, false>(a, batch, st);
-      case 2: return launch_f32<1, 2, 1, 1, 8, 4, ACT, DUAL, false>(a, batch, st);
-      default: return launch_f32<1, 1, 1, 1, 16, 4, ACT, DUAL, false>(a, batch, st);
+    switch (pick_f32(c, a.M, a.N, a.K)) {
+      case 0: return launch_f32<2, 2, 2, 2, 2, 4, ACT, DUAL, false>(a, st);
+      case 1: return launch_f32<2, 2, 1, 1, 8, 4, ACT, DUAL, false>(a, st);
+      case 2: return launch_f32<1, 2, 1, 1, 8, 4, ACT, DUAL, false>(a, st);
+      default: return launch_f32<1, 1, 1, 1, 16, 4, ACT, DUAL, false>(a, st);
     }
   }
 }
 
-int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st, int batch) {
+int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return 0;
   if ((a.K & 3) || (a.lda & 3) || (a.ldb & 3) || (a.split_col & 3)) return -1;
   const bool dual = a.A1 != nullptr;
   if (score) {
-    if (act == ACT_GELU) return launch_f32<2, 4, 2, 2, 1, 2, ACT_GELU, false, true>(a, 1, st);
-    if (act == ACT_GLU) return launch_f32<2, 4, 2, 2, 1, 2, ACT_GLU, false, true>(a, 1, st);
+    if (act == ACT_GELU) return launch_f32<2, 4, 2, 2, 1, 2, ACT_GELU, false, true>(a, st);
+    if (act == ACT_GLU) return launch_f32<2, 4, 2, 2, 1, 2, ACT_GLU, false, true>(a, st);
     return -1;
   }
-  if (act == ACT_NONE) return launch_f32_act<ACT_NONE, false>(a, batch, st);
-  if (act == ACT_POLY) return launch_f32_act<ACT_POLY, false>(a, batch, st);
-  if (act == ACT_GELU) return launch_f32_act<ACT_GELU, false>(a, batch, st);
-  if (act == ACT_GLU && !dual) return launch_f32_act<ACT_GLU, false>(a, batch, st);
-  if (act == ACT_GLU && dual) return launch_f32_act<ACT_GLU, true>(a, batch, st);
+  if (act == ACT_NONE) return launch_f32_act<ACT_NONE, false>(a, st);
+  if (act == ACT_GELU) return launch_f32_act<ACT_GELU, false>(a, st);
+  if (act == ACT_GLU && !dual) return launch_f32_act<ACT_GLU, false>(a, st);
+  if (act == ACT_GLU && dual) return launch_f32_act<ACT_GLU, true>(a, st);
   return -1;
 }
 

@@ -1,10 +1,17 @@
-// Internal: coefficients of the odd matrix iteration for the polar factor (factor.hip),
+// Internal: coefficients of the odd matrix iteration for the polar factor (polar.hip),
 //   X <- (a I + b X X^T + c (X X^T)^2) X,
-// which maps every singular value x of X to x (a + b x^2 + c x^4).  Pure host arithmetic.
+// which maps every singular value x of X to x (a + b x^2 + c x^4): polar_steps, the steps that take any
+// spectrum to 1 (host), and polar_decide, which picks them one by one from what X X^T shows (device).
 #pragma once
 #include <algorithm>
 #include <math.h>
 #include <utility>
+
+#ifdef __HIPCC__
+#define FFS_HOST_DEVICE __host__ __device__
+#else
+#define FFS_HOST_DEVICE
+#endif
 
 namespace ffsplit {
 
@@ -98,6 +105,128 @@ inline int polar_steps(int r, float (*coef)[3]) {
     ++n;
   }
   return n;
+}
+
+// The same iteration with its steps chosen as it goes.  polar_steps must assume that the least singular
+// value is 1 / (1024 r) of the norm; a sketch of a weight matrix has its own far above that (a ratio of 2 to 4 to the
+// largest for a flat spectrum, 20 to 400 for spectra that decay like i^-1/2 and 1/i), so that most of its
+// steps stretch what needs no stretching: rank 512, 13 steps where 4 do.  Two figures of G = X X^T are enough:
+//   before the first step a bound of the largest value (the row sums of |G| and ||G||_F), by which X is
+//     scaled: up to 7 times closer than the norm itself;
+//   before every later step D = ||G - I||_F^2, the sum of (1 - x^2)^2 over the values x.
+// GROW    the minimax quintic of [0.15, 1], until D <= POLAR_BULK r: the bulk of the values is past 0.5 then
+//         (or, at the latest, everything is: max_grow steps, those of polar_steps).
+// RANGE1, RANGE2   the minimax quintics of [0.5, 1] and of its image: what was past 0.5 ends within 1e-5 of 1.
+// FINISH  D now counts the values that were smaller.  The quintics with p(1) = 1, p'(1) = 0 keep the others
+//         at 1: slope 2.7 at zero (K) while D > 0.5, that is while a value may be below 0.54, then
+//         (15 x - 10 x^3 + 3 x^5) / 8.  Slopes from 2.9 on are not safe: the inner maximum comes
+//         too near the repelling fixed point sqrt((a - 1) / (a - 1.5)); 2.7: 1.10 and 1.19.
+// The iteration ends with the cubic step that starts from D <= POLAR_DONE: no value is further than 2.3e-3
+// from 1 before it, so none further than 3e-8 after it.  max_steps is what the least value that polar_steps
+// takes to 1 needs, wherever the bulk lies; past it (values smaller still, or zero) nothing is promised, as there.
+constexpr float POLAR_BULK = 0.35f, POLAR_DONE = 2e-5f;
+enum { POLAR_GROW = 0, POLAR_RANGE2 = 1, POLAR_FINISH = 2, POLAR_ENDED = 3 };
+struct PolarPlan {
+  float grow[3], range1[3], range2[3], climb[3], cubic[3];   // grow: for values up to 1, into (0, 1]
+  int max_grow, max_steps;
+  int fixed;                          // no choice: the max_steps steps of polar_steps, this launch's is coef
+  float coef[3];
+};
+struct PolarState {
+  int mode, grown;
+  int parity;   // which of the two buffers holds X
+  int act;      // the step is carried out
+  int last;     // and is the last
+};
+
+// Matrices [r, d].  A flat sketch that is nearly square needs most of the steps anyway: from 2 r > d on those of
+// polar_steps are taken, of which there are two or three fewer (768 x 768: 13 instead of 15).
+inline PolarPlan polar_plan(int r, int d) {
+  PolarPlan p = {};
+  if (2 * r > d) {
+    float coef[POLAR_MAX_STEPS][3];
+    p.fixed = 1;
+    p.max_steps = polar_steps(r, coef);
+    return p;
+  }
+  double q[3], at[2], grow[3], r1[3], r2[3];
+  const auto peak = [&](const double* c, double lo, double end) {   // largest value over [lo, end]
+    double most = std::max(quintic(c, lo), quintic(c, end));
+    const int n = quintic_extrema(c, at);
+    for (int i = 0; i < n; ++i)
+      if (at[i] >= lo && at[i] <= end) most = std::max(most, quintic(c, at[i]));
+    return most;
+  };
+  minimax_quintic(0.15, 1.0, q);
+  const double top = peak(q, 0.0, 1.0);
+  for (int i = 0; i < 3; ++i) p.grow[i] = (float)(grow[i] = q[i] / top);
+  minimax_quintic(0.5, POLAR_RANGE_ROOM, r1);
+  for (int i = 0; i < 3; ++i) p.range1[i] = (float)r1[i];
+  const double hi = peak(r1, 0.5, POLAR_RANGE_ROOM);
+  minimax_quintic(quintic(r1, 0.5), hi * POLAR_RANGE_ROOM, r2);
+  for (int i = 0; i < 3; ++i) p.range2[i] = (float)r2[i];
+  const double k[3] = {2.7, -2.9, 1.2}, f[3] = {1.875, -1.25, 0.375};
+  for (int i = 0; i < 3; ++i) { p.climb[i] = (float)k[i]; p.cubic[i] = (float)f[i]; }
+  // the least value alone, the bulk past 0.5 after j growth steps
+  const double g = POLAR_GROW_ROOM, least = 1.0 / (1024.0 * r);
+  const auto grown = [&](double x) { return quintic(grow, x / g); };
+  for (double x = least; x < 0.5; x = grown(x)) ++p.max_grow;
+  for (int j = 1; j <= std::max(p.max_grow, 1); ++j) {
+    double x = least;
+    for (int i = 0; i < j; ++i) x = grown(x);
+    x = quintic(r2, quintic(r1, x));
+    int n = j + 2;
+    for (double dev = (1 - x * x) * (1 - x * x); dev > POLAR_DONE / 2; dev = (1 - x * x) * (1 - x * x), ++n)
+      x = quintic(dev > 0.5 ? k : f, x);
+    p.max_steps = std::max(p.max_steps, n + 1);
+  }
+  p.max_grow = std::max(p.max_grow, 1);
+  return p;
+}
+
+// Step `step` (0 .. max_steps - 1) of a matrix of r rows: its coefficients and the state after it.  fig: the
+// bound of the largest value before the first step, D before the others.
+FFS_HOST_DEVICE inline PolarState polar_decide(const PolarPlan& p, int step, int r, PolarState s, float fig, float (&c)[3]) {
+  c[0] = c[1] = c[2] = 0.f;
+  if (step > 0 && (s.mode == POLAR_ENDED || s.last)) {
+    s.mode = POLAR_ENDED;
+    s.act = s.last = 0;
+    return s;
+  }
+  if (step == 0) s.mode = POLAR_GROW, s.grown = 0, s.parity = 0;
+  if (p.fixed) {
+    for (int i = 0; i < 3; ++i) c[i] = p.coef[i];
+    s.act = 1;
+    s.last = step == p.max_steps - 1;
+    s.parity ^= 1;
+    return s;
+  }
+  const float* from = p.cubic;
+  float end = 1.f;
+  bool done = false;
+  if (s.mode == POLAR_GROW) {
+    if (step > 0 && (fig <= POLAR_BULK * (float)r || s.grown >= p.max_grow)) {
+      from = p.range1;
+      s.mode = POLAR_RANGE2;
+    } else {
+      from = p.grow;
+      // (a zero matrix has no bound, nor has one with NaN)
+      end = (float)POLAR_GROW_ROOM * (step == 0 && fig > 1e-6f && fig < 1.f ? fig : 1.f);
+      ++s.grown;
+    }
+  } else if (s.mode == POLAR_RANGE2) {
+    from = p.range2;
+    s.mode = POLAR_FINISH;
+  } else {
+    done = fig <= POLAR_DONE;
+    if (fig > 0.5f) from = p.climb;
+  }
+  const float e = 1.f / end, e2 = e * e;
+  c[0] = from[0] * e; c[1] = from[1] * (e * e2); c[2] = from[2] * (e * e2 * e2);
+  s.act = 1;
+  s.last = done || step == p.max_steps - 1;
+  s.parity ^= 1;
+  return s;
 }
 
 }  // namespace ffsplit
