@@ -140,7 +140,7 @@ def select_heavy(scores, k, want_perm=False, workspace=None):
     dev = scores.device
     idx = torch.empty(max(k, 1), dtype=torch.int32, device=dev)[:k]
     perm = torch.empty(d_ff, dtype=torch.int32, device=dev) if want_perm else None
-    flag = torch.zeros(1, dtype=torch.int32, device=dev)
+    flag = torch.empty(1, dtype=torch.int32, device=dev)   # (every call writes it)
     ws = _ws(int(lib.ffsplit_workspace_bytes(ctypes.byref(make_desc(8, d_ff)), WS_SELECT, 0)), workspace, dev)
     rc = lib.ffsplit_select_heavy(_ptr(scores), d_ff, k, _ptr(idx) if k > 0 else None, _ptr(perm), _ptr(flag),
                                   _ptr(ws), ws.numel(), _stream())

@@ -227,14 +227,16 @@ int ffsplit_score_neurons(const ffsplit_desc_t* d, const void* X, int64_t T, con
   hipStream_t st = (hipStream_t)stream;
   const int bf16 = d->dtype == FFSPLIT_BF16;
   const int esz = bf16 ? 2 : 4;
+  const float *p2 = nullptr, *p1 = nullptr;   // partial sums that the scores' kernel adds to acc
+  int tiles = 0, n_out = 0;
   if (T > 0) {
     const ScoreWs w = make_score_ws(*d, T);
     if (!workspace || workspace_bytes < w.total_bytes) return FFSPLIT_E_WORKSPACE;
     if (((uintptr_t)workspace & 255u) != 0) return FFSPLIT_E_ALIGN;
     char* ws = (char*)workspace;
     void* Wt = ws + w.off_wt;
-    float* p2 = (float*)(ws + w.off_p2);
-    float* p1 = (float*)(ws + w.off_p1);
+    p2 = (float*)(ws + w.off_p2);
+    p1 = (float*)(ws + w.off_p1);
     // transposed (neuron-major) copy of the up projection(s); rows beyond d_ff are zero
     // (the tiled form writes its own padding)
     if (!reuse_tiled && !bf16) FFS_TRY(launch_fill_zero(Wt, w.wt_bytes, st));
@@ -261,14 +263,17 @@ int ffsplit_score_neurons(const ffsplit_desc_t* d, const void* X, int64_t T, con
     g.Bt = Wt; g.ldb = w.dk;
     g.M = (int)T; g.N = w.n_gemm; g.K = d->d_model;
     g.act_cols = w.n_gemm;
-    g.part_s2 = p2; g.part_s1 = p1; g.n_out = w.n_out;
+    g.part_s2 = (float*)(ws + w.off_p2); g.part_s1 = (float*)(ws + w.off_p1); g.n_out = w.n_out;
     if (bf16) FFS_TRY(launch_gemm_bf16(g, act_of(d), true, GEMM_256x256, 1, st));
     else FFS_TRY(launch_gemm_f32(g, act_of(d), true, st));
-    FFS_TRY(launch_reduce_partials(p2, p1, w.tiles_m, w.n_out, d->d_ff, acc, st));
+    tiles = w.tiles_m;
+    n_out = w.n_out;
+    if (!scores) FFS_TRY(launch_reduce_partials(p2, p1, tiles, n_out, d->d_ff, acc, st));
     *T_total += T;
   }
   if (scores)
-    FFS_TRY(launch_finalize_scores(W2, bf16, d->d_model, d->d_ff, acc, (float)*T_total, score_kind, scores, st));
+    FFS_TRY(launch_finalize_scores(W2, bf16, d->d_model, d->d_ff, acc, p2, p1, tiles, n_out, (float)*T_total, score_kind, scores,
+                                   st));
   return FFSPLIT_OK;
 }
 

@@ -30,8 +30,9 @@ int launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 int launch_permute_transpose(const PermArgs& a, int esize, hipStream_t st);
 int launch_reduce_partials(const float* p2, const float* p1, int tiles, int n_out, int d_ff, float* acc,
                            hipStream_t st);
-int launch_finalize_scores(const void* W2, int bf16, int d_model, int d_ff, const float* acc, float t_total,
-                           int kind, float* scores, hipStream_t st);
+// scores from the accumulator, to which the partial sums of `tiles` row tiles (may be 0) are added first
+int launch_finalize_scores(const void* W2, int bf16, int d_model, int d_ff, float* acc, const float* p2, const float* p1,
+                           int tiles, int n_out, float t_total, int kind, float* scores, hipStream_t st);
 
 // per-token RMS normalisation of an fp32 stream into bf16 or fp32 (the pre-norm of a layer stack)
 int launch_token_rmsnorm(const float* x, int64_t T, int d, float eps, int bf16, void* out, hipStream_t st);

@@ -152,53 +152,102 @@ int launch_reduce_partials(const float* p2, const float* p1, int tiles, int n_ou
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// One wavefront per neuron: n2 = sum_c W2[j,c]^2 by lane-strided partial sums
-// and a fixed butterfly of wavefront shuffles, then the score of the given kind.
+// n2 = sum_c W2[j,c]^2 by one wavefront per neuron (lane-strided partial sums and a fixed butterfly of
+// wavefront shuffles), then the score of the given kind.  A workgroup takes 16 neurons, its wavefronts two each, eight
+// loads in flight: bound by reading W2 once.
+// tiles > 0: the call's partial sums of the activations are added to the accumulator first (reduce_partials
+// on these 16 neurons, requested ahead of the rows; as a launch of its own 6.8 us of latency).
+struct ScoreArgs {
+  const void* W2;
+  int d_model, d_ff;
+  float* acc;
+  const float *part_s2, *part_s1;
+  int tiles, n_out;
+  float t_total;
+  int kind;
+  float* scores;
+};
 template <bool BF16>
-__global__ void finalize_scores_kernel(const void* W2, int d_model, int d_ff, const float* acc, float t_total,
-                                       int kind, float* scores) {
-  const int lane = threadIdx.x & 63;
-  const int j = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (j >= d_ff) return;
-  float n2 = 0.f;
-  if (kind != 2) {
-    if (BF16) {
-      const bf16_t* row = (const bf16_t*)W2 + (int64_t)j * d_model;
-      for (int c = lane * 8; c < d_model; c += 64 * 8) {
-        const uint4 v = *(const uint4*)(row + c);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+__global__ void __launch_bounds__(512) finalize_scores_kernel(const ScoreArgs a) {
+  __shared__ float s_acc[2][16];
+  constexpr int PT = 8;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j0 = blockIdx.x * 16;
+  // thread (which sum, neuron): tiles in ascending order, PT in flight
+  const int which = threadIdx.x >> 4, jp = j0 + (threadIdx.x & 15);
+  const bool adds = threadIdx.x < 32 && jp < a.d_ff;
+  const float* part = (which ? a.part_s1 : a.part_s2) + jp;
+  float s = 0.f, old = 0.f;
+  if (adds) {
+    old = a.acc[which * a.d_ff + jp];
+    for (int t = 0; t < a.tiles; t += PT) {
+      float v[PT];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = __uint_as_float(w[e] << 16), hi = __uint_as_float(w[e] & 0xffff0000u);
-          n2 = fmaf(lo, lo, n2);
-          n2 = fmaf(hi, hi, n2);
+      for (int u = 0; u < PT; ++u) v[u] = part[(int64_t)min(t + u, a.tiles - 1) * a.n_out];
+#pragma unroll
+      for (int u = 0; u < PT; ++u)
+        if (t + u < a.tiles) s += v[u];
+    }
+  }
+  float n2[2] = {0.f, 0.f};
+  if (a.kind != 2) {
+    constexpr int E = BF16 ? 8 : 4, ESZ = BF16 ? 2 : 4, U = 4;   // 16 bytes a lane, U loads of a row at once
+    const char* row[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) row[i] = (const char*)a.W2 + (int64_t)min(j0 + wave * 2 + i, a.d_ff - 1) * a.d_model * ESZ;
+    for (int c0 = lane * E; c0 < a.d_model; c0 += 64 * E * U) {
+      uint4 v[U][2];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * 64 * E;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) v[u][i] = c < a.d_model ? *(const uint4*)(row[i] + (int64_t)c * ESZ) : make_uint4(0, 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint32_t w[4] = {v[u][i].x, v[u][i].y, v[u][i].z, v[u][i].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (BF16) {
+              const float lo = __uint_as_float(w[e] << 16), hi = __uint_as_float(w[e] & 0xffff0000u);
+              n2[i] = fmaf(lo, lo, n2[i]);
+              n2[i] = fmaf(hi, hi, n2[i]);
+            } else {
+              n2[i] = fmaf(__uint_as_float(w[e]), __uint_as_float(w[e]), n2[i]);
+            }
+          }
         }
-      }
-    } else {
-      const float* row = (const float*)W2 + (int64_t)j * d_model;
-      for (int c = lane * 4; c < d_model; c += 64 * 4) {
-        const float4 v = *(const float4*)(row + c);
-        n2 = fmaf(v.x, v.x, n2); n2 = fmaf(v.y, v.y, n2); n2 = fmaf(v.z, v.z, n2); n2 = fmaf(v.w, v.w, n2);
-      }
     }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) n2 += __shfl_xor(n2, o);
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) n2[i] += __shfl_xor(n2[i], o);
   }
-  if (lane == 0) {
-    float s;
-    if (kind == 0) s = acc[j] * n2;
-    else if (kind == 1) s = (acc[d_ff + j] / fmaxf(t_total, 1.f)) * sqrtf(n2);
-    else s = acc[j];
-    scores[j] = s + 0.f;
+  if (adds) {
+    if (a.tiles > 0) a.acc[which * a.d_ff + jp] = old + s;
+    s_acc[which][threadIdx.x & 15] = old + s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int jl = wave * 2 + i, j = j0 + jl;
+    if (lane != 0 || j >= a.d_ff) continue;
+    float v;
+    if (a.kind == 0) v = s_acc[0][jl] * n2[i];
+    else if (a.kind == 1) v = (s_acc[1][jl] / fmaxf(a.t_total, 1.f)) * sqrtf(n2[i]);
+    else v = s_acc[0][jl];
+    a.scores[j] = v + 0.f;
   }
 }
 
-int launch_finalize_scores(const void* W2, int bf16, int d_model, int d_ff, const float* acc, float t_total,
-                           int kind, float* scores, hipStream_t st) {
+int launch_finalize_scores(const void* W2, int bf16, int d_model, int d_ff, float* acc, const float* p2, const float* p1,
+                           int tiles, int n_out, float t_total, int kind, float* scores, hipStream_t st) {
   if (d_ff <= 0) return 0;
-  const int blocks = (d_ff + 3) / 4;
-  if (bf16) hipLaunchKernelGGL(finalize_scores_kernel<true>, dim3(blocks), dim3(256), 0, st, W2, d_model, d_ff, acc, t_total, kind, scores);
-  else hipLaunchKernelGGL(finalize_scores_kernel<false>, dim3(blocks), dim3(256), 0, st, W2, d_model, d_ff, acc, t_total, kind, scores);
+  const ScoreArgs a = {W2, d_model, d_ff, acc, p2, p1, tiles, n_out, t_total, kind, scores};
+  const dim3 grid((d_ff + 15) / 16), blk(512);
+  if (bf16) hipLaunchKernelGGL(finalize_scores_kernel<true>, grid, blk, 0, st, a);
+  else hipLaunchKernelGGL(finalize_scores_kernel<false>, grid, blk, 0, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -1,9 +1,10 @@
 // Bit-exact top-k of the neuron scores (heavy-hitter selection, Sec. 4.1/5.1.1).
-// Integer work only: scores are mapped to order-preserving uint32 keys, the k-th
-// largest key is found by a 32-step search over its bits (each step one count over the
-// keys, which a workgroup of 1024 threads holds in registers), the chosen elements are
-// compacted in index order (equal keys: lowest indices first) and finally ranked
-// by counting, which yields the order (score descending, index ascending).
+// Integer work only: scores are mapped to order-preserving uint32 keys.
+// Up to SELECT_COUNT_MAX_N scores every element is ranked by counting the elements in front of it, n^2
+// comparisons over the whole machine, and a second kernel numbers what was not chosen; beyond, one
+// workgroup finds the k-th largest key by a 32-step search over its bits (each step one count over the
+// keys, which 1024 threads hold in registers), compacts the chosen elements in index order (equal keys:
+// lowest indices first), and these are ranked by counting.  Order: score descending, index ascending.
 #include "prep.h"
 #include <atomic>
 
@@ -154,11 +155,105 @@ __global__ void __launch_bounds__(256) select_rank_kernel(const uint32_t* cand_k
   }
 }
 
+// Rank of every element = elements with a larger key, or with the same key at a lower index.  A workgroup ranks 32
+// elements: each of its 16 wavefronts holds them twice, in its lower and its upper half, and meets two
+// 1/32 shares of the keys, which come from LDS, the same four to every lane of a half.  Two vector instructions
+// a comparison (compare, add with carry): 8192 scores 2 us of arithmetic; what is left is a launch
+// and converting the scores.  Where the keys lie before or after the 32 elements, ties need no look at the index.
+constexpr int SEL_CHUNK = 8192;   // keys in LDS at a time
+__global__ void __launch_bounds__(1024) select_count_kernel(const float* scores, int n, int k, int32_t* rank, int32_t* idx,
+                                                            int32_t* perm, int32_t* nan_flag) {
+  __shared__ __align__(16) uint32_t key[SEL_CHUNK];
+  __shared__ int part[16][32];
+  __shared__ int s_nan;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i0 = blockIdx.x * 32, i = i0 + (lane & 31);
+  int saw = 0, cnt = 0;
+  const uint32_t ki = i < n ? score_key(scores[i], &saw) : 0xffffffffu;
+  if (tid == 0) s_nan = 0;
+  saw = 0;
+  for (int c0 = 0; c0 < n; c0 += SEL_CHUNK) {
+    const int m = min(SEL_CHUNK, n - c0), m4 = (m + 127) & ~127;   // (padded with key 0: real keys are > 0)
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < SEL_CHUNK / 1024; ++u) {
+      const int j = u * 1024 + tid;
+      if (j < m4) key[j] = j < m ? score_key(scores[c0 + j], &saw) : 0u;
+    }
+    __syncthreads();
+    // share of this half wavefront: groups of four keys, s, s + 32, ...
+    const int share = wave * 2 + (lane >> 5), groups = m4 / 4;
+    // groups that end before element i0, start behind i0 + 31, and the eight (at most) between
+    const int lo = max(0, min(groups, (i0 - c0) >> 2)), hi = max(0, min(groups, (i0 + 32 - c0) >> 2));
+    int g = share;
+#pragma unroll 4
+    for (; g < lo; g += 32) {
+      const uint4 q = *(const uint4*)(key + 4 * g);
+      cnt += q.x >= ki; cnt += q.y >= ki; cnt += q.z >= ki; cnt += q.w >= ki;
+    }
+    for (; g < hi; g += 32) {
+      const uint4 q = *(const uint4*)(key + 4 * g);
+      const int d = i - (c0 + 4 * g);
+      cnt += q.x > ki || (q.x == ki && d > 0); cnt += q.y > ki || (q.y == ki && d > 1);
+      cnt += q.z > ki || (q.z == ki && d > 2); cnt += q.w > ki || (q.w == ki && d > 3);
+    }
+#pragma unroll 4
+    for (; g < groups; g += 32) {
+      const uint4 q = *(const uint4*)(key + 4 * g);
+      cnt += q.x > ki; cnt += q.y > ki; cnt += q.z > ki; cnt += q.w > ki;
+    }
+  }
+  if (blockIdx.x == 0 && saw) s_nan = 1;
+  cnt += __shfl_xor(cnt, 32);
+  if (lane < 32) part[wave][lane] = cnt;
+  __syncthreads();
+  if (blockIdx.x == 0 && tid == 0 && nan_flag) *nan_flag = s_nan ? -7 : 0;
+  if (tid >= 32 || i >= n) return;
+  int r = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) r += part[w][tid];
+  rank[i] = r;
+  if (r < k) {
+    idx[r] = i;
+    if (perm) perm[r] = i;
+  }
+}
+
+// perm[k ..]: the elements of rank >= k in index order; a workgroup counts the chosen ones before its 1024
+__global__ void __launch_bounds__(1024) select_rest_kernel(const int32_t* rank, int n, int k, int32_t* perm) {
+  __shared__ int wsum[16];
+  __shared__ int before;
+  const int tid = threadIdx.x, i0 = blockIdx.x * 1024, i = i0 + tid;
+  int c = 0;
+  for (int j = tid; j < i0; j += 1024) c += rank[j] < k;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+  if (tid == 0) before = 0;
+  __syncthreads();
+  if ((tid & 63) == 0 && c > 0) atomicAdd(&before, c);
+  const bool sel = i < n && rank[i] < k;
+  int total, sp = block_prefix_1024(sel, wsum, &total);   // (its barriers come behind the sums above)
+  sp += before;
+  if (i < n && !sel) perm[k + (i - sp)] = i;
+}
+
+// Ranking by counting grows with n^2, the search on one CU with n.  Both sides (us, a calibration call of 256 tokens
+// and width 512 with the selection, search / counting): 1500 scores 55.0 / 45.3, 8192 (4096 tokens, width 2048)
+// 165 / 142, 16384 88.7 / 63.8, 20480 92.3 / 84.8, 24576 102.3 / 95.4.
+constexpr int SELECT_COUNT_MAX_N = 24576;
+
 size_t select_workspace_bytes(int d_ff) { return (size_t)12 * (size_t)(d_ff > 0 ? d_ff : 1) + 256; }
 
 int launch_select(const float* scores, int d_ff, int k, int32_t* idx, int32_t* perm, int32_t* nan_flag, void* ws,
                   hipStream_t st) {
   if (d_ff <= 0) return 0;
+  if (d_ff <= SELECT_COUNT_MAX_N) {
+    int32_t* rank = (int32_t*)ws;
+    hipLaunchKernelGGL(select_count_kernel, dim3((d_ff + 31) / 32), dim3(1024), 0, st, scores, d_ff, k, rank, idx, perm, nan_flag);
+    if (perm && k < d_ff)
+      hipLaunchKernelGGL(select_rest_kernel, dim3((d_ff + 1023) / 1024), dim3(1024), 0, st, rank, d_ff, k, perm);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+  }
   uint32_t* keys = (uint32_t*)ws;
   uint32_t* cand_key = keys + d_ff;
   int32_t* cand_idx = (int32_t*)(cand_key + d_ff);
