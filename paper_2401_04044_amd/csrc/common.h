@@ -168,6 +168,13 @@ struct SkinnyQ {
 size_t skinny_q_part_bytes(int n_max);
 int launch_skinny_q_pair(const GemmArgs& g8, const SkinnyQ& q8, const GemmArgs& g3, const SkinnyQ& q3, float* part,
                          int n_split[2], hipStream_t st);
+// The two products of a layer with at most 16 tokens (quant16_fits), one launch each:
+//   up    g as for a (gated) bf16 product over n8 rows of 8 bits, then n3 of 3 bits (act_cols = N = n8 + n3), with
+//         a tiled fp16 destination;
+//   down  g.A tiled fp16 [32, q8.Kp + q3.Kp], g.N a multiple of 128, with every addition of the epilogue.
+bool quant16_fits(int M, int d_model);
+int launch_quant16_up(const GemmArgs& g, int act, const SkinnyQ& q8, int n8, const SkinnyQ& q3, int n3, hipStream_t st);
+int launch_quant16_down(const GemmArgs& g, const SkinnyQ& q8, const SkinnyQ& q3, hipStream_t st);
 // reduce with n_split ranges for row blocks below rb_split and n_split_b from there on
 int launch_skinny_reduce2(const GemmArgs& a, int act, const float* part, int n_split, int rb_split, int n_split_b,
                           int f16_out, hipStream_t st);

@@ -318,6 +318,38 @@ int w3h8_forward_small(const ffsplit_desc_t& d, const Layout& L, const FwdWs& w,
   float* part = (float*)(ws + w.off_kpart);
   const size_t esz = 2;
   auto koff = [&](int col) { return (size_t)(col / 16) * 1024; };
+  // at most 16 tokens: one launch per product
+  if (L.k4 > 0 && quant16_fits(M, dm)) {
+    SkinnyQ q8 = {split + L.off_qc[0], split + L.off_qs[0], 8, 0, L.groups, L.kp};
+    SkinnyQ q3 = {split + L.off_qc[1], split + L.off_qs[1], 3, 0, L.groups, L.mp};
+    GemmArgs g = {};
+    g.A = X; g.lda = dm; g.M = M; g.K = dm;
+    g.N = g.act_cols = L.n_up * L.k4; g.split_col = L.k4;
+    g.C0 = cat; g.ldc0 = L.k4; g.c0_tiled = 1;
+    if (launch_quant16_up(g, act, q8, L.n_up * L.kp, q3, L.n_up * L.mp, st)) return -1;
+    q8.codes = split + L.off_qc[2]; q8.scales = split + L.off_qs[2];
+    q3.codes = split + L.off_qc[3]; q3.scales = split + L.off_qs[3];
+    g = {};
+    g.A = cat; g.lda = L.k4; g.a_tiled = 1; g.M = M; g.N = dm;
+    g.split_col = dm; g.C0 = Y; g.ldc0 = dm; g.n_store = dm;
+    g.bias = ep.b2; g.bias_cols = ep.b2 ? dm : 0; g.resid = ep.resid; g.ldr = dm; g.out_f32 = ep.out_f32;
+    if (launch_quant16_down(g, q8, q3, st)) return -1;
+    // the halves on their own: the other part of the reduction is empty
+    g.bias = nullptr; g.bias_cols = 0; g.resid = nullptr; g.out_f32 = 0;
+    if (Y_heavy) {
+      SkinnyQ none = q3;
+      none.Kp = 0;
+      g.C0 = Y_heavy;
+      if (L.kp > 0 ? launch_quant16_down(g, q8, none, st) : launch_fill_zero(Y_heavy, (size_t)M * dm * esz, st)) return -1;
+    }
+    if (Y_rem) {
+      SkinnyQ none = q8;
+      none.Kp = 0;
+      g.C0 = Y_rem; g.A = cat + koff(L.kp);
+      if (L.mp > 0 ? launch_quant16_down(g, none, q3, st) : launch_fill_zero(Y_rem, (size_t)M * dm * esz, st)) return -1;
+    }
+    return 0;
+  }
   // up / gate product, heavy rows (8 bits) then remainder rows (3 bits): act(X W) into cat
   {
     GemmArgs g8 = {}, g3 = {};

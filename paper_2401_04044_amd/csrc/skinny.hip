@@ -2,7 +2,8 @@
 // product is bound by streaming its weights from HBM once.
 //   D[M, N] = A[M, K] * Bt[N, K]^T
 // rows16_kernel: bf16 weights in the 32 x 16-block tiled layout, M <= 64, one launch per product.
-// skinny_stream_q2_kernel + skinny_reduce_kernel: 8- and 3-bit weights (qformat.h), M <= 32.
+// quant16_up_kernel, quant16_down_kernel: 8- and 3-bit weights (qformat.h), M <= 16, one launch per product.
+// skinny_stream_q2_kernel + skinny_reduce_kernel: the same weights, M <= 32.
 #include "common.h"
 #include "layout.h"
 #include "qformat.h"
@@ -638,6 +639,300 @@ __global__ void __launch_bounds__(NW * 64) rows16_kernel(const Rows16Args p) {
   }
 }
 
+// ---- 8- and 3-bit weights, at most 16 tokens: one launch per product, no sums across workgroups.
+// A piece is 16 weight rows: lane (r, q) = (lane & 15, lane >> 4) takes what lane 32 (q & 1) + r of the piece's half
+// holds of the 32 x 64 block 2 u + (q >> 1), so that one 12-byte (8 bits: two 16-byte) load a lane is a unit of
+// 16 rows x 128 reduction elements and, unpacked, the operands of four v_mfma_f32_16x16x32: MFMA j covers the
+// elements 64 (q >> 1) + 16 j + 8 (q & 1) + 0..7 of quad q, and the activations are loaded to match.
+//   UP    A workgroup of eight wavefronts keeps all 16 tokens in registers, wavefront w the groups w, w + 8, ..
+//         of 128 inputs, and walks over pairs of pieces (16 gate and their 16 up rows, or the two halves of a row block);
+//         the next pair's weights are requested before this one's are multiplied.  The constant of the
+//         offset-binary codes enters as the accumulator's start value, -132 (-1152) times the group's sum
+//         of the tokens, computed once.  3 bits: the four pairs of an operand share one rotated dword of third
+//         bits, pair i as 128 + 2^i u, and the tokens it meets are scaled by 2^-i (exact) beforehand: 52
+//         vector instructions for 16 x 128 codes instead of 64.  The wavefronts' sums meet in LDS, where
+//         one of them adds, activates and stores the pair while the others go on.
+//   DOWN  A workgroup owns one piece of 16 outputs (4096 outputs: one each CU) over the whole reduction, its wavefronts
+//         an eighth each; weights, activations and scales run through rings of registers.
+// The kernels below spend half of their 32-row MFMAs on absent tokens, a second MFMA on the constant of UP, and two
+// launches on sums across workgroups.  us, a layer of 16 tokens with its norm, those -> these: 4096 x 11008 gated 44.9 ->
+// 34.8 (up 19.9 + 5.0 -> 16.7, down 13.8 + 4.1 -> 12.8), 2048 x 8192 25.7 -> 20.1, 1280 x 4000 22.3 -> 14.9; with its start
+// values and operands scaled by powers of two up takes 16.7 instead of 17.9.  Bound by the unpacking (half of the
+// time), the ramp of each launch, and in DOWN the 8 KB of activations and scales that every 1.5 KB of codes meets.
+constexpr int Q16_NW = 8;
+constexpr int Q16_MAX_GPW = 4;   // groups of 128 inputs a wavefront holds
+
+struct Q16UpArgs {
+  const void* X;
+  int64_t lda;
+  int M, G;
+  const char* codes[2];          // 8 bits, 3 bits
+  const uint16_t* scales[2];
+  int units8, units3, wgs3, rb3;   // rb3: first row block of the 3-bit part in the output's order
+  SkinnyReduceArgs e;
+};
+
+typedef __attribute__((ext_vector_type(4))) float q16_f32x4;
+
+template <int BITS, int GPW, bool GLU>
+__device__ __forceinline__ void quant16_up(const Q16UpArgs& p, int u0, int step, int units, float4* red) {
+  constexpr int PART = BITS == 8 ? 0 : 1, BB = BITS == 8 ? 2048 : 768;
+  const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the tokens: groups wave, wave + 8, .. (zeros past the last group)
+  QFrag x[GPW][4];
+  {
+    const char* xr = (const char*)p.X + ((int64_t)min(r, p.M - 1) * p.lda + (q >> 1) * 64 + (q & 1) * 8) * 2;
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) {
+      const int gi = wave + g * Q16_NW;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        x[g][j].u = gi < p.G ? *(const u32x4_t*)(xr + (int64_t)gi * 256 + j * 32) : u32x4_t{0, 0, 0, 0};
+    }
+  }
+  struct Wts {
+    QPacked<BITS> w[2][GPW];
+    u32x2_t s[2][GPW];
+  };
+  // the packed codes and the lane's four row scales of both pieces (a group past the last repeats it: its tokens are zero)
+  auto piece_rb = [&](int u, int i) { return GLU ? (u & ~1) + i : u; };
+  auto piece_sub = [&](int u, int i) { return GLU ? (u & 1) : i; };
+  auto load = [&](Wts& w, int u) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int rb = piece_rb(u, i), sub = piece_sub(u, i);
+      const char* base = p.codes[PART] + (int64_t)rb * p.G * 2 * BB + (int64_t)(q >> 1) * BB;
+      const uint16_t* sb = p.scales[PART] + (int64_t)rb * p.G * 32 + sub * 16 + 4 * q;
+#pragma unroll
+      for (int g = 0; g < GPW; ++g) {
+        const int gi = min(wave + g * Q16_NW, p.G - 1);
+        const char* blk = base + (int64_t)gi * 2 * BB;
+        if constexpr (BITS == 8) w.w[i][g] = q_load8(blk, 32 * (q & 1) + 16 * sub + r);
+        else w.w[i][g] = q_load3(blk, 32 * (q & 1) + 16 * sub + r);
+        w.s[i][g] = *(const u32x2_t*)(sb + gi * 32);
+      }
+    }
+  };
+  Wts wa;
+  load(wa, u0);
+  // start values: every row of the operand holds the negated constants, so a token's is the same in all rows
+  float start[GPW];
+  {
+    QFrag negc;
+    if (BITS == 8) negc.u = u32x4_t{0xE480E480u, 0xE480E480u, 0xE480E480u, 0xE480E480u};   // fp16 -1152
+    else negc.u = u32x4_t{0xC304C304u, 0xC308C308u, 0xC310C310u, 0xC320C320u};             // bf16 -(128 + 4 2^i)
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) {
+      q16_f32x4 st = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if constexpr (BITS == 8) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {   // bf16 -> fp16: eight significant bits, exact
+            const auto h = __builtin_amdgcn_cvt_pkrtz(__uint_as_float(x[g][j].u[i] << 16), __uint_as_float(x[g][j].u[i] & 0xffff0000u));
+            uint32_t hb;
+            __builtin_memcpy(&hb, &h, 4);
+            x[g][j].u[i] = hb;
+          }
+          st = __builtin_amdgcn_mfma_f32_16x16x32_f16(negc.h, x[g][j].h, st, 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int i = 1; i < 4; ++i) {
+            const float s = i == 1 ? 0.5f : i == 2 ? 0.25f : 0.125f;
+            x[g][j].u[i] = pack_bf16x2(__uint_as_float(x[g][j].u[i] << 16) * s, __uint_as_float(x[g][j].u[i] & 0xffff0000u) * s);
+          }
+          st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(negc.b, x[g][j].b, st, 0, 0, 0);
+        }
+      }
+      start[g] = st[0];
+    }
+  }
+  int buf = 0, owner = 0;
+  auto unit = [&](const Wts& w, int u) {
+    q16_f32x4 tot[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      tot[i] = q16_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int g = 0; g < GPW; ++g) {
+        q16_f32x4 ag = {start[g], start[g], start[g], start[g]};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          QFrag wf;
+          if constexpr (BITS == 8) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) wf.u[e] = q_pair(w.w[i][g], j, e, 0x64646464u);
+          } else {
+            q_pairs_scaled(w.w[i][g], j, wf.u);
+          }
+          if constexpr (BITS == 8) ag = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf.h, x[g][j].h, ag, 0, 0, 0);
+          else ag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.b, x[g][j].b, ag, 0, 0, 0);
+        }
+        const u32x2_t sc = w.s[i][g];
+        tot[i][0] = fmaf(q_half((uint16_t)(sc[0] & 0xffffu)), ag[0], tot[i][0]);
+        tot[i][1] = fmaf(q_half((uint16_t)(sc[0] >> 16)), ag[1], tot[i][1]);
+        tot[i][2] = fmaf(q_half((uint16_t)(sc[1] & 0xffffu)), ag[2], tot[i][2]);
+        tot[i][3] = fmaf(q_half((uint16_t)(sc[1] >> 16)), ag[3], tot[i][3]);
+      }
+    }
+    // (two buffers: nobody is more than one barrier ahead of the wavefront that adds)
+    float4* const m = red + buf * Q16_NW * 2 * 64;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) m[(wave * 2 + i) * 64 + lane] = make_float4(tot[i][0], tot[i][1], tot[i][2], tot[i][3]);
+    __syncthreads();
+    if (wave == owner) {
+      float v[2][4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        float4 t = m[i * 64 + lane];
+#pragma unroll
+        for (int w2 = 1; w2 < Q16_NW; ++w2) {
+          const float4 o = m[(w2 * 2 + i) * 64 + lane];
+          t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+        }
+        v[i][0] = t.x; v[i][1] = t.y; v[i][2] = t.z; v[i][3] = t.w;
+      }
+      const int rb0 = PART ? p.rb3 : 0;
+      if (GLU) {
+        sk_emit(p.e, rb0 + (u & ~1), 16 * (u & 1) + 4 * q, r, v[0], v[1]);
+      } else {
+        const float none[4] = {0.f, 0.f, 0.f, 0.f};
+        sk_emit(p.e, rb0 + u, 4 * q, r, v[0], none);
+        sk_emit(p.e, rb0 + u, 16 + 4 * q, r, v[1], none);
+      }
+    }
+    buf ^= 1;
+    owner = (owner + 1) % Q16_NW;
+  };
+  if constexpr (BITS == 8) {   // (one pair a workgroup)
+    unit(wa, u0);
+    return;
+  }
+  Wts wb;
+  for (int u = u0; u < units; u += 2 * step) {
+    const bool two = u + step < units;
+    if (two) load(wb, u + step);
+    __builtin_amdgcn_sched_barrier(0);
+    unit(wa, u);
+    if (!two) break;
+    if (u + 2 * step < units) load(wa, u + 2 * step);
+    __builtin_amdgcn_sched_barrier(0);
+    unit(wb, u + step);
+  }
+}
+
+template <int GPW, bool GLU>
+__global__ void __launch_bounds__(Q16_NW * 64) quant16_up_kernel(const Q16UpArgs p) {
+  __shared__ float4 red[2 * Q16_NW * 2 * 64];
+  if ((int)blockIdx.x < p.units8) quant16_up<8, GPW, GLU>(p, blockIdx.x, 0, 0, red);
+  else quant16_up<3, GPW, GLU>(p, (int)blockIdx.x - p.units8, p.wgs3, p.units3, red);
+}
+
+struct Q16DownArgs {
+  const void* H;                 // [32, k4] tiled fp16
+  const char* codes[2];
+  const uint16_t* scales[2];
+  int Kp[2];                     // padded neurons of the 8- and the 3-bit part; the second follows the first in H
+  SkinnyReduceArgs e;
+};
+
+// this wavefront's share of one part of the reduction, in units of 128 neurons
+template <int BITS>
+__device__ __forceinline__ void quant16_down(const Q16DownArgs& p, int piece, q16_f32x4& tot) {
+  constexpr int PART = BITS == 8 ? 0 : 1, BB = BITS == 8 ? 2048 : 768, UW = BITS == 8 ? 2 : 6, UA = 2;
+  const int Kp = p.Kp[PART], units = (Kp + 127) / 128;
+  const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c0 = units * wave / Q16_NW, c1 = units * (wave + 1) / Q16_NW;
+  if (c0 >= c1) return;
+  const int rb = piece >> 1, sub = piece & 1;
+  // (past the last block of 64 neurons, and past the share, loads are out of range: zero)
+  const rsrc_t wr = sk_rsrc(p.codes[PART] + (int64_t)rb * (Kp / 64) * BB, (uint32_t)min(c1 * 2, Kp / 64) * BB);
+  const rsrc_t hr = sk_rsrc((const char*)p.H + (PART ? (size_t)p.Kp[0] * 64 : 0), (uint32_t)min(c1 * 128, Kp) * 64u);
+  const rsrc_t sr = sk_rsrc(p.scales[PART] + (int64_t)(rb >> 2) * Kp, (uint32_t)min(c1 * 128, Kp) * 2u);
+  const uint32_t wofs = (uint32_t)(q >> 1) * BB + (uint32_t)(32 * (q & 1) + 16 * sub + r) * (BITS == 8 ? 16 : 12);
+  const uint32_t hofs = (uint32_t)((q >> 1) * 4 * 64 + (q & 1) * 32 + r) * 16;
+  const uint32_t sofs = (uint32_t)((q >> 1) * 64 + (q & 1) * 8) * 2;
+  QPacked<BITS> w[UW];
+  QFrag h[UA][4], sc[UA][4];
+  auto load_w = [&](QPacked<BITS>& d, int c) {
+    const uint32_t o = wofs + (uint32_t)c * 2 * BB;
+    if constexpr (BITS == 8) {
+      d.h[0] = sk_load(wr, o);
+      d.h[1] = sk_load(wr, o + 1024);
+    } else {
+      typedef __attribute__((ext_vector_type(3))) uint32_t u32x3_t;
+      const u32x3_t v = __builtin_bit_cast(u32x3_t, __builtin_amdgcn_raw_buffer_load_b96(wr, o, 0, 0));
+      d.lo[0] = v[0]; d.lo[1] = v[1]; d.hi = v[2];
+    }
+  };
+  auto load_a = [&](QFrag (&hh)[4], QFrag (&ss)[4], int c) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      hh[j].u = sk_load(hr, hofs + (uint32_t)c * 8192 + j * 1024);
+      ss[j].u = sk_load(sr, sofs + (uint32_t)c * 256 + j * 32);
+    }
+  };
+  QFrag negc;
+  const uint32_t cc = BITS == 8 ? 0xE480E480u /* -1152 */ : 0xE404E404u /* -1028 */;
+  negc.u = u32x4_t{cc, cc, cc, cc};
+  auto unit = [&](const QPacked<BITS>& d, QFrag (&hh)[4], const QFrag (&ss)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      QFrag wf, a;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        H2 v, s2;
+        v.u = hh[j].u[i];
+        s2.u = ss[j].u[i];
+        v.h = v.h * s2.h;
+        a.u[i] = v.u;
+        wf.u[i] = q_pair(d, j, i, BITS == 8 ? 0x64646464u : 0x64006400u);
+      }
+      tot = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf.h, a.h, tot, 0, 0, 0);
+      tot = __builtin_amdgcn_mfma_f32_16x16x32_f16(negc.h, a.h, tot, 0, 0, 0);
+    }
+  };
+  static_assert(UW % UA == 0, "");
+#pragma unroll
+  for (int i = 0; i < UA; ++i) load_a(h[i], sc[i], c0 + i);
+#pragma unroll
+  for (int i = 0; i < UW; ++i) load_w(w[i], c0 + i);
+  for (int c = c0; c < c1; c += UW) {
+#pragma unroll
+    for (int i = 0; i < UW; ++i) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (c + i < c1) {   // (uniform)
+        unit(w[i], h[i % UA], sc[i % UA]);
+        if (c + i + UW < c1) load_w(w[i], c + i + UW);
+        if (c + i + UA < c1) load_a(h[i % UA], sc[i % UA], c + i + UA);
+      }
+    }
+  }
+}
+
+__global__ void __launch_bounds__(Q16_NW * 64) quant16_down_kernel(const Q16DownArgs p) {
+  __shared__ float4 red[Q16_NW * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int piece = blockIdx.x;
+  q16_f32x4 tot = {0.f, 0.f, 0.f, 0.f};
+  quant16_down<3>(p, piece, tot);
+  quant16_down<8>(p, piece, tot);
+  red[wave * 64 + lane] = make_float4(tot[0], tot[1], tot[2], tot[3]);
+  __syncthreads();
+  if (wave != 0) return;
+  float4 t = red[lane];
+#pragma unroll
+  for (int w = 1; w < Q16_NW; ++w) {
+    const float4 o = red[w * 64 + lane];
+    t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+  }
+  float v[4] = {t.x, t.y, t.z, t.w};
+  const float none[4] = {0.f, 0.f, 0.f, 0.f};
+  sk_emit(p.e, piece >> 1, 16 * (piece & 1) + 4 * (lane >> 4), lane & 15, v, none);
+}
+
 }  // namespace
 
 size_t skinny_part_bytes(int M) {
@@ -714,6 +1009,52 @@ int launch_skinny_reduce2(const GemmArgs& g, int act, const float* part, int n_s
   r.c0_tiled = g.c0_tiled; r.c1_tiled = g.c1_tiled; r.n_store = g.n_store;
   r.bias = g.bias; r.bias_cols = g.bias_cols; r.resid = g.resid; r.ldr = g.ldr; r.out_f32 = g.out_f32;
   hipLaunchKernelGGL(skinny_reduce_kernel, dim3(r.n_rb), dim3(256), 0, st, r);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// Up to a d_model of 4096: 256 pieces of outputs are one each CU, and four groups a wavefront fit its registers.
+// 5120 x 13824 (320 pieces, five groups) takes 68 us a layer this way, 60 on the kernels for 32 tokens.
+bool quant16_fits(int M, int d_model) { return M <= 16 && d_model <= 128 * Q16_NW * Q16_MAX_GPW; }
+
+template <bool GLU>
+static void launch_q16_up(const Q16UpArgs& a, hipStream_t st) {
+  const dim3 grid(a.units8 + a.wgs3), blk(Q16_NW * 64);
+  switch ((a.G + Q16_NW - 1) / Q16_NW) {
+    case 1: hipLaunchKernelGGL((quant16_up_kernel<1, GLU>), grid, blk, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((quant16_up_kernel<2, GLU>), grid, blk, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((quant16_up_kernel<3, GLU>), grid, blk, 0, st, a); break;
+    default: hipLaunchKernelGGL((quant16_up_kernel<4, GLU>), grid, blk, 0, st, a); break;
+  }
+}
+
+int launch_quant16_up(const GemmArgs& g, int act, const SkinnyQ& q8, int n8, const SkinnyQ& q3, int n3, hipStream_t st) {
+  if (n8 + n3 <= 0) return 0;
+  const bool glu = act == ACT_GLU;
+  if (g.M <= 0 || !quant16_fits(g.M, g.K) || (g.K & 127) || (n8 & 63) || (n3 & 63)) return -1;
+  Q16UpArgs a = {};
+  a.X = g.A; a.lda = g.lda; a.M = g.M; a.G = g.K / 128;
+  a.codes[0] = (const char*)q8.codes; a.codes[1] = (const char*)q3.codes;
+  a.scales[0] = (const uint16_t*)q8.scales; a.scales[1] = (const uint16_t*)q3.scales;
+  a.units8 = n8 / 32; a.units3 = n3 / 32; a.rb3 = n8 / 32;
+  // one pair of 8-bit pieces a workgroup (they are 2.7 times as long); the 3-bit ones share what is left of one
+  // round of the machine
+  a.wgs3 = a.units3 < 1 ? 0 : a.units8 < 192 ? (a.units3 < 256 - a.units8 ? a.units3 : 256 - a.units8) : (a.units3 < 256 ? a.units3 : 256);
+  fill_reduce_args(a.e, g, act);
+  a.e.f16_out = 1;
+  if (glu) launch_q16_up<true>(a, st);
+  else launch_q16_up<false>(a, st);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_quant16_down(const GemmArgs& g, const SkinnyQ& q8, const SkinnyQ& q3, hipStream_t st) {
+  if (g.M <= 0 || g.M > 16 || (g.N & 127) || !g.a_tiled || (q8.Kp & 63) || (q3.Kp & 63)) return -1;
+  Q16DownArgs a = {};
+  a.H = g.A;
+  a.codes[0] = (const char*)q8.codes; a.codes[1] = (const char*)q3.codes;
+  a.scales[0] = (const uint16_t*)q8.scales; a.scales[1] = (const uint16_t*)q3.scales;
+  a.Kp[0] = q8.Kp; a.Kp[1] = q3.Kp;
+  fill_reduce_args(a.e, g, ACT_NONE);
+  hipLaunchKernelGGL(quant16_down_kernel, dim3(g.N / 16), dim3(Q16_NW * 64), 0, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -1,0 +1,36 @@
+"""8-bit heavy / 3-bit remainder with at most 16 tokens (one launch per product): group counts on every side of the
+eight wavefronts, odd numbers of 64-neuron blocks, either part empty, the sizes where the kernels change."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from gpu_util import assert_close, desc_for, dev, guarded_forward, host, layer_to_dev
+from oracle import ffsplit_oracle as orc
+from workloads.configs import C2, C4, reduced
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(C4, 128, 130, 10), (C4, 384, 500, 100), (C4, 1024, 320, 0), (C4, 1152, 300, 300), (C4, 2176, 200, 64),
+         (C2, 128, 96, 30), (C2, 896, 700, 129), (C2, 2048, 260, 60), (C4, 4096, 200, 70), (C4, 4224, 150, 20)]
+
+
+@pytest.mark.parametrize("base,d,n,k", CASES, ids=[f"{c[0].act}_d{c[1]}_n{c[2]}_k{c[3]}" for c in CASES])
+def test_up_to_16_tokens(base, d, n, k):
+    import paper_2401_04044_amd as ff
+    cfg = reduced(base, d, n)
+    L = wl.make_layer(cfg)
+    idx = np.random.default_rng(d).permutation(n)[:k].astype(np.int32)
+    Ld = layer_to_dev(L, cfg.dtype)
+    desc = desc_for(ff, cfg, "w3h8", k=k)
+    split = ff.build_split(desc, Ld["W1"], Ld["Wg"], Ld["W2"], torch.from_numpy(idx).cuda())
+    for T in (1, 15, 16, 17):
+        X = wl.make_tokens(cfg, T)
+        got = guarded_forward(ff, desc, split, dev(X, cfg.dtype), want_parts=True)
+        torch.cuda.synchronize()
+        want = orc.forward_split(X, L["W1"], L["W2"], L["Wg"], idx, cfg.act, "w3h8", group=128)
+        for g, w, nm in zip(got, want, ("Y", "Y_heavy", "Y_rem")):
+            if np.linalg.norm(w) == 0:
+                assert not host(g).any()
+            else:
+                assert_close(host(g), w, "bf16", f"d{d} n{n} k{k} T={T} {nm}")
