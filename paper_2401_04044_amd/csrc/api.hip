@@ -67,26 +67,34 @@ static int forward_chain(const ffsplit_desc_t* d, const Layout& L, const FwdWs& 
   bool first = true;   // the first product zeroes the arrival counters of those after it
   auto run = [&](GemmArgs& g, int a) -> int {
     g.m_pad = w.t_pad;
-    if (!bf16) return launch_gemm_f32(g, a, false, st);
-    if (small_m && (g.N & 31) == 0) {
-      unsigned* cnt = (unsigned*)(ws + w.off_cnt);
-      const bool clear = first;
-      first = false;
-      return launch_skinny_bf16(g, a, (float*)(ws + w.off_kpart), cnt, clear ? w.n_cnt : 0, st);
+    unsigned* cnt = (unsigned*)(ws + w.off_cnt);
+    float* part = (float*)(ws + w.off_kpart);
+    const bool clear = first;
+    first = false;
+    if (small_m && (g.N & 31) == 0) return launch_skinny_bf16(g, a, part, cnt, clear ? w.n_cnt : 0, st);
+    if (clear) { g.clear = cnt; g.n_clear = w.n_cnt; }
+    // un-activated products behind the first may add the ranges of their reduction inside the launch
+    const bool fix = !clear && a == ACT_NONE && w.n_cnt >= FIX_COUNTERS;
+    if (!bf16) {
+      if (fix) { g.fix_part = part; g.fix_cnt = cnt; }
+      return launch_gemm_f32(g, a, false, st);
     }
     const bool dual = g.A1 != nullptr;
     const bool paired = a == ACT_GLU;
-    GemmPlan plan = gemm_plan(M, g.N, g.K, paired, dual, g.a_tiled != 0, !dual);
-    const int ldp = round_up(g.N, 32);
+    GemmPlan plan = gemm_plan(M, g.N, g.K, paired, dual, g.a_tiled != 0, !dual, fix && g.a_tiled != 0);
     // (never beyond the scratch the workspace was sized with: the plain launch is always valid; the
     // separate halves Y_heavy and Y_rem have reductions of their own)
-    if (plan.split > 1 && gemm_part_bytes(M, g.N, plan.split) > w.kpart_bytes)
+    if (plan.split > 1 && (plan.fix ? gemm_fix_bytes(M, g.N, plan.split) : gemm_part_bytes(M, g.N, plan.split)) > w.kpart_bytes)
       plan = gemm_plan(M, g.N, g.K, paired, dual, g.a_tiled != 0, false);
+    if (plan.fix) {
+      g.fix_part = part; g.fix_cnt = cnt; g.fix_split = plan.split;
+      return launch_gemm_bf16(g, a, false, plan.shape, plan.split, st);
+    }
     if (plan.split > 1) {
-      float* part = (float*)(ws + w.off_kpart);
+      const int ldp = round_up(g.N, 32);
       GemmArgs gp = g;
       gp.partial = 1; gp.C0 = part; gp.ldc0 = ldp; gp.split_col = ldp; gp.act_cols = 0;
-      gp.c0_tiled = 0; gp.c1_tiled = 0;
+      gp.c0_tiled = 0; gp.c1_tiled = 0; gp.n_clear = 0;
       gp.bias = nullptr; gp.bias_cols = 0; gp.resid = nullptr; gp.out_f32 = 0;   // applied with the sum
       if (launch_gemm_bf16(gp, ACT_NONE, false, plan.shape, plan.split, st) != 0) return -1;
       return launch_splitk_epilogue(part, plan.split, ldp, g, a, st);

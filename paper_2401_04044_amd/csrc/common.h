@@ -107,6 +107,15 @@ struct GemmArgs {
   const float* resid;
   int64_t ldr;
   int out_f32;
+  // A reduction cut into fix_split ranges (gridDim.y) that the last workgroup of a tile to arrive adds up, in
+  // range order, before the ordinary epilogue: fix_part holds every range's accumulators, fix_cnt one counter
+  // per tile (zero before the launch and left zero).  Un-activated products; bf16: tiled left operand.
+  float* fix_part;
+  unsigned* fix_cnt;
+  int fix_split;
+  // this launch zeroes clear[0 .. n_clear) (the counters of the launches behind it)
+  unsigned* clear;
+  int n_clear;
   // score mode: per-row-tile partial column sums of h^2 and |h|
   float* part_s2;  // [tiles_m, n_out]
   float* part_s1;
@@ -123,13 +132,16 @@ struct Epilogue {
   int out_f32;
 };
 
-// K, lda, ldb, split_col multiples of 4
+// K, lda, ldb, split_col multiples of 4; with fix_part (gemm_f32_part_bytes() bytes) and fix_cnt an un-activated
+// product of few tiles cuts its reduction by itself
+size_t gemm_f32_part_bytes();
 int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st);
 // shape: one of gemm_plan.h.
 // n_split > 1 only with a.partial
 int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_split, hipStream_t st);
 // gated product with two left operands on 256 x 256 tiles (gemm_dual.hip); everything tiled
 int launch_gemm_dual(const GemmArgs& a, hipStream_t st);
+constexpr int FIX_COUNTERS = 256;   // tiles of a product whose ranges are added by the last to arrive
 // sum of the fp32 partials [n_split][a.M][ldp] of a whole product (written with a.partial, no
 // activation, GEMM column order) + the store epilogue described by a (activation act)
 int launch_splitk_epilogue(const float* part, int n_split, int ldp, const GemmArgs& a, int act, hipStream_t st);

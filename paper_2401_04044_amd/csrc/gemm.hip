@@ -19,7 +19,8 @@
 // A workgroup is WGM x WGN wavefronts per k group and KW k groups, which take every KW-th slab and
 // add their accumulators through LDS in a fixed order: products of a hundred tokens are bound by
 // the latency of their chain of slabs, and this shortens it without partial sums in memory or a
-// second launch.  (BERT-base layer, 128 tokens: six launches with split reductions took 63 us.)
+// second launch.  (BERT-base layer, 128 tokens: six launches with split reductions took 63 us, four 26.6, with short
+// and long reductions on tiles and ranges of their own 20.6.)
 #include "common.h"
 #include <algorithm>
 
@@ -37,7 +38,10 @@ __device__ __forceinline__ f32x4_t buffer_f32x4(const float* base, uint32_t lane
   return f;
 }
 
-template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE>
+// FIX: the reduction is cut into gridDim.y ranges, added in range order by the last workgroup of a tile to
+// arrive (one wavefront a tile: its store, its arrival and its reads are in order by themselves).
+constexpr int F32_MAX_SPLIT = 8;
+template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE, bool FIX>
 __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmArgs p) {
   constexpr int BM = WGM * TM * 16, BN = WGN * TN * 16;
   constexpr int NA = DUAL ? 2 : 1;
@@ -47,6 +51,9 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kw = wave / (WGM * WGN), wt = wave % (WGM * WGN), wm = wt / WGN, wn = wt % WGN;
+  static_assert(!FIX || (TM * TN * WGM * WGN == 1 && KW > 1 && ACT == ACT_NONE && !SCORE), "");
+  if (!FIX && blockIdx.x == 0)
+    for (int i = tid; i < p.n_clear; i += WGM * WGN * KW * 64) p.clear[i] = 0u;
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
   const int m0 = tm * BM + wm * TM * 16, n0 = tn * BN + wn * TN * 16;   // the wavefront's corner
@@ -72,13 +79,16 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int slabs = (p.K + 15) / 16;
+  const int all = (p.K + 15) / 16;
+  const int base = FIX ? (int)((int64_t)all * blockIdx.y / gridDim.y) : 0;
+  const int slabs = (FIX ? (int)((int64_t)all * (blockIdx.y + 1) / gridDim.y) : all) - base;
+  const int k_end = FIX ? min(p.K, (base + slabs) * 16) : p.K;
   const int n = (slabs - kw + KW - 1) / KW;   // this k group's slabs: kw, kw + KW, ...
   f32x4_t ga[PF][NA][TM], gb[PF][TN];   // in flight, as loaded
   f32x4_t fa[2][NA][TM], fb[2][TN];     // the slab being multiplied and the next one
   auto load = [&](int slot, int i) {
-    const int k0 = (kw + i * KW) * 16;
-    const bool ok = k0 + 4 * (lane & 3) < p.K;   // (K is a multiple of 4: whole chunks)
+    const int k0 = (base + kw + i * KW) * 16;
+    const bool ok = k0 + 4 * (lane & 3) < k_end;   // (K is a multiple of 4: whole chunks)
 #pragma unroll
     for (int t = 0; t < TM; ++t) {
       ga[slot][0][t] = buffer_f32x4(a_base, ok ? a_off[t] : ~0u, k0 * 4);
@@ -167,6 +177,32 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
         for (int b = 0; b < TN; ++b) acc[a][b] = sm[(wt * TM * TN + a * TN + b) * 64 + lane];
     }
   }
+  if constexpr (FIX) {
+    unsigned long long* q = (unsigned long long*)p.fix_part + ((int64_t)blockIdx.x * gridDim.y * 64 + lane) * 2;
+    auto bits = [](float a, float b) { return (unsigned long long)__float_as_uint(a) | ((unsigned long long)__float_as_uint(b) << 32); };
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      __hip_atomic_store(q + (int64_t)blockIdx.y * 128 + h, bits(acc[0][0][2 * h], acc[0][0][2 * h + 1]), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    unsigned before = 0;
+    if (lane == 0) before = __hip_atomic_fetch_add(p.fix_cnt + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(before) != gridDim.y - 1) return;
+    if (lane == 0) __hip_atomic_store(p.fix_cnt + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long v[F32_MAX_SPLIT][2];
+#pragma unroll
+    for (int s = 0; s < F32_MAX_SPLIT; ++s)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        v[s][h] = __hip_atomic_load(q + (int64_t)min(s, (int)gridDim.y - 1) * 128 + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    f32x4_t t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < F32_MAX_SPLIT; ++s)
+      if (s < (int)gridDim.y)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] += __uint_as_float((unsigned)(v[s][e >> 1] >> (32 * (e & 1))));
+    acc[0][0] = t;
+  }
 
   if (!SCORE) {
     // lane: row r16, columns 4 quad + 0..3 of each 16x16 tile
@@ -254,7 +290,7 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
 
 // ------------------------------------------------------------------ host launchers
 
-template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE>
+template <int TM, int TN, int WGM, int WGN, int KW, int PF, int ACT, bool DUAL, bool SCORE, bool FIX = false>
 static int launch_f32(const GemmArgs& a, hipStream_t st) {
   constexpr int BM = WGM * TM * 16, BN = WGN * TN * 16;
   constexpr size_t waves = WGM * WGN * KW;
@@ -262,7 +298,7 @@ static int launch_f32(const GemmArgs& a, hipStream_t st) {
                                   std::max(KW > 1 ? waves * TM * TN * 1024 : (size_t)0, (size_t)(SCORE ? WGM * BN * 8 : 0)));
   static_assert(lds <= 64 * 1024, "within the default limit of dynamic LDS");
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, WGM, WGN, KW, PF, ACT, DUAL, SCORE>), dim3(tiles),
+  hipLaunchKernelGGL((gemm_f32_kernel<TM, TN, WGM, WGN, KW, PF, ACT, DUAL, SCORE, FIX>), dim3(tiles, FIX ? a.fix_split : 1),
                      dim3(WGM * WGN * KW * 64), lds, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -296,7 +332,23 @@ static int launch_f32_act(const GemmArgs& a, hipStream_t st) {
   } else {
     // (128 x 128 on four wavefronts was slower everywhere: one wavefront per SIMD shows every wait)
     static const F32Shape c[] = {{64, 64, 2, 2}, {32, 32, 1, 1}, {16, 32, 1, 1}, {16, 16, 1, 1}};
-    switch (pick_f32(c, a.M, a.N, a.K)) {
+    const int pick = pick_f32(c, a.M, a.N, a.K);
+    // A short reduction has no k groups to share, and a 64x64 tile leaves its erf to few wavefronts (128 x 2944 x 64:
+    // 8.5 us, 4.7 on 32x32 tiles).  Not where the tiles fill the machine (512 x 3072 x 64: 36.4 and more).
+    if (pick == 0 && a.K <= 128 && (a.M + 63) / 64 * ((a.N + 63) / 64) <= 256)
+      return launch_f32<1, 1, 2, 2, 1, 4, ACT, DUAL, false>(a, st);
+    if constexpr (ACT == ACT_NONE) {
+      // few 16x16 tiles and a long reduction: ranges of at least 32 slabs on the idle CUs (a BERT-base-sized layer of
+      // 128 tokens, 32 tiles: 23.5 -> 20.6 us; 1024 wide, 16 tokens 26.1 -> 21.2)
+      const int tiles = (a.M + 15) / 16 * ((a.N + 15) / 16);
+      const int s = std::min({F32_MAX_SPLIT, 256 / tiles, (a.K + 15) / 16 / 32});
+      if (pick == 3 && a.fix_cnt != nullptr && s > 1) {
+        GemmArgs g = a;
+        g.fix_split = s;
+        return launch_f32<1, 1, 1, 1, 16, 4, ACT, DUAL, false, true>(g, st);
+      }
+    }
+    switch (pick) {
       case 0: return launch_f32<2, 2, 2, 2, 2, 4, ACT, DUAL, false>(a, st);
       case 1: return launch_f32<2, 2, 1, 1, 8, 4, ACT, DUAL, false>(a, st);
       case 2: return launch_f32<1, 2, 1, 1, 8, 4, ACT, DUAL, false>(a, st);
@@ -304,6 +356,8 @@ static int launch_f32_act(const GemmArgs& a, hipStream_t st) {
     }
   }
 }
+
+size_t gemm_f32_part_bytes() { return (size_t)256 * 1024; }   // 256 workgroups, one KiB each
 
 int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return 0;

@@ -245,8 +245,48 @@ __device__ __forceinline__ void wait_lgkmcnt() {
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
 #define FFS_ORDER __builtin_amdgcn_sched_barrier(0)   // instructions keep the written order
 
+// The accumulators of a tile's ranges (blockIdx.y) added by the last workgroup to arrive, which gets them in
+// acc and true; the others are done.  The XCDs' L2 caches are not coherent within a launch: device-scope
+// stores and loads.  Every thread waits for its own stores before the barrier, and only behind it is the
+// workgroup counted in, so that the last one finds every range in place.  All ranges come from memory, its own
+// too, in one round trip, and are added in range order: the result does not depend on the order of arrival.
+constexpr int DEV_SCOPE = 16;   // sc1
+template <int NT, int NR>
+__device__ __forceinline__ bool last_range(const GemmArgs& p, f32x4_t* acc, int tile, int tid, int* flag) {
+  const int n = p.fix_split;
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((char*)p.fix_part + (int64_t)tile * n * NR * NT * 16, 0,
+                                                                     n * NR * NT * 16, 0x00027000);
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i]), r, tid * 16, ((int)blockIdx.y * NR + i) * (NT * 16),
+                                           DEV_SCOPE);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    const bool last = __hip_atomic_fetch_add(p.fix_cnt + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(n - 1);
+    if (last) __hip_atomic_store(p.fix_cnt + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = last;
+  }
+  __syncthreads();
+  if (!*flag) return false;
+  u32x4_t v[GEMM_FIX_MAX_SPLIT][NR];
+#pragma unroll
+  for (int s = 0; s < GEMM_FIX_MAX_SPLIT; ++s)
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      v[s][i] = __builtin_amdgcn_raw_buffer_load_b128(r, tid * 16, ((s < n ? s : n - 1) * NR + i) * (NT * 16), DEV_SCOPE);
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    acc[i] = __builtin_bit_cast(f32x4_t, v[0][i]);
+#pragma unroll
+    for (int s = 1; s < GEMM_FIX_MAX_SPLIT; ++s)
+      if (s < n) acc[i] += __builtin_bit_cast(f32x4_t, v[s][i]);
+  }
+  return true;
+}
+
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA, int ACT, bool DUAL, bool SCORE, bool A_TILED,
-          bool EPI>
+          bool EPI, bool FIX>
 __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm_bf16_dl_kernel(const GemmArgs p) {
   constexpr int NW = WGM * WGN;
@@ -266,11 +306,15 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
   static_assert(ACT != ACT_GLU || WN % 64 == 0, "(gate, up) pairs must lie inside one wavefront");
   static_assert(TM % 2 == 0 && (!DUAL || A_TILED), "row tiles are stored in pairs; two left operands are tiled");
 
+  static_assert(!FIX || (ACT == ACT_NONE && A_TILED && !DUAL && !SCORE), "");
+
   extern __shared__ u32x4_t smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
+  if (!A_TILED && blockIdx.x == 0)
+    for (int i = tid; i < p.n_clear; i += NW * 64) p.clear[i] = 0u;
   const int tiles_n = (p.N + BN - 1) / BN;
   const int tiles_m = (p.M + BM - 1) / BM;
   const int logical = xcd_remap(blockIdx.x, tiles_m * tiles_n);
@@ -354,7 +398,7 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
   // one dependent round trip per tile between the last product and the stores.  This workgroup
   // alone reads and later writes these elements, so the destination may be the residual buffer.
   if (EPI && ACT == ACT_NONE && !SCORE) {
-    if (p.resid != nullptr && !p.partial && !p.c0_tiled) {
+    if (p.resid != nullptr && !p.partial && !p.c0_tiled && (!FIX || blockIdx.y == 0)) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int cb = n0 + wn * WN + j * 16;
@@ -507,6 +551,9 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
     wait_lgkmcnt<0>();
     lds_barrier();   // the epilogue reuses the stage memory
   }
+  if constexpr (FIX) {
+    if (!last_range<NW * 64, TM * TN>(p, &acc[0][0], logical, tid, (int*)smem)) return;
+  }
   gemm_epilogue<BM, BN, WGM, WGN, ACT, SCORE, EPI>(p, acc, m0, n0, tm, wm, wn, lane, tid, smem);
 }
 
@@ -528,9 +575,13 @@ struct SplitEpiArgs {
   const float* resid;
   int64_t ldr;
   int out_f32;
+  unsigned* clear;
+  int n_clear;
 };
 
 __global__ void __launch_bounds__(256) splitk_epilogue_kernel(const SplitEpiArgs p) {
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < p.n_clear; i += 256) p.clear[i] = 0u;
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int cpr = p.n_out / 8;
   if (id >= (int64_t)p.rows * cpr) return;
@@ -600,6 +651,7 @@ int launch_splitk_epilogue(const float* part, int n_split, int ldp, const GemmAr
   a.C0 = g.C0; a.C1 = g.C1; a.ldc0 = g.ldc0; a.ldc1 = g.ldc1;
   a.c0_tiled = g.c0_tiled; a.c1_tiled = g.c1_tiled; a.n_store = g.n_store;
   a.bias = g.bias; a.bias_cols = g.bias_cols; a.resid = g.resid; a.ldr = g.ldr; a.out_f32 = g.out_f32;
+  a.clear = g.clear; a.n_clear = g.n_clear;
   if ((a.n_out & 7) || (g.split_col & 7) || (g.act_cols & 63)) return -1;
   const int64_t n = (int64_t)a.rows * (a.n_out / 8);
   if (n <= 0) return 0;
@@ -610,12 +662,12 @@ int launch_splitk_epilogue(const float* part, int n_split, int ldp, const GemmAr
 // ------------------------------------------------------------------ host launcher
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA, int ACT, bool DUAL, bool SCORE, bool A_TILED,
-          bool EPI>
+          bool EPI, bool FIX>
 static int launch_dl_epi(const GemmArgs& a, int n_split, hipStream_t st) {
   constexpr int NWH = WGM * WGN;
   constexpr size_t lds = (size_t)STAGES * 1024 * ((DUAL ? 2 : 1) * (BM / 16) + (BN / 16 + NWH - 1) / NWH * NWH);
   static_assert(lds <= 160 * 1024, "LDS budget of a CU");
-  auto kern = gemm_bf16_dl_kernel<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, EPI>;
+  auto kern = gemm_bf16_dl_kernel<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, EPI, FIX>;
   // The kernel needs more dynamic LDS than the default limit: the attribute is set once per
   // device and instantiation.  The only state kept is this set-once bit mask (one bit per
   // device ordinal); setting the attribute twice from racing first calls is harmless.
@@ -646,13 +698,21 @@ static int launch_dl_epi(const GemmArgs& a, int n_split, hipStream_t st) {
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA, int ACT, bool DUAL, bool SCORE, bool A_TILED>
 static int launch_dl_cfg(const GemmArgs& a, int n_split, hipStream_t st) {
   // (the calibration product, the gated products and the two-operand product take no additions)
-  if constexpr (!SCORE && !DUAL && ACT != ACT_GLU) {
-    if (a.bias != nullptr || a.resid != nullptr || a.out_f32)
-      return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true>(a, n_split, st);
-  } else {
-    if (a.bias != nullptr || a.resid != nullptr || a.out_f32) return -1;
+  const bool adds = a.bias != nullptr || a.resid != nullptr || a.out_f32;
+  if constexpr (ACT == ACT_NONE && A_TILED && !DUAL && !SCORE && BM == 64 && BN == 64) {
+    if (a.fix_split > 1) {
+      if (a.partial || a.fix_split != n_split || a.fix_split > GEMM_FIX_MAX_SPLIT) return -1;
+      return adds ? launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true, true>(a, n_split, st)
+                  : launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false, true>(a, n_split, st);
+    }
   }
-  return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false>(a, n_split, st);
+  if (a.fix_split > 1) return -1;
+  if constexpr (!SCORE && !DUAL && ACT != ACT_GLU) {
+    if (adds) return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true, false>(a, n_split, st);
+  } else {
+    if (adds) return -1;
+  }
+  return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false, false>(a, n_split, st);
 }
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA>

@@ -962,16 +962,22 @@ FwdWs make_fwd_ws(const ffsplit_desc_t& d, const Layout& L, int64_t T) {
   w.off_t = off; off = align256(off + (size_t)w.t_pad * L.n_up * L.rp * L.esz);
   w.off_h2 = off; off = align256(off + (size_t)w.t_pad * L.mp * L.esz);
   w.off_cnt = w.off_kpart = off;
+  if (!L.tiled && T > 0) {
+    w.n_cnt = FIX_COUNTERS;
+    w.off_kpart = align256(off + (size_t)w.n_cnt * 4);
+    w.kpart_bytes = gemm_f32_part_bytes();
+    off = align256(w.off_kpart + w.kpart_bytes);
+  }
   if (L.tiled && T > 0) {
     // What follows does not shrink as T grows, so that a buffer sized for a batch serves every smaller one.
-    w.n_cnt = SKINNY_COUNTERS;
+    w.n_cnt = T > SKINNY_MAX_M ? FIX_COUNTERS : SKINNY_COUNTERS;
     w.off_kpart = align256(off + (size_t)w.n_cnt * 4);
     // partial sums: at most SKINNY_MAX_M tokens take the weight-streaming kernels ...
     w.kpart_bytes = skinny_part_bytes((int)std::min<int64_t>(T, SKINNY_MAX_M));
     if (T > SKINNY_MAX_M) {
       // ... more of them the tiled ones, whose reductions may be split
       const bool glu = L.n_up == 2, lr = L.rp > 0 && L.mp > 0;
-      const size_t b[4] = {gemm_part_room(T, L.n1, d.d_model, glu, false),
+      const size_t b[] = {gemm_part_room(T, L.n1, d.d_model, glu, false),
                            lr && !glu ? gemm_part_room(T, L.mp, L.rp, false, true) : 0,   // (two left operands: never)
                            lr ? gemm_part_room(T, L.rp, L.mp, false, true) : 0,
                            gemm_part_room(T, d.d_model, L.k4, false, true)};
