@@ -113,6 +113,9 @@ struct GemmArgs {
   float* fix_part;
   unsigned* fix_cnt;
   int fix_split;
+  // bf16, tiled left operand, un-activated: the left operand starts again after each a_wrap columns of K (a multiple
+  // of 32; 0: it has K columns), up to three times
+  int a_wrap;
   // this launch zeroes clear[0 .. n_clear) (the counters of the launches behind it)
   unsigned* clear;
   int n_clear;

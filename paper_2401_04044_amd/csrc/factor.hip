@@ -85,14 +85,26 @@ __global__ void __launch_bounds__(256) gather_tiled_kernel(const uint16_t* src, 
   constexpr int LD = 72;
   __shared__ __align__(16) uint16_t tile[32 * LD];
   const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 64, t = threadIdx.x, l = t & 63;
+  if (by_rows) {   // (lds a multiple of 8: 16 bytes a thread, 26 -> 12 us for 7946 x 2048)
+    const int r = r0 + (t >> 3), c = c0 + (t & 7) * 8;
+    uint4 w = make_uint4(0, 0, 0, 0);
+    if (r < rows && c < cols) w = *(const uint4*)(src + (int64_t)rest[r] * lds + c);
+    *(uint4*)(tile + (t >> 3) * LD + (t & 7) * 8) = w;
+    __syncthreads();
+    const int row = t & 31, c8 = (t >> 5) * 8;
+    if (c0 + c8 >= cols_pad) return;
+    *(uint4*)(dst + (((int64_t)blockIdx.y * (cols_pad / 16) + (c0 + c8) / 16) * 64 + ((c8 >> 3) & 1) * 32 + row) * 8) =
+        *(const uint4*)(tile + row * LD + c8);
+    return;
+  }
   const int c = c0 + l;
-  const int64_t sc = c < cols ? (by_rows ? c : rest[c]) : -1;
+  const int64_t sc = c < cols ? rest[c] : -1;
   uint16_t v[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int r = r0 + i * 4 + (t >> 6);
     v[i] = 0;
-    if (r < rows && sc >= 0) v[i] = src[(int64_t)(by_rows ? rest[r] : r) * lds + sc];
+    if (r < rows && sc >= 0) v[i] = src[(int64_t)r * lds + sc];
   }
 #pragma unroll
   for (int i = 0; i < 8; ++i) tile[(i * 4 + (t >> 6)) * LD + l] = v[i];
@@ -104,10 +116,10 @@ __global__ void __launch_bounds__(256) gather_tiled_kernel(const uint16_t* src, 
 }
 
 // X [r8, ldx] fp32 (row r and beyond zero; in the copy that the state names) -> three bf16 terms whose sum is X to
-// the last bit of fp32 (each takes the leading 8 bits of what is left), tiled [r32, dk] each
+// the last bit of fp32 (each takes the leading 8 bits of what is left), side by side in one tiled matrix
+// [r32, 3 dk], the smallest first
 __global__ void __launch_bounds__(256) split_terms_kernel(const float* X, const PolarState* state, int64_t flip, int64_t ldx,
-                                                          int r8, int d, int r32, int dk, uint16_t* hi, uint16_t* mid,
-                                                          uint16_t* lo) {
+                                                          int r8, int d, int r32, int dk, uint16_t* terms) {
   X += state->parity * flip;
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;   // one 16-byte chunk of each term
   const int kbs = dk / 16;
@@ -125,9 +137,9 @@ __global__ void __launch_bounds__(256) split_terms_kernel(const float* X, const 
       w[t][e >> 1] = (e & 1) ? (w[t][e >> 1] | (b << 16)) : b;
     }
   }
-  *(uint4*)(hi + id * 8) = make_uint4(w[0][0], w[0][1], w[0][2], w[0][3]);
-  *(uint4*)(mid + id * 8) = make_uint4(w[1][0], w[1][1], w[1][2], w[1][3]);
-  *(uint4*)(lo + id * 8) = make_uint4(w[2][0], w[2][1], w[2][2], w[2][3]);
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+    *(uint4*)(terms + (((int64_t)rb * 3 * kbs + (2 - t) * kbs + kb) * 64 + lane) * 8) = make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]);
 }
 
 // sum of squares in two fixed-order stages: 256 block partials, then one block (blockIdx.y: matrix)
@@ -207,7 +219,7 @@ struct FactorWs {
   int mats, m4, r8, r32, mk, dk;
   size_t off_z, off_zt, off_om, off_part, off_terms, off_xt, off_c, off_red, off_polar, total;
   PolarWs polar;
-  size_t part_bytes, term_bytes;
+  size_t part_bytes;
 };
 
 FactorWs make_factor_ws(const ffsplit_desc_t& d) {
@@ -229,8 +241,7 @@ FactorWs make_factor_ws(const ffsplit_desc_t& d) {
     const GemmPlan p = gemm_plan(dm, w.r8, m, false, false, true, true);
     w.part_bytes = p.split > 1 ? (size_t)p.split * dm * w.r32 * 4 : 0;
     w.off_part = take(w.part_bytes);
-    w.term_bytes = align256((size_t)w.r32 * w.dk * 2);
-    w.off_terms = take(3 * w.term_bytes);
+    w.off_terms = take((size_t)w.r32 * 3 * w.dk * 2);
     w.off_c = take((size_t)m * w.r8 * 4);   // (B^T Z)^T
   } else {
     w.off_z = take((size_t)dm * w.m4 * 4);
@@ -359,14 +370,13 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
       char* term = ws + w.off_terms;
       const int64_t chunks = (int64_t)(w.r32 / 32) * (w.dk / 16) * 64;
       hipLaunchKernelGGL(split_terms_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st, Xi, si, flip,
-                         (int64_t)pw.dk, r8, dm, w.r32, w.dk, (uint16_t*)term, (uint16_t*)(term + w.term_bytes), (uint16_t*)(term + 2 * w.term_bytes));
+                         (int64_t)pw.dk, r8, dm, w.r32, w.dk, (uint16_t*)term);
       FKL();
-      for (int t = 2; t >= 0; --t) {   // smallest term first
-        GemmArgs g = gemm_nt(Z, w.dk, term + t * w.term_bytes, w.dk, m, r8, dm, C, r8);
-        g.a_tiled = 1; g.out_f32 = 1;
-        if (t < 2) { g.resid = C; g.ldr = r8; }
-        FK(launch_gemm_bf16(g, ACT_NONE, false, gemm_plan(m, r8, dm, false, false, true, false).shape, 1, st));
-      }
+      // all three terms in one reduction: three launches that each read back the sums took 73 us, one 53
+      // (7946 x 512 x 2048)
+      GemmArgs g = gemm_nt(Z, w.dk, term, 3 * w.dk, m, r8, 3 * w.dk, C, r8);
+      g.a_tiled = 1; g.out_f32 = 1; g.a_wrap = w.dk;
+      FK(launch_gemm_bf16(g, ACT_NONE, false, gemm_plan(m, r8, 3 * w.dk, false, false, true, false).shape, 1, st));
     } else {
       const unsigned gz = (unsigned)(((int64_t)dm * m4 + 255) / 256);
       hipLaunchKernelGGL(gather_z_kernel, dim3(gz), dim3(256), 0, st, (const float*)Ws[i], dm, d.d_ff, rest, m, m4, (int)down,

@@ -250,6 +250,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "me
 // stores and loads.  Every thread waits for its own stores before the barrier, and only behind it is the
 // workgroup counted in, so that the last one finds every range in place.  All ranges come from memory, its own
 // too, in one round trip, and are added in range order: the result does not depend on the order of arrival.
+enum { MODE_PLAIN = 0, MODE_FIX = 1, MODE_WRAP = 2 };
 constexpr int DEV_SCOPE = 16;   // sc1
 template <int NT, int NR>
 __device__ __forceinline__ bool last_range(const GemmArgs& p, f32x4_t* acc, int tile, int tid, int* flag) {
@@ -286,7 +287,7 @@ __device__ __forceinline__ bool last_range(const GemmArgs& p, f32x4_t* acc, int 
 }
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA, int ACT, bool DUAL, bool SCORE, bool A_TILED,
-          bool EPI, bool FIX>
+          bool EPI, int MODE>
 __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm_bf16_dl_kernel(const GemmArgs p) {
   constexpr int NW = WGM * WGN;
@@ -306,7 +307,8 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
   static_assert(ACT != ACT_GLU || WN % 64 == 0, "(gate, up) pairs must lie inside one wavefront");
   static_assert(TM % 2 == 0 && (!DUAL || A_TILED), "row tiles are stored in pairs; two left operands are tiled");
 
-  static_assert(!FIX || (ACT == ACT_NONE && A_TILED && !DUAL && !SCORE), "");
+  constexpr bool FIX = MODE == MODE_FIX, WRAP = MODE == MODE_WRAP;   // GemmArgs::fix_split, a_wrap
+  static_assert(MODE == MODE_PLAIN || (ACT == ACT_NONE && A_TILED && !DUAL && !SCORE), "");
 
   extern __shared__ u32x4_t smem[];
 
@@ -361,6 +363,7 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
     soff[LA + i] = ((uint32_t)rb * (uint32_t)(p.ldb / 16) + (b & 1)) * 1024;
   }
   const uint32_t lane16 = lane * 16;
+  const int wrap = WRAP ? p.a_wrap / 32 : 0;   // slabs
   auto tile_base = [&](const void* a) {
     return A_TILED ? (const char*)a + ((int64_t)(m0 / 32) * (p.lda / 16) + 2 * kt0) * 1024
                    : (const char*)a + (int64_t)m0 * p.lda * 2;
@@ -378,7 +381,9 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
     } else if (A_TILED) {
       // (with two left operands the first BM / 16 blocks are A's, the others A1's: uniform per i)
       static_assert(!DUAL || (BM / 16) % NW == 0, "a load belongs to one left operand");
-      buffer_to_lds((DUAL && i >= LA / 2) ? base_a1 : base_a, dst, lane16, soff[i] + rel * 2048);
+      int ra = rel;
+      if (WRAP) ra -= rel >= 2 * wrap ? 2 * wrap : rel >= wrap ? wrap : 0;   // (the whole reduction: kt0 = 0)
+      buffer_to_lds((DUAL && i >= LA / 2) ? base_a1 : base_a, dst, lane16, soff[i] + ra * 2048);
     } else if (!check) {
       buffer_to_lds(base_a, dst, a_row[i] + a_col * 2, (kt0 + rel) * 64);
     } else {
@@ -662,12 +667,12 @@ int launch_splitk_epilogue(const float* part, int n_split, int ldp, const GemmAr
 // ------------------------------------------------------------------ host launcher
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA, int ACT, bool DUAL, bool SCORE, bool A_TILED,
-          bool EPI, bool FIX>
+          bool EPI, int MODE>
 static int launch_dl_epi(const GemmArgs& a, int n_split, hipStream_t st) {
   constexpr int NWH = WGM * WGN;
   constexpr size_t lds = (size_t)STAGES * 1024 * ((DUAL ? 2 : 1) * (BM / 16) + (BN / 16 + NWH - 1) / NWH * NWH);
   static_assert(lds <= 160 * 1024, "LDS budget of a CU");
-  auto kern = gemm_bf16_dl_kernel<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, EPI, FIX>;
+  auto kern = gemm_bf16_dl_kernel<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, EPI, MODE>;
   // The kernel needs more dynamic LDS than the default limit: the attribute is set once per
   // device and instantiation.  The only state kept is this set-once bit mask (one bit per
   // device ordinal); setting the attribute twice from racing first calls is harmless.
@@ -702,17 +707,24 @@ static int launch_dl_cfg(const GemmArgs& a, int n_split, hipStream_t st) {
   if constexpr (ACT == ACT_NONE && A_TILED && !DUAL && !SCORE && BM == 64 && BN == 64) {
     if (a.fix_split > 1) {
       if (a.partial || a.fix_split != n_split || a.fix_split > GEMM_FIX_MAX_SPLIT) return -1;
-      return adds ? launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true, true>(a, n_split, st)
-                  : launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false, true>(a, n_split, st);
+      return adds ? launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true, MODE_FIX>(a, n_split, st)
+                  : launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false, MODE_FIX>(a, n_split, st);
     }
   }
   if (a.fix_split > 1) return -1;
+  if constexpr (ACT == ACT_NONE && A_TILED && !DUAL && !SCORE) {
+    if (a.a_wrap > 0) {
+      if (n_split != 1 || (a.a_wrap & 31) || a.K > 3 * a.a_wrap) return -1;
+      return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true, MODE_WRAP>(a, 1, st);
+    }
+  }
+  if (a.a_wrap > 0) return -1;
   if constexpr (!SCORE && !DUAL && ACT != ACT_GLU) {
-    if (adds) return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true, false>(a, n_split, st);
+    if (adds) return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true, MODE_PLAIN>(a, n_split, st);
   } else {
     if (adds) return -1;
   }
-  return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false, false>(a, n_split, st);
+  return launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false, MODE_PLAIN>(a, n_split, st);
 }
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool DBLA>

@@ -8,7 +8,7 @@
 // product (polar_launched); the steps after those, which flat and mildly decaying spectra do not need, are one
 // launch of a work queue that returns at once when nothing is left.  (A launch that does nothing costs 3.5 us:
 // three for every step of the worst sketch of rank 512 were 115 us of 816.)  Measured, us, a layer compressed and
-// tried (two matrices): 2048 x 7946 rank 512 1235 -> 715, 1536 x 4800 rank 400 gated 1130 -> 655, 512 x 1450 rank 64 276 -> 240.
+// tried (two matrices): 2048 x 7946 rank 512 1235 -> 715, 1536 x 4800 rank 400 gated 1130 -> 655, 512 x 1450 rank 64 276 -> 240 (with the projections in one launch each 657, 607, 222).
 // Factorisation alone at 2048 x 7946 with singular values i^-a: a = 0 1140 -> 620, 1/2 1140 -> 720, 1 1140 -> 950;
 // the other way round where the queue does most of the steps: a = 2 1620, rank one 1990.
 // All products are true fp32 (v_mfma_f32_16x16x4_f32, 256 flop per clock and CU), staged through LDS by loads

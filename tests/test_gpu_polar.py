@@ -42,3 +42,19 @@ def test_factors_of_decaying_remainders(ff, cfg, decay):
     for p, q in (("P1", "Q1"), ("Pg", "Qg"), ("P2", "Q2")):
         if p in want:
             assert relf(got[p] @ got[q], want[p] @ want[q]) < 1e-4, p
+
+
+@pytest.mark.parametrize("cfg", [reduced(C2, 72, 400, rank=8), reduced(C3, 264, 300, rank=130), reduced(C2, 1032, 2100, rank=72), reduced(C2, 2056, 700, rank=250)],
+                         ids=["d72", "d264_gated", "d1032", "d2056"])
+def test_projection_of_three_terms_in_one_reduction(ff, cfg):
+    """bf16 factors at widths that are no multiple of 64 (the left operand of the projection starts again at the
+    padded width): products like the oracle's in fp64 but for two bf16 roundings."""
+    L = wl.make_layer(cfg)
+    idx, Ld = L["planted"], layer_to_dev(L, "bf16")
+    fd = ff.factorize_remainder(desc_for(ff, cfg, "lowrank"), Ld["W1"], Ld["Wg"], Ld["W2"], torch.from_numpy(idx).cuda(), seed=9)
+    torch.cuda.synchronize()
+    got = {k: host(v) for k, v in fd.items() if v is not None}
+    want = orc.factorize_remainder(L["W1"], L["W2"], L["Wg"], idx, cfg.rank, seed=9)
+    for p, q in (("P1", "Q1"), ("Pg", "Qg"), ("P2", "Q2")):
+        if p in want:
+            assert relf(got[p] @ got[q], want[p] @ want[q]) < 6e-3, p
