@@ -80,8 +80,8 @@ __global__ void __launch_bounds__(WGM* WGN* KW * 64) gemm_f32_kernel(const GemmA
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const int all = (p.K + 15) / 16;
-  const int base = FIX ? (int)((int64_t)all * blockIdx.y / gridDim.y) : 0;
-  const int slabs = (FIX ? (int)((int64_t)all * (blockIdx.y + 1) / gridDim.y) : all) - base;
+  const int base = FIX ? (int)((uint32_t)all * blockIdx.y / gridDim.y) : 0;
+  const int slabs = (FIX ? (int)((uint32_t)all * (blockIdx.y + 1) / gridDim.y) : all) - base;
   const int k_end = FIX ? min(p.K, (base + slabs) * 16) : p.K;
   const int n = (slabs - kw + KW - 1) / KW;   // this k group's slabs: kw, kw + KW, ...
   f32x4_t ga[PF][NA][TM], gb[PF][TN];   // in flight, as loaded

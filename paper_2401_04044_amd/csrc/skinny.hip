@@ -474,10 +474,13 @@ __device__ __forceinline__ void rows16_unit(const Rows16Args& p, int unit, int s
                                             const int (&sub)[RB], bool pair, float4* red, int* flag) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   constexpr int NA = DUAL ? 2 : 1;
+  constexpr bool TURN = !A_TILED && TB > 1;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // this workgroup's range, then this wavefront's share of it (may be empty: it then adds zeros)
-  const int w0 = (int)((int64_t)p.steps * sp / p.n_split), wn = (int)((int64_t)p.steps * (sp + 1) / p.n_split) - w0;
+  const uint32_t steps = p.steps, parts = SPLIT ? p.n_split : 1;
+  const int w0 = SPLIT ? (int)(steps * (uint32_t)sp / parts) : 0;
+  const int wn = (SPLIT ? (int)(steps * (uint32_t)(sp + 1) / parts) : p.steps) - w0;
   const int s0 = w0 + wn * wave / NW, s1 = w0 + wn * (wave + 1) / NW;
   const int r = lane & 15, q8 = (lane >> 4) * 8;
 
@@ -493,6 +496,7 @@ __device__ __forceinline__ void rows16_unit(const Rows16Args& p, int unit, int s
   }
   const int k_end = min(p.K, s1 * 32);
   rsrc_t ar[NA][(TB + 1) / 2];   // tiled: one per block of 32 tokens
+  const int ac = TURN ? (lane & 3) * 8 : q8;   // row-major: the lane's chunk of a step
   uint32_t aofs[TB];
 #pragma unroll
   for (int i = 0; i < NA; ++i)
@@ -505,8 +509,15 @@ __device__ __forceinline__ void rows16_unit(const Rows16Args& p, int unit, int s
 #pragma unroll
   for (int t = 0; t < TB; ++t) {
     if (A_TILED) aofs[t] = lofs + (uint32_t)(t & 1) * 256u;
-    else aofs[t] = (uint32_t)(min(t * 16 + r, p.M - 1) * (int)p.lda + q8) * 2u;
+    else aofs[t] = (uint32_t)(min(t * 16 + (TURN ? lane >> 2 : r), p.M - 1) * (int)p.lda + ac) * 2u;
   }
+  // Row-major tokens, more than 16: four neighbouring lanes read 64 bytes of a row (a row per lane, as the MFMA wants
+  // them, comes at 16 bytes a clock instead of 61), and the wavefront turns the step round in LDS of its
+  // own, where its sums go at the end: lane l holds chunk l & 3 of token l >> 2 and gets chunk l >> 4 of token
+  // l & 15.  us, a Llama-2-7B-sized layer: 32 tokens 35.4 -> 33.2, 64 tokens 47.6 -> 42.2; up to 16 tokens the turn
+  // costs what it saves (1 token 29.0 -> 29.4).
+  u32x4_t* const turn = (u32x4_t*)red + wave * RB * TB * 64;
+  const int put_at = (lane & ~3) | ((lane & 3) ^ ((lane >> 4) & 3)), get_at = r * 4 + ((lane >> 4) ^ (r >> 2));
   u32x4_t w[U][RB], a[U][NA][TB];
   auto load = [&](int u, int s) {
 #pragma unroll
@@ -516,7 +527,7 @@ __device__ __forceinline__ void rows16_unit(const Rows16Args& p, int unit, int s
 #pragma unroll
       for (int t = 0; t < TB; ++t) {
         if (A_TILED) a[u][i][t] = sk_load(ar[i][t / 2], aofs[t] + (uint32_t)s * 2048u);
-        else a[u][i][t] = sk_load(ar[i][t / 2], s * 32 + q8 < k_end ? aofs[t] + (uint32_t)s * 64u : 0xfffffff0u);
+        else a[u][i][t] = sk_load(ar[i][t / 2], s * 32 + ac < k_end ? aofs[t] + (uint32_t)s * 64u : 0xfffffff0u);
       }
   };
   f32x4_t acc[RB][TB];
@@ -524,30 +535,45 @@ __device__ __forceinline__ void rows16_unit(const Rows16Args& p, int unit, int s
   for (int i = 0; i < RB; ++i)
 #pragma unroll
     for (int t = 0; t < TB; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  auto step = [&](int u) {
+  u32x4_t turned[TB];   // TURN: the tokens of the step that is multiplied next
+  auto turn_round = [&](int u) {
+#pragma unroll
+    for (int t = 0; t < TB; ++t) turn[t * 64 + put_at] = a[u][0][t];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) turned[t] = turn[t * 64 + get_at];
+  };
+  // (next: the ring's following step, -1 past the last)
+  auto step = [&](int u, int next) {
     __builtin_amdgcn_sched_barrier(0);
+    u32x4_t now[TB];
+    if (TURN) {
+#pragma unroll
+      for (int t = 0; t < TB; ++t) now[t] = turned[t];
+      if (next >= 0) turn_round(next);
+    }
 #pragma unroll
     for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int t = 0; t < TB; ++t) {
         SFrag wf, af;
         wf.u = w[u][i];
-        af.u = a[u][DUAL ? i : 0][t];
+        af.u = TURN ? now[t] : a[u][DUAL ? i : 0][t];
         acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.v, af.v, acc[i][t], 0, 0, 0);
       }
   };
   if (s0 < s1) {
 #pragma unroll
     for (int u = 0; u < U; ++u) load(u, s0 + u);
+    if (TURN) turn_round(0);
     for (int s = s0 + U; s < s1; s += U) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        step(u);
+        step(u, (u + 1) % U);
         load(u, s + u);
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) step(u);
+    for (int u = 0; u < U; ++u) step(u, u + 1 < U ? u + 1 : -1);
   }
   // lane: token t * 16 + r, rows 4 (lane >> 4) + 0..3 of the piece
 #pragma unroll
