@@ -474,7 +474,7 @@ __device__ __forceinline__ void rows16_unit(const Rows16Args& p, int unit, int s
                                             const int (&sub)[RB], bool pair, float4* red, int* flag) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
   constexpr int NA = DUAL ? 2 : 1;
-  constexpr bool TURN = !A_TILED && TB > 1;
+  constexpr bool TURN = !A_TILED && (TB > 1 || SPLIT);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // this workgroup's range, then this wavefront's share of it (may be empty: it then adds zeros)
@@ -511,11 +511,12 @@ __device__ __forceinline__ void rows16_unit(const Rows16Args& p, int unit, int s
     if (A_TILED) aofs[t] = lofs + (uint32_t)(t & 1) * 256u;
     else aofs[t] = (uint32_t)(min(t * 16 + (TURN ? lane >> 2 : r), p.M - 1) * (int)p.lda + ac) * 2u;
   }
-  // Row-major tokens, more than 16: four neighbouring lanes read 64 bytes of a row (a row per lane, as the MFMA wants
+  // Row-major tokens (not gated ones up to 16): four neighbouring lanes read 64 bytes of a row (a row per lane, as the MFMA wants
   // them, comes at 16 bytes a clock instead of 61), and the wavefront turns the step round in LDS of its
   // own, where its sums go at the end: lane l holds chunk l & 3 of token l >> 2 and gets chunk l >> 4 of token
-  // l & 15.  us, a Llama-2-7B-sized layer: 32 tokens 35.4 -> 33.2, 64 tokens 47.6 -> 42.2; up to 16 tokens the turn
-  // costs what it saves (1 token 29.0 -> 29.4).
+  // l & 15.  us, a Llama-2-7B-sized layer: 32 tokens 35.4 -> 33.2, 64 tokens 47.6 -> 42.2 (8 tokens 29.0 either way, 1 token
+  // 29.0 -> 29.4).  Ungated, with a ring of eight instead of four, which pays only then: four layers of 2048 x 8192,
+  // 16 tokens 94.9 -> 91.3, of 5120 x 20480, 1 token 177.5 -> 171.9, 16 tokens 183.8 -> 183.5.
   u32x4_t* const turn = (u32x4_t*)red + wave * RB * TB * 64;
   const int put_at = (lane & ~3) | ((lane & 3) ^ ((lane >> 4) & 3)), get_at = r * 4 + ((lane >> 4) ^ (r >> 2));
   u32x4_t w[U][RB], a[U][NA][TB];
@@ -1018,7 +1019,7 @@ int launch_skinny_bf16(const GemmArgs& g, int act, float* part, unsigned* counte
     return one ? launch_rows16<true, 1, 4, false, false>(a, st) : launch_rows16<true, 2, 6, false, false>(a, st);
   }
   if (glu) return one ? launch_rows16<false, 1, 4, true, false>(a, st) : launch_rows16<false, 2, 6, true, false>(a, st);
-  return one ? launch_rows16<false, 1, 4, false, false>(a, st) : launch_rows16<false, 2, 6, false, false>(a, st);
+  return one ? launch_rows16<false, 1, 8, false, false>(a, st) : launch_rows16<false, 2, 6, false, false>(a, st);
 }
 
 int launch_skinny_reduce(const GemmArgs& g, int act, const float* part, int n_split, int f16_out, hipStream_t st) {
