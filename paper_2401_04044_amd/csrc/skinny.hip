@@ -673,21 +673,24 @@ __global__ void __launch_bounds__(NW * 64) rows16_kernel(const Rows16Args p) {
 // elements 64 (q >> 1) + 16 j + 8 (q & 1) + 0..7 of quad q, and the activations are loaded to match.
 //   UP    A workgroup of eight wavefronts keeps all 16 tokens in registers, wavefront w the groups w, w + 8, ..
 //         of 128 inputs, and walks over pairs of pieces (16 gate and their 16 up rows, or the two halves of a row block);
-//         the next pair's weights are requested before this one's are multiplied.  The constant of the
+//         a group's registers are refilled for the next pair as soon as it is multiplied.  The constant of the
 //         offset-binary codes enters as the accumulator's start value, -132 (-1152) times the group's sum
 //         of the tokens, computed once.  3 bits: the four pairs of an operand share one rotated dword of third
 //         bits, pair i as 128 + 2^i u, and the tokens it meets are scaled by 2^-i (exact) beforehand: 52
 //         vector instructions for 16 x 128 codes instead of 64.  The wavefronts' sums meet in LDS, where
 //         one of them adds, activates and stores the pair while the others go on.
 //   DOWN  A workgroup owns one piece of 16 outputs (4096 outputs: one each CU) over the whole reduction, its wavefronts
-//         an eighth each; weights, activations and scales run through rings of registers.
+//         an eighth each; the codes run through a ring of two registers sets, activations and scales are requested a
+//         unit ahead.  Deeper rings are slower (six and two: 2 us a launch): the code is run once or twice
+//         over, and twice its size costs more than the loads it has in flight.
 // The kernels below spend half of their 32-row MFMAs on absent tokens, a second MFMA on the constant of UP, and two
 // launches on sums across workgroups.  us, a layer of 16 tokens with its norm, those -> these: 4096 x 11008 gated 44.9 ->
-// 34.8 (up 19.9 + 5.0 -> 16.7, down 13.8 + 4.1 -> 12.8), 2048 x 8192 25.7 -> 20.1, 1280 x 4000 22.3 -> 14.9; with its start
-// values and operands scaled by powers of two up takes 16.7 instead of 17.9.  Bound by the unpacking (half of the
-// time), the ramp of each launch, and in DOWN the 8 KB of activations and scales that every 1.5 KB of codes meets.
-constexpr int Q16_NW = 8;
-constexpr int Q16_MAX_GPW = 4;   // groups of 128 inputs a wavefront holds
+// 32.0 (up 19.9 + 5.0 -> 16.6, down 13.8 + 4.1 -> 11.0), 2048 x 8192 25.7 -> 19.0, 1280 x 4000 22.3 -> 14.3; the operands
+// scaled by powers of two are 1.2 of up's us, one set of registers instead of two another 1.2 (8.5 us of 124 for four
+// layers of one token).  Bound by the unpacking (half of the time), the ramp of each launch, and in DOWN the
+// 8 KB of activations and scales that every 1.5 KB of codes meets.
+constexpr int Q16_NW = 8, Q16_DOWN_NW = 8;   // (sixteen for DOWN: 2 % slower, twelve: 1 % faster at one shape, slower at others)
+constexpr int Q16_MAX_GPW = 5;   // groups of 128 inputs a wavefront holds
 
 struct Q16UpArgs {
   const void* X;
@@ -718,31 +721,34 @@ __device__ __forceinline__ void quant16_up(const Q16UpArgs& p, int u0, int step,
         x[g][j].u = gi < p.G ? *(const u32x4_t*)(xr + (int64_t)gi * 256 + j * 32) : u32x4_t{0, 0, 0, 0};
     }
   }
+  // One set of registers for the packed codes and the lane's four row scales of both pieces, refilled piece by piece:
+  // as soon as a group is multiplied its registers are loaded for the next pair.  (A second set, filled ahead, has the code
+  // twice and no room to spare.)  Past the last pair the loads are out of range: zero, and no traffic.  A
+  // group past the last repeats it: its tokens are zero.
   struct Wts {
     QPacked<BITS> w[2][GPW];
     u32x2_t s[2][GPW];
-  };
-  // the packed codes and the lane's four row scales of both pieces (a group past the last repeats it: its tokens are zero)
-  auto piece_rb = [&](int u, int i) { return GLU ? (u & ~1) + i : u; };
-  auto piece_sub = [&](int u, int i) { return GLU ? (u & 1) : i; };
-  auto load = [&](Wts& w, int u) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int rb = piece_rb(u, i), sub = piece_sub(u, i);
-      const char* base = p.codes[PART] + (int64_t)rb * p.G * 2 * BB + (int64_t)(q >> 1) * BB;
-      const uint16_t* sb = p.scales[PART] + (int64_t)rb * p.G * 32 + sub * 16 + 4 * q;
-#pragma unroll
-      for (int g = 0; g < GPW; ++g) {
-        const int gi = min(wave + g * Q16_NW, p.G - 1);
-        const char* blk = base + (int64_t)gi * 2 * BB;
-        if constexpr (BITS == 8) w.w[i][g] = q_load8(blk, 32 * (q & 1) + 16 * sub + r);
-        else w.w[i][g] = q_load3(blk, 32 * (q & 1) + 16 * sub + r);
-        w.s[i][g] = *(const u32x2_t*)(sb + gi * 32);
-      }
+  } wts;
+  auto load = [&](int i, int g, int u, uint32_t limit) {
+    const rsrc_t cr = sk_rsrc(p.codes[PART], limit), sr = sk_rsrc(p.scales[PART], limit);
+    const int rb = GLU ? (u & ~1) + i : u, sub = GLU ? (u & 1) : i;
+    const int gi = min(wave + g * Q16_NW, p.G - 1);
+    const uint32_t blk = ((uint32_t)rb * p.G + gi) * 2 * BB, lo = (uint32_t)(q >> 1) * BB + (uint32_t)(32 * (q & 1) + r) * (BITS == 8 ? 16 : 12);
+    if constexpr (BITS == 8) {
+      wts.w[i][g].h[0] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(cr, lo, blk + sub * 256, 0));
+      wts.w[i][g].h[1] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(cr, lo, blk + sub * 256 + 1024, 0));
+    } else {
+      typedef __attribute__((ext_vector_type(3))) uint32_t u32x3_t;
+      const u32x3_t v = __builtin_bit_cast(u32x3_t, __builtin_amdgcn_raw_buffer_load_b96(cr, lo, blk + sub * 192, 0));
+      wts.w[i][g].lo[0] = v[0]; wts.w[i][g].lo[1] = v[1]; wts.w[i][g].hi = v[2];
     }
+    wts.s[i][g] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(sr, 8 * q, ((uint32_t)rb * p.G + gi) * 64 + sub * 32, 0));
   };
-  Wts wa;
-  load(wa, u0);
+  constexpr uint32_t ALL = 0xfffffff0u;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) load(i, g, u0, ALL);
   // start values: every row of the operand holds the negated constants, so a token's is the same in all rows
   float start[GPW];
   {
@@ -776,7 +782,8 @@ __device__ __forceinline__ void quant16_up(const Q16UpArgs& p, int u0, int step,
     }
   }
   int buf = 0, owner = 0;
-  auto unit = [&](const Wts& w, int u) {
+  auto unit = [&](int u, int next, bool more) {
+    const uint32_t limit = more ? ALL : 0u;
     q16_f32x4 tot[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -789,18 +796,22 @@ __device__ __forceinline__ void quant16_up(const Q16UpArgs& p, int u0, int step,
           QFrag wf;
           if constexpr (BITS == 8) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) wf.u[e] = q_pair(w.w[i][g], j, e, 0x64646464u);
+            for (int e = 0; e < 4; ++e) wf.u[e] = q_pair(wts.w[i][g], j, e, 0x64646464u);
           } else {
-            q_pairs_scaled(w.w[i][g], j, wf.u);
+            q_pairs_scaled(wts.w[i][g], j, wf.u);
           }
           if constexpr (BITS == 8) ag = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf.h, x[g][j].h, ag, 0, 0, 0);
           else ag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.b, x[g][j].b, ag, 0, 0, 0);
         }
-        const u32x2_t sc = w.s[i][g];
+        const u32x2_t sc = wts.s[i][g];
         tot[i][0] = fmaf(q_half((uint16_t)(sc[0] & 0xffffu)), ag[0], tot[i][0]);
         tot[i][1] = fmaf(q_half((uint16_t)(sc[0] >> 16)), ag[1], tot[i][1]);
         tot[i][2] = fmaf(q_half((uint16_t)(sc[1] & 0xffffu)), ag[2], tot[i][2]);
         tot[i][3] = fmaf(q_half((uint16_t)(sc[1] >> 16)), ag[3], tot[i][3]);
+        if constexpr (BITS == 3) {
+          __builtin_amdgcn_sched_barrier(0);
+          load(i, g, next, limit);
+        }
       }
     }
     // (two buffers: nobody is more than one barrier ahead of the wavefront that adds)
@@ -833,19 +844,9 @@ __device__ __forceinline__ void quant16_up(const Q16UpArgs& p, int u0, int step,
     owner = (owner + 1) % Q16_NW;
   };
   if constexpr (BITS == 8) {   // (one pair a workgroup)
-    unit(wa, u0);
-    return;
-  }
-  Wts wb;
-  for (int u = u0; u < units; u += 2 * step) {
-    const bool two = u + step < units;
-    if (two) load(wb, u + step);
-    __builtin_amdgcn_sched_barrier(0);
-    unit(wa, u);
-    if (!two) break;
-    if (u + 2 * step < units) load(wa, u + 2 * step);
-    __builtin_amdgcn_sched_barrier(0);
-    unit(wb, u + step);
+    unit(u0, u0, false);
+  } else {
+    for (int u = u0; u < units; u += step) unit(u, u + step < units ? u + step : u, u + step < units);
   }
 }
 
@@ -867,11 +868,11 @@ struct Q16DownArgs {
 // this wavefront's share of one part of the reduction, in units of 128 neurons
 template <int BITS>
 __device__ __forceinline__ void quant16_down(const Q16DownArgs& p, int piece, q16_f32x4& tot) {
-  constexpr int PART = BITS == 8 ? 0 : 1, BB = BITS == 8 ? 2048 : 768, UW = BITS == 8 ? 2 : 6, UA = 2;
+  constexpr int PART = BITS == 8 ? 0 : 1, BB = BITS == 8 ? 2048 : 768, UW = BITS == 8 ? 1 : 2, UA = 1;
   const int Kp = p.Kp[PART], units = (Kp + 127) / 128;
   const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c0 = units * wave / Q16_NW, c1 = units * (wave + 1) / Q16_NW;
+  const int c0 = units * wave / Q16_DOWN_NW, c1 = units * (wave + 1) / Q16_DOWN_NW;
   if (c0 >= c1) return;
   const int rb = piece >> 1, sub = piece & 1;
   // (past the last block of 64 neurons, and past the share, loads are out of range: zero)
@@ -939,8 +940,8 @@ __device__ __forceinline__ void quant16_down(const Q16DownArgs& p, int piece, q1
   }
 }
 
-__global__ void __launch_bounds__(Q16_NW * 64) quant16_down_kernel(const Q16DownArgs p) {
-  __shared__ float4 red[Q16_NW * 64];
+__global__ void __launch_bounds__(Q16_DOWN_NW * 64) quant16_down_kernel(const Q16DownArgs p) {
+  __shared__ float4 red[Q16_DOWN_NW * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int piece = blockIdx.x;
   q16_f32x4 tot = {0.f, 0.f, 0.f, 0.f};
@@ -951,7 +952,7 @@ __global__ void __launch_bounds__(Q16_NW * 64) quant16_down_kernel(const Q16Down
   if (wave != 0) return;
   float4 t = red[lane];
 #pragma unroll
-  for (int w = 1; w < Q16_NW; ++w) {
+  for (int w = 1; w < Q16_DOWN_NW; ++w) {
     const float4 o = red[w * 64 + lane];
     t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
   }
@@ -1016,7 +1017,7 @@ int launch_skinny_bf16(const GemmArgs& g, int act, float* part, unsigned* counte
   }
   if (dual) return launch_rows16<true, 2, 4, true, true>(a, st);
   if (at) {
-    return one ? launch_rows16<true, 1, 4, false, false>(a, st) : launch_rows16<true, 2, 6, false, false>(a, st);
+    return one ? launch_rows16<true, 1, 6, false, false>(a, st) : launch_rows16<true, 2, 6, false, false>(a, st);
   }
   if (glu) return one ? launch_rows16<false, 1, 4, true, false>(a, st) : launch_rows16<false, 2, 6, true, false>(a, st);
   return one ? launch_rows16<false, 1, 8, false, false>(a, st) : launch_rows16<false, 2, 6, false, false>(a, st);
@@ -1039,9 +1040,10 @@ int launch_skinny_reduce2(const GemmArgs& g, int act, const float* part, int n_s
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Up to a d_model of 4096: 256 pieces of outputs are one each CU, and four groups a wavefront fit its registers.
-// 5120 x 13824 (320 pieces, five groups) takes 68 us a layer this way, 60 on the kernels for 32 tokens.
-bool quant16_fits(int M, int d_model) { return M <= 16 && d_model <= 128 * Q16_NW * Q16_MAX_GPW; }
+// Four groups a wavefront (d_model 4096) and with them one piece of outputs a CU; five and up to 320 pieces only for
+// gated layers.  Both sides (us, four layers of 16 tokens, the kernels for 32 / these): 5120 x 13824 gated 241 /
+// 203, 4608 x 12000 gated 203 / 185, 5120 x 20480 not gated 231 / 234.
+bool quant16_fits(int M, int d_model, bool gated) { return M <= 16 && d_model <= 128 * Q16_NW * (gated ? Q16_MAX_GPW : Q16_MAX_GPW - 1); }
 
 template <bool GLU>
 static void launch_q16_up(const Q16UpArgs& a, hipStream_t st) {
@@ -1050,14 +1052,15 @@ static void launch_q16_up(const Q16UpArgs& a, hipStream_t st) {
     case 1: hipLaunchKernelGGL((quant16_up_kernel<1, GLU>), grid, blk, 0, st, a); break;
     case 2: hipLaunchKernelGGL((quant16_up_kernel<2, GLU>), grid, blk, 0, st, a); break;
     case 3: hipLaunchKernelGGL((quant16_up_kernel<3, GLU>), grid, blk, 0, st, a); break;
-    default: hipLaunchKernelGGL((quant16_up_kernel<4, GLU>), grid, blk, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((quant16_up_kernel<4, GLU>), grid, blk, 0, st, a); break;
+    default: hipLaunchKernelGGL((quant16_up_kernel<5, GLU>), grid, blk, 0, st, a); break;
   }
 }
 
 int launch_quant16_up(const GemmArgs& g, int act, const SkinnyQ& q8, int n8, const SkinnyQ& q3, int n3, hipStream_t st) {
   if (n8 + n3 <= 0) return 0;
   const bool glu = act == ACT_GLU;
-  if (g.M <= 0 || !quant16_fits(g.M, g.K) || (g.K & 127) || (n8 & 63) || (n3 & 63)) return -1;
+  if (g.M <= 0 || !quant16_fits(g.M, g.K, glu) || (g.K & 127) || (n8 & 63) || (n3 & 63)) return -1;
   Q16UpArgs a = {};
   a.X = g.A; a.lda = g.lda; a.M = g.M; a.G = g.K / 128;
   a.codes[0] = (const char*)q8.codes; a.codes[1] = (const char*)q3.codes;
@@ -1081,7 +1084,7 @@ int launch_quant16_down(const GemmArgs& g, const SkinnyQ& q8, const SkinnyQ& q3,
   a.scales[0] = (const uint16_t*)q8.scales; a.scales[1] = (const uint16_t*)q3.scales;
   a.Kp[0] = q8.Kp; a.Kp[1] = q3.Kp;
   fill_reduce_args(a.e, g, ACT_NONE);
-  hipLaunchKernelGGL(quant16_down_kernel, dim3(g.N / 16), dim3(Q16_NW * 64), 0, st, a);
+  hipLaunchKernelGGL(quant16_down_kernel, dim3(g.N / 16), dim3(Q16_DOWN_NW * 64), 0, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

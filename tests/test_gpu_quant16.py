@@ -12,7 +12,8 @@ from workloads.configs import C2, C4, reduced
 pytestmark = pytest.mark.gpu
 
 CASES = [(C4, 128, 130, 10), (C4, 384, 500, 100), (C4, 1024, 320, 0), (C4, 1152, 300, 300), (C4, 2176, 200, 64),
-         (C2, 128, 96, 30), (C2, 896, 700, 129), (C2, 2048, 260, 60), (C4, 4096, 200, 70), (C4, 4224, 150, 20)]
+         (C2, 128, 96, 30), (C2, 896, 700, 129), (C2, 2048, 260, 60), (C4, 4096, 200, 70), (C4, 4224, 150, 20), (C4, 5120, 96, 30),
+         (C2, 4224, 100, 30), (C4, 5248, 64, 10)]
 
 
 @pytest.mark.parametrize("base,d,n,k", CASES, ids=[f"{c[0].act}_d{c[1]}_n{c[2]}_k{c[3]}" for c in CASES])
