@@ -2,13 +2,14 @@
 // orthonormal by X <- (c0 I + c1 G + c2 G^2) X, G = X X^T, with coefficients chosen step by step on the
 // device (polar_steps.h).  Per step three products for all matrices of a layer:
 //   gram    S = X X^T (one triangle, mirrored) and the tiles' shares of ||S - I||_F^2,
-//   poly    the step's coefficients, T = c0 I + c1 S + c2 S^2 (one triangle, mirrored),
-//   apply   X' = T X into the other buffer.
+//   poly    the step's coefficients, T - I for T = c0 I + c1 S + c2 S^2 (one triangle, mirrored),
+//   apply   X' = X + (T - I) X into the other buffer: near the end T - I is small, and with it the rounding of the sums.
 // The host cannot know how many steps a matrix takes and must not wait.  It launches the first steps product by
 // product (polar_launched); the steps after those, which flat and mildly decaying spectra do not need, are one
 // launch of a work queue that returns at once when nothing is left.  (A launch that does nothing costs 3.5 us:
 // three for every step of the worst sketch of rank 512 were 115 us of 816.)  Measured, us, a layer compressed and
-// tried (two matrices): 2048 x 7946 rank 512 1235 -> 715, 1536 x 4800 rank 400 gated 1130 -> 655, 512 x 1450 rank 64 276 -> 240 (with the projections in one launch each 657, 607, 222).
+// tried (two matrices): 2048 x 7946 rank 512 1235 -> 715, 1536 x 4800 rank 400 gated 1130 -> 655, 512 x 1450 rank 64 276 -> 240 (with the
+// projections in one launch each 672, 616, 229).
 // Factorisation alone at 2048 x 7946 with singular values i^-a: a = 0 1140 -> 620, 1/2 1140 -> 720, 1 1140 -> 950;
 // the other way round where the queue does most of the steps: a = 2 1620, rank one 1990.
 // All products are true fp32 (v_mfma_f32_16x16x4_f32, 256 flop per clock and CU), staged through LDS by loads
@@ -124,7 +125,12 @@ struct TileProduct {
       }
     }
   }
-  __device__ __forceinline__ static void mma(const Frags& f, f32x4_t (&acc)[TL][TL]) {
+  // Sums in NS accumulators of a tile, added in pairs at the end: with one, a chain of 512 roundings at d = 2048, the
+  // basis was 6.8e-7 off orthonormal.  (2048 x 7946 rank 512 in fp32, root mean square: 2.3e-7 with these, 1.7e-7 with T - I
+  // applied; the products straight from registers had 2.2e-7.)
+  static constexpr int NS = TL == 1 ? 8 : 4;
+  typedef f32x4_t Sums[NS][TL][TL];
+  __device__ __forceinline__ static void mma(const Frags& f, Sums& acc) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -132,8 +138,10 @@ struct TileProduct {
 #pragma unroll
         for (int i = 0; i < TL; ++i)
 #pragma unroll
-          for (int j = 0; j < TL; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.b[h][j][t], f.a[h][i][t], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < TL; ++j) {
+            f32x4_t& c = acc[(h * 4 + t) % NS][i][j];
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(f.b[h][j][t], f.a[h][i][t], c, 0, 0, 0);
+          }
   }
   // slab s has landed for every wavefront, and slab s - 1 is in everyone's registers: the ring moves on
   __device__ __forceinline__ void advance(int s) {
@@ -143,7 +151,8 @@ struct TileProduct {
     if (s + STAGES - 1 < n) issue(s + STAGES - 1);
   }
   // the fragments of a slab are read while the one before is multiplied
-  __device__ __forceinline__ void run(f32x4_t (&acc)[TL][TL]) {
+  __device__ __forceinline__ void run(f32x4_t (&out)[TL][TL]) {
+    Sums acc = {};
     Frags f0, f1;
     advance(0);
     read(f0);
@@ -164,6 +173,18 @@ struct TileProduct {
     } else {
       mma(f0, acc);
     }
+#pragma unroll
+    for (int n = NS / 2; n > 0; n /= 2)
+#pragma unroll
+      for (int k = 0; k < n; ++k)
+#pragma unroll
+        for (int i = 0; i < TL; ++i)
+#pragma unroll
+          for (int j = 0; j < TL; ++j) acc[k][i][j] += acc[k + n][i][j];
+#pragma unroll
+    for (int i = 0; i < TL; ++i)
+#pragma unroll
+      for (int j = 0; j < TL; ++j) out[i][j] = acc[0][i][j];
   }
 };
 
@@ -175,7 +196,7 @@ struct PolarArgs {
   float* X;              // [2][mats][r8, dk]
   int64_t flip;          // elements between the two buffers
   float* S;              // [mats][r8, rk]
-  float* T;
+  float* T;              // (T - I)
   int gram_tiles, poly_tiles, apply_tiles;
   float* share;          // [mats][gram_tiles]: the tiles' shares of ||S - I||_F^2
   float* rows;           // [mats][2][r8]: sums of |S| and of S^2 along its rows
@@ -355,7 +376,7 @@ __device__ __forceinline__ void poly_tile(const PolarArgs& p, int step, int mat,
       const int row = row0 + i * 16, col = col0 + j * 16;
       f32x4_t v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = c[2] * acc[i][j][e] + c[1] * g[i][j][e] + (row == col + e ? c[0] : 0.f);
+      for (int e = 0; e < 4; ++e) v[e] = c[2] * acc[i][j][e] + c[1] * g[i][j][e] + (row == col + e ? c[0] - 1.f : 0.f);
       store_sym<DEV>(T, p.r8, p.rk, row, col, tm != tn, v);
     }
 }
@@ -370,11 +391,20 @@ __device__ __forceinline__ void apply_tile(const PolarArgs& p, int step, int mat
   const float* X = p.X + (step & 1) * p.flip + at;
   TileProduct<TL, true> prod;
   prod.start(T, p.rk, p.r8 - tm * 64, X + tn * 64, p.dk, p.dk - tn * 64, p.r8, p.rk / 32, smem);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  f32x4_t x[TL][TL];
+#pragma unroll
+  for (int i = 0; i < TL; ++i)
+#pragma unroll
+    for (int j = 0; j < TL; ++j) {
+      const int row = tm * 64 + (wave >> 1) * 32 + i * 16 + (lane & 15);
+      const int col = tn * 64 + (wave & 1) * 32 + j * 16 + 4 * (lane >> 4);
+      x[i][j] = row < p.r8 && col < p.dk ? *(const f32x4_t*)(X + (int64_t)row * p.dk + col) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
   const PolarState s = load_state(p.state + (int64_t)(step + 1) * p.mats + mat);
   if (!s.act) { prod.drain(); return; }
   f32x4_t acc[TL][TL] = {};
   prod.run(acc);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float* O = p.X + ((step & 1) ^ 1) * p.flip + at;
 #pragma unroll
   for (int i = 0; i < TL; ++i)
@@ -382,7 +412,7 @@ __device__ __forceinline__ void apply_tile(const PolarArgs& p, int step, int mat
     for (int j = 0; j < TL; ++j) {
       const int row = tm * 64 + (wave >> 1) * 32 + i * 16 + (lane & 15);
       const int col = tn * 64 + (wave & 1) * 32 + j * 16 + 4 * (lane >> 4);
-      if (row < p.r8 && col < p.dk) put4<DEV>(O + (int64_t)row * p.dk + col, col < p.d ? acc[i][j] : f32x4_t{0.f, 0.f, 0.f, 0.f});
+      if (row < p.r8 && col < p.dk) put4<DEV>(O + (int64_t)row * p.dk + col, col < p.d ? x[i][j] + acc[i][j] : f32x4_t{0.f, 0.f, 0.f, 0.f});
     }
 }
 

@@ -29,37 +29,37 @@ G = r"gemm_bf16_dl_kernel<"
 SIGNATURES = {
     "C5_stack_layer": [
         ("pre-norm  token_rmsnorm_kernel", r"token_rmsnorm_kernel<true>", 4096, 1),
-        ("G1 X [W1h | P1]  128x320 tiles", G + r"128, 320, 2, 4, 4, true, 1, false, false, false, false>", 224, 1),
-        ("G2 gelu(t Q1)  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 1, false, false, true, false>", 992, 1),
-        ("G3 h2 P2  256x256 tiles x 3 ranges", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 80, 3),
+        ("G1 X [W1h | P1]  128x320 tiles", G + r"128, 320, 2, 4, 4, true, 1, false, false, false, false, 0>", 224, 1),
+        ("G2 gelu(t Q1)  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 1, false, false, true, false, 0>", 992, 1),
+        ("G3 h2 P2  256x256 tiles x 3 ranges", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false, 0>", 80, 3),
         ("G3 sum of the ranges", r"splitk_epilogue_kernel", 2560, 1),
-        ("G4 [h1 | t2] [W2h ; Q2] + residual, fp32 out  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 0, false, false, true, true>", 256, 1),
+        ("G4 [h1 | t2] [W2h ; Q2] + residual, fp32 out  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 0, false, false, true, true, 0>", 256, 1),
     ],
     "C5_prefill": [
-        ("G1  128x320 tiles", G + r"128, 320, 2, 4, 4, true, 1, false, false, false, false>", 224, 1),
-        ("G2  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 1, false, false, true, false>", 992, 1),
-        ("G3  256x256 tiles x 3 ranges", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 80, 3),
+        ("G1  128x320 tiles", G + r"128, 320, 2, 4, 4, true, 1, false, false, false, false, 0>", 224, 1),
+        ("G2  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 1, false, false, true, false, 0>", 992, 1),
+        ("G3  256x256 tiles x 3 ranges", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false, 0>", 80, 3),
         ("G3 sum of the ranges", r"splitk_epilogue_kernel", 2560, 1),
-        ("G4  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 0, false, false, true, false>", 256, 1, r"splitk_epilogue_kernel"),
+        ("G4  256x320 tiles", G + r"256, 320, 2, 4, 4, false, 0, false, false, true, false, 0>", 256, 1, r"splitk_epilogue_kernel"),
     ],
     "C3_prefill": [
-        ("G1 X [gate/up heavy | Pg | P1]  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 2, false, false, false, false>", 208, 1),
+        ("G1 X [gate/up heavy | Pg | P1]  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 2, false, false, false, false, 0>", 208, 1),
         ("G2 silu(tg Qg) * (tu Q1), two left operands  256x256 tiles", r"gemm_dual_kernel", 1312, 1),
-        ("G3 h2 P2  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 256, 1, r"gemm_dual_kernel"),
-        ("G4  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false>", 256, 1, G + r"128, 128, 2, 2, 4, true, 0"),
+        ("G3 h2 P2  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false, 0>", 256, 1, r"gemm_dual_kernel"),
+        ("G4  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 0, false, false, true, false, 0>", 256, 1, G + r"128, 128, 2, 2, 4, true, 0"),
     ],
     "C2_prefill": [
-        ("G1  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 1, false, false, false, false>", 192, 1),
-        ("G2  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false>", 1024, 1),
-        ("G3  128x128 tiles x 2 ranges", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 128, 2),
+        ("G1  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 1, false, false, false, false, 0>", 192, 1),
+        ("G2  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false, 0>", 1024, 1),
+        ("G3  128x128 tiles x 2 ranges", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false, 0>", 128, 2),
         ("G3 sum of the ranges", r"splitk_epilogue_kernel", 1024, 1),
-        ("G4  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false>", 512, 1),
+        ("G4  128x128 tiles", G + r"128, 128, 2, 2, 4, true, 0, false, false, true, false, 0>", 512, 1),
     ],
     "C2_prefill_T16384": [
-        ("G1  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 1, false, false, false, false>", 192, 1),
-        ("G2  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false>", 4096, 1),
-        ("G3  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 0, false, false, true, false>", 256, 1),
-        ("G4  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 0, false, false, true, false>", 1024, 1),
+        ("G1  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 1, false, false, false, false, 0>", 192, 1),
+        ("G2  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 1, false, false, true, false, 0>", 4096, 1),
+        ("G3  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 0, false, false, true, false, 0>", 256, 1),
+        ("G4  128x256 tiles", G + r"128, 256, 1, 4, 3, true, 0, false, false, true, false, 0>", 1024, 1),
     ],
     "C4_int4_decode": [
         ("phase 1: gate/up, activation", r"int4_phase1_kernel<4, 8, 2>", 253, 1),
@@ -70,30 +70,27 @@ SIGNATURES = {
         ("expand down to bf16", r"expand_down_kernel", 5568, 1),
     ],
     "C4_w3h8_decode": [
-        ("up/gate stream (int8 heavy + int3 rest)", r"skinny_stream_q2_kernel<false>", 764, 1),
-        ("sum, activation", r"skinny_reduce_kernel", 692, 1),
-        ("down stream", r"skinny_stream_q2_kernel<true>", 576, 1),
-        ("sum", r"skinny_reduce_kernel", 128, 1),
+        ("up/gate (int8 heavy + int3 rest), activation", r"quant16_up_kernel<4, true>", 256, 1),
+        ("down", r"quant16_down_kernel", 256, 1),
     ],
     "C3_lowrank_decode": [
         ("G1", r"rows16_kernel<false, 1, 1, 4, 4, true, false>", 164, 1),
         ("G2 (two left operands, SwiGLU)", r"rows16_kernel<true, 1, 2, 4, 4, true, true>", 656, 1),
-        ("G3, 4 ranges", r"rows16_kernel<true, 1, 1, 4, 4, false, false>", 256, 1, r"rows16_kernel<true, 1, 2, 4, 4, true, true>"),
-        ("G4", r"rows16_kernel<true, 1, 1, 4, 4, false, false>", 256, 1, r"rows16_kernel<true, 1, 1,"),
+        ("G3, 4 ranges", r"rows16_kernel<true, 1, 1, 4, 6, false, false>", 256, 1, r"rows16_kernel<true, 1, 2, 4, 4, true, true>"),
+        ("G4", r"rows16_kernel<true, 1, 1, 4, 6, false, false>", 256, 1, r"rows16_kernel<true, 1, 1,"),
     ],
     "C5_lowrank_decode": [
-        ("G1", r"rows16_kernel<false, 1, 1, 4, 4, false, false>", 132, 1),
+        ("G1", r"rows16_kernel<false, 1, 1, 4, 8, false, false>", 132, 1),
         ("G2", r"rows16_kernel<true, 1, 2, 4, 6, false, false>", 616, 1),
-        ("G3, 3 ranges", r"rows16_kernel<true, 1, 1, 4, 4, false, false>", 240, 1),
+        ("G3, 3 ranges", r"rows16_kernel<true, 1, 1, 4, 6, false, false>", 240, 1),
         ("G4", r"rows16_kernel<true, 1, 2, 4, 6, false, false>", 160, 1),
     ],
     "C2_calibration": [
         ("re-tile W1 (neuron-major)", r"permute_transpose_tiled_kernel<true>", 128, 32),
-        ("score product X W1, gelu, column sums  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 1, false, true, false, false>", 512, 1),
-        ("sum of the row tiles' partials", r"reduce_partials_kernel", 32, 1),
-        ("row norms of W2, score", r"finalize_scores_kernel<true>", 2048, 1),
-        ("selection: bit search + compaction", r"select_compact_kernel<8>", 1, 1),
-        ("selection: ranking", r"select_rank_kernel", 62, 1),
+        ("score product X W1, gelu, column sums  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 1, false, true, false, false, 0>", 512, 1),
+        ("sum of the row tiles' partials, row norms of W2, score", r"finalize_scores_kernel<true>", 512, 1),
+        ("selection: ranking by counting", r"select_count_kernel", 256, 1),
+        ("selection: numbering the rest", r"select_rest_kernel", 8, 1),
     ],
     "ceilings": [
         ("pure MFMA loop (ffsplit_probe_mfma)", r"probe_mfma_kernel", 2048, 1),
