@@ -90,7 +90,6 @@ SIGNATURES = {
         ("score product X W1, gelu, column sums  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 1, false, true, false, false, 0>", 512, 1),
         ("sum of the row tiles' partials, row norms of W2, score", r"finalize_scores_kernel<true>", 512, 1),
         ("selection: ranking by counting", r"select_count_kernel", 256, 1),
-        ("selection: numbering the rest", r"select_rest_kernel", 8, 1),
     ],
     "ceilings": [
         ("pure MFMA loop (ffsplit_probe_mfma)", r"probe_mfma_kernel", 2048, 1),
@@ -184,7 +183,7 @@ def write_kernel_stats(csv_path, out_dir, cmd):
     rows = list(csv.DictReader(open(csv_path)))
     rows.sort(key=lambda r: -float(r["TotalDurationNs"]))
     lines = ["# rocprofv3 --kernel-trace --stats: per-kernel statistics of one bench.py run", "",
-             "Command (from the repository root on the MI355X box, after `cd /tmp && export TMPDIR=/tmp`):", "",
+             "Command (from the repository root on an MI355X, after `cd /tmp && export TMPDIR=/tmp`):", "",
              "    " + cmd, "",
              "Rows are rocprofv3's `kernel_stats` (one per kernel name, all workloads of the run together; the",
              "per-workload tables in this folder split them by workgroup count). The 30 largest by total time.", "",
@@ -225,7 +224,7 @@ def main():
                     "--preheat-ms 0 --no-cpu")
     for wl_name, sig in SIGNATURES.items():
         lines = [f"# rocprofv3 summary: {wl_name}", "",
-                 "Commands (each its own run, from the repository root on the MI355X box, after `cd /tmp && export TMPDIR=/tmp`):", ""]
+                 "Commands (each its own run, from the repository root on an MI355X, after `cd /tmp && export TMPDIR=/tmp`):", ""]
         lines += ["    " + c for c in cmds]
         lines += ["", f"Summary written by `python -m paper_2401_04044_amd.profile_summary`.", ""]
         head = "| launch | kernel | workgroups | calls | avg us | min us |"
