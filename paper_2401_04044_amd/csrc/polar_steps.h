@@ -201,28 +201,32 @@ FFS_HOST_DEVICE inline PolarState polar_decide(const PolarPlan& p, int step, int
     s.parity ^= 1;
     return s;
   }
-  const float* from = p.cubic;
+  // (the coefficients are picked by value: with an address into the plan every thread of the kernel kept a copy of its
+  // arguments in scratch memory, 256 bytes: poly at rank 512 18 us instead of 11, in every launch, carried out or not)
+  int pick = 4;
   float end = 1.f;
   bool done = false;
   if (s.mode == POLAR_GROW) {
     if (step > 0 && (fig <= POLAR_BULK * (float)r || s.grown >= p.max_grow)) {
-      from = p.range1;
+      pick = 1;
       s.mode = POLAR_RANGE2;
     } else {
-      from = p.grow;
+      pick = 0;
       // (a zero matrix has no bound, nor has one with NaN)
       end = (float)POLAR_GROW_ROOM * (step == 0 && fig > 1e-6f && fig < 1.f ? fig : 1.f);
       ++s.grown;
     }
   } else if (s.mode == POLAR_RANGE2) {
-    from = p.range2;
+    pick = 2;
     s.mode = POLAR_FINISH;
   } else {
     done = fig <= POLAR_DONE;
-    if (fig > 0.5f) from = p.climb;
+    if (fig > 0.5f) pick = 3;
   }
   const float e = 1.f / end, e2 = e * e;
-  c[0] = from[0] * e; c[1] = from[1] * (e * e2); c[2] = from[2] * (e * e2 * e2);
+  const float scale[3] = {e, e * e2, e * e2 * e2};
+  for (int i = 0; i < 3; ++i)
+    c[i] = scale[i] * (pick == 0 ? p.grow[i] : pick == 1 ? p.range1[i] : pick == 2 ? p.range2[i] : pick == 3 ? p.climb[i] : p.cubic[i]);
   s.act = 1;
   s.last = done || step == p.max_steps - 1;
   s.parity ^= 1;
