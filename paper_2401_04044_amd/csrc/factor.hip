@@ -156,10 +156,8 @@ __global__ void __launch_bounds__(256) sumsq_stage1_kernel(const float* x, int64
   }
   if (threadIdx.x == 0) part[blockIdx.y * 260 + blockIdx.x] = red[0];
 }
-// (it also zeroes the polar iteration's queue)
-__global__ void __launch_bounds__(256) sumsq_stage2_kernel(float* part, int n_part, unsigned* queue, int queue_words) {
+__global__ void __launch_bounds__(256) sumsq_stage2_kernel(float* part, int n_part) {
   __shared__ float red[256];
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < queue_words; i += 256 * gridDim.x) queue[i] = 0u;
   part += blockIdx.x * 260;
   red[threadIdx.x] = (int)threadIdx.x < n_part ? part[threadIdx.x] : 0.f;
   __syncthreads();
@@ -339,8 +337,7 @@ int launch_factorize(const ffsplit_desc_t& d, const void* W1, const void* Wg, co
   }
   // ---- unit Frobenius norm, rows of d, polar factor
   hipLaunchKernelGGL(sumsq_stage1_kernel, dim3(256, w.mats), dim3(256), 0, st, XT, nx, red);
-  hipLaunchKernelGGL(sumsq_stage2_kernel, dim3(w.mats), dim3(256), 0, st, red, 256,
-                     (unsigned*)(ws + w.off_polar + pw.off_queue), pw.queue_words);
+  hipLaunchKernelGGL(sumsq_stage2_kernel, dim3(w.mats), dim3(256), 0, st, red, 256);
   hipLaunchKernelGGL(scale_transpose_kernel, dim3(pw.dk / 32, (r8 + 31) / 32, w.mats), dim3(32, 8), 0, st, XT, (int64_t)r8, X,
                      (int64_t)pw.dk, r8, dm, red);
   FKL();

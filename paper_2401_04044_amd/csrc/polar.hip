@@ -4,21 +4,22 @@
 //   gram    S = X X^T (one triangle, mirrored) and the tiles' shares of ||S - I||_F^2,
 //   poly    the step's coefficients, T - I for T = c0 I + c1 S + c2 S^2 (one triangle, mirrored),
 //   apply   X' = X + (T - I) X into the other buffer: near the end T - I is small, and with it the rounding of the sums.
-// The host cannot know how many steps a matrix takes and must not wait.  It launches the first steps product by
-// product (polar_launched); the steps after those, which flat and mildly decaying spectra do not need, are one
-// launch of a work queue that returns at once when nothing is left.  (A launch that does nothing costs 3.5 us:
-// three for every step of the worst sketch of rank 512 were 115 us of 816.)  Measured, us, a layer compressed and
-// tried (two matrices): 2048 x 7946 rank 512 1235 -> 715, 1536 x 4800 rank 400 gated 1130 -> 655, 512 x 1450 rank 64 276 -> 240 (with the
-// projections in one launch each 672, 616, 229).
-// Factorisation alone at 2048 x 7946 with singular values i^-a: a = 0 1140 -> 620, 1/2 1140 -> 720, 1 1140 -> 950;
-// the other way round where the queue does most of the steps: a = 2 1620, rank one 1990.
+// The host cannot know how many steps a matrix takes and must not wait: it launches as many as the worst sketch may need,
+// and the kernels of a step behind a matrix's last return at their first load.  Such a launch costs 3.8 us; up to rank 128
+// poly and apply are one.  (The steps from the seventh on in one launch of a work queue, which returned at once when nothing
+// was left, took 1.4 to 2.8 times as long a step as launches: 2048 x 7944 rank 512 with singular values i^-2 2030 us, 1608 x
+// 4849 rank 800 4530.)
+// Measured, us, a factorisation with singular values i^-a, a = 0, 1, 2, two matrices, the steps of polar_steps for every sketch
+// / these: 2048 x 7944 rank 512 1130 / 570, 785, 1055; 1536 x 4849 rank 400 gated 1065 / 545, 720, 985; 4096 x 10675 rank 1024
+// gated 8150 / 3420, 4940, 6840; 1608 x 4849 rank 800 2097 / 855, 1238, 1812; 512 x 1455 rank 64 260 / 184, 198, 236; 2048 x 7944
+// rank 128 478 / 329, -, 480; of rank one, 2048 x 7944 rank 512, 1126 / 1000.
 // All products are true fp32 (v_mfma_f32_16x16x4_f32, 256 flop per clock and CU), staged through LDS by loads
 // without registers.  A tile asks the caches for 16 (64x64) or 32 bytes per clock of 61: what bounds them is
 // the matrix rate, and at the usual ranks the start of a launch and the latency of its first loads.  So the
 // triangles take 32x32 tiles (272 workgroups for two matrices of rank 512: 25 us; 64x64 ones cut into seven ranges of
-// d, summed by the last to arrive: 31), rings are seven slabs deep, and every launch requests its first slabs
-// before it looks at the state: buffer s & 1 holds the X of step s of every matrix that takes that step.
-// Of a step's 65 us gram is 25, poly 16, apply 25 (24, 12.5 and 29 with the operands straight from registers).
+// d, summed by the last to arrive: 31; two or four groups of wavefronts that share a tile's reduction: within 1 %), or 16x16 ones
+// where those are few, and rings are seven slabs deep.  Buffer s & 1 holds the X of step s of every matrix that takes that step.
+// Of a step's 62 us at rank 512 gram is 25, poly 11, apply 25.
 // Rows of X and S are padded to 32 floats of zeros, so no product looks at its last slab of K.
 #include "polar.h"
 #include "common.h"
@@ -45,13 +46,13 @@ __device__ __forceinline__ void wait_loads() {
 // A product acc += A[rows][K] * B^T over K in slabs of 32, a (32 TL)^2 tile on 2 x 2 wavefronts of (16 TL)^2.
 //   A: row-major, K contiguous.  B: the same (rows = output columns), or with COLS K x N, N contiguous.
 // Stage: 32 TL rows x 128 bytes of A, then of B; the 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7)
-// (16 lanes then read 16 different bank groups).  COLS: 32 rows (k) of 256 bytes, chunk c of row k at
-// c ^ (4 ((k >> 2) & 3)), read a float at a time without conflicts.
+// (16 lanes then read 16 different bank groups).  COLS: 32 rows (k) of 32 TL columns, read a float at a time
+// without conflicts: TL 2, chunk c of row k at c ^ (4 ((k >> 2) & 3)); TL 1, row k in place k ^ ((k >> 2) & 1) and its
+// chunk c at c ^ (4 ((k >> 3) & 1)).
 // a_rows, b_rows: rows from the tile's first (rows past the operands repeat the last one: their results are not
 // stored); COLS: b_rows is the columns of B from the tile's first, k_rows its rows.
 template <int TL, bool COLS>
 struct TileProduct {
-  static_assert(!COLS || TL == 2, "a row of 64 columns is 256 bytes");
   static constexpr int OPER = TL * 1024;               // floats of one operand in a stage
   static constexpr int STAGES = TL == 1 ? 7 : 3;       // 56 or 48 KiB: two workgroups a CU and more
   static constexpr int LDS = STAGES * 2 * OPER * 4;
@@ -75,7 +76,7 @@ struct TileProduct {
       const uint32_t col = 16 * ((lane & 7) ^ ((row >> 1) & 7));
       a_off[i] = (uint32_t)min(row, a_rows - 1) * (uint32_t)(lda * 4) + col;
       if (COLS) {
-        const int c = (lane & 15) ^ (4 * (blk & 3));
+        const int c = TL == 2 ? (lane & 15) ^ (4 * (blk & 3)) : (lane & 7) ^ (4 * (blk & 1));
         b_off[i] = (uint32_t)(c * 4 < b_rows ? c : 0) * 16;
       } else {
         b_off[i] = (uint32_t)min(row, b_rows - 1) * (uint32_t)(ldb * 4) + col;
@@ -93,15 +94,14 @@ struct TileProduct {
       const int blk = wave * TL + i;
       to_lds(A, (lptr_t)(st + blk * 256), a_off[i], (uint32_t)s * 128);
       if (COLS) {   // (k rows past the last repeat it: A is zero there)
-        const int k = min(s * 32 + blk * 4 + (lane >> 4), k_rows - 1);
+        const int place = blk * 8 + (lane >> 3);
+        const int k = min(s * 32 + (TL == 2 ? blk * 4 + (lane >> 4) : place ^ ((place >> 2) & 1)), k_rows - 1);
         to_lds(B, (lptr_t)(st + OPER + blk * 256), b_off[i] + (uint32_t)k * (uint32_t)(ldb * 4), 0);
       } else {
         to_lds(B, (lptr_t)(st + OPER + blk * 256), b_off[i], (uint32_t)s * 128);
       }
     }
   }
-  // the loads requested so far have landed: the workgroup may end, or use its LDS for another product
-  static __device__ __forceinline__ void drain() { wait_loads<0>(); }
 
   struct Frags { f32x4_t a[2][TL], b[2][TL]; };
   __device__ __forceinline__ void read(Frags& f) {
@@ -116,9 +116,13 @@ struct TileProduct {
 #pragma unroll
       for (int j = 0; j < TL; ++j) {
         if (COLS) {
-          const int c = wn * 32 + j * 16 + r16, at = ((c >> 2) ^ (4 * quad)) * 4 + (c & 3);
+          const int c = wn * 16 * TL + j * 16 + r16;
+          const int at = ((c >> 2) ^ (TL == 2 ? 4 * quad : 4 * (quad >> 1))) * 4 + (c & 3);
 #pragma unroll
-          for (int t = 0; t < 4; ++t) f.b[h][j][t] = st[OPER + (4 * (quad + 4 * h) + t) * 64 + at];
+          for (int t = 0; t < 4; ++t) {
+            const int k = 4 * (quad + 4 * h) + t;
+            f.b[h][j][t] = st[OPER + (TL == 2 ? k * 64 : (k ^ (quad & 1)) * 32) + at];
+          }
         } else {
           f.b[h][j] = *(const f32x4_t*)(st + OPER + (wn * 16 * TL + j * 16 + r16) * 32 + pos * 4);
         }
@@ -190,17 +194,18 @@ struct TileProduct {
 
 struct PolarArgs {
   PolarPlan plan;
-  PolarState* state;     // [max_steps + 1][mats]: state[s] is what step s starts from
+  PolarState* state;     // [max_steps + 1][mats]: state[s] is what step s starts from, for steps carried out
   PolarState* result;    // [mats]: behind the last step carried out
+  int* ended;            // [mats]: that step, a large number before it is known
   int step, mats, r, r8, rk, d, dk;
   float* X;              // [2][mats][r8, dk]
   int64_t flip;          // elements between the two buffers
   float* S;              // [mats][r8, rk]
   float* T;              // (T - I)
-  int gram_tiles, poly_tiles, apply_tiles;
-  float* share;          // [mats][gram_tiles]: the tiles' shares of ||S - I||_F^2
+  int shares;
+  float* share;          // [mats][shares]: the gram tiles' shares of ||S - I||_F^2
   float* rows;           // [mats][2][r8]: sums of |S| and of S^2 along its rows
-  unsigned* queue;       // [product][POLAR_SHARDS drawn, POLAR_SHARDS done, 1 finished][POLAR_SHARD_WORDS], zero
+  int may_be_idle;       // matrices may have ended before this step: its kernels look before they request anything
 };
 
 // lower triangle, row by row: tile t is (i, j <= i)
@@ -211,79 +216,40 @@ __device__ __forceinline__ void triangle(int t, int& i, int& j) {
   j = t - i * (i + 1) / 2;
 }
 
-// sum over the 256 threads in a fixed order, in every thread
-__device__ __forceinline__ float block_sum(float v, float* red) {
+// sum over a wavefront in a fixed order, in every lane
+__device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return ((red[0] + red[1]) + red[2]) + red[3];
-}
-
-// DEV (within the queue's launch): device-scope stores, which go through to where all XCDs see them
-template <bool DEV>
-__device__ __forceinline__ void put4(float* p, f32x4_t v) {
-  if (DEV) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      __hip_atomic_store((unsigned long long*)p + h, (unsigned long long)__float_as_uint(v[2 * h]) |
-                                                         ((unsigned long long)__float_as_uint(v[2 * h + 1]) << 32),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else {
-    *(f32x4_t*)p = v;
-  }
-}
-template <bool DEV, typename V>
-__device__ __forceinline__ void put1(V* p, V v) {
-  if (DEV) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else *p = v;
+  return v;
 }
 
 // four columns col .. of a row of a symmetric matrix [r8, rk], and their mirror images; what lies in
 // the padding columns is written as zero
-template <bool DEV>
 __device__ __forceinline__ void store_sym(float* S, int r8, int rk, int row, int col, bool mirror, f32x4_t v) {
-  if (row < r8 && col < rk) put4<DEV>(S + (int64_t)row * rk + col, col < r8 ? v : f32x4_t{0.f, 0.f, 0.f, 0.f});
+  if (row < r8 && col < rk) *(f32x4_t*)(S + (int64_t)row * rk + col) = col < r8 ? v : f32x4_t{0.f, 0.f, 0.f, 0.f};
   if (mirror && row < rk && col < r8) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) put1<DEV>(S + (int64_t)(col + e) * rk + row, row < r8 ? v[e] : 0.f);
+    for (int e = 0; e < 4; ++e) S[(int64_t)(col + e) * rk + row] = row < r8 ? v[e] : 0.f;
   }
 }
 
-__device__ __forceinline__ PolarState load_state(const PolarState* s) {
-  // (device scope: within the queue's launch it may have been written by another XCD)
-  PolarState v;
-  const int* q = (const int*)s;
-  int* o = (int*)&v;
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(PolarState) / 4); ++i) o[i] = __hip_atomic_load(q + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return v;
-}
-
-__device__ __forceinline__ void store_state(PolarState* s, const PolarState& v) {
-  int* q = (int*)s;
-  const int* o = (const int*)&v;
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(PolarState) / 4); ++i) put1<true>(q + i, o[i]);
-}
-
-// tile `tile` of the S that step `step` starts from
-template <int TL, bool DEV>
-__device__ __forceinline__ void gram_tile(const PolarArgs& p, int step, int mat, int tile, float* smem, float* red) {
+// the S that step p.step starts from
+template <int TL>
+__global__ void __launch_bounds__(256) polar_gram_kernel(const PolarArgs p) {
   constexpr int B = 32 * TL;
+  extern __shared__ float polar_smem[];
+  __shared__ float red[4];
+  const int mat = blockIdx.y, tile = blockIdx.x;
+  if (p.may_be_idle && p.ended[mat] < p.step) return;
   int tm, tn;
   triangle(tile, tm, tn);
-  const float* X = p.X + (step & 1) * p.flip + (int64_t)mat * p.r8 * p.dk;
+  const float* X = p.X + (p.step & 1) * p.flip + (int64_t)mat * p.r8 * p.dk;
   TileProduct<TL, false> prod;
-  prod.start(X + (int64_t)tm * B * p.dk, p.dk, p.r8 - tm * B, X + (int64_t)tn * B * p.dk, p.dk, p.r8 - tn * B, 0, p.dk / 32, smem);
-  if (step > 0) {
-    const PolarState s = load_state(p.state + (int64_t)step * p.mats + mat);
-    if (!s.act || s.last) { prod.drain(); return; }
-  }
+  prod.start(X + (int64_t)tm * B * p.dk, p.dk, p.r8 - tm * B, X + (int64_t)tn * B * p.dk, p.dk, p.r8 - tn * B, 0, p.dk / 32,
+             polar_smem);
   f32x4_t acc[TL][TL] = {};
   prod.run(acc);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = prod.lane, wave = prod.wave;
   float* S = p.S + (int64_t)mat * p.r8 * p.rk;
   float dev = 0.f;
 #pragma unroll
@@ -292,15 +258,78 @@ __device__ __forceinline__ void gram_tile(const PolarArgs& p, int step, int mat,
     for (int j = 0; j < TL; ++j) {
       const int row = tm * B + (wave >> 1) * 16 * TL + i * 16 + (lane & 15);
       const int col = tn * B + (wave & 1) * 16 * TL + j * 16 + 4 * (lane >> 4);
-      store_sym<DEV>(S, p.r8, p.rk, row, col, tm != tn, acc[i][j]);
+      store_sym(S, p.r8, p.rk, row, col, tm != tn, acc[i][j]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float x = acc[i][j][e] - (row == col + e ? 1.f : 0.f);
         if (row < p.r && col + e < p.r) dev = fmaf(x, x, dev);
       }
     }
-  dev = block_sum(dev, red);
-  if (threadIdx.x == 0) put1<DEV>(p.share + (int64_t)mat * p.gram_tiles + tile, tm != tn ? 2.f * dev : dev);
+  dev = wave_sum(dev);
+  if (lane == 0) red[wave] = dev;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    dev = ((red[0] + red[1]) + red[2]) + red[3];
+    p.share[(int64_t)mat * p.shares + tile] = tm != tn ? 2.f * dev : dev;
+  }
+}
+
+// A 16 x 16 block of a row-major operand for the MFMA, straight from the caches.  Four neighbouring lanes load one 64-byte
+// piece, lane l chunk l & 3 of row l >> 2 (where every lane has a row of its own, as the MFMA wants it, the vector cache
+// delivers 16 bytes a clock instead of 61), and the wavefront turns the block round in 1 KiB of LDS of its own: lane
+// (r16, quad) gets the elements 4 quad .. + 3 of row r16.
+__device__ __forceinline__ f32x4_t turn_round(f32x4_t v, f32x4_t* area) {
+  const int l = threadIdx.x & 63, r = l & 15;
+  area[(l & ~3) | ((l & 3) ^ ((l >> 4) & 3))] = v;
+  return area[r * 4 + ((l >> 4) ^ (r >> 2))];
+}
+
+// The same for few tiles: 16x16 ones on 16 wavefronts, which take every 16th slab of 16, eight in flight, and meet in LDS.
+// (32x32 tiles of rank 128 are 20 workgroups for two matrices, and a chain of 64 slabs at d = 2048.)
+__global__ void __launch_bounds__(1024) polar_gram16_kernel(const PolarArgs p) {
+  __shared__ f32x4_t area[2][16][64];
+  const int mat = blockIdx.y, tile = blockIdx.x, lane = threadIdx.x & 63, r16 = lane & 15, quad = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (p.may_be_idle && p.ended[mat] < p.step) return;
+  int tm, tn;
+  triangle(tile, tm, tn);
+  const float* const X = p.X + (p.step & 1) * p.flip + (int64_t)mat * p.r8 * p.dk + 4 * (lane & 3);
+  const float* const xa = X + (int64_t)min(tm * 16 + (lane >> 2), p.r8 - 1) * p.dk;
+  const float* const xb = X + (int64_t)min(tn * 16 + (lane >> 2), p.r8 - 1) * p.dk;
+  f32x4_t acc[4] = {};
+  const int slabs = p.dk / 16;
+  for (int s0 = wave; s0 < slabs; s0 += 16 * 8) {
+    f32x4_t a[8], b[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {   // (past the last slab: it again, not used)
+      const int s = min(s0 + 16 * u, slabs - 1);
+      a[u] = *(const f32x4_t*)(xa + s * 16);
+      b[u] = *(const f32x4_t*)(xb + s * 16);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (s0 + 16 * u < slabs) {
+        const f32x4_t ta = turn_round(a[u], area[0][wave]), tb = turn_round(b[u], area[1][wave]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(tb[e], ta[e], acc[e], 0, 0, 0);
+      }
+  }
+  area[0][wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  __syncthreads();
+  if (wave != 0) return;
+  f32x4_t v = area[0][0][lane];
+#pragma unroll
+  for (int w = 1; w < 16; ++w) v += area[0][w][lane];
+  const int row = tm * 16 + r16, col = tn * 16 + 4 * quad;
+  store_sym(p.S + (int64_t)mat * p.r8 * p.rk, p.r8, p.rk, row, col, tm != tn, v);
+  float dev = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float x = v[e] - (row == col + e ? 1.f : 0.f);
+    if (row < p.r && col + e < p.r) dev = fmaf(x, x, dev);
+  }
+  dev = wave_sum(dev);
+  if (lane == 0) p.share[(int64_t)mat * p.shares + tile] = tm != tn ? 2.f * dev : dev;
 }
 
 // sums of |S| and of S^2 along the rows: the largest of the first bounds the largest eigenvalue, as
@@ -316,18 +345,65 @@ __global__ void __launch_bounds__(256) polar_rows_kernel(const PolarArgs p) {
   if (lane == 0) { p.rows[(int64_t)mat * 2 * p.r8 + row] = a; p.rows[((int64_t)mat * 2 + 1) * p.r8 + row] = q; }
 }
 
-// tile `tile` of T for step `step`
-template <int TL, bool DEV>
-__device__ __forceinline__ void poly_tile(const PolarArgs& p, int step, int mat, int tile, float* smem, float* red) {
+// What the choice of step p.step needs: the state and the first 256 shares, requested ahead of everything else.  Then the
+// choice itself: its coefficients, and from the thread that `writes` the state behind the step.  Every wavefront adds up
+// the shares by itself, so that no LDS is read: loads return in order, and those on their way into LDS need not be
+// waited for.
+__device__ __forceinline__ void request_choice(const PolarArgs& p, int mat, PolarState& s, float (&first)[4]) {
+  const int lane = threadIdx.x & 63;
+  if (p.step > 0) s = p.state[(int64_t)p.step * p.mats + mat];
+  const float* const share = p.share + (int64_t)mat * p.shares;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) first[u] = p.step > 0 && lane + 64 * u < p.shares ? share[lane + 64 * u] : 0.f;
+}
+__device__ __forceinline__ void choose(const PolarArgs& p, int mat, bool writes, PolarState s, const float (&first)[4], float (&c)[3]) {
+  const int lane = threadIdx.x & 63;
+  float fig, sum = ((first[0] + first[1]) + first[2]) + first[3];
+  if (p.step == 0) {
+    const float* rows = p.rows + (int64_t)mat * 2 * p.r8;
+    float most = 0.f;
+    for (int i = lane; i < p.r; i += 64) { most = fmaxf(most, rows[i]); sum += rows[p.r8 + i]; }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o));
+    fig = sqrtf(fminf(most, sqrtf(wave_sum(sum))));
+  } else {
+    for (int i = lane + 256; i < p.shares; i += 64) sum += p.share[(int64_t)mat * p.shares + i];
+    fig = wave_sum(sum);
+  }
+  s = polar_decide(p.plan, p.step, p.r, s, fig, c);
+  if (writes && threadIdx.x == 0) {
+    p.state[(int64_t)(p.step + 1) * p.mats + mat] = s;
+    p.result[mat] = s;
+    p.ended[mat] = s.last ? p.step : 1 << 30;
+  }
+}
+
+// an element of T - I.  In the last steps the three terms of the diagonal, 0.875 - 1.25 + 0.375, cancel: in this order the
+// one rounding that stays is that of their difference.  (|| B B^T - I ||_F / sqrt(r) at 2048 x 2600 rank 512: 1.6e-7; with
+// c1 g rounded by itself 1.8e-7.)
+__device__ __forceinline__ float t_minus_i(const float (&c)[3], float ss, float s, bool diagonal) {
+  return fmaf(c[2], ss, fmaf(c[1], s, diagonal ? c[0] - 1.f : 0.f));
+}
+
+// T - I for step p.step
+template <int TL>
+__global__ void __launch_bounds__(256) polar_poly_kernel(const PolarArgs p) {
   constexpr int B = 32 * TL;
+  extern __shared__ float polar_smem[];
+  const int mat = blockIdx.y, tile = blockIdx.x, lane = threadIdx.x & 63;
+  // (the launch's first tile may have named this very step by now; where there is nothing to do nothing is stored, which
+  // would cost the end of the launch 2 us)
+  if (p.may_be_idle && p.ended[mat] < p.step) return;
+  PolarState s = {};
+  float first[4];
+  request_choice(p, mat, s, first);
   int tm, tn;
   triangle(tile, tm, tn);
   const float* S = p.S + (int64_t)mat * p.r8 * p.rk;
   TileProduct<TL, false> prod;
-  prod.start(S + (int64_t)tm * B * p.rk, p.rk, p.r8 - tm * B, S + (int64_t)tn * B * p.rk, p.rk, p.r8 - tn * B, 0, p.rk / 32, smem);
-  // (everything the tile needs is requested at once: the loads' latency is most of this kernel)
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row0 = tm * B + (wave >> 1) * 16 * TL + (lane & 15), col0 = tn * B + (wave & 1) * 16 * TL + 4 * (lane >> 4);
+  prod.start(S + (int64_t)tm * B * p.rk, p.rk, p.r8 - tm * B, S + (int64_t)tn * B * p.rk, p.rk, p.r8 - tn * B, 0, p.rk / 32,
+             polar_smem);
+  const int row0 = tm * B + (prod.wave >> 1) * 16 * TL + (lane & 15), col0 = tn * B + (prod.wave & 1) * 16 * TL + 4 * (lane >> 4);
   f32x4_t g[TL][TL];
 #pragma unroll
   for (int i = 0; i < TL; ++i)
@@ -335,37 +411,8 @@ __device__ __forceinline__ void poly_tile(const PolarArgs& p, int step, int mat,
     for (int j = 0; j < TL; ++j)
       g[i][j] = row0 + i * 16 < p.r8 && col0 + j * 16 < p.rk ? *(const f32x4_t*)(S + (int64_t)(row0 + i * 16) * p.rk + col0 + j * 16)
                                                              : f32x4_t{0.f, 0.f, 0.f, 0.f};
-  PolarState s = {};
-  float most = 0.f, sum = 0.f;
-  if (step == 0) {
-    const float* rows = p.rows + (int64_t)mat * 2 * p.r8;
-    for (int i = threadIdx.x; i < p.r; i += 256) { most = fmaxf(most, rows[i]); sum += rows[p.r8 + i]; }
-  } else {
-    for (int i = threadIdx.x; i < p.gram_tiles; i += 256) sum += p.share[(int64_t)mat * p.gram_tiles + i];
-    s = load_state(p.state + (int64_t)step * p.mats + mat);
-    if (s.mode == POLAR_ENDED || s.last) {
-      prod.drain();
-      s.mode = POLAR_ENDED; s.act = s.last = 0;
-      if (tile == 0 && threadIdx.x == 0) store_state(p.state + (int64_t)(step + 1) * p.mats + mat, s);
-      return;
-    }
-  }
-  float fig = block_sum(sum, red);
-  if (step == 0) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o));
-    __syncthreads();
-    if (lane == 0) red[wave] = most;
-    __syncthreads();
-    most = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    fig = sqrtf(fminf(most, sqrtf(fig)));
-  }
   float c[3];
-  s = polar_decide(p.plan, step, p.r, s, fig, c);
-  if (tile == 0 && threadIdx.x == 0) {
-    store_state(p.state + (int64_t)(step + 1) * p.mats + mat, s);
-    store_state(p.result + mat, s);
-  }
+  choose(p, mat, tile == 0, s, first, c);
   f32x4_t acc[TL][TL] = {};
   prod.run(acc);
   float* T = p.T + (int64_t)mat * p.r8 * p.rk;
@@ -376,149 +423,127 @@ __device__ __forceinline__ void poly_tile(const PolarArgs& p, int step, int mat,
       const int row = row0 + i * 16, col = col0 + j * 16;
       f32x4_t v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = c[2] * acc[i][j][e] + c[1] * g[i][j][e] + (row == col + e ? c[0] - 1.f : 0.f);
-      store_sym<DEV>(T, p.r8, p.rk, row, col, tm != tn, v);
+      for (int e = 0; e < 4; ++e) v[e] = t_minus_i(c, acc[i][j][e], g[i][j][e], row == col + e);
+      store_sym(T, p.r8, p.rk, row, col, tm != tn, v);
     }
 }
 
-// tile `tile` of the X behind step `step`
-template <bool DEV>
-__device__ __forceinline__ void apply_tile(const PolarArgs& p, int step, int mat, int tile, float* smem) {
-  constexpr int TL = 2;
-  const int tiles_m = (p.r8 + 63) / 64, tm = tile % tiles_m, tn = tile / tiles_m;
+// the X behind step p.step
+template <int TL>
+__global__ void __launch_bounds__(256) polar_apply_kernel(const PolarArgs p) {
+  constexpr int B = 32 * TL;
+  extern __shared__ float polar_smem[];
+  const int mat = blockIdx.y, tiles_m = (p.r8 + B - 1) / B, tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
+  if (p.may_be_idle && p.ended[mat] < p.step) return;
   const int64_t at = (int64_t)mat * p.r8 * p.dk;
-  const float* T = p.T + (int64_t)mat * p.r8 * p.rk + (int64_t)tm * 64 * p.rk;
-  const float* X = p.X + (step & 1) * p.flip + at;
+  const float* T = p.T + (int64_t)mat * p.r8 * p.rk + (int64_t)tm * B * p.rk;
+  const float* X = p.X + (p.step & 1) * p.flip + at;
   TileProduct<TL, true> prod;
-  prod.start(T, p.rk, p.r8 - tm * 64, X + tn * 64, p.dk, p.dk - tn * 64, p.r8, p.rk / 32, smem);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  prod.start(T, p.rk, p.r8 - tm * B, X + tn * B, p.dk, p.dk - tn * B, p.r8, p.rk / 32, polar_smem);
+  const int lane = prod.lane, wave = prod.wave;
   f32x4_t x[TL][TL];
 #pragma unroll
   for (int i = 0; i < TL; ++i)
 #pragma unroll
     for (int j = 0; j < TL; ++j) {
-      const int row = tm * 64 + (wave >> 1) * 32 + i * 16 + (lane & 15);
-      const int col = tn * 64 + (wave & 1) * 32 + j * 16 + 4 * (lane >> 4);
+      const int row = tm * B + (wave >> 1) * 16 * TL + i * 16 + (lane & 15);
+      const int col = tn * B + (wave & 1) * 16 * TL + j * 16 + 4 * (lane >> 4);
       x[i][j] = row < p.r8 && col < p.dk ? *(const f32x4_t*)(X + (int64_t)row * p.dk + col) : f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
-  const PolarState s = load_state(p.state + (int64_t)(step + 1) * p.mats + mat);
-  if (!s.act) { prod.drain(); return; }
   f32x4_t acc[TL][TL] = {};
   prod.run(acc);
-  float* O = p.X + ((step & 1) ^ 1) * p.flip + at;
+  float* O = p.X + ((p.step & 1) ^ 1) * p.flip + at;
 #pragma unroll
   for (int i = 0; i < TL; ++i)
 #pragma unroll
     for (int j = 0; j < TL; ++j) {
-      const int row = tm * 64 + (wave >> 1) * 32 + i * 16 + (lane & 15);
-      const int col = tn * 64 + (wave & 1) * 32 + j * 16 + 4 * (lane >> 4);
-      if (row < p.r8 && col < p.dk) put4<DEV>(O + (int64_t)row * p.dk + col, col < p.d ? x[i][j] + acc[i][j] : f32x4_t{0.f, 0.f, 0.f, 0.f});
+      const int row = tm * B + (wave >> 1) * 16 * TL + i * 16 + (lane & 15);
+      const int col = tn * B + (wave & 1) * 16 * TL + j * 16 + 4 * (lane >> 4);
+      if (row < p.r8 && col < p.dk) *(f32x4_t*)(O + (int64_t)row * p.dk + col) = col < p.d ? x[i][j] + acc[i][j] : f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 }
 
-template <int TL>
-__global__ void __launch_bounds__(256) polar_gram_kernel(const PolarArgs p) {
-  extern __shared__ float polar_smem[];
-  __shared__ float red[4];
-  gram_tile<TL, false>(p, p.step, blockIdx.y, blockIdx.x, polar_smem, red);
-}
-template <int TL>
-__global__ void __launch_bounds__(256) polar_poly_kernel(const PolarArgs p) {
-  extern __shared__ float polar_smem[];
-  __shared__ float red[4];
-  poly_tile<TL, false>(p, p.step, blockIdx.y, blockIdx.x, polar_smem, red);
-}
-__global__ void __launch_bounds__(256) polar_apply_kernel(const PolarArgs p) {
-  extern __shared__ float polar_smem[];
-  apply_tile<false>(p, p.step, blockIdx.y, blockIdx.x, polar_smem);
-}
-
-// Steps p.step .. max_steps - 1 in one launch.  The tiles of a product are cut into chunks, one or more per
-// workgroup of the launch, which the workgroups draw from POLAR_SHARDS counters (their own, then any that has some
-// left; one counter for all of them took 70 us a step more).  A workgroup moves on to the next product when every
-// chunk of this one has been drawn, and starts on it when every chunk is done.  The chunks it waits for are then all
-// in the hands of workgroups that run and wait for earlier products only: every wait ends, however few workgroups
-// are resident.
-// Results go out with device-scope stores that every thread waits for before its chunk is counted done; a
-// workgroup that starts on a product invalidates what its caches hold from before.  Everyone leaves at the
-// first step that finds all matrices ended.
-template <int TL>
-__global__ void __launch_bounds__(256) polar_queue_kernel(const PolarArgs p) {
-  extern __shared__ float polar_smem[];
-  __shared__ float red[4];
-  __shared__ int s_chunk;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int own = (int)blockIdx.x % POLAR_SHARDS;
-  auto load = [](const unsigned* q) { return (int)__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  auto add1 = [](unsigned* q) { return (int)__hip_atomic_fetch_add(q, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  int waiting_for = 0;   // shards of the product before, counted at `before`
-  unsigned *drawn = p.queue, *before = nullptr;
-  for (int step = p.step; step < p.plan.max_steps; ++step)
-    for (int product = 0; product < 3; ++product) {
-      if (product == 2 && step + 1 == p.plan.max_steps) return;   // (no step follows)
-      const int per_mat = product == 0 ? p.poly_tiles : product == 1 ? p.apply_tiles : p.gram_tiles;
-      const int tasks = per_mat * p.mats, size = (tasks + (int)gridDim.x - 1) / (int)gridDim.x, chunks = (tasks + size - 1) / size;
-      unsigned* const done = drawn + POLAR_SHARDS * POLAR_SHARD_WORDS;
-      unsigned* const finished = done + POLAR_SHARDS * POLAR_SHARD_WORDS;   // shards all of whose chunks are done
-      int ahead = 0;   // (the first draw travels while the workgroup waits)
-      if (threadIdx.x == 0) ahead = add1(drawn + own * POLAR_SHARD_WORDS);
-      if (before != nullptr) {
-        if (wave == 0) {
-          while (load(before) < waiting_for) __builtin_amdgcn_s_sleep(8);
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // (the wavefronts share the caches)
-        }
-        __syncthreads();
+// poly and apply in one launch for r <= RK: a workgroup works out the 32 rows of T - I that its 32x32 tile of X' needs
+// (turn_round) and keeps them in LDS.  Up to rank 128 that is 1 MFLOP a workgroup, and a launch less a step, carried out or not.
+template <int RK>
+__global__ void __launch_bounds__(256, 2) polar_poly_apply_kernel(const PolarArgs p) {
+  constexpr int NK = RK / 16, CB = RK / 64, LD = RK + 4;   // slabs of K; blocks of 16 columns of T a wavefront
+  __shared__ __align__(16) float t[32 * LD];
+  __shared__ f32x4_t area[4][64];
+  const int mat = blockIdx.y, tiles_m = (p.r8 + 31) / 32, tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
+  const int lane = threadIdx.x & 63, r16 = lane & 15, quad = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
+  if (p.may_be_idle && p.ended[mat] < p.step) return;
+  PolarState s = {};
+  float first[4];
+  request_choice(p, mat, s, first);
+  const float* S = p.S + (int64_t)mat * p.r8 * p.rk;
+  const float* X = p.X + (p.step & 1) * p.flip + (int64_t)mat * p.r8 * p.dk + tn * 32 + wn * 16;
+  auto at_s = [&](int row, int col) {   // (past rk: zero; past r8: the last row, not used)
+    return col < p.rk ? *(const f32x4_t*)(S + (int64_t)min(row, p.r8 - 1) * p.rk + col) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+  };
+  f32x4_t sa[2][NK], sb[CB][NK], g[2][CB];
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) sa[i][k] = at_s(tm * 32 + i * 16 + (lane >> 2), k * 16 + 4 * (lane & 3));
+#pragma unroll
+    for (int j = 0; j < CB; ++j) sb[j][k] = at_s((wave * CB + j) * 16 + (lane >> 2), k * 16 + 4 * (lane & 3));
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < CB; ++j) g[i][j] = at_s(tm * 32 + i * 16 + r16, (wave * CB + j) * 16 + 4 * quad);
+  const int row = tm * 32 + wm * 16 + r16;   // of X'
+  const f32x4_t old = *(const f32x4_t*)(X + (int64_t)min(row, p.r8 - 1) * p.dk + 4 * quad);
+  f32x4_t x[NK];
+#pragma unroll
+  for (int k = 0; k < NK; ++k)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[k][e] = X[(int64_t)min(k * 16 + 4 * quad + e, p.r8 - 1) * p.dk + r16];   // (T is zero past r8)
+  float c[3];
+  choose(p, mat, blockIdx.x == 0, s, first, c);
+  f32x4_t acc[2][2][CB] = {};
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) sa[i][k] = turn_round(sa[i][k], area[wave]);
+#pragma unroll
+    for (int j = 0; j < CB; ++j) sb[j][k] = turn_round(sb[j][k], area[wave]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j)
+          acc[e & 1][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(sb[j][k][e], sa[i][k][e], acc[e & 1][i][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < CB; ++j) {
+      const int col = (wave * CB + j) * 16 + 4 * quad;
+      f32x4_t v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float sum = acc[0][i][j][e] + acc[1][i][j][e];
+        v[e] = col + e < p.r8 ? t_minus_i(c, sum, g[i][j][e], tm * 32 + i * 16 + r16 == col + e) : 0.f;
       }
-      if (product == 0) {
-        bool all = true;
-        for (int m = 0; m < p.mats; ++m) {
-          const PolarState s = load_state(p.state + (int64_t)step * p.mats + m);
-          all = all && (s.mode == POLAR_ENDED || s.last);
-        }
-        if (all) return;
-      }
-      for (bool first = true;; first = false) {
-        if (wave == 0) {
-          int shard = own, chunk = -1;
-          for (bool look = !first;; look = true) {
-            if (look) {   // a shard with chunks left, the own one first
-              const int l = lane % POLAR_SHARDS, sh = (own + l) % POLAR_SHARDS;
-              const unsigned long long some = __ballot(sh + POLAR_SHARDS * load(drawn + sh * POLAR_SHARD_WORDS) < chunks);
-              if (some == 0) break;
-              shard = (own + (int)__builtin_ctzll(some)) % POLAR_SHARDS;
-            }
-            int v = ahead;
-            if (look && lane == 0) v = add1(drawn + shard * POLAR_SHARD_WORDS);
-            v = shard + POLAR_SHARDS * __builtin_amdgcn_readfirstlane(v);
-            if (v < chunks) { chunk = v; break; }
-          }
-          if (lane == 0) s_chunk = chunk;
-        }
-        __syncthreads();
-        const int chunk = __builtin_amdgcn_readfirstlane(s_chunk);
-        if (chunk < 0) break;
-        for (int t = chunk * size; t < min(tasks, (chunk + 1) * size); ++t) {
-          const int mat = t / per_mat, tile = t % per_mat;
-          if (product == 0) poly_tile<TL, true>(p, step, mat, tile, polar_smem, red);
-          else if (product == 1) apply_tile<true>(p, step, mat, tile, polar_smem);
-          else gram_tile<TL, true>(p, step + 1, mat, tile, polar_smem, red);
-          __syncthreads();   // the LDS is free again
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (threadIdx.x == 0) {
-          const int shard = chunk % POLAR_SHARDS, of = (chunks - shard + POLAR_SHARDS - 1) / POLAR_SHARDS;
-          if (add1(done + shard * POLAR_SHARD_WORDS) == of - 1) add1(finished);
-        }
-      }
-      __syncthreads();   // (s_chunk has been read by all)
-      waiting_for = chunks < POLAR_SHARDS ? chunks : POLAR_SHARDS;
-      before = finished;
-      drawn = finished + POLAR_SHARD_WORDS;
+      *(f32x4_t*)(t + (i * 16 + r16) * LD + col) = v;
     }
+  __syncthreads();
+  f32x4_t y[4] = {};
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+    const f32x4_t a = *(const f32x4_t*)(t + (wm * 16 + r16) * LD + k * 16 + 4 * quad);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[k][e], a[e], y[e], 0, 0, 0);
+  }
+  const f32x4_t v = old + ((y[0] + y[1]) + (y[2] + y[3]));
+  const int col = tn * 32 + wn * 16 + 4 * quad;
+  float* O = p.X + ((p.step & 1) ^ 1) * p.flip + (int64_t)mat * p.r8 * p.dk;
+  if (row < p.r8) *(f32x4_t*)(O + (int64_t)row * p.dk + col) = col < p.d ? v : f32x4_t{0.f, 0.f, 0.f, 0.f};
 }
-
-constexpr int POLAR_QUEUE_WGS = 512;   // (256: a step of rank 512 takes a third longer)
 
 __global__ void __launch_bounds__(256) polar_settle_kernel(const PolarState* state, float* X, int64_t flip, int64_t n) {
   if (!state[blockIdx.y].parity) return;
@@ -538,49 +563,57 @@ PolarWs make_polar_ws(int mats, int r, int d) {
   w.r8 = round_up(r, 8);
   w.rk = round_up(r, 32);
   w.dk = round_up(d, 32);
-  // triangles on 64x64 tiles once those fill the machine (from a rank of about 1000 on)
-  w.side = tri_tiles(w.r8, 64) * mats >= 256 ? 64 : 32;
-  w.tri = tri_tiles(w.r8, w.side);
+  // X X^T on 64x64 tiles once those fill the machine (from a rank of about 1000 on), on 16x16 ones where those are few; up
+  // to 512 of them where the reduction is long.  Both sides (us, a factorisation of a flat / an i^-2 remainder, two matrices,
+  // 32x32 / 16x16): 4096 x 10675 rank 256, 272 tiles, 765 / 733 and 1156 / 1046; 2048 x 7944 rank 300, 380 tiles, 473 / 464 and
+  // 755 / 707; 512 x 1455 rank 300 379 / 392.
+  const int t16 = tri_tiles(w.r8, 16) * mats;
+  w.side = tri_tiles(w.r8, 64) * mats >= 256 ? 64 : t16 <= (d >= 1024 ? 512 : 256) ? 16 : 32;
+  w.tri = tri_tiles(w.side == 16 ? w.rk : w.r8, w.side);   // (they write the padding columns of S)
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
   w.nx = (int64_t)w.r8 * w.dk;
   w.off_x = take((size_t)2 * mats * w.nx * 4);
   w.off_s = take((size_t)mats * w.r8 * w.rk * 4);
   w.off_t = take((size_t)mats * w.r8 * w.rk * 4);
-  const PolarPlan plan = polar_plan(r, d);
-  const int queued = plan.max_steps - std::min(polar_launched(plan), plan.max_steps);
-  w.queue_words = 3 * queued * (2 * POLAR_SHARDS + 1) * POLAR_SHARD_WORDS;
-  w.off_queue = take((size_t)w.queue_words * 4);
   w.off_share = take((size_t)mats * w.tri * 4);
   w.off_rows = take((size_t)mats * 2 * w.r8 * 4);
-  w.off_state = take((size_t)(plan.max_steps + 2) * mats * sizeof(PolarState));
+  w.off_state = take((size_t)(polar_plan(r, d).max_steps + 2) * mats * sizeof(PolarState));
+  w.off_ended = take((size_t)mats * 4);
   w.bytes = off;
   return w;
 }
 
-template <int TL>
-static int launch_polar_tl(PolarArgs p, hipStream_t st) {
-  constexpr int lds1 = TileProduct<TL, false>::LDS, lds2 = TileProduct<2, true>::LDS;
-  const dim3 blk(256), g_tri(p.gram_tiles, p.mats), g_apply(p.apply_tiles, p.mats);
+// GRAM: side of the tiles of S, 16 to 64; FUSED: 0, or the rank up to which poly and apply are one launch
+template <int GRAM, int TA, int FUSED>
+static int launch_polar_as(PolarArgs p, hipStream_t st) {
+  constexpr int TL = GRAM == 64 ? 2 : 1, lds1 = TileProduct<TL, false>::LDS, lds2 = TileProduct<TA, true>::LDS;
+  const dim3 blk(256), g_gram(p.shares, p.mats), g_poly(tri_tiles(p.r8, 32 * TL), p.mats);
+  const dim3 g_apply((p.r8 + 32 * TA - 1) / (32 * TA) * ((p.dk + 32 * TA - 1) / (32 * TA)), p.mats);
   float coef[POLAR_MAX_STEPS][3];
   if (p.plan.fixed) polar_steps(p.r, coef);
-  const int launched = std::min(polar_launched(p.plan), p.plan.max_steps);
-  hipLaunchKernelGGL(polar_gram_kernel<TL>, g_tri, blk, lds1, st, p);
+  auto gram = [&] {
+    if constexpr (GRAM == 16) hipLaunchKernelGGL(polar_gram16_kernel, g_gram, dim3(1024), 0, st, p);
+    else hipLaunchKernelGGL(polar_gram_kernel<TL>, g_gram, blk, lds1, st, p);
+  };
+  gram();
   hipLaunchKernelGGL(polar_rows_kernel, dim3((p.r8 + 3) / 4, p.mats), blk, 0, st, p);
-  for (int s = 0; s < launched; ++s) {
+  for (int s = 0; s < p.plan.max_steps; ++s) {
     p.step = s;
+    p.may_be_idle = !p.plan.fixed && s >= POLAR_LEAST_STEPS;
     if (p.plan.fixed) std::copy(coef[s], coef[s] + 3, p.plan.coef);
-    hipLaunchKernelGGL(polar_poly_kernel<TL>, g_tri, blk, lds1, st, p);
-    hipLaunchKernelGGL(polar_apply_kernel, g_apply, blk, lds2, st, p);
+    if constexpr (FUSED > 0) {
+      hipLaunchKernelGGL(polar_poly_apply_kernel<FUSED>, g_apply, blk, 0, st, p);
+    } else {
+      hipLaunchKernelGGL(polar_poly_kernel<TL>, g_poly, blk, lds1, st, p);
+      hipLaunchKernelGGL(polar_apply_kernel<TA>, g_apply, blk, lds2, st, p);
+    }
     p.step = s + 1;
-    if (s + 1 < p.plan.max_steps) hipLaunchKernelGGL(polar_gram_kernel<TL>, g_tri, blk, lds1, st, p);
+    p.may_be_idle = !p.plan.fixed && s + 1 >= POLAR_LEAST_STEPS;
+    if (s + 1 < p.plan.max_steps) gram();
     if (hipGetLastError() != hipSuccess) return -1;
   }
-  if (launched < p.plan.max_steps) {
-    const int tasks = std::max(p.gram_tiles, p.apply_tiles) * p.mats;
-    hipLaunchKernelGGL(polar_queue_kernel<TL>, dim3(std::min(POLAR_QUEUE_WGS, tasks)), blk, std::max(lds1, lds2), st, p);
-  }
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  return 0;
 }
 
 int launch_polar(const PolarWs& w, char* ws, const PolarState** state, hipStream_t st) {
@@ -589,14 +622,25 @@ int launch_polar(const PolarWs& w, char* ws, const PolarState** state, hipStream
   p.mats = w.mats; p.r = w.r; p.r8 = w.r8; p.rk = w.rk; p.d = w.d; p.dk = w.dk;
   p.X = (float*)(ws + w.off_x); p.flip = w.mats * w.nx;
   p.S = (float*)(ws + w.off_s); p.T = (float*)(ws + w.off_t);
-  p.gram_tiles = p.poly_tiles = w.tri;
-  p.apply_tiles = (w.r8 + 63) / 64 * ((w.dk + 63) / 64);
+  p.shares = w.tri;
   p.share = (float*)(ws + w.off_share); p.rows = (float*)(ws + w.off_rows);
-  p.queue = (unsigned*)(ws + w.off_queue);
   p.result = (PolarState*)(ws + w.off_state);
   p.state = p.result + w.mats;
+  p.ended = (int*)(ws + w.off_ended);
   *state = p.result;
-  return w.side == 64 ? launch_polar_tl<2>(p, st) : launch_polar_tl<1>(p, st);
+  if (w.side == 64) return launch_polar_as<64, 2, 0>(p, st);
+  // poly and apply together while the workgroups (four of rank 64 a CU, two of rank 128) are one round of the machine: us as
+  // above, apart / together, 512 x 1455 rank 64 224 / 186 and 287 / 255, 1024 x 3972 rank 128 292 / 258 and 398 / 401, 4096 x 10675
+  // rank 64 (512 workgroups) 513 / 485 and 635 / 613, 2048 x 7944 rank 128 (512) 344 / 329 and 460 / 480
+  const int wgs = (w.r8 + 31) / 32 * (w.dk / 32) * w.mats;
+  // the last product on 32x32 tiles where 64x64 ones do not fill the machine (512 x 1455 rank 300: 412 -> 373)
+  const bool small = (w.r8 + 63) / 64 * ((w.dk + 63) / 64) * w.mats < 256;
+  if (w.side == 16) {
+    if (w.r <= 64 && wgs <= 1024) return launch_polar_as<16, 1, 64>(p, st);
+    if (w.r > 64 && w.r <= 128 && wgs <= 512) return launch_polar_as<16, 1, 128>(p, st);
+    return small ? launch_polar_as<16, 1, 0>(p, st) : launch_polar_as<16, 2, 0>(p, st);
+  }
+  return small ? launch_polar_as<32, 1, 0>(p, st) : launch_polar_as<32, 2, 0>(p, st);
 }
 
 int launch_polar_settle(const PolarWs& w, char* ws, const PolarState* state, hipStream_t st) {

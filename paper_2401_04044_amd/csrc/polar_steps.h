@@ -122,18 +122,29 @@ inline int polar_steps(int r, float (*coef)[3]) {
 //         (15 x - 10 x^3 + 3 x^5) / 8.  Slopes from 2.9 on are not safe: the inner maximum comes
 //         too near the repelling fixed point sqrt((a - 1) / (a - 1.5)); 2.7: 1.10 and 1.19.
 // The iteration ends with the cubic step that starts from D <= POLAR_DONE: no value is further than 2.3e-3
-// from 1 before it, so none further than 3e-8 after it.  max_steps is what the least value that polar_steps
-// takes to 1 needs, wherever the bulk lies; past it (values smaller still, or zero) nothing is promised, as there.
+// from 1 before it, so none further than 3e-8 after it.
+//
+// A step of FINISH takes a small value up by 2.7 where GROW takes it up by 3.6, and D does not show how small the values
+// are that it counts.  So the climbs after j growth steps are numbered: when no more of them are left (climbs[j]) than the
+// least value that polar_steps takes to 1 can afford, growth is resumed (regrow[j] steps, which spread the values
+// at 1 over [0.5, 1] again), and RANGE1, RANGE2 and one cubic step end it.  max_steps is then at most two more than the
+// steps of polar_steps (rank 512: 15 and 13; rank 200: 14 and 12, by climbing alone 16), whatever the spectrum; what was left at
+// the end (values smaller still, or zero) is promised nothing, as there.
 constexpr float POLAR_BULK = 0.35f, POLAR_DONE = 2e-5f;
-enum { POLAR_GROW = 0, POLAR_RANGE2 = 1, POLAR_FINISH = 2, POLAR_ENDED = 3 };
+constexpr double POLAR_CLIMB_ROOM = 1.12;   // (the climbs' inner maximum is 1.10)
+constexpr int POLAR_LEAST_STEPS = 4;   // GROW, RANGE1, RANGE2 and a last one (a fixed plan has more)
+constexpr int POLAR_MAX_GROW = 16, POLAR_NO_LIMIT = 15;
+enum { POLAR_GROW = 0, POLAR_RANGE2 = 1, POLAR_FINISH = 2, POLAR_ENDED = 3, POLAR_REGROW = 4 };
 struct PolarPlan {
   float grow[3], range1[3], range2[3], climb[3], cubic[3];   // grow: for values up to 1, into (0, 1]
   int max_grow, max_steps;
+  unsigned long long climbs, regrow;   // four bits for each j below POLAR_MAX_GROW
   int fixed;                          // no choice: the max_steps steps of polar_steps, this launch's is coef
   float coef[3];
 };
 struct PolarState {
-  int mode, grown;
+  int mode;
+  int grown;    // growth steps; from bit 8 on climbs, or growth steps resumed
   int parity;   // which of the two buffers holds X
   int act;      // the step is carried out
   int last;     // and is the last
@@ -171,16 +182,38 @@ inline PolarPlan polar_plan(int r, int d) {
   const double g = POLAR_GROW_ROOM, least = 1.0 / (1024.0 * r);
   const auto grown = [&](double x) { return quintic(grow, x / g); };
   for (double x = least; x < 0.5; x = grown(x)) ++p.max_grow;
-  for (int j = 1; j <= std::max(p.max_grow, 1); ++j) {
+  p.max_grow = std::min(std::max(p.max_grow, 1), POLAR_MAX_GROW);   // (12 at rank 8192)
+  const auto behind = [&](int j, int climbs) {   // j growth steps, both range steps, some climbs
     double x = least;
     for (int i = 0; i < j; ++i) x = grown(x);
     x = quintic(r2, quintic(r1, x));
+    for (int i = 0; i < climbs; ++i) x = quintic(k, x);
+    return x;
+  };
+  // steps in all if nothing but climbs follow, for the least value; and one more (D adds up several that are nearly done)
+  const auto climbing = [&](int j) {
+    double x = behind(j, 0);
     int n = j + 2;
     for (double dev = (1 - x * x) * (1 - x * x); dev > POLAR_DONE / 2; dev = (1 - x * x) * (1 - x * x), ++n)
       x = quintic(dev > 0.5 ? k : f, x);
-    p.max_steps = std::max(p.max_steps, n + 1);
+    return n + 2;
+  };
+  const auto resumed = [&](int j, int climbs) {   // growth steps after some climbs
+    int n = 1;
+    for (double x = grown(behind(j, climbs) / POLAR_CLIMB_ROOM); x < 0.5; x = grown(x)) ++n;
+    return n;
+  };
+  p.max_steps = p.max_grow + 3;
+  for (int j = 1; j < p.max_grow; ++j) p.max_steps = std::max(p.max_steps, std::min(climbing(j), j + 5 + resumed(j, 0)));
+  for (int j = 1; j < p.max_grow; ++j) {
+    int c = POLAR_NO_LIMIT, g = 0;
+    if (climbing(j) > p.max_steps) {
+      for (c = 0; j + 5 + c + 1 + resumed(j, c + 1) <= p.max_steps;) ++c;
+      g = resumed(j, c);
+    }
+    p.climbs |= (unsigned long long)c << (4 * j);
+    p.regrow |= (unsigned long long)g << (4 * j);
   }
-  p.max_grow = std::max(p.max_grow, 1);
   return p;
 }
 
@@ -194,6 +227,7 @@ FFS_HOST_DEVICE inline PolarState polar_decide(const PolarPlan& p, int step, int
     return s;
   }
   if (step == 0) s.mode = POLAR_GROW, s.grown = 0, s.parity = 0;
+  const int j = s.grown & 255, count = s.grown >> 8;
   if (p.fixed) {
     for (int i = 0; i < 3; ++i) c[i] = p.coef[i];
     s.act = 1;
@@ -201,13 +235,13 @@ FFS_HOST_DEVICE inline PolarState polar_decide(const PolarPlan& p, int step, int
     s.parity ^= 1;
     return s;
   }
-  // (the coefficients are picked by value: with an address into the plan every thread of the kernel kept a copy of its
-  // arguments in scratch memory, 256 bytes: poly at rank 512 18 us instead of 11, in every launch, carried out or not)
+  // (the coefficients are picked by value: an address into the plan or an index that is not constant would put a copy of
+  // the kernel's arguments in every thread's scratch memory)
   int pick = 4;
   float end = 1.f;
   bool done = false;
   if (s.mode == POLAR_GROW) {
-    if (step > 0 && (fig <= POLAR_BULK * (float)r || s.grown >= p.max_grow)) {
+    if (step > 0 && (fig <= POLAR_BULK * (float)r || j >= p.max_grow)) {
       pick = 1;
       s.mode = POLAR_RANGE2;
     } else {
@@ -219,9 +253,29 @@ FFS_HOST_DEVICE inline PolarState polar_decide(const PolarPlan& p, int step, int
   } else if (s.mode == POLAR_RANGE2) {
     pick = 2;
     s.mode = POLAR_FINISH;
-  } else {
-    done = fig <= POLAR_DONE;
-    if (fig > 0.5f) pick = 3;
+  } else if (s.mode == POLAR_REGROW) {
+    if (count >= (int)(p.regrow >> (4 * j) & 15)) {
+      pick = 1;
+      s.mode = POLAR_RANGE2;
+      s.grown = p.max_grow;
+    } else {
+      pick = 0;
+      end = (float)POLAR_GROW_ROOM;
+      s.grown += 256;
+    }
+  } else if (j >= p.max_grow || fig <= POLAR_DONE) {
+    done = true;
+  } else if (fig > 0.5f) {
+    const int most = (int)(p.climbs >> (4 * j) & 15);
+    if (most == POLAR_NO_LIMIT || count < most) {
+      pick = 3;
+      s.grown += 256;
+    } else {
+      pick = 0;
+      end = (float)(POLAR_GROW_ROOM * POLAR_CLIMB_ROOM);
+      s.mode = POLAR_REGROW;
+      s.grown = j + 256;
+    }
   }
   const float e = 1.f / end, e2 = e * e;
   const float scale[3] = {e, e * e2, e * e2 * e2};

@@ -1,5 +1,5 @@
-"""The polar iteration on the device where it leaves the steps launched one by one (the work queue), where the
-matrices of a layer end at different steps, and on 64x64 tiles of the symmetric products."""
+"""The polar iteration on the device: remainders that decay and so take many steps, matrices of a layer that end at different
+steps, and every form that its products are launched in."""
 import numpy as np
 import pytest
 import torch
@@ -58,3 +58,47 @@ def test_projection_of_three_terms_in_one_reduction(ff, cfg):
     for p, q in (("P1", "Q1"), ("Pg", "Qg"), ("P2", "Q2")):
         if p in want:
             assert relf(got[p] @ got[q], want[p] @ want[q]) < 6e-3, p
+
+
+# || B B^T - I ||_F / sqrt(r): what a row of B lacks of unit length and of being orthogonal to the others.  Rounding the last sum
+# of each element takes a row's length by up to 2^-25; rounding T - I, and the sums of the last X X^T behind it, by as much
+# each; the off-diagonal elements add as much again: 4 x 2^-24 = 2.4e-7.  Where the rows' energy lies in few columns (decaying
+# remainders) fewer roundings average out: 6 x 2^-24.  At 2048 x 2600 rank 512 the iteration has 1.7e-7 (3.0e-7 with i^-1);
+# with one accumulator a tile, a chain of d / 4 terms, it had 6.8e-7.
+ORTHONORMAL, ORTHONORMAL_DECAY = 4 * 2.0 ** -24, 6 * 2.0 ** -24
+
+
+def off_orthonormal(b):
+    b = b.astype(np.float64)
+    return float(np.linalg.norm(b @ b.T - np.eye(len(b))) / np.sqrt(len(b)))
+
+
+# every form that the products are launched in: tiles of X X^T of 16, 32 and 64, the other two products together (rank 64,
+# rank 128) and apart, the last one on 32x32 and on 64x64 tiles; ranks and widths that no tile divides
+FORMS = [(C2, 72, 300, 8), (C3, 264, 400, 33), (C2, 520, 700, 64), (C2, 1032, 1200, 65), (C2, 2056, 2300, 128), (C3, 640, 900, 130),
+         (C2, 1024, 1400, 256), (C2, 1000, 1300, 256), (C2, 4104, 2300, 250), (C3, 360, 900, 175), (C2, 8, 40, 1)]
+
+
+@pytest.mark.parametrize("base,d,n,r", FORMS, ids=[f"{c[0].act}_d{c[1]}_n{c[2]}_r{c[3]}" for c in FORMS])
+def test_every_form_of_the_products(ff, base, d, n, r):
+    """W1 flat, W2 with singular values i^-3/2 (the matrices of the layer end at different steps): the basis orthonormal, the
+    products those of the oracle in fp64, and every call like the first."""
+    cfg = reduced(base, d, n, rank=r)
+    cfg = cfg.__class__(**{**cfg.__dict__, "dtype": "f32"})
+    L = {k: v.copy() if isinstance(v, np.ndarray) else v for k, v in wl.make_layer(cfg).items()}
+    L["W2"] = (L["W2"] * (np.arange(1, d + 1) ** -1.5)).astype(np.float32)
+    idx, Ld = L["planted"], layer_to_dev(L, "f32")
+    desc = desc_for(ff, cfg, "lowrank")
+    args = (desc, Ld["W1"], Ld["Wg"], Ld["W2"], torch.from_numpy(idx).cuda())
+    ws = torch.full((int(ff.workspace_bytes(desc, ff.WS_FACTORIZE, 0)),), 0xA5, dtype=torch.uint8, device="cuda")
+    fd = ff.factorize_remainder(*args, seed=3, workspace=ws)
+    again = ff.factorize_remainder(*args, seed=3, workspace=ws)
+    torch.cuda.synchronize()
+    assert all(torch.equal(v, again[k]) for k, v in fd.items() if v is not None)
+    got = {k: host(v) for k, v in fd.items() if v is not None}
+    want = orc.factorize_remainder(L["W1"], L["W2"], L["Wg"], idx, cfg.rank, seed=3)
+    for b, most in ((got["P1"].T, ORTHONORMAL), (got.get("Pg", got["P1"]).T, ORTHONORMAL), (got["Q2"], ORTHONORMAL_DECAY)):
+        assert off_orthonormal(b) < most, off_orthonormal(b)
+    for p, q in (("P1", "Q1"), ("Pg", "Qg"), ("P2", "Q2")):
+        if p in want:
+            assert relf(got[p] @ got[q], want[p] @ want[q]) < 1e-4, p

@@ -16,6 +16,7 @@ def lib(tmp_path_factory):
     src, so = d / "plan.cpp", d / "plan.so"
     src.write_text('#include "polar_steps.h"\nusing namespace ffsplit;\n'
                    'extern "C" int max_steps(int r) { return polar_plan(r, 2 * r).max_steps; }\n'
+                   'extern "C" int fixed_steps(int r) { float c[POLAR_MAX_STEPS][3]; return polar_steps(r, c); }\n'
                    'extern "C" void decide(int r, int step, int* s, float fig, float* c) {\n'
                    '  float k[3]; PolarState t = {s[0], s[1], s[2], s[3], s[4]};\n'
                    '  t = polar_decide(polar_plan(r, 2 * r), step, r, t, fig, k);\n'
@@ -115,3 +116,25 @@ def test_fp32_iteration_takes_few_steps_and_ends_orthonormal(lib):
                     lambda: float(((st["S"] - np.eye(r)) ** 2).sum()))
         assert n <= most, n
         assert np.abs(st["S"] - np.eye(r)).max() < 1e-5
+
+
+@pytest.mark.parametrize("r", [8, 33, 64, 100, 128, 200, 300, 400, 512, 800, 1024, 1380, 2000, 5120])
+def test_no_spectrum_takes_many_more_steps_than_the_fixed_ones(lib, r):
+    """At most two more than the steps that take any spectrum to 1: a few values that are left far behind when the bulk
+    is past 0.5 must not be climbed after one by one (16 steps instead of 13 at rank 512)."""
+    least = 1.0 / (1024 * r)
+    assert lib.max_steps(r) <= lib.fixed_steps(r) + 2
+    rng = np.random.default_rng(r)
+    for share in (0.02, 0.1, 0.2, 0.34):
+        for low in (least, 3 * least, 30 * least, 1e-2):
+            n = max(1, int(share * r))
+            x = np.r_[rng.uniform(0.5, 1.0, r - n), np.full(n, low * np.sqrt(r))]
+            state = {"x": np.maximum(x / np.linalg.norm(x), least)}
+
+            def apply(c):
+                v = state["x"]
+                state["x"] = v * (c[0] + v * v * (c[1] + v * v * c[2])) * (1 + 1e-6 * np.cos(np.arange(r)))
+                assert (state["x"] > 0).all() and state["x"].max() < 1.2
+
+            iterate(lib, r, apply, lambda: min(1.0, 1.5 * state["x"].max()), lambda: float(((1 - state["x"] ** 2) ** 2).sum()))
+            assert np.abs(state["x"] - 1).max() < 3e-6, (share, low, np.abs(state["x"] - 1).max())
