@@ -102,3 +102,16 @@ def test_every_form_of_the_products(ff, base, d, n, r):
     for p, q in (("P1", "Q1"), ("Pg", "Qg"), ("P2", "Q2")):
         if p in want:
             assert relf(got[p] @ got[q], want[p] @ want[q]) < 1e-4, p
+
+
+@pytest.mark.parametrize("d,r,decay", [(2048, 512, 0.0), (2048, 512, 1.0), (1608, 800, 0.0), (768, 768, 0.0), (1024, 128, 0.0)])
+def test_basis_is_as_orthonormal_as_fp32_sums_allow(ff, d, r, decay):
+    cfg = reduced(C2, d, 2600, rank=r)
+    cfg = cfg.__class__(**{**cfg.__dict__, "dtype": "f32"})
+    L = {k: v.copy() if isinstance(v, np.ndarray) else v for k, v in wl.make_layer(cfg).items()}
+    L["W2"] = (L["W2"] * (np.arange(1, d + 1) ** -decay)).astype(np.float32)
+    Ld = layer_to_dev(L, "f32")
+    fd = ff.factorize_remainder(desc_for(ff, cfg, "lowrank"), Ld["W1"], Ld["Wg"], Ld["W2"], torch.from_numpy(L["planted"]).cuda(), seed=5)
+    torch.cuda.synchronize()
+    assert off_orthonormal(host(fd["P1"]).T) < ORTHONORMAL
+    assert off_orthonormal(host(fd["Q2"])) < (ORTHONORMAL_DECAY if decay else ORTHONORMAL), off_orthonormal(host(fd["Q2"]))
