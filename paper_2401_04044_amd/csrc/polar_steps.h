@@ -5,6 +5,7 @@
 #pragma once
 #include <algorithm>
 #include <math.h>
+#include <stdint.h>
 #include <utility>
 
 #ifdef __HIPCC__
@@ -150,11 +151,14 @@ struct PolarState {
   int last;     // and is the last
 };
 
-// Matrices [r, d].  A flat sketch that is nearly square needs most of the steps anyway: from 2 r > d on those of
-// polar_steps are taken, of which there are two or three fewer (768 x 768: 13 instead of 15).
+// Matrices [r, d].  The least value of a flat sketch is 1 - sqrt(r / d) of the largest, and of a square one far below: from
+// 10 r > 9 d on the steps of polar_steps are taken, of which there are two fewer.  us a factorisation of two matrices, singular
+// values i^0 / i^-1/2 / i^-1, fixed steps and chosen ones: 512 x 1986 rank 456 438 and 371 / 389 / 426, rank 512 493 and 468 / 491 /
+// 558; 1024 x 3972 rank 520 797 and 509 / 511 / 596, rank 816 1190 and 775 / 849 / 1068, rank 920 1347 and 951 / 1037 / 1204, rank
+// 1024 1680 and 1925; 2048 x 7944 rank 1432 5206 and 2611 / 3268 / 3925, rank 1840 7825 and 4820 / 5319 / 6849, rank 2048 9340 and 10610.
 inline PolarPlan polar_plan(int r, int d) {
   PolarPlan p = {};
-  if (2 * r > d) {
+  if (10 * (int64_t)r > 9 * (int64_t)d) {
     float coef[POLAR_MAX_STEPS][3];
     p.fixed = 1;
     p.max_steps = polar_steps(r, coef);

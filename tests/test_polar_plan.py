@@ -16,6 +16,7 @@ def lib(tmp_path_factory):
     src, so = d / "plan.cpp", d / "plan.so"
     src.write_text('#include "polar_steps.h"\nusing namespace ffsplit;\n'
                    'extern "C" int max_steps(int r) { return polar_plan(r, 2 * r).max_steps; }\n'
+                   'extern "C" int is_fixed(int r, int d) { return polar_plan(r, d).fixed; }\n'
                    'extern "C" int fixed_steps(int r) { float c[POLAR_MAX_STEPS][3]; return polar_steps(r, c); }\n'
                    'extern "C" void decide(int r, int step, int* s, float fig, float* c) {\n'
                    '  float k[3]; PolarState t = {s[0], s[1], s[2], s[3], s[4]};\n'
@@ -138,3 +139,24 @@ def test_no_spectrum_takes_many_more_steps_than_the_fixed_ones(lib, r):
 
             iterate(lib, r, apply, lambda: min(1.0, 1.5 * state["x"].max()), lambda: float(((1 - state["x"] ** 2) ** 2).sum()))
             assert np.abs(state["x"] - 1).max() < 3e-6, (share, low, np.abs(state["x"] - 1).max())
+
+
+@pytest.mark.parametrize("share,decay", [(0.5, 0.0), (0.75, 0.0), (0.9, 0.0), (0.9, 0.5), (0.9, 1.0)])
+def test_chosen_steps_are_no_more_than_the_fixed_ones_where_they_are_taken(lib, share, decay):
+    """Gaussian sketches of r = share d rows: up to nine tenths of d the steps are chosen, and there are no more of them."""
+    rng = np.random.default_rng(7)
+    d = 400
+    r = int(share * d)
+    assert not lib.is_fixed(r, d) and lib.is_fixed(d, d) and lib.is_fixed(int(0.91 * d), d)
+    Y = rng.standard_normal((r, d)) * np.arange(1, d + 1) ** -decay
+    Y /= np.linalg.norm(Y)
+    G = Y @ Y.T
+    state = {"x": np.linalg.svd(Y, compute_uv=False)}
+
+    def apply(c):
+        v = state["x"]
+        state["x"] = v * (c[0] + v * v * (c[1] + v * v * c[2]))
+
+    n = iterate(lib, r, apply, lambda: float(np.sqrt(min(np.abs(G).sum(1).max(), np.linalg.norm(G)))),
+                lambda: float(((1 - state["x"] ** 2) ** 2).sum()))
+    assert np.abs(state["x"] - 1).max() < 3e-6 and n <= lib.fixed_steps(r), (n, lib.fixed_steps(r))
