@@ -42,10 +42,10 @@ __device__ __forceinline__ int block_scan_1024(int v, int* wsum) {
   return before + inc - v;
 }
 
-template <int KPT>
 __global__ void __launch_bounds__(1024) select_compact_kernel(const float* scores, int n, int k, uint32_t* keys,
                                                               uint32_t* cand_key, int32_t* cand_idx, int32_t* perm,
                                                               int32_t* nan_flag) {
+  constexpr int KPT = 32;
   __shared__ int wsum[16];
   __shared__ int csum[2][16];
   __shared__ int s_nan;
@@ -239,15 +239,17 @@ __global__ void __launch_bounds__(1024) select_rest_kernel(const int32_t* rank, 
 
 // Ranking by counting grows with n^2, the search on one CU with n.  Both sides (us, a calibration call of 256 tokens
 // and width 512 with the selection, search / counting): 1500 scores 55.0 / 45.3, 8192 (4096 tokens, width 2048)
-// 165 / 142, 16384 88.7 / 63.8, 20480 92.3 / 84.8, 24576 102.3 / 95.4.
-constexpr int SELECT_COUNT_MAX_N = 24576;
+// 165 / 142, 16384 88.7 / 63.8, 20480 92.3 / 84.8, 24576 102.3 / 95.4.  The selection alone, with the permutation, for any k
+// from 1 on: 8192 32 / 17, 16384 53 / 30, 24576 61 / 57.  With k = 0 there is nothing to search for (17 at any size): 8192
+// 16.7 / 16.9, 10240 16.7 / 20.8, 24576 18.1 / 56.5.
+constexpr int SELECT_COUNT_MAX_N = 24576, SELECT_COUNT_MAX_N_OF_NONE = 8192;
 
 size_t select_workspace_bytes(int d_ff) { return (size_t)12 * (size_t)(d_ff > 0 ? d_ff : 1) + 256; }
 
 int launch_select(const float* scores, int d_ff, int k, int32_t* idx, int32_t* perm, int32_t* nan_flag, void* ws,
                   hipStream_t st) {
   if (d_ff <= 0) return 0;
-  if (d_ff <= SELECT_COUNT_MAX_N) {
+  if (d_ff <= (k > 0 ? SELECT_COUNT_MAX_N : SELECT_COUNT_MAX_N_OF_NONE)) {
     int32_t* rank = (int32_t*)ws;
     hipLaunchKernelGGL(select_count_kernel, dim3((d_ff + 31) / 32), dim3(1024), 0, st, scores, d_ff, k, rank, idx, perm, nan_flag);
     if (perm && k < d_ff)
@@ -257,13 +259,8 @@ int launch_select(const float* scores, int d_ff, int k, int32_t* idx, int32_t* p
   uint32_t* keys = (uint32_t*)ws;
   uint32_t* cand_key = keys + d_ff;
   int32_t* cand_idx = (int32_t*)(cand_key + d_ff);
-  // registers for the whole run where it is short (the search makes 33 passes over them)
-  if (d_ff <= 8 * 1024)
-    hipLaunchKernelGGL(select_compact_kernel<8>, dim3(1), dim3(1024), 0, st, scores, d_ff, k, keys, cand_key,
-                       cand_idx, perm, nan_flag);
-  else
-    hipLaunchKernelGGL(select_compact_kernel<32>, dim3(1), dim3(1024), 0, st, scores, d_ff, k, keys, cand_key,
-                       cand_idx, perm, nan_flag);
+  hipLaunchKernelGGL(select_compact_kernel, dim3(1), dim3(1024), 0, st, scores, d_ff, k, keys, cand_key, cand_idx, perm,
+                     nan_flag);
   if (hipGetLastError() != hipSuccess) return -1;
   if (k > 0) {
     hipLaunchKernelGGL(select_rank_kernel, dim3((k + 3) / 4), dim3(256), 0, st, cand_key, cand_idx, k, idx, perm);

@@ -24,3 +24,18 @@ def test_selection_by_counting(n):
             assert np.array_equal(idx.cpu().numpy(), want) and torch.equal(only, idx), (n, k)
             assert np.array_equal(perm.cpu().numpy(), orc.neuron_permutation(want, n)), (n, k)
             assert int(flag.item()) == 0
+
+
+@pytest.mark.parametrize("n", [8192, 8193, 20000])
+def test_nothing_selected(n):
+    """k = 0: no index, the identity as permutation, and the flag of a NaN all the same (beyond 8192 scores without ranking)."""
+    import paper_2401_04044_amd as ff
+    scores = torch.rand(n, device="cuda")
+    for nan in (False, True):
+        if nan:
+            scores[n - 1] = float("nan")
+        idx, perm, flag = ff.select_heavy(scores, 0, want_perm=True)
+        only = ff.select_heavy(scores, 0)[2]
+        torch.cuda.synchronize()
+        assert idx.numel() == 0 and torch.equal(perm.cpu(), torch.arange(n, dtype=torch.int32))
+        assert int(flag.item()) == int(only.item()) == (-7 if nan else 0)
