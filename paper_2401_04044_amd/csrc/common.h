@@ -144,7 +144,6 @@ int launch_gemm_f32(const GemmArgs& a, int act, bool score, hipStream_t st);
 int launch_gemm_bf16(const GemmArgs& a, int act, bool score, int shape, int n_split, hipStream_t st);
 // gated product with two left operands on 256 x 256 tiles (gemm_dual.hip); everything tiled
 int launch_gemm_dual(const GemmArgs& a, hipStream_t st);
-constexpr int FIX_COUNTERS = 256;   // tiles of a product whose ranges are added by the last to arrive
 // sum of the fp32 partials [n_split][a.M][ldp] of a whole product (written with a.partial, no
 // activation, GEMM column order) + the store epilogue described by a (activation act)
 int launch_splitk_epilogue(const float* part, int n_split, int ldp, const GemmArgs& a, int act, hipStream_t st);

@@ -707,6 +707,7 @@ static int launch_dl_cfg(const GemmArgs& a, int n_split, hipStream_t st) {
   if constexpr (ACT == ACT_NONE && A_TILED && !DUAL && !SCORE && BM == 64 && BN == 64) {
     if (a.fix_split > 1) {
       if (a.partial || a.fix_split != n_split || a.fix_split > GEMM_FIX_MAX_SPLIT) return -1;
+      if ((int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) > FIX_COUNTERS) return -1;   // (a counter a tile)
       return adds ? launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, true, MODE_FIX>(a, n_split, st)
                   : launch_dl_epi<BM, BN, WGM, WGN, STAGES, DBLA, ACT, DUAL, SCORE, A_TILED, false, MODE_FIX>(a, n_split, st);
     }

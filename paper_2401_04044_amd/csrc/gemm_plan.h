@@ -58,6 +58,7 @@ inline size_t gemm_part_bytes(int64_t M, int N, int split) { return (size_t)spli
 // take as long as that launch or longer (256x256, three ranges: equal; four: 36 us of 365 slower).
 constexpr double GEMM_FIX_GAIN_US = 1.7;
 constexpr int GEMM_FIX_MAX_SPLIT = 8;
+constexpr int FIX_COUNTERS = 256;   // tiles of a product whose ranges are added inside the launch (two ranges fill its one round)
 inline size_t gemm_fix_bytes(int64_t M, int N, int split) { return (size_t)((M + 63) / 64) * ((N + 63) / 64) * split * 16384; }
 
 // A reduction is split only to fill one round of the machine (256 CUs times the residents of a CU).
@@ -97,13 +98,15 @@ inline size_t gemm_part_room(int64_t M, int N, int K, bool glu, bool a_tiled) {
     const int64_t tiles_n = (N + c.bn - 1) / c.bn;
     for (int sp = 2; sp <= GEMM_MAX_SPLIT && slabs / sp >= GEMM_MIN_SLABS; ++sp) {
       const int64_t rows = 256 * c.per_cu / (sp * tiles_n) * c.bm;
-      const double gain = (slabs - (slabs + sp - 1) / sp) * c.t1 * (a_tiled ? 1.0 : c.row) - GEMM_SUM_US - GEMM_SUM_RANGE_US * (sp - 1);
+      const bool in_launch = a_tiled && !glu && s == GEMM_64x64 && sp <= GEMM_FIX_MAX_SPLIT;
+      const double gain = (slabs - (slabs + sp - 1) / sp) * c.t1 * (a_tiled ? 1.0 : c.row) - GEMM_SUM_US -
+                          GEMM_SUM_RANGE_US * (sp - 1) + (in_launch ? GEMM_FIX_GAIN_US : 0.0);
       if (rows <= 0 || gain <= 0) continue;
       const int64_t m = rows < M ? rows : M;
       const size_t fits = gemm_part_bytes(m, N, sp), pays = (size_t)(gain * GEMM_SUM_BYTES_PER_US) + 256;
       size_t b = fits < pays ? fits : pays;
       // (whole tiles where the ranges are added inside the launch)
-      if (s == GEMM_64x64 && sp <= GEMM_FIX_MAX_SPLIT && gemm_fix_bytes(m, N, sp) > b) b = gemm_fix_bytes(m, N, sp);
+      if (in_launch && gemm_fix_bytes(m, N, sp) > b) b = gemm_fix_bytes(m, N, sp);
       if (b > room) room = b;
     }
   }

@@ -17,20 +17,53 @@ def plan(tmp_path_factory):
     d = tmp_path_factory.mktemp("plan")
     src, so = d / "plan.cpp", d / "plan.so"
     src.write_text('#include "gemm_plan.h"\n'
-                   'extern "C" void plan(long M, int N, int K, int glu, int dual, int a_tiled, int can_split, int* out) {\n'
-                   '  const ffsplit::GemmPlan p = ffsplit::gemm_plan(M, N, K, glu, dual, a_tiled, can_split);\n'
-                   '  out[0] = p.shape; out[1] = p.split; }\n')
+                   'extern "C" void plan(long M, int N, int K, int glu, int dual, int a_tiled, int can_split, int fix, int* out) {\n'
+                   '  const ffsplit::GemmPlan p = ffsplit::gemm_plan(M, N, K, glu, dual, a_tiled, can_split, fix);\n'
+                   '  out[0] = p.shape; out[1] = p.split; out[2] = p.fix; }\n'
+                   'extern "C" size_t room(long M, int N, int K, int glu, int a_tiled) { return ffsplit::gemm_part_room(M, N, K, glu, a_tiled); }\n'
+                   'extern "C" size_t need(long M, int N, int split, int fix) {\n'
+                   '  return fix ? ffsplit::gemm_fix_bytes(M, N, split) : ffsplit::gemm_part_bytes(M, N, split); }\n'
+                   'extern "C" int limits(int i) { return i ? ffsplit::GEMM_FIX_MAX_SPLIT : ffsplit::FIX_COUNTERS; }\n')
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-shared", "-fPIC",
                            "-I" + os.path.join(ROOT, "paper_2401_04044_amd", "csrc"), str(src), "-o", str(so)])
     lib = ctypes.CDLL(str(so))
-    lib.plan.argtypes = [ctypes.c_long] + [ctypes.c_int] * 6 + [ctypes.POINTER(ctypes.c_int)]
+    lib.plan.argtypes = [ctypes.c_long] + [ctypes.c_int] * 7 + [ctypes.POINTER(ctypes.c_int)]
+    lib.room.argtypes, lib.room.restype = [ctypes.c_long] + [ctypes.c_int] * 4, ctypes.c_size_t
+    lib.need.argtypes, lib.need.restype = [ctypes.c_long] + [ctypes.c_int] * 3, ctypes.c_size_t
 
     def get(M, N, K, glu=False, dual=False, a_tiled=True, can_split=True):
-        out = (ctypes.c_int * 2)()
-        lib.plan(M, N, K, glu, dual, a_tiled, can_split, out)
-        return out[0], out[1]
+        return planned(M, N, K, glu, dual, a_tiled, can_split, False)[:2]
 
+    def planned(M, N, K, glu, dual, a_tiled, can_split, fix):
+        out = (ctypes.c_int * 3)()
+        lib.plan(M, N, K, glu, dual, a_tiled, can_split, fix, out)
+        return out[0], out[1], out[2]
+
+    get.with_fix = lambda M, N, K: planned(M, N, K, False, False, True, True, True)
+    get.lib = lib
     return get
+
+
+def test_ranges_added_inside_the_launch_have_counters_and_room(plan):
+    """Un-activated products on a tiled operand behind the first, as the forward pass plans them: only 64x64 tiles, at most
+    GEMM_FIX_MAX_SPLIT ranges and FIX_COUNTERS tiles, and whatever is split, either way, fits the scratch that a workspace
+    of at least as many tokens holds for the product."""
+    counters, most = plan.lib.limits(0), plan.lib.limits(1)
+    rng = np.random.default_rng(5)
+    shapes = [(130, 800, 1728), (423, 32, 1280)] + [(int(2 ** rng.uniform(6, 13.5)), 32 * int(rng.integers(1, 200)), 64 * int(rng.integers(1, 260)))
+                                                    for _ in range(20000)]
+    seen = 0
+    for M, N, K in shapes:
+        s, sp, fix = plan.with_fix(M, N, K)
+        if fix:
+            seen += 1
+            assert s == T64x64 and 1 < sp <= most and -(-M // 64) * -(-N // 64) <= counters, (M, N, K)
+        if sp > 1:
+            assert plan.lib.need(M, N, sp, fix) <= plan.lib.room(M, N, K, False, True) <= plan.lib.room(2 * M, N, K, False, True), (M, N, K)
+        s, sp = plan(M, N, K, False, False, True)
+        if sp > 1:
+            assert plan.lib.need(M, N, sp, 0) <= plan.lib.room(M, N, K, False, True), (M, N, K)
+    assert seen > 500
 
 
 def test_split_products_fill_at_most_one_round_and_only_valid_tiles_are_chosen(plan):
@@ -66,6 +99,8 @@ TIMED = [
 @pytest.mark.parametrize("M,N,K,glu,rows,allowed", TIMED)
 def test_choice_is_among_the_best_of_the_timed_ones(plan, M, N, K, glu, rows, allowed):
     assert plan(M, N, K, glu, False, not rows) in allowed
+    if not rows and not glu:   # (as it is planned behind the first product)
+        assert plan.with_fix(M, N, K)[:2] in allowed
 
 
 def test_device_cases_reach_every_form(plan):
