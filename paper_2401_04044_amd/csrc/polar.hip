@@ -95,8 +95,9 @@ struct TileProduct {
       to_lds(A, (lptr_t)(st + blk * 256), a_off[i], (uint32_t)s * 128);
       if (COLS) {   // (k rows past the last repeat it: A is zero there)
         const int place = blk * 8 + (lane >> 3);
-        const int k = min(s * 32 + (TL == 2 ? blk * 4 + (lane >> 4) : place ^ ((place >> 2) & 1)), k_rows - 1);
-        to_lds(B, (lptr_t)(st + OPER + blk * 256), b_off[i] + (uint32_t)k * (uint32_t)(ldb * 4), 0);
+        const int k = min(TL == 2 ? blk * 4 + (lane >> 4) : place ^ ((place >> 2) & 1), k_rows - 1 - s * 32);
+        // (X may be larger than the 4 GiB that an offset reaches: only the rows of a slab are offsets)
+        to_lds(B + (int64_t)s * 32 * ldb, (lptr_t)(st + OPER + blk * 256), b_off[i] + (uint32_t)k * (uint32_t)(ldb * 4), 0);
       } else {
         to_lds(B, (lptr_t)(st + OPER + blk * 256), b_off[i], (uint32_t)s * 128);
       }

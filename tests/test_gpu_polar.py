@@ -115,3 +115,22 @@ def test_basis_is_as_orthonormal_as_fp32_sums_allow(ff, d, r, decay):
     torch.cuda.synchronize()
     assert off_orthonormal(host(fd["P1"]).T) < ORTHONORMAL
     assert off_orthonormal(host(fd["Q2"])) < (ORTHONORMAL_DECAY if decay else ORTHONORMAL), off_orthonormal(host(fd["Q2"]))
+
+
+def test_basis_larger_than_four_gib(ff):
+    """X of 1104 x 1048608 floats, further than a 32-bit offset reaches from its first element: rows from 1024 on must not be taken
+    for the first ones, which would leave their rows' lengths wrong by as much as the steps change them."""
+    d, n, k, r = 1048608, 1208, 8, 1100
+    desc = ff.make_desc(d, n, k=k, rank=r, act="gelu", dtype="f32", rem_kind="lowrank")
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    W1 = torch.randn(d, n, device="cuda", generator=gen)
+    W2 = torch.randn(n, d, device="cuda", generator=gen)
+    fd = ff.factorize_remainder(desc, W1, None, W2, torch.arange(k, dtype=torch.int32, device="cuda"), seed=3)
+    eye = torch.eye(r, dtype=torch.float64, device="cuda")
+    for b in (fd["Q2"], fd["P1"].t()):
+        g = torch.zeros(r, r, dtype=torch.float64, device="cuda")
+        for c in range(0, d, 65536):
+            x = b[:, c:c + 65536].double().contiguous()
+            g += x @ x.t().contiguous()
+        off = float((g - eye).norm()) / r ** 0.5
+        assert off < 1e-3, off
