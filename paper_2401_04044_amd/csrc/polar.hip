@@ -61,7 +61,7 @@ struct TileProduct {
   int64_t ldb;
   int k_rows, n, lane, wave;
   int put, get;   // stage that the next slab goes to, that the next one is read from
-  uint32_t a_off[TL], b_off[TL];
+  uint32_t a_off[TL], b_off[TL], b_last[TL];   // (b_last, COLS: of the last slab)
 
   // requests the first STAGES - 1 slabs
   __device__ __forceinline__ void start(const float* A_, int64_t lda, int a_rows, const float* B_, int64_t ldb_, int b_rows,
@@ -77,7 +77,10 @@ struct TileProduct {
       a_off[i] = (uint32_t)min(row, a_rows - 1) * (uint32_t)(lda * 4) + col;
       if (COLS) {
         const int c = TL == 2 ? (lane & 15) ^ (4 * (blk & 3)) : (lane & 7) ^ (4 * (blk & 1));
-        b_off[i] = (uint32_t)(c * 4 < b_rows ? c : 0) * 16;
+        const int place = blk * 8 + (lane >> 3), k = TL == 2 ? blk * 4 + (lane >> 4) : place ^ ((place >> 2) & 1);
+        const uint32_t col = (uint32_t)(c * 4 < b_rows ? c : 0) * 16;
+        b_off[i] = col + (uint32_t)k * (uint32_t)(ldb * 4);
+        b_last[i] = col + (uint32_t)min(k, k_rows - 1 - (n - 1) * 32) * (uint32_t)(ldb * 4);
       } else {
         b_off[i] = (uint32_t)min(row, b_rows - 1) * (uint32_t)(ldb * 4) + col;
       }
@@ -94,14 +97,12 @@ struct TileProduct {
       const int blk = wave * TL + i;
       to_lds(A, (lptr_t)(st + blk * 256), a_off[i], (uint32_t)s * 128);
       if (COLS) {   // (k rows past the last repeat it: A is zero there)
-        const int place = blk * 8 + (lane >> 3);
-        const int k = min(TL == 2 ? blk * 4 + (lane >> 4) : place ^ ((place >> 2) & 1), k_rows - 1 - s * 32);
-        // (X may be larger than the 4 GiB that an offset reaches: only the rows of a slab are offsets)
-        to_lds(B + (int64_t)s * 32 * ldb, (lptr_t)(st + OPER + blk * 256), b_off[i] + (uint32_t)k * (uint32_t)(ldb * 4), 0);
+        to_lds(B, (lptr_t)(st + OPER + blk * 256), s + 1 < n ? b_off[i] : b_last[i], 0);
       } else {
         to_lds(B, (lptr_t)(st + OPER + blk * 256), b_off[i], (uint32_t)s * 128);
       }
     }
+    if (COLS) B += 32 * ldb;   // (X may be larger than the 4 GiB that an offset reaches; slabs are requested in order)
   }
 
   struct Frags { f32x4_t a[2][TL], b[2][TL]; };
@@ -132,8 +133,10 @@ struct TileProduct {
   }
   // Sums in NS accumulators of a tile, added in pairs at the end: with one, a chain of 512 roundings at d = 2048, the
   // basis was 6.8e-7 off orthonormal.  (2048 x 7946 rank 512 in fp32, root mean square: 2.3e-7 with these, 1.7e-7 with T - I
-  // applied; the products straight from registers had 2.2e-7.)
-  static constexpr int NS = TL == 1 ? 8 : 4;
+  // applied; the products straight from registers had 2.2e-7.)  Every 4096 elements of K they are added up and start again: the
+  // matrix unit's roundings do not average out over long chains (32768 x 700: 8.9e-8, 1.5e-6 with products straight from
+  // registers; 1048608 x 1100: 2.1e-7, and 5.8e-5 with chains of 65536).
+  static constexpr int NS = TL == 1 ? 8 : 4, FOLD = 64;   // (pairs of slabs)
   typedef f32x4_t Sums[NS][TL][TL];
   __device__ __forceinline__ static void mma(const Frags& f, Sums& acc) {
 #pragma unroll
@@ -155,29 +158,8 @@ struct TileProduct {
     asm volatile("s_barrier" ::: "memory");
     if (s + STAGES - 1 < n) issue(s + STAGES - 1);
   }
-  // the fragments of a slab are read while the one before is multiplied
-  __device__ __forceinline__ void run(f32x4_t (&out)[TL][TL]) {
-    Sums acc = {};
-    Frags f0, f1;
-    advance(0);
-    read(f0);
-    int s = 1;
-    for (; s + 1 < n; s += 2) {
-      advance(s);
-      read(f1);
-      mma(f0, acc);
-      advance(s + 1);
-      read(f0);
-      mma(f1, acc);
-    }
-    if (s < n) {
-      advance(s);
-      read(f1);
-      mma(f0, acc);
-      mma(f1, acc);
-    } else {
-      mma(f0, acc);
-    }
+  // out += the accumulators, which start again
+  __device__ __forceinline__ static void fold(Sums& acc, f32x4_t (&out)[TL][TL]) {
 #pragma unroll
     for (int n = NS / 2; n > 0; n /= 2)
 #pragma unroll
@@ -189,7 +171,44 @@ struct TileProduct {
 #pragma unroll
     for (int i = 0; i < TL; ++i)
 #pragma unroll
-      for (int j = 0; j < TL; ++j) out[i][j] = acc[0][i][j];
+      for (int j = 0; j < TL; ++j) {
+        out[i][j] += acc[0][i][j];
+#pragma unroll
+        for (int k = 0; k < NS; ++k) acc[k][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
+  }
+  // out (zero) = the product; the fragments of a slab are read while the one before is multiplied
+  __device__ __forceinline__ void run(f32x4_t (&out)[TL][TL]) {
+    Sums acc = {};
+    Frags f0, f1;
+    advance(0);
+    read(f0);
+    int s = 1;
+    auto pairs = [&](int end) {
+      for (; s + 1 < end; s += 2) {
+        advance(s);
+        read(f1);
+        mma(f0, acc);
+        advance(s + 1);
+        read(f0);
+        mma(f1, acc);
+      }
+    };
+    // (a loop of its own: with the fold inside the one that short products take these were 5 % slower)
+    while (__builtin_expect(n - s > 2 * FOLD, 0)) {
+      pairs(s + 2 * FOLD);
+      fold(acc, out);
+    }
+    pairs(n);
+    if (s < n) {
+      advance(s);
+      read(f1);
+      mma(f0, acc);
+      mma(f1, acc);
+    } else {
+      mma(f0, acc);
+    }
+    fold(acc, out);
   }
 };
 
