@@ -100,15 +100,15 @@ __device__ __forceinline__ uint32_t q_pair(const QPacked<3>& p, int j, int i, ui
   const uint32_t r = q_and_or(p.lo[j >> 1] >> (2 * (pr & 7)), 0x00030003u, magic);
   return q_and_or(__builtin_amdgcn_alignbit(p.hi, p.hi, pr), 0x00040004u, r);
 }
-// the four registers of operand block j as the bf16 pairs 128 + 2^i u, register i: one rotation of the third bits
-// serves all four
-__device__ __forceinline__ void q_pairs_scaled(const QPacked<3>& p, int j, q_u32x4& out) {
+// the four registers of operand block j as the pairs magic + 2^i u, register i (bf16 128, 0x4300, or fp16 1024, 0x6400):
+// one rotation of the third bits serves all four
+__device__ __forceinline__ void q_pairs_scaled(const QPacked<3>& p, int j, uint32_t magic, q_u32x4& out) {
   const uint32_t lo = p.lo[j >> 1], hi = j == 0 ? p.hi : __builtin_amdgcn_alignbit(p.hi, p.hi, 4 * j);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     // (the pair's low bits are at 2 i + 8 (j & 1), its third bits at 2 + i after the rotation)
     const int sh = i + 8 * (j & 1);
-    out[i] = q_and_or(hi, 0x00040004u << i, q_and_or(sh ? lo >> sh : lo, 0x00030003u << i, 0x43004300u));
+    out[i] = q_and_or(hi, 0x00040004u << i, q_and_or(sh ? lo >> sh : lo, 0x00030003u << i, magic));
   }
 }
 // 8 bits: bytes (2 i, 2 i + 1) of operand block j under the high byte of magic

@@ -680,9 +680,14 @@ __global__ void __launch_bounds__(NW * 64) rows16_kernel(const Rows16Args p) {
 //         vector instructions for 16 x 128 codes instead of 64.  The wavefronts' sums meet in LDS, where
 //         one of them adds, activates and stores the pair while the others go on.
 //   DOWN  A workgroup owns one piece of 16 outputs (4096 outputs: one each CU) over the whole reduction, its wavefronts
-//         an eighth each; the codes run through a ring of two registers sets, activations and scales are requested a
-//         unit ahead.  Deeper rings are slower (six and two: 2 us a launch): the code is run once or twice
-//         over, and twice its size costs more than the loads it has in flight.
+//         an eighth each; the 3-bit codes alternate between two sets of registers, the 8-bit ones have one, and so have
+//         activations and scales: they are requested when the unit before is multiplied and needed at once, so that their
+//         latency is covered by the other wavefronts only.  Deeper rings are slower (six sets of codes and two of activations:
+//         2 us a launch): the code is run once or twice over, and twice its size costs more than the loads it has in flight.
+//         The codes become exact fp16 integers in one more packed operation each (3 bits: 2^i u with the rotation shared as in UP,
+//         scaled and shifted by one v_pk_fma_f16), which costs no time: the MFMA on the negated constant that went with operands
+//         of 1024 + u goes.  With these the sums passed through 1024 times those of activations of one sign: relative error of an fp32
+//         result, 2048 x 16384 GeLU, 16 tokens, 3.9e-4 in the kernels below, 2.9e-4 here, all of it the activations' own rounding.
 // The kernels below spend half of their 32-row MFMAs on absent tokens, a second MFMA on the constant of UP, and two
 // launches on sums across workgroups.  us, a layer of 16 tokens with its norm, those -> these: 4096 x 11008 gated 44.9 ->
 // 32.0 (up 19.9 + 5.0 -> 16.6, down 13.8 + 4.1 -> 11.0), 2048 x 8192 25.7 -> 19.0, 1280 x 4000 22.3 -> 14.3; the operands
@@ -798,7 +803,7 @@ __device__ __forceinline__ void quant16_up(const Q16UpArgs& p, int u0, int step,
 #pragma unroll
             for (int e = 0; e < 4; ++e) wf.u[e] = q_pair(wts.w[i][g], j, e, 0x64646464u);
           } else {
-            q_pairs_scaled(wts.w[i][g], j, wf.u);
+            q_pairs_scaled(wts.w[i][g], j, 0x43004300u, wf.u);
           }
           if constexpr (BITS == 8) ag = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf.h, x[g][j].h, ag, 0, 0, 0);
           else ag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.b, x[g][j].b, ag, 0, 0, 0);
@@ -902,24 +907,30 @@ __device__ __forceinline__ void quant16_down(const Q16DownArgs& p, int piece, q1
       ss[j].u = sk_load(sr, sofs + (uint32_t)c * 256 + j * 32);
     }
   };
-  QFrag negc;
-  const uint32_t cc = BITS == 8 ? 0xE480E480u /* -1152 */ : 0xE404E404u /* -1028 */;
-  negc.u = u32x4_t{cc, cc, cc, cc};
   auto unit = [&](const QPacked<BITS>& d, QFrag (&hh)[4], const QFrag (&ss)[4]) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       QFrag wf, a;
+      if constexpr (BITS == 3) q_pairs_scaled(d, j, 0x64006400u, wf.u);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        H2 v, s2;
+        H2 v, s2, q, one, off;
         v.u = hh[j].u[i];
         s2.u = ss[j].u[i];
         v.h = v.h * s2.h;
         a.u[i] = v.u;
-        wf.u[i] = q_pair(d, j, i, BITS == 8 ? 0x64646464u : 0x64006400u);
+        if constexpr (BITS == 3) {   // (1024 + 2^i u) 2^-i - (1024 2^-i + 4)
+          constexpr uint32_t ONE[4] = {0x3C003C00u, 0x38003800u, 0x34003400u, 0x30003000u};
+          constexpr uint32_t OFF[4] = {0xE404E404u, 0xE008E008u, 0xDC10DC10u, 0xD820D820u};
+          q.u = wf.u[i]; one.u = ONE[i]; off.u = OFF[i];
+          q.h = __builtin_elementwise_fma(q.h, one.h, off.h);
+        } else {                     // 1024 + 128 + code
+          q.u = q_pair(d, j, i, 0x64646464u); off.u = 0xE480E480u;
+          q.h = q.h + off.h;
+        }
+        wf.u[i] = q.u;
       }
       tot = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf.h, a.h, tot, 0, 0, 0);
-      tot = __builtin_amdgcn_mfma_f32_16x16x32_f16(negc.h, a.h, tot, 0, 0, 0);
     }
   };
   static_assert(UW % UA == 0, "");

@@ -35,3 +35,37 @@ def test_up_to_16_tokens(base, d, n, k):
                 assert not host(g).any()
             else:
                 assert_close(host(g), w, "bf16", f"d{d} n{n} k{k} T={T} {nm}")
+
+
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+def test_down_product_rounds_the_activations_only(act):
+    """fp32 output against fp64 on the split's own weights: the activations are rounded to fp16 once and once more with their scales,
+    2^-10 / sqrt(12) x 0.72 each (the mean of 1 / x over a binade), 2.9e-4 together; the codes enter exactly.  (As 1024 + code, with the
+    constant subtracted from the sums, activations of one sign put another 2e-4 there.)"""
+    import paper_2401_04044_amd as ff
+    d, f, k, T = 1024, 12288, 1224, 16
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    rnd = lambda *s: (torch.randn(*s, device="cuda", generator=gen) * 0.05).to(torch.bfloat16)
+    W1, W2, Wg = rnd(d, f), rnd(f, d), rnd(d, f) if act == "swiglu" else None
+    desc = ff.make_desc(d, f, act, "bf16", k, "w3h8", 0, 128)
+    split = ff.build_split(desc, W1, Wg, W2, torch.arange(k, dtype=torch.int32, device="cuda"))
+    X = rnd(T, d) * 20
+
+    def weights(what):
+        q, s = ff.split_export(desc, split, what)
+        return host(q).astype(np.float64) * np.repeat(host(s.view(torch.float16)).astype(np.float64), 128, axis=1)
+
+    up, down = np.vstack([weights(3), weights(0)]), np.vstack([weights(5), weights(2)])
+    x = host(X).astype(np.float64)
+    h = x @ up.T
+    if act == "swiglu":
+        g = x @ np.vstack([weights(4), weights(1)]).T
+        h = h * g / (1 + np.exp(-g))
+    else:
+        h = torch.nn.functional.gelu(torch.from_numpy(h)).numpy()
+    want = h @ down
+    got = torch.empty(T, d, device="cuda")
+    ff.forward_ex(desc, split, X, got, y_f32=True)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(host(got).astype(np.float64) - want) / np.linalg.norm(want)
+    assert err < 3.1e-4, err
