@@ -186,7 +186,7 @@ int launch_skinny_q_pair(const GemmArgs& g8, const SkinnyQ& q8, const GemmArgs& 
 //   up    g as for a (gated) bf16 product over n8 rows of 8 bits, then n3 of 3 bits (act_cols = N = n8 + n3), with
 //         a tiled fp16 destination;
 //   down  g.A tiled fp16 [32, q8.Kp + q3.Kp], g.N a multiple of 128, with every addition of the epilogue.
-bool quant16_fits(int M, int d_model, bool gated);
+bool quant16_fits(int M, int d_model, int neurons, bool gated);   // (neurons: padded)
 int launch_quant16_up(const GemmArgs& g, int act, const SkinnyQ& q8, int n8, const SkinnyQ& q3, int n3, hipStream_t st);
 int launch_quant16_down(const GemmArgs& g, const SkinnyQ& q8, const SkinnyQ& q3, hipStream_t st);
 // reduce with n_split ranges for row blocks below rb_split and n_split_b from there on

@@ -319,7 +319,7 @@ int w3h8_forward_small(const ffsplit_desc_t& d, const Layout& L, const FwdWs& w,
   const size_t esz = 2;
   auto koff = [&](int col) { return (size_t)(col / 16) * 1024; };
   // at most 16 tokens: one launch per product
-  if (L.k4 > 0 && quant16_fits(M, dm, act == ACT_GLU) && L.total_bytes < 0xfffffff0u) {   // (their offsets are 32 bits wide)
+  if (L.k4 > 0 && quant16_fits(M, dm, L.k4, act == ACT_GLU) && L.total_bytes < 0xfffffff0u) {   // (their offsets are 32 bits wide)
     SkinnyQ q8 = {split + L.off_qc[0], split + L.off_qs[0], 8, 0, L.groups, L.kp};
     SkinnyQ q3 = {split + L.off_qc[1], split + L.off_qs[1], 3, 0, L.groups, L.mp};
     GemmArgs g = {};

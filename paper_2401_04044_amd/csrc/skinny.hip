@@ -1054,7 +1054,14 @@ int launch_skinny_reduce2(const GemmArgs& g, int act, const float* part, int n_s
 // Four groups a wavefront (d_model 4096) and with them one piece of outputs a CU; five and up to 320 pieces only for
 // gated layers.  Both sides (us, four layers of 16 tokens, the kernels for 32 / these): 5120 x 13824 gated 241 /
 // 203, 4608 x 12000 gated 203 / 185, 5120 x 20480 not gated 231 / 234.
-bool quant16_fits(int M, int d_model, bool gated) { return M <= 16 && d_model <= 128 * Q16_NW * (gated ? Q16_MAX_GPW : Q16_MAX_GPW - 1); }
+// Long reductions are left to them too where few outputs make few workgroups of DOWN (their ranges fill the machine): both sides, 8
+// tokens, not gated 128 x 13824 16.5 / 15.6, x 24576 19.9 / 22.8; 512 x 16384 18.7 / 17.5, x 32768 26.7 / 28.4; 1024 x 24576 27.9 /
+// 24.5, x 49152 36.8 / 41.7; 2048 x 32768 37.6 / 35.6, x 49152 48.0 / 48.6; gated 128 x 16384 19.7 / 18.4, x 32768 28.2 / 30; 512 x
+// 24576 28.4 / 24.9, x 49152 37.1 / 42.6; 1024 x 32768 36.9 / 33, x 49152 46.0 / 45.
+bool quant16_fits(int M, int d_model, int neurons, bool gated) {
+  if (M > 16 || d_model > 128 * Q16_NW * (gated ? Q16_MAX_GPW : Q16_MAX_GPW - 1)) return false;
+  return neurons <= (gated ? 20480 + 24 * d_model : 14336 + 16 * d_model);
+}
 
 template <bool GLU>
 static void launch_q16_up(const Q16UpArgs& a, hipStream_t st) {
@@ -1071,15 +1078,21 @@ static void launch_q16_up(const Q16UpArgs& a, hipStream_t st) {
 int launch_quant16_up(const GemmArgs& g, int act, const SkinnyQ& q8, int n8, const SkinnyQ& q3, int n3, hipStream_t st) {
   if (n8 + n3 <= 0) return 0;
   const bool glu = act == ACT_GLU;
-  if (g.M <= 0 || !quant16_fits(g.M, g.K, glu) || (g.K & 127) || (n8 & 63) || (n3 & 63)) return -1;
+  if (g.M <= 0 || !quant16_fits(g.M, g.K, (n8 + n3) / (glu ? 2 : 1), glu) || (g.K & 127) || (n8 & 63) || (n3 & 63)) return -1;
   Q16UpArgs a = {};
   a.X = g.A; a.lda = g.lda; a.M = g.M; a.G = g.K / 128;
   a.codes[0] = (const char*)q8.codes; a.codes[1] = (const char*)q3.codes;
   a.scales[0] = (const uint16_t*)q8.scales; a.scales[1] = (const uint16_t*)q3.scales;
   a.units8 = n8 / 32; a.units3 = n3 / 32; a.rb3 = n8 / 32;
-  // one pair of 8-bit pieces a workgroup (they are 2.7 times as long); the 3-bit ones share what is left of one
-  // round of the machine
-  a.wgs3 = a.units3 < 1 ? 0 : a.units8 < 192 ? (a.units3 < 256 - a.units8 ? a.units3 : 256 - a.units8) : (a.units3 < 256 ? a.units3 : 256);
+  // One pair of 8-bit pieces a workgroup (2.7 times as long as a 3-bit one).  The 3-bit ones share what is left of one round of the
+  // machine, unless a whole round for them behind the 8-bit ones is shorter: 16 tokens, left / whole round, gated 4096 x 24576 with a
+  // tenth of 8 bits 56.7 / 44.3, not gated 4096 x 32768 49.0 / 45.4, 4096 x 24576 35.0 / 37.7.  Two workgroups of one group a
+  // wavefront are resident a CU (110 registers; 512 x 8192: 12.6 -> 11.8), and more of equal length gain nothing there.
+  const int round = a.G <= Q16_NW ? 512 : 256, left = round - a.units8;
+  const int whole = (a.units3 + round - 1) / round, shared = left > 0 ? (a.units3 + left - 1) / left : a.units3;
+  const bool behind = left <= 0 || shared > whole + 2.7;
+  const int wgs = behind ? round : left, each = behind ? whole : shared;
+  a.wgs3 = a.units3 < 1 ? 0 : round == 512 ? (a.units3 + each - 1) / each : a.units3 < wgs ? a.units3 : wgs;
   fill_reduce_args(a.e, g, act);
   a.e.f16_out = 1;
   if (glu) launch_q16_up<true>(a, st);

@@ -37,6 +37,17 @@ def test_up_to_16_tokens(base, d, n, k):
                 assert_close(host(g), w, "bf16", f"d{d} n{n} k{k} T={T} {nm}")
 
 
+# more neurons than quant16_fits allows, and just below; 8-bit parts between a third of a round and a round, with the 3-bit part in
+# what is left of it or behind it; two workgroups a CU
+SPLITS = [(C2, 128, 16300, 40), (C2, 128, 16500, 40), (C4, 128, 23600, 40), (C4, 128, 8000, 3900), (C2, 1152, 9000, 5800),
+          (C4, 1152, 3000, 2900), (C4, 1152, 9000, 1500), (C2, 256, 4200, 4100)]
+
+
+@pytest.mark.parametrize("base,d,n,k", SPLITS, ids=[f"{c[0].act}_d{c[1]}_n{c[2]}_k{c[3]}" for c in SPLITS])
+def test_every_split_of_the_machine(base, d, n, k):
+    test_up_to_16_tokens(base, d, n, k)
+
+
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 def test_down_product_rounds_the_activations_only(act):
     """fp32 output against fp64 on the split's own weights: the activations are rounded to fp16 once and once more with their scales,
