@@ -67,10 +67,6 @@ __global__ void __launch_bounds__(1024) select_compact_kernel(const float* score
   if (saw) s_nan = 1;
   __syncthreads();
   if (tid == 0 && nan_flag) *nan_flag = s_nan ? -7 : 0;
-  if (k <= 0) {
-    if (perm) for (int i = tid; i < n; i += 1024) perm[i] = i;
-    return;
-  }
   // number of keys >= c (c > 0), the same value in every thread; buf alternates so that one
   // barrier per call is enough
   int buf = 0;
@@ -237,19 +233,44 @@ __global__ void __launch_bounds__(1024) select_rest_kernel(const int32_t* rank, 
   if (i < n && !sel) perm[k + (i - sp)] = i;
 }
 
+// Nothing is chosen: the flag, and the identity.  us, with the permutation, replayed from a graph, by the search / ranked by
+// counting / so: 1500 scores 3.9 / 6.7 / 2.2, 8192 7.2 / 13.4 / 2.6, 24576 15.1 / - / 4.3.
+__global__ void __launch_bounds__(1024) select_none_kernel(const float* scores, int n, int32_t* perm, int32_t* nan_flag) {
+  __shared__ int s_nan;
+  if (threadIdx.x == 0) s_nan = 0;
+  __syncthreads();
+  int saw = 0;
+  if (nan_flag)
+    for (int i0 = threadIdx.x; i0 < n; i0 += 8 * 1024) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = scores[min(i0 + u * 1024, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) score_key(v[u], &saw);
+    }
+  if (perm)
+    for (int i = threadIdx.x; i < n; i += 1024) perm[i] = i;
+  if (saw) s_nan = 1;
+  __syncthreads();
+  if (threadIdx.x == 0 && nan_flag) *nan_flag = s_nan ? -7 : 0;
+}
+
 // Ranking by counting grows with n^2, the search on one CU with n.  Both sides (us, a calibration call of 256 tokens
 // and width 512 with the selection, search / counting): 1500 scores 55.0 / 45.3, 8192 (4096 tokens, width 2048)
 // 165 / 142, 16384 88.7 / 63.8, 20480 92.3 / 84.8, 24576 102.3 / 95.4.  The selection alone, with the permutation, for any k
-// from 1 on: 8192 32 / 17, 16384 53 / 30, 24576 61 / 57.  With k = 0 there is nothing to search for (17 at any size): 8192
-// 16.7 / 16.9, 10240 16.7 / 20.8, 24576 18.1 / 56.5.
-constexpr int SELECT_COUNT_MAX_N = 24576, SELECT_COUNT_MAX_N_OF_NONE = 8192;
+// from 1 on: 8192 32 / 17, 16384 53 / 30, 24576 61 / 57.
+constexpr int SELECT_COUNT_MAX_N = 24576;
 
 size_t select_workspace_bytes(int d_ff) { return (size_t)12 * (size_t)(d_ff > 0 ? d_ff : 1) + 256; }
 
 int launch_select(const float* scores, int d_ff, int k, int32_t* idx, int32_t* perm, int32_t* nan_flag, void* ws,
                   hipStream_t st) {
   if (d_ff <= 0) return 0;
-  if (d_ff <= (k > 0 ? SELECT_COUNT_MAX_N : SELECT_COUNT_MAX_N_OF_NONE)) {
+  if (k <= 0) {
+    hipLaunchKernelGGL(select_none_kernel, dim3(1), dim3(1024), 0, st, scores, d_ff, perm, nan_flag);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+  }
+  if (d_ff <= SELECT_COUNT_MAX_N) {
     int32_t* rank = (int32_t*)ws;
     hipLaunchKernelGGL(select_count_kernel, dim3((d_ff + 31) / 32), dim3(1024), 0, st, scores, d_ff, k, rank, idx, perm, nan_flag);
     if (perm && k < d_ff)
@@ -262,11 +283,8 @@ int launch_select(const float* scores, int d_ff, int k, int32_t* idx, int32_t* p
   hipLaunchKernelGGL(select_compact_kernel, dim3(1), dim3(1024), 0, st, scores, d_ff, k, keys, cand_key, cand_idx, perm,
                      nan_flag);
   if (hipGetLastError() != hipSuccess) return -1;
-  if (k > 0) {
-    hipLaunchKernelGGL(select_rank_kernel, dim3((k + 3) / 4), dim3(256), 0, st, cand_key, cand_idx, k, idx, perm);
-    if (hipGetLastError() != hipSuccess) return -1;
-  }
-  return 0;
+  hipLaunchKernelGGL(select_rank_kernel, dim3((k + 3) / 4), dim3(256), 0, st, cand_key, cand_idx, k, idx, perm);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int select_static_max_dff() { return SELECT_STATIC_MAX_DFF; }

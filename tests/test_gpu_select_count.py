@@ -26,9 +26,9 @@ def test_selection_by_counting(n):
             assert int(flag.item()) == 0
 
 
-@pytest.mark.parametrize("n", [8192, 8193, 20000])
+@pytest.mark.parametrize("n", [1, 1024, 1025, 8192, 8193, 20000, 60001])
 def test_nothing_selected(n):
-    """k = 0: no index, the identity as permutation, and the flag of a NaN all the same (beyond 8192 scores without ranking)."""
+    """k = 0: no index, the identity as permutation, and the flag of a NaN all the same (nothing is ranked)."""
     import paper_2401_04044_amd as ff
     scores = torch.rand(n, device="cuda")
     for nan in (False, True):
