@@ -153,10 +153,11 @@ int launch_reduce_partials(const float* p2, const float* p1, int tiles, int n_ou
 }
 
 // n2 = sum_c W2[j,c]^2 by one wavefront per neuron (lane-strided partial sums and a fixed butterfly of
-// wavefront shuffles), then the score of the given kind.  A workgroup takes 16 neurons, its wavefronts two each, eight
-// loads in flight: bound by reading W2 once.
-// tiles > 0: the call's partial sums of the activations are added to the accumulator first (reduce_partials
-// on these 16 neurons, requested ahead of the rows; as a launch of its own 6.8 us of latency).
+// wavefront shuffles), then the score of the given kind.  Bound by reading W2 once.
+// ADDS: the call's partial sums of the activations are added to the accumulator first (reduce_partials, requested ahead of
+// the rows; as a launch of its own 6.8 us of latency); a workgroup takes 16 neurons for it, its wavefronts two each, eight
+// loads in flight.  Without, a neuron a wavefront, twice the wavefronts: bf16 8192 x 8192 26.4 -> 22.1 us, 24576 neurons of 512
+// 6.2 -> 5.7.
 struct ScoreArgs {
   const void* W2;
   int d_model, d_ff;
@@ -167,14 +168,14 @@ struct ScoreArgs {
   int kind;
   float* scores;
 };
-template <bool BF16>
-__global__ void __launch_bounds__(512) finalize_scores_kernel(const ScoreArgs a) {
+template <bool BF16, bool ADDS>
+__global__ void __launch_bounds__(ADDS ? 512 : 256) finalize_scores_kernel(const ScoreArgs a) {
   __shared__ float s_acc[2][16];
-  constexpr int PT = 8;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j0 = blockIdx.x * 16;
+  constexpr int PT = 8, R = ADDS ? 2 : 1;   // neurons a wavefront
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), j0 = blockIdx.x * (ADDS ? 16 : 4);
   // thread (which sum, neuron): tiles in ascending order, PT in flight
   const int which = threadIdx.x >> 4, jp = j0 + (threadIdx.x & 15);
-  const bool adds = threadIdx.x < 32 && jp < a.d_ff;
+  const bool adds = ADDS && threadIdx.x < 32 && jp < a.d_ff;
   const float* part = (which ? a.part_s1 : a.part_s2) + jp;
   float s = 0.f, old = 0.f;
   if (adds) {
@@ -188,24 +189,24 @@ __global__ void __launch_bounds__(512) finalize_scores_kernel(const ScoreArgs a)
         if (t + u < a.tiles) s += v[u];
     }
   }
-  float n2[2] = {0.f, 0.f};
+  float n2[R] = {};
   if (a.kind != 2) {
-    constexpr int E = BF16 ? 8 : 4, ESZ = BF16 ? 2 : 4, U = 4;   // 16 bytes a lane, U loads of a row at once
-    const char* row[2];
+    constexpr int E = BF16 ? 8 : 4, ESZ = BF16 ? 2 : 4, U = ADDS ? 4 : 1;   // 16 bytes a lane, U loads of a row at once
+    const char* row[R];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) row[i] = (const char*)a.W2 + (int64_t)min(j0 + wave * 2 + i, a.d_ff - 1) * a.d_model * ESZ;
+    for (int i = 0; i < R; ++i) row[i] = (const char*)a.W2 + (int64_t)min(j0 + wave * R + i, a.d_ff - 1) * a.d_model * ESZ;
     for (int c0 = lane * E; c0 < a.d_model; c0 += 64 * E * U) {
-      uint4 v[U][2];
+      uint4 v[U][R];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int c = c0 + u * 64 * E;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) v[u][i] = c < a.d_model ? *(const uint4*)(row[i] + (int64_t)c * ESZ) : make_uint4(0, 0, 0, 0);
+        for (int i = 0; i < R; ++i) v[u][i] = c < a.d_model ? *(const uint4*)(row[i] + (int64_t)c * ESZ) : make_uint4(0, 0, 0, 0);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < R; ++i) {
           const uint32_t w[4] = {v[u][i].x, v[u][i].y, v[u][i].z, v[u][i].w};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -220,23 +221,24 @@ __global__ void __launch_bounds__(512) finalize_scores_kernel(const ScoreArgs a)
         }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < R; ++i)
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) n2[i] += __shfl_xor(n2[i], o);
   }
   if (adds) {
-    if (a.tiles > 0) a.acc[which * a.d_ff + jp] = old + s;
+    a.acc[which * a.d_ff + jp] = old + s;
     s_acc[which][threadIdx.x & 15] = old + s;
   }
-  __syncthreads();
+  if (ADDS) __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int jl = wave * 2 + i, j = j0 + jl;
+  for (int i = 0; i < R; ++i) {
+    const int jl = wave * R + i, j = j0 + jl;
     if (lane != 0 || j >= a.d_ff) continue;
+    const float sum = ADDS ? s_acc[a.kind == 1][jl] : a.acc[(a.kind == 1 ? a.d_ff : 0) + j];
     float v;
-    if (a.kind == 0) v = s_acc[0][jl] * n2[i];
-    else if (a.kind == 1) v = (s_acc[1][jl] / fmaxf(a.t_total, 1.f)) * sqrtf(n2[i]);
-    else v = s_acc[0][jl];
+    if (a.kind == 0) v = sum * n2[i];
+    else if (a.kind == 1) v = (sum / fmaxf(a.t_total, 1.f)) * sqrtf(n2[i]);
+    else v = sum;
     a.scores[j] = v + 0.f;
   }
 }
@@ -245,9 +247,14 @@ int launch_finalize_scores(const void* W2, int bf16, int d_model, int d_ff, floa
                            int tiles, int n_out, float t_total, int kind, float* scores, hipStream_t st) {
   if (d_ff <= 0) return 0;
   const ScoreArgs a = {W2, d_model, d_ff, acc, p2, p1, tiles, n_out, t_total, kind, scores};
-  const dim3 grid((d_ff + 15) / 16), blk(512);
-  if (bf16) hipLaunchKernelGGL(finalize_scores_kernel<true>, grid, blk, 0, st, a);
-  else hipLaunchKernelGGL(finalize_scores_kernel<false>, grid, blk, 0, st, a);
+  const dim3 grid(tiles > 0 ? (d_ff + 15) / 16 : (d_ff + 3) / 4), blk(tiles > 0 ? 512 : 256);
+  if (tiles > 0) {
+    if (bf16) hipLaunchKernelGGL((finalize_scores_kernel<true, true>), grid, blk, 0, st, a);
+    else hipLaunchKernelGGL((finalize_scores_kernel<false, true>), grid, blk, 0, st, a);
+  } else {
+    if (bf16) hipLaunchKernelGGL((finalize_scores_kernel<true, false>), grid, blk, 0, st, a);
+    else hipLaunchKernelGGL((finalize_scores_kernel<false, false>), grid, blk, 0, st, a);
+  }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -88,7 +88,7 @@ SIGNATURES = {
     "C2_calibration": [
         ("re-tile W1 (neuron-major)", r"permute_transpose_tiled_kernel<true>", 128, 32),
         ("score product X W1, gelu, column sums  256x256 tiles", G + r"256, 256, 2, 4, 4, false, 1, false, true, false, false, 0>", 512, 1),
-        ("sum of the row tiles' partials, row norms of W2, score", r"finalize_scores_kernel<true>", 512, 1),
+        ("sum of the row tiles' partials, row norms of W2, score", r"finalize_scores_kernel<true, true>", 512, 1),
         ("selection: ranking by counting", r"select_count_kernel", 256, 1),
     ],
     "ceilings": [
