@@ -339,10 +339,12 @@ static int launch_f32_act(const GemmArgs& a, hipStream_t st) {
       return launch_f32<1, 1, 2, 2, 1, 4, ACT, DUAL, false>(a, st);
     if constexpr (ACT == ACT_NONE) {
       // few 16x16 tiles and a long reduction: ranges of at least 32 slabs on the idle CUs (a BERT-base-sized layer of
-      // 128 tokens, 32 tiles: 23.5 -> 20.6 us; 1024 wide, 16 tokens 26.1 -> 21.2)
+      // 128 tokens, 32 tiles: 23.5 -> 20.6 us; 1024 wide, 16 tokens 26.1 -> 21.2), where each of the 16 wavefronts is
+      // spared four slabs (2048 x 256, 128 tokens 17.2 -> 17.0, 1536 x 256, 1 token 9.2 either way; two slabs, 1024 x 256, 1 and
+      // 128 tokens: 8.6 -> 9.05 and 13.5 -> 14.0)
       const int tiles = (a.M + 15) / 16 * ((a.N + 15) / 16);
       const int s = std::min({F32_MAX_SPLIT, 256 / tiles, (a.K + 15) / 16 / 32});
-      if (pick == 3 && a.fix_cnt != nullptr && s > 1) {
+      if (pick == 3 && a.fix_cnt != nullptr && (a.K + 15) / 16 * (s - 1) >= 64 * s) {
         GemmArgs g = a;
         g.fix_split = s;
         return launch_f32<1, 1, 1, 1, 16, 4, ACT, DUAL, false, true>(g, st);
