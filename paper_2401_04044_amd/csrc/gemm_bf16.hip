@@ -338,7 +338,7 @@ gemm_bf16_dl_kernel(const GemmArgs p) {
   // row r goes to position 4 r + (c ^ (r >> 2)), so that the fragment reads (16 rows, one chunk
   // number) of 16 consecutive lanes fall into 16 different 16-byte bank groups.  (The counters
   // still show conflicts on this form alone: 6.9e6 cycles over the machine at 4096 x 3200 x 4096, a sixth
-  // of the kernel's; tiled operands have none.)
+  // of the kernel's; tiled operands have none.  So the lanes of a pass are probably not consecutive ones.)
   // All loads are buffer loads: the tile's base in scalar registers, a byte offset per lane that the
   // loop never changes, and a scalar offset that walks along K.
   uint32_t soff[LPW];       // uniform: the block's offset inside the tile

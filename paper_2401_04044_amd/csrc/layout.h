@@ -131,7 +131,7 @@ struct FwdWs {
   // INT4 decode scratch
   size_t off_h, off_part, off_cnt;
   int n_split;
-  int n_cnt;       // bf16: arrival counters of small batches at off_cnt
+  int n_cnt;       // arrival counters at off_cnt: products whose ranges the last workgroup to arrive adds
   // INT4 with many tokens: bf16 image of the split in the DENSE layout, then that chain's scratch
   int i4_prefill;
   size_t off_img, off_dense;

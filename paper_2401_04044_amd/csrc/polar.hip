@@ -12,7 +12,10 @@
 // Measured, us, a factorisation with singular values i^-a, a = 0, 1, 2, two matrices, the steps of polar_steps for every sketch
 // / these: 2048 x 7944 rank 512 1130 / 570, 785, 1055; 1536 x 4849 rank 400 gated 1065 / 545, 720, 985; 4096 x 10675 rank 1024
 // gated 8150 / 3420, 4940, 6840; 1608 x 4849 rank 800 2097 / 855, 1238, 1812; 512 x 1455 rank 64 260 / 184, 198, 236; 2048 x 7944
-// rank 128 478 / 329, -, 480; of rank one, 2048 x 7944 rank 512, 1126 / 1000.
+// rank 128 478 / 329, -, 480; of rank one, 2048 x 7944 rank 512, 1126 / 1000.  Where every matrix decays like i^-2, which takes one or
+// two steps more than the fixed schedule, small ones are slower: 128 x 1000 rank 100 191 / 159, 176, 211; 768 x 2976 rank 128 319 /
+// 238, 273, 332; 256 x 776 rank 200 275 / 208, 253, 299; 2048 x 7944 rank 512 1123 / 564, 774, 1038.  (Growth not left any more in its
+// last two steps: 202, 328 and 272 there, but 283 with i^-1 at rank 200, which then resumes growth.)
 // All products are true fp32 (v_mfma_f32_16x16x4_f32, 256 flop per clock and CU), staged through LDS by loads
 // without registers.  A tile asks the caches for 16 (64x64) or 32 bytes per clock of 61: what bounds them is
 // the matrix rate, and at the usual ranks the start of a launch and the latency of its first loads.  So the
