@@ -67,6 +67,7 @@ __global__ void __launch_bounds__(1024) select_compact_kernel(const float* score
   if (saw) s_nan = 1;
   __syncthreads();
   if (tid == 0 && nan_flag) *nan_flag = s_nan ? -7 : 0;
+  if (k <= 0) return;   // (never: without it the compiler's schedule takes 2 us more, 24600 scores 55.3 -> 57.0)
   // number of keys >= c (c > 0), the same value in every thread; buf alternates so that one
   // barrier per call is enough
   int buf = 0;
